@@ -801,7 +801,6 @@ void band_factor_t(BandSet& bs, T* v, T* dinv, hipStream_t st, FactorJob& job, b
   // columns by group g - 2, which ran on the second stream), then its k_chain and k_far;
   // then the update of the columns from group g + 2 on by its panels on the second stream,
   // at the same time as group g + 1's work on st.
-  GX_HIP(hipStreamCreateWithFlags(&job.la, hipStreamNonBlocking));
   GX_HIP(hipEventCreateWithFlags(&job.chain, hipEventDisableTiming));
   GX_HIP(hipEventCreateWithFlags(&job.rest[0], hipEventDisableTiming));
   GX_HIP(hipEventCreateWithFlags(&job.rest[1], hipEventDisableTiming));
@@ -866,13 +865,13 @@ FactorJob::~FactorJob() {
   if (chain) (void)hipEventDestroy(chain);
   for (hipEvent_t e : rest)
     if (e) (void)hipEventDestroy(e);
-  if (la) (void)hipStreamDestroy(la);
 }
 
-void band_factor_start(BandSet& bs, hipStream_t st, FactorJob& job, const char* what,
-                       bool threaded) {
+void band_factor_start(BandSet& bs, hipStream_t st, hipStream_t la, FactorJob& job,
+                       const char* what, bool threaded) {
   GX_REQUIRE(!job.st, "factorisation job already started");
   job.st = st;
+  job.la = la;
   job.what = what;
   job.err.alloc(1);
   zero(job.err, st);
@@ -896,9 +895,9 @@ void band_factor_finish(FactorJob& job) {
                 "non-positive pivot in the banded Cholesky factorisation of " + job.what);
 }
 
-void band_factor(BandSet& bs, hipStream_t st, const char* what) {
+void band_factor(gx_ctx* c, BandSet& bs, hipStream_t st, const char* what) {
   FactorJob job;
-  band_factor_start(bs, st, job, what);
+  band_factor_start(bs, st, aux_stream(c->look[0]), job, what);
   band_factor_finish(job);
 }
 
@@ -2132,7 +2131,7 @@ extern "C" gx_status gx_band_factor_solve(gx_ctx* c, int32_t n_mat, const int64_
                      d_doff.p, n_mat, bs.d_off.p, bs.d_B.p, fp32 ? bs.v32.p : nullptr,
                      fp32 ? nullptr : bs.v64.p);
   GX_HIP(hipGetLastError());
-  band_factor(bs, s, "the given band matrices");
+  band_factor(c, bs, s, "the given band matrices");
   if (fp32)
     hipLaunchKernelGGL(k_scale_rhs, dim3(nblocks(doff[n_mat] * nrhs, 256)), dim3(256), 0, s,
                        doff[n_mat], nrhs, dsc.p, x);

@@ -205,6 +205,11 @@ void dev_forget(const gx_ctx* c) {
     }
 }
 
+hipStream_t aux_stream(hipStream_t& st) {
+  if (!st) GX_HIP(hipStreamCreateWithFlags(&st, hipStreamNonBlocking));
+  return st;
+}
+
 IdleScope::IdleScope() : prev(tls_idle) { tls_idle = true; }
 IdleScope::~IdleScope() { tls_idle = prev; }
 
@@ -330,7 +335,11 @@ void gx_destroy(gx_ctx* c) {
   if (!c) return;
   (void)hipSetDevice(c->device);
   if (c->stream) (void)hipStreamSynchronize(c->stream);
+  for (hipStream_t st : {c->side, c->look[0], c->look[1]})
+    if (st) (void)hipStreamSynchronize(st);
   gx::dev_forget(c);                               // before the address can be reused
+  for (hipStream_t st : {c->side, c->look[0], c->look[1]})
+    if (st) (void)hipStreamDestroy(st);
   if (c->own_stream) (void)hipStreamDestroy(c->stream);
   gx::IdleScope idle;                              // its buffers are released unused
   delete c;

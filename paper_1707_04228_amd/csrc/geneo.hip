@@ -981,7 +981,7 @@ void geneo_coarse(gx_ctx* c, const gx_geneo_opts* o, const std::function<void()>
     to_host(&hferr, ferr.p, 1, s);
     GX_REQUIRE(!hferr, "a block row of K is longer than the Neumann assembly takes");
     try {
-      band_factor(Mb, s, "the shifted Neumann matrices (GenEO eigensolver)");
+      band_factor(c, Mb, s, "the shifted Neumann matrices (GenEO eigensolver)");
     } catch (const Error& e) {
       if (!fp32 || e.code != GX_ENOTSPD) throw;
       // an FP32 factor broke down: this matrix set is refactored in FP64 (reported)
@@ -993,7 +993,7 @@ void geneo_coarse(gx_ctx* c, const gx_geneo_opts* o, const std::function<void()>
                          c->row_ptr.p, c->col.p, sigma, bv, d_doff.p, (const double*)nullptr,
                          Mb.v64.p, ferr.p);
       GX_HIP(hipGetLastError());
-      band_factor(Mb, s, "the shifted Neumann matrices (GenEO eigensolver)");
+      band_factor(c, Mb, s, "the shifted Neumann matrices (GenEO eigensolver)");
     }
   }
   if (after_factor) after_factor();
@@ -1270,7 +1270,7 @@ void geneo_coarse(gx_ctx* c, const gx_geneo_opts* o, const std::function<void()>
   hipLaunchKernelGGL(k_coarse_fill, dim3(nblocks(n0 * n0, 256)), dim3(256), 0, s, n0, K0.p,
                      sw.C.B[0], sw.C.ld[0], sw.C.v64.p);
   GX_HIP(hipGetLastError());
-  band_factor(sw.C, s, "the coarse matrix K0 (near-dependent coarse vectors?)");
+  band_factor(c, sw.C, s, "the coarse matrix K0 (near-dependent coarse vectors?)");
   const int64_t zero64 = 0;
   sw.d_c_xoff.alloc(1);
   to_dev(sw.d_c_xoff.p, &zero64, 1, s);
@@ -1286,20 +1286,6 @@ void geneo_coarse(gx_ctx* c, const gx_geneo_opts* o, const std::function<void()>
 using namespace gx;
 
 extern "C" {
-
-// A stream of the set-up's own (default priority), drained before it goes.
-struct SideStream {
-  hipStream_t st = nullptr;
-  SideStream() { GX_HIP(hipStreamCreateWithFlags(&st, hipStreamNonBlocking)); }
-  ~SideStream() {
-    if (st) {
-      (void)hipStreamSynchronize(st);
-      (void)hipStreamDestroy(st);
-    }
-  }
-  SideStream(const SideStream&) = delete;
-  SideStream& operator=(const SideStream&) = delete;
-};
 
 gx_status gx_geneo_setup(gx_ctx* c, const gx_geneo_opts* o, int32_t* nev_out,
                          int64_t* n0_out) {
@@ -1326,23 +1312,27 @@ gx_status gx_geneo_setup(gx_ctx* c, const gx_geneo_opts* o, int32_t* nev_out,
     // starts once the eigensolver's factorisation is done, so that it runs beside the
     // eigensolver's iterations (bound by memory traffic), not beside the other
     // factorisation, and a host thread of the job enqueues its launches, so that this
-    // thread goes on to the iterations at once.  The side stream is declared first, so the
-    // job (which waits for its streams when it goes) is destroyed before it.
-    SideStream side;
+    // thread goes on to the iterations at once.
+    const hipStream_t side = aux_stream(c->side);
+    // whatever ends the set-up, its work on the side stream ends before its buffers go
+    struct Drain {
+      hipStream_t st;
+      ~Drain() { (void)hipStreamSynchronize(st); }
+    } drain{side};
     InteriorJob job;
     EventPair ev;
     {
-      StreamScope scope(side.st);
-      GX_HIP(hipEventRecord(ev.a, side.st));
-      interior_factors_prepare(c, o->precision, side.st, job);
+      StreamScope scope(side);
+      GX_HIP(hipEventRecord(ev.a, side));
+      interior_factors_prepare(c, o->precision, side, job);
     }
     auto start_interior = [&]() {
-      StreamScope scope(side.st);
-      interior_factors_launch(c, side.st, job, true);
+      StreamScope scope(side);
+      interior_factors_launch(c, side, job, true);
     };
     geneo_coarse(c, o, start_interior);
     interior_factors_finish(c, job);                 // joins the launching thread
-    GX_HIP(hipEventRecord(ev.b, side.st));
+    GX_HIP(hipEventRecord(ev.b, side));
     c->phase_ms[2] = ev.ms();
   } else {
     Timer t2(c->stream);

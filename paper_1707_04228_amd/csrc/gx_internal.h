@@ -319,6 +319,9 @@ struct gx_ctx {
   hipStream_t stream = nullptr;
   bool own_stream = false;
   std::string err;
+  // streams of the set-up (default priority), created when first needed and kept until the
+  // context goes: released device blocks remember the stream their work ran on
+  hipStream_t side = nullptr, look[2] = {nullptr, nullptr};
   // mesh copy
   int64_t n_nodes = 0, n_elems = 0;
   gx::DevBuf<double> xyz;
@@ -388,11 +391,13 @@ double interior_refactor_ms(gx_ctx* c);
 // tables), otherwise the band itself is taken
 void band_layout(BandSet& bs, const std::vector<int64_t>& n, const std::vector<int64_t>& B,
                  bool fp32, hipStream_t st, const std::vector<int32_t>* first_node = nullptr);
-void band_factor(BandSet& bs, hipStream_t st, const char* what);
+void band_factor(gx_ctx* c, BandSet& bs, hipStream_t st, const char* what);
+// one of the context's set-up streams, created if it is not there
+hipStream_t aux_stream(hipStream_t& st);
 // A banded factorisation in flight (band_factor_start enqueues it on st, band_factor_finish
-// waits for it and raises GX_ENOTSPD on a non-positive pivot).  It owns the look-ahead
-// stream, the diagonal-block scratch and the pivot-error word; its destructor waits for
-// both streams first, so none of them is released while a kernel of the job may run.
+// waits for it and raises GX_ENOTSPD on a non-positive pivot).  It owns the diagonal-block
+// scratch and the pivot-error word; its destructor waits for its stream and its look-ahead
+// stream first, so neither is released while a kernel of the job may run.
 struct FactorJob {
   hipStream_t st = nullptr;
   std::string what;
@@ -400,7 +405,7 @@ struct FactorJob {
   DevBuf<double> inv;                          // inverse diagonal blocks handed over
   DevBuf<int> flags;                           // per panel block: epoch of its completion;
                                                // then per launch: the work-group counter
-  hipStream_t la = nullptr;                    // trailing-update stream (default priority)
+  hipStream_t la = nullptr;                    // trailing-update stream of the context
   hipEvent_t chain = nullptr, rest[2] = {nullptr, nullptr};
   std::thread launcher;                        // enqueues the launches of a threaded job
   std::exception_ptr launch_error;
@@ -412,7 +417,8 @@ struct FactorJob {
 // threaded: a host thread of the job enqueues the launches, so the caller goes on at once
 // (a long chain of launches blocks the enqueuing thread once the device's queues are
 // full); band_factor_finish joins it.
-void band_factor_start(BandSet& bs, hipStream_t st, FactorJob& job, const char* what,
+void band_factor_start(BandSet& bs, hipStream_t st, hipStream_t la, FactorJob& job,
+                       const char* what,
                        bool threaded = false);
 void band_factor_finish(FactorJob& job);
 // The interior factorisation as a job that can run on a side stream (see schwarz.hip).

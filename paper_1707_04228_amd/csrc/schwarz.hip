@@ -337,7 +337,8 @@ void interior_factors_prepare(gx_ctx* c, int precision, hipStream_t s, InteriorJ
 }
 
 void interior_factors_launch(gx_ctx* c, hipStream_t s, InteriorJob& job, bool threaded) {
-  band_factor_start(c->sw.A, s, job.factor, "the subdomain matrices", threaded);
+  band_factor_start(c->sw.A, s, aux_stream(c->look[1]), job.factor, "the subdomain matrices",
+                    threaded);
 }
 
 void interior_factors_start(gx_ctx* c, int precision, hipStream_t s, InteriorJob& job) {
@@ -363,7 +364,7 @@ void interior_factors_finish(gx_ctx* c, InteriorJob& job) {
                        c->row_ptr.p, c->col.p, c->val.p, (const double*)nullptr, sw.I_nodes.p,
                        sw.d_offI.p, sw.d_nI.p, sw.I_loc.p, N, bv64, sw.A.v64.p);
     GX_HIP(hipGetLastError());
-    band_factor(sw.A, s, "the subdomain matrices");
+    band_factor(c, sw.A, s, "the subdomain matrices");
     sw.precision = GX_FP64;
   }
   std::vector<int64_t> xo(n_sub + 1, 0);
@@ -406,7 +407,7 @@ double interior_refactor_ms(gx_ctx* c) {
   GX_HIP(hipEventRecord(ev.a, s));
   {
     FactorJob job;
-    band_factor_start(sw.A, s, job, "the subdomain matrices");
+    band_factor_start(sw.A, s, aux_stream(c->look[1]), job, "the subdomain matrices");
     GX_HIP(hipEventRecord(ev.b, s));
     band_factor_finish(job);
   }
