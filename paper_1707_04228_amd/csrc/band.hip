@@ -6,7 +6,13 @@
 // half bandwidth of about two lattice planes, so its Cholesky factor fits in band storage
 // with no fill outside the band.
 //
-// Storage of matrix j: entry (r, c), r - B_j <= c <= r, at off_j + r * ld_j + (c - r + B_j).
+// Storage of a part: entry (r, c), r - B <= c <= r, at off + r * ld + (c - r + B).
+//
+// Both the factorisation and the solves are chains of dependent 64-row steps, and with few
+// matrices a chain's latency, not bandwidth or arithmetic, sets the time.  A matrix whose
+// order is several times its bandwidth is therefore eliminated from both ends at once, in
+// two parts that meet in a separator of one bandwidth (BandPart, split_rows): half the
+// chain, the same entries and the same flops.
 //
 // Factorisation: right-looking, block columns of NB taken GP at a time; one launch per
 // group factors its panels (diagonal blocks, their inverses, kept for the solves, and the
@@ -54,13 +60,10 @@ struct Mfma<float> {
 };
 
 struct BandArgs {
-  const int64_t* n;
-  const int64_t* B;
-  const int64_t* ld;
-  const int64_t* off;
-  const int64_t* eoff;                            // envelope tables by 64-row blocks
-  const int64_t* fcb;
+  const BandPart* part;
+  const int64_t* fcb;                             // envelope tables by 64-row blocks
   const int64_t* lrb;
+  int phase;                                      // factorisation: before, at the separators
 };
 
 // ---- Factorisation: right-looking blocked Cholesky in groups of GP panels of NB columns.
@@ -68,7 +71,8 @@ struct BandArgs {
 // group's own rows, k_far for the rows below them.  The update of the trailing window by
 // the group's panels is split in two k_syrk_wide launches: the next group's columns (then
 // that group's k_chain, on the same stream), and all further columns on a second stream,
-// at the same time.
+// at the same time.  The separators of split matrices follow in a second phase of the same
+// launches, after k_merge.  k0 counts from the first column of the part's phase.
 constexpr int GP = 4;                             // panels per group
 constexpr int CT = 256;                           // threads of a panel work-group
 constexpr int64_t SPIN_LIMIT = (int64_t)1 << 22;  // polls before a wait gives up
@@ -138,9 +142,9 @@ struct Chunk<float> {
 //   3. The flag of (p, j, t) is raised.
 // A non-positive pivot raises bit 1 of the error word and is replaced by 1.
 template <class T>
-__global__ void __launch_bounds__(CT) k_chain(BandArgs a, T* v, int64_t k0, int NR, int n_mat,
+__global__ void __launch_bounds__(CT) k_chain(BandArgs a, T* v, int64_t kg, int NR, int n_mat,
                                               int* flags, int* ticket, int epoch, double* inv,
-                                              T* dinv, const int64_t* boff, int* err) {
+                                              T* dinv, int* err) {
   typedef Mfma<T> MT;
   typedef typename MT::S S;
   constexpr int KC = Chunk<S>::KC, KS = Chunk<S>::KS;
@@ -185,15 +189,17 @@ __global__ void __launch_bounds__(CT) k_chain(BandArgs a, T* v, int64_t k0, int 
   const int tr = p + t;                          // row block, counted from k0
   const int NRT = NR + GP - 1;
   int* fj = flags + (int64_t)j * GP * NRT;       // flag of (q, j, row block b): fj[q NRT + b]
-  const int64_t n = a.n[j], B = a.B[j], ld = a.ld[j];
+  const BandPart& P = a.part[j];
+  const int64_t n = P.rows, B = P.B, ld = P.ld;
+  const int64_t k0 = P.fb[a.phase] + kg, ce = P.fe[a.phase];
   const int64_t c0 = k0 + (int64_t)NB * p, r0 = c0 + (int64_t)NB * t;
   // no entries, or rows below the group (k_far's): only the flag
-  if (c0 >= n || r0 >= n || r0 > c0 + NB - 1 + B || tr >= GP) {
+  if (c0 >= ce || r0 >= n || r0 > c0 + NB - 1 + B || tr >= GP) {
     if (threadIdx.x == 0) __hip_atomic_store(fj + p * NRT + tr, epoch, __ATOMIC_RELEASE,
                                              __HIP_MEMORY_SCOPE_AGENT);
     return;
   }
-  T* base = v + a.off[j];
+  T* base = v + P.off;
   const int64_t rs = ld - 1;                     // entry (r, c) at r * rs + B + c
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int li = lane & 15, lk = lane >> 4;
@@ -201,7 +207,7 @@ __global__ void __launch_bounds__(CT) k_chain(BandArgs a, T* v, int64_t k0, int 
   const int kc_t = threadIdx.x % KC, i0 = threadIdx.x / KC;
   // the block's entries, loaded now and used after step 1 (entries outside the matrix or
   // the band read as 0; the diagonal block keeps its lower triangle)
-  const int nb = (int)min<int64_t>(NB, n - c0);  // columns of the panel inside the matrix
+  const int nb = (int)min<int64_t>(NB, ce - c0); // columns of the panel inside the matrix
   double av[2][4][2];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
@@ -230,7 +236,7 @@ __global__ void __launch_bounds__(CT) k_chain(BandArgs a, T* v, int64_t k0, int 
       }
     __syncthreads();
     // the first chunk with an entry inside the envelope of the block's rows
-    const int64_t lo = max(r0 - B, a.fcb[a.eoff[j] + r0 / NB]);
+    const int64_t lo = max(r0 - B, a.fcb[P.eoff + r0 / NB]);
     const int64_t kstart = lo > k0 ? k0 + (lo - k0) / KC * KC : k0;
     S xr[PER], xs[PER];
     // 32-bit terms relative to the block: row i of a block is inside the matrix if
@@ -386,7 +392,7 @@ __global__ void __launch_bounds__(CT) k_chain(BandArgs a, T* v, int64_t k0, int 
         }
     }
     __syncthreads();
-    T* dj = dinv + boff[j] + (c0 / NB) * NB * NB;
+    T* dj = dinv + P.boff + (c0 / NB) * NB * NB;
     for (int idx = threadIdx.x; idx < NB * NB; idx += CT) {
       const int i = idx / NB, l = idx % NB;
       const double lv = (i >> 4) > (l >> 4)    ? Li[i][l]
@@ -452,7 +458,7 @@ __global__ void __launch_bounds__(CT) k_chain(BandArgs a, T* v, int64_t k0, int 
 // itself, so nothing is waited for and plain loads suffice; the products are the same,
 // in the same order, as k_chain's.
 template <class T>
-__global__ void __launch_bounds__(CT, 2) k_far(BandArgs a, T* v, int64_t k0, int NF, int n_mat,
+__global__ void __launch_bounds__(CT, 2) k_far(BandArgs a, T* v, int64_t kg, int NF, int n_mat,
                                                const double* inv) {
   typedef Mfma<T> MT;
   typedef typename MT::S S;
@@ -470,10 +476,12 @@ __global__ void __launch_bounds__(CT, 2) k_far(BandArgs a, T* v, int64_t k0, int
   S* Ps = reinterpret_cast<S*>(&Li[0][0]);
   const int j = blockIdx.x / NF, f = blockIdx.x % NF;
   if (j >= n_mat) return;
-  const int64_t n = a.n[j], B = a.B[j], ld = a.ld[j];
+  const BandPart& P = a.part[j];
+  const int64_t n = P.rows, B = P.B, ld = P.ld;
+  const int64_t k0 = P.fb[a.phase] + kg, ce = P.fe[a.phase];
   const int64_t r0 = k0 + (int64_t)NB * (GP + f);
-  if (r0 >= n) return;
-  T* base = v + a.off[j];
+  if (k0 >= ce || r0 >= n) return;
+  T* base = v + P.off;
   const int64_t rs = ld - 1;                     // entry (r, c) at r * rs + B + c
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int li = lane & 15, lk = lane >> 4;
@@ -482,8 +490,8 @@ __global__ void __launch_bounds__(CT, 2) k_far(BandArgs a, T* v, int64_t k0, int
 #pragma unroll 1
   for (int p = 0; p < GP; ++p) {
     const int64_t c0 = k0 + (int64_t)NB * p;
-    if (c0 >= n || r0 > c0 + NB - 1 + B) continue;   // no entries in this panel
-    const int nb = (int)min<int64_t>(NB, n - c0);
+    if (c0 >= ce || r0 > c0 + NB - 1 + B) continue;  // no entries in this panel
+    const int nb = (int)min<int64_t>(NB, ce - c0);
     // the block's entries and the inverse of the panel's diagonal block are loaded first, so
     // that they arrive during the update
     T av[2][4][2];
@@ -507,7 +515,7 @@ __global__ void __launch_bounds__(CT, 2) k_far(BandArgs a, T* v, int64_t k0, int
 #pragma unroll
       for (int jj = 0; jj < 2; ++jj) acc[i][jj] = typename MT::V{0, 0, 0, 0};
     if (p > 0) {
-      const int64_t lo = max(r0 - B, a.fcb[a.eoff[j] + r0 / NB]);
+      const int64_t lo = max(r0 - B, a.fcb[P.eoff + r0 / NB]);
       const int64_t kstart = lo > k0 ? k0 + (lo - k0) / KC * KC : k0;
       // Each thread loads VW consecutive entries of a row at once (16 bytes: rows start on
       // 128-byte lines and k0 + (kc - k0) + kc_t is a multiple of VW, so the loads are
@@ -635,7 +643,7 @@ struct Wide<float> {
 };
 
 template <class T>
-__device__ inline void wide_tile(BandArgs a, T* v, int64_t k0, int64_t kk, int64_t ts_lo,
+__device__ inline void wide_tile(BandArgs a, T* v, int64_t kg, int64_t kk, int64_t ts_lo,
                                  int64_t ts_hi, int64_t per_mat, int64_t lin) {
   typedef Mfma<T> MT;
   typedef typename MT::S S;
@@ -648,9 +656,11 @@ __device__ inline void wide_tile(BandArgs a, T* v, int64_t k0, int64_t kk, int64
   __shared__ __attribute__((aligned(16))) S Ps[T2][KS];
   const int j = (int)(lin / per_mat);
   const int64_t tile = lin - (int64_t)j * per_mat;
-  const int64_t n = a.n[j], B = a.B[j], ld = a.ld[j];
-  if (k0 >= n) return;
-  const int64_t kj = min<int64_t>(kk, n - k0);
+  const BandPart& P = a.part[j];
+  const int64_t n = P.rows, B = P.B, ld = P.ld;
+  const int64_t k0 = P.fb[a.phase] + kg, ce = P.fe[a.phase];
+  if (k0 >= ce) return;
+  const int64_t kj = min<int64_t>(kk, ce - k0);
   const int64_t t0 = k0 + kj;
   const int64_t W = min<int64_t>(B, n - t0);
   if (W <= 0) return;
@@ -660,12 +670,12 @@ __device__ inline void wide_tile(BandArgs a, T* v, int64_t k0, int64_t kk, int64
   for (ts = ts_lo; ts < te && rem >= nt - ts; ++ts) rem -= nt - ts;
   if (ts >= te) return;
   const int64_t tr = ts + rem;
-  T* base = v + a.off[j];
+  T* base = v + P.off;
   const int64_t r0 = t0 + tr * T2, s0 = t0 + ts * T2, wend = t0 + W;
   const int64_t rs = ld - 1;                     // entry (r, c) at r * rs + B + c
   const int kc_t = threadIdx.x % (KW / VW) * VW, i0 = threadIdx.x / (KW / VW);
   // first chunk with an entry inside the envelope of the tile's rows (its two 64-row blocks)
-  const int64_t* fcj = a.fcb + a.eoff[j];
+  const int64_t* fcj = a.fcb + P.eoff;
   const int64_t b0 = r0 / NB;
   const int64_t fmin = b0 + 1 < (n + NB - 1) / NB ? min(fcj[b0], fcj[b0 + 1]) : fcj[b0];
   const int64_t lo = max(r0 - B, fmin) - k0;
@@ -775,68 +785,121 @@ static int64_t wide_tiles(int64_t max_B, int64_t lo, int64_t hi) {
 }
 
 
+// The separators between the phases: what the lower part's elimination left in its
+// separator window is added to the upper part's window, entry (s, t) of the separator there
+// and (ns - 1 - t, ns - 1 - s) in the reversed part.  One 32 x 32 tile per work-group,
+// turned in LDS so that both sides run along rows; the window is read and written once.
+constexpr int MG = 32;
+template <class T>
+__global__ void __launch_bounds__(256) k_merge(const BandPart* part, const int32_t* part_of,
+                                               T* v) {
+  __shared__ T tile[MG][MG + 1];
+  const int j = blockIdx.z;
+  if (part_of[2 * j + 1] < 0) return;
+  const BandPart& u = part[part_of[2 * j]];
+  const BandPart& l = part[part_of[2 * j + 1]];
+  const int64_t ns = u.rows - u.sep;
+  const int64_t s0 = (int64_t)blockIdx.y * MG, t0 = (int64_t)blockIdx.x * MG;
+  if (s0 >= ns || t0 > s0 || s0 - (t0 + MG - 1) > u.B) return;
+  const int x = threadIdx.x % MG, y = threadIdx.x / MG;
+  for (int q = y; q < MG; q += 256 / MG) {          // lower part's row of t0 + q, s along it
+    const int64_t s = s0 + x, t = t0 + q;
+    if (s < ns && t <= s && s - t <= u.B)
+      tile[q][x] = v[l.off + (l.cols + ns - 1 - t) * l.ld + (t - s + l.B)];
+  }
+  __syncthreads();
+  for (int q = y; q < MG; q += 256 / MG) {
+    const int64_t s = s0 + q, t = t0 + x;
+    if (s < ns && t <= s && s - t <= u.B)
+      v[u.off + (u.sep + s) * u.ld + (t - s + u.B)] += tile[x][q];
+  }
+}
+
 template <class T>
 void band_factor_t(BandSet& bs, T* v, T* dinv, hipStream_t st, FactorJob& job, bool threaded) {
-  BandArgs a{bs.d_n.p, bs.d_B.p, bs.d_ld.p, bs.d_off.p, bs.d_eoff.p, bs.d_fcb.p, bs.d_lrb.p};
   static_assert(GP * NB % T2 == 0, "a group spans whole wide tile columns");
   constexpr int64_t NEXT_TS = GP * NB / T2;              // tile columns of the next group
-  for (int j = 0; j < bs.n_mat; ++j)
-    GX_REQUIRE((bs.n[j] + T2) * bs.ld[j] + 64 < ((int64_t)1 << 31),
+  for (const BandPart& p : bs.part)
+    GX_REQUIRE((p.rows + T2) * p.ld + 64 < ((int64_t)1 << 31),
                "a band matrix of 2^31 entries or more exceeds the update's 32-bit offsets");
   const int NR = (int)((bs.max_B + NB - 1) / NB) + 1;   // row blocks of a panel
   // k_chain takes the group's own rows (GP row blocks per panel, those below the group
   // exit at once), k_far the NF row blocks below the group
   const int NRC = GP, NRT = NRC + GP - 1, NF = NR - 1;
-  job.inv.alloc((size_t)bs.n_mat * GP * NB * NB);
-  const int64_t n_groups = (bs.max_n + GP * NB - 1) / (GP * NB);
-  job.flags.alloc((size_t)bs.n_mat * GP * NRT + n_groups);   // then one ticket counter per launch
+  const int n_part = bs.n_part, n_mat = bs.n_mat;
+  job.inv.alloc((size_t)n_part * GP * NB * NB);
+  // columns of the longest part in each phase, and the largest separator
+  int64_t span[2] = {0, 0}, max_sep = 0;
+  for (const BandPart& p : bs.part) {
+    for (int h = 0; h < 2; ++h) span[h] = std::max(span[h], p.fe[h] - p.fb[h]);
+    max_sep = std::max(max_sep, p.rows - p.sep);
+  }
+  int64_t n_groups = 0;
+  for (int h = 0; h < 2; ++h) n_groups += (span[h] + GP * NB - 1) / (GP * NB);
+  job.flags.alloc((size_t)n_part * GP * NRT + n_groups);   // then one ticket counter per launch
   zero(job.flags, st);
-  int* tickets = job.flags.p + (int64_t)bs.n_mat * GP * NRT;
+  int* tickets = job.flags.p + (int64_t)n_part * GP * NRT;
   const int64_t nt2 = (bs.max_B + T2 - 1) / T2;
-  const int64_t per_rest = wide_tiles(bs.max_B, NEXT_TS, nt2), tot_rest = per_rest * bs.n_mat;
-  const int64_t per_next = wide_tiles(bs.max_B, 0, NEXT_TS), tot_next = per_next * bs.n_mat;
-  const unsigned chain_blocks = (unsigned)((int64_t)GP * bs.n_mat * NRC);
-  const unsigned far_blocks = (unsigned)((int64_t)bs.n_mat * NF);
+  const int64_t per_rest = wide_tiles(bs.max_B, NEXT_TS, nt2), tot_rest = per_rest * n_part;
+  const int64_t per_next = wide_tiles(bs.max_B, 0, NEXT_TS), tot_next = per_next * n_part;
+  const unsigned chain_blocks = (unsigned)((int64_t)GP * n_part * NRC);
+  const unsigned far_blocks = (unsigned)((int64_t)n_part * NF);
   // group g on st: the update of its columns by group g - 1 (after the update of the same
   // columns by group g - 2, which ran on the second stream), then its k_chain and k_far;
   // then the update of the columns from group g + 2 on by its panels on the second stream,
-  // at the same time as group g + 1's work on st.
+  // at the same time as group g + 1's work on st.  Where a separator follows, the last
+  // group's updates of it complete the first phase.
   GX_HIP(hipEventCreateWithFlags(&job.chain, hipEventDisableTiming));
   GX_HIP(hipEventCreateWithFlags(&job.rest[0], hipEventDisableTiming));
   GX_HIP(hipEventCreateWithFlags(&job.rest[1], hipEventDisableTiming));
-  const int64_t max_n = bs.max_n, max_B = bs.max_B;
-  const int n_mat = bs.n_mat;
-  const int64_t* boff = bs.d_boff.p;
+  const int64_t max_B = bs.max_B, span0 = span[0], span1 = span[1];
+  const bool split = bs.split;
+  const BandPart* part = bs.d_part.p;
+  const int32_t* part_of = bs.d_part_of.p;
+  const int64_t *fcb = bs.d_fcb.p, *lrb = bs.d_lrb.p;
   int* flags = job.flags.p;
   double* inv = job.inv.p;
   int* err = job.err.p;
   hipStream_t la = job.la;
   hipEvent_t ev_chain = job.chain, ev_rest[2] = {job.rest[0], job.rest[1]};
   auto launches = [=]() {
-    bool recorded[2] = {false, false};
-    int g = 0;
-    for (int64_t k0 = 0; k0 < max_n; k0 += GP * NB, ++g) {
-      if (recorded[g % 2]) GX_HIP(hipStreamWaitEvent(st, ev_rest[g % 2], 0));
-      if (g > 0 && max_B > 0)
-        hipLaunchKernelGGL(k_syrk_wide<T>, dim3((unsigned)tot_next), dim3(U2), 0, st, a, v,
-                           k0 - GP * NB, (int64_t)GP * NB, (int64_t)0, NEXT_TS, per_next,
-                           tot_next);
-      hipLaunchKernelGGL(k_chain<T>, dim3(chain_blocks), dim3(CT), 0, st, a, v, k0, NRC,
-                         n_mat, flags, tickets + g, g + 1, inv, dinv, boff, err);
-      if (far_blocks)
-        hipLaunchKernelGGL(k_far<T>, dim3(far_blocks), dim3(CT), 0, st, a, v, k0, NF, n_mat,
-                           (const double*)inv);
-      if (tot_rest && k0 + GP * NB < max_n) {
-        GX_HIP(hipEventRecord(ev_chain, st));
-        GX_HIP(hipStreamWaitEvent(la, ev_chain, 0));
-        hipLaunchKernelGGL(k_syrk_wide<T>, dim3((unsigned)tot_rest), dim3(U2), 0, la, a, v,
-                           k0, (int64_t)GP * NB, NEXT_TS, nt2, per_rest, tot_rest);
-        GX_HIP(hipEventRecord(ev_rest[g % 2], la));
-        recorded[g % 2] = true;
+    int g = 0;                                      // groups launched in both phases
+    for (int phase = 0; phase < (split ? 2 : 1); ++phase) {
+      const BandArgs a{part, fcb, lrb, phase};
+      const int64_t cols = phase ? span1 : span0;
+      const bool tail = split && phase == 0;        // rows remain after the last group
+      bool recorded[2] = {false, false};
+      int64_t k0 = 0;
+      for (;; k0 += GP * NB, ++g) {
+        const bool last = k0 >= cols;
+        if (last && !tail) break;
+        if (recorded[g % 2]) GX_HIP(hipStreamWaitEvent(st, ev_rest[g % 2], 0));
+        if (k0 > 0 && max_B > 0)
+          hipLaunchKernelGGL(k_syrk_wide<T>, dim3((unsigned)tot_next), dim3(U2), 0, st, a, v,
+                             k0 - GP * NB, (int64_t)GP * NB, (int64_t)0, NEXT_TS, per_next,
+                             tot_next);
+        if (last) break;
+        hipLaunchKernelGGL(k_chain<T>, dim3(chain_blocks), dim3(CT), 0, st, a, v, k0, NRC,
+                           n_part, flags, tickets + g, g + 1, inv, dinv, err);
+        if (far_blocks)
+          hipLaunchKernelGGL(k_far<T>, dim3(far_blocks), dim3(CT), 0, st, a, v, k0, NF, n_part,
+                             (const double*)inv);
+        if (tot_rest && (tail || k0 + GP * NB < cols)) {
+          GX_HIP(hipEventRecord(ev_chain, st));
+          GX_HIP(hipStreamWaitEvent(la, ev_chain, 0));
+          hipLaunchKernelGGL(k_syrk_wide<T>, dim3((unsigned)tot_rest), dim3(U2), 0, la, a, v,
+                             k0, (int64_t)GP * NB, NEXT_TS, nt2, per_rest, tot_rest);
+          GX_HIP(hipEventRecord(ev_rest[g % 2], la));
+          recorded[g % 2] = true;
+        }
+      }
+      for (int q = 0; q < 2; ++q)
+        if (recorded[q]) GX_HIP(hipStreamWaitEvent(st, ev_rest[q], 0));
+      if (tail) {
+        const unsigned nt = (unsigned)((max_sep + MG - 1) / MG);
+        hipLaunchKernelGGL(k_merge<T>, dim3(nt, nt, n_mat), dim3(256), 0, st, part, part_of, v);
       }
     }
-    for (int q = 0; q < 2; ++q)
-      if (recorded[q]) GX_HIP(hipStreamWaitEvent(st, ev_rest[q], 0));
     GX_HIP(hipGetLastError());
   };
   if (!threaded) {
@@ -907,16 +970,26 @@ void band_factor(gx_ctx* c, BandSet& bs, hipStream_t st, const char* what) {
 // through the explicit inverse of each 64x64 diagonal block (kept by the factorisation),
 // so the serial part of a block is one small product, not a 64-step substitution.
 //
-// G work-groups share a matrix: block k belongs to work-group k mod G in the forward sweep
-// and to (nblk - 1 - k) mod G in the backward sweep.  A work-group first adds the
-// contributions of the blocks that are complete by construction (its own previous block
-// and everything before it), then takes the at most G - 1 blocks still in flight from the
-// other work-groups (bounded polls of their solutions, below), applies the inverse
-// diagonal block and hands its block on.  A timed-out poll raises the launch's error word
-// and proceeds, so every wave always reaches the end of the kernel.
+// G work-groups share a part: block k belongs to work-group k mod G in the forward sweep and
+// likewise from the end in the backward sweep.  A work-group first adds the contributions of
+// the blocks that are complete by construction (its own previous block and everything
+// before it), then takes the at most G - 1 blocks still in flight from the other
+// work-groups (bounded polls of their solutions, below), applies the inverse diagonal block
+// and hands its block on.  A timed-out poll raises the launch's error word and proceeds, so
+// every wave always reaches the end of the kernel.
+//
+// What bounds the one-right-hand-side solve: a work-group streams about 22 GB/s however idle
+// the device is, and a hand-over costs 2.5 to 3 us, so few matrices need many groups, and
+// the chain of (n + B) / 128 hand-overs per sweep is the rest.  Per solve, unsplit with four
+// groups -> split with up to eight (FP64 but where noted): 4 matrices of n = 3,500, B = 370:
+// 0.29 -> 0.18 ms; 6 of 16,000, 1,020: 1.77 -> 0.73 ms; 16 of 37,000, 1,220 (9.5 GB): 4.85 ->
+// 2.03 ms; 5 of 45,000, 2,080, FP32: 6.12 -> 2.03 ms; 16 of 91,000, 1,630 (26 GB): 15.1 -> 5.8
+// ms.  64 of those fill the device with one group per compute unit and stay where they
+// were (118 GB in 22 to 23 ms, FP32 59 GB in 12.9 ms).
 constexpr int SW = SOLVE_THREADS / 64;           // waves per work-group (8)
 constexpr int RPW = SB / SW;                      // forward rows per wave (8)
-constexpr int GMAX = 4;                           // work-groups per matrix, 1-RHS solve
+constexpr int GMAX = 8;                           // work-groups per part, 1-RHS solve
+constexpr int FL = 3;                             // blocks in flight taken at a time
 constexpr int DL = SB * SB / SOLVE_THREADS;       // inverse-block entries per thread (8)
 static_assert(DL == RPW, "the inverse-block products reuse the 8-row lane reduction");
 constexpr int64_t BAND_PAD = 1024;               // trailing entries of a band allocation
@@ -1009,118 +1082,205 @@ __device__ inline bool poll_give_up(int64_t& spins, int* err) {
   return false;
 }
 
-// Work-group g of the G that solve one matrix of n rows, half-bandwidth B and row stride
-// ld: factor from base, inverse diagonal blocks from dv, envelope tables fcb / lrb (by
-// 64-row blocks), right-hand side x, scratch y, z.
+// One part in the single-right-hand-side solve: factor entries from base, inverse diagonal
+// blocks from dv, envelope tables fcb / lrb (by 64-row blocks), the matrix's right-hand side
+// x, scratch y, z, and the mate's (BandPtrs) scratch.
 template <class T>
-__device__ __forceinline__ void band_solve_1_mat(int64_t n, int64_t B, int64_t ld,
-                                                 const T* base, const T* dv,
-                                                 const int64_t* fcb, const int64_t* lrb,
-                                                 const double* x, double* y, double* z, int g,
-                                                 int G, int* err) {
+struct Solve1 {
+  int64_t n, cols, sep, N, B, ld;
+  int kind;
+  const T* base;
+  const T* dv;
+  const int64_t* fcb;
+  const int64_t* lrb;
+  const double* x;
+  double* y;
+  double* z;
+  const double* mate;
+};
+
+// Work-group g of the G that solve part `own` (load(i): the Solve1 of part i; `upper`: the
+// upper part of a split matrix).  A split matrix is swept in two segments: the parts' own
+// columns, each by its work-groups, and the separator, held by the upper part, by the
+// work-groups of both (as many as the in-flight registers allow), so that none is idle
+// meanwhile.  The lower part's rows past its own columns (the separator) only sum its
+// contributions to them, which the separator's blocks take from its y; its backward sweep
+// takes the separator's solution from the upper part's z.  A segment begins with a wait
+// for the one before it, which the count of complete blocks rests on.
+template <class T, class Load>
+__device__ __forceinline__ void band_solve_1_mat(Load load, int own, int upper, int g, int G,
+                                                 int* err) {
+  int n, cols, sep, B, rs, N;                       // (a part has less than 2^31 entries)
+  const T *base, *dv;
+  const int64_t *fcb, *lrb;
+  const double *x, *mate;                           // row r at x[dx r], mate[-r]
+  double *y, *z;
+  int dx;
+  bool lower;
+  auto use = [&](int part) {
+    const Solve1<T> S = load(part);
+    n = (int)S.n, cols = (int)S.cols, sep = (int)S.sep, B = (int)S.B, rs = (int)S.ld - 1;
+    N = (int)S.N;
+    base = S.base, dv = S.dv, fcb = S.fcb, lrb = S.lrb;
+    lower = S.kind == PART_LOWER;
+    x = lower ? S.x + N - 1 : S.x;
+    dx = lower ? -1 : 1;
+    y = S.y, z = S.z;
+    mate = S.mate + N - 1;
+  };
+  use(own);
+  const bool split = upper >= 0, own_lower = lower;
+  // separator groups
+  const bool both = 2 * G <= GMAX;
+  const int GS = both ? 2 * G : G, gs = both ? 2 * g + own_lower : own_lower ? -1 : g;
   __shared__ double acc[SB];
   __shared__ double part[SW][SB];
-  __shared__ double xs[GMAX - 1][SB];               // polled solutions of blocks in flight
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t nblk = (n + SB - 1) / SB;
+  __shared__ double xs[FL][SB];               // polled solutions of blocks in flight
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   constexpr int UB = 32;                           // band rows in flight per wave (backward)
   // ---- forward: wave w owns rows 8w..8w+7 of the block, lanes run along the columns
-  for (int64_t k = g; k < nblk; k += G) {
-    const int64_t i0 = k * SB;
-    const int nb = (int)min<int64_t>(SB, n - i0);
-    const int64_t kdone = max<int64_t>(k - G + 1, 0);        // column blocks < kdone complete
-    const int64_t done_end = kdone * SB;
-    const int64_t ifirst = i0 + RPW * wave;
+#pragma unroll 1
+  for (int seg = 0; seg < (split ? 2 : 1); ++seg) {
+  int kfirst = 0, step = G, mine = g;          // first block of the segment, of this group
+  if (seg) {
+    if (gs < 0) break;
+    use(upper);
+    kfirst = sep / SB;
+    step = GS;
+    mine = kfirst + gs;
+    if (threadIdx.x < SB) {
+      int64_t spins = 0;
+      while (is_mark(poll_load(y + sep - SB + threadIdx.x)) && !poll_give_up(spins, err)) {}
+    }
+    __syncthreads();
+  }
+  const int ncb = (cols + SB - 1) / SB;         // blocks with columns of their own
+  const int nblk = seg || !split || lower ? (n + SB - 1) / SB : sep / SB;
+  for (int k = mine; k < nblk; k += step) {
+    const int i0 = k * SB;
+    const int nb = (int)min<int>(SB, n - i0);
+    const int kc = min(k, ncb);                // column blocks left of the block
+    const int kdone = min(max(k - step + 1, kfirst), kc);   // those < kdone are complete
+    const int done_end = kdone * SB;
+    const int ifirst = i0 + RPW * wave;
     // the right-hand side of the row this lane reduces
     const int ii = RPW * wave + (lane >> 3);
     const bool own = (lane & 7) == 0 && ii < nb;
-    const double bval = own ? x[i0 + ii] : 0.0;
-    const T* rp[RPW];                              // rp[r][c] = entry (row, c)
+    double bval = own && k < ncb ? x[dx * (i0 + ii)] : 0.0;
+    const T* rp[RPW];                              // rp[r][c] = entry (row, c); scalar, the
+                                                   // lanes' offsets from it are 32-bit
 #pragma unroll
     for (int r = 0; r < RPW; ++r) {
-      const int64_t rc = min<int64_t>(ifirst + r, n - 1);
-      rp[r] = base + rc * ld - rc + B;
+      const int rc = min<int>(ifirst + r, n - 1);
+      rp[r] = base + ((int64_t)rc * rs + B);
     }
     double s[RPW];
 #pragma unroll
     for (int r = 0; r < RPW; ++r) s[r] = 0.0;
     // envelope start, rounded down to a 128-byte line (rows start on one: see band_layout)
-    constexpr int64_t LA = 128 / sizeof(T);
-    const int64_t cstart = max(max<int64_t>(ifirst - B, 0), fcb[k]) / LA * LA;
+    constexpr int LA = 128 / (int)sizeof(T);
+    const int cstart = max(max<int>(ifirst - B, 0), (int)fcb[k]) / LA * LA;
     {
       // a lane loads V adjacent columns of a row at once (16 bytes: two FP64 or four FP32
       // entries; columns from a line start are multiples of V, so every load is aligned),
       // 64 V columns per step, 512 columns per pass
-      constexpr int V = 16 / sizeof(T);
+      constexpr int V = 16 / (int)sizeof(T);
       constexpr int US = 512 / (64 * V);            // steps per pass
       typedef T TV __attribute__((ext_vector_type(V)));
-      for (int64_t c0 = cstart + V * lane; c0 < done_end + V * lane; c0 += 64 * V * US) {
+      const int done = (int)(done_end - cstart);    // columns counted from cstart
+      const int lo = (int)(ifirst - B - cstart);    // row r's band starts at lo + r
+      const double* yc = y + cstart;
+      for (int c0 = V * lane; c0 < done + V * lane; c0 += 64 * V * US) {
         TV l[US][RPW];
         double xv[US][V];
 #pragma unroll
         for (int u = 0; u < US; ++u) {
-          const int64_t cc = c0 + 64 * V * u;
+          const uint32_t cc = c0 + 64 * V * u;
 #pragma unroll
-          for (int e = 0; e < V; ++e) xv[u][e] = poll_load(y + min<int64_t>(cc + e, done_end - 1));
+          for (int e = 0; e < V; ++e) xv[u][e] = poll_load(yc + min<uint32_t>(cc + e, (uint32_t)done - 1));
 #pragma unroll
-          for (int r = 0; r < RPW; ++r) l[u][r] = *reinterpret_cast<const TV*>(rp[r] + cc);
+          for (int r = 0; r < RPW; ++r)
+            l[u][r] = *reinterpret_cast<const TV*>(rp[r] + cstart + cc);
         }
 #pragma unroll
         for (int u = 0; u < US; ++u) {
-          const int64_t cc = c0 + 64 * V * u;
+          const int cc = c0 + 64 * V * u;
 #pragma unroll
           for (int e = 0; e < V; ++e) {
-            const double xe = cc + e < done_end ? xv[u][e] : 0.0;
+            const double xe = cc + e < done ? xv[u][e] : 0.0;
 #pragma unroll
             for (int r = 0; r < RPW; ++r)
-              s[r] += (double)l[u][r][e] * (cc + e >= ifirst + r - B ? xe : 0.0);
+              s[r] += (double)l[u][r][e] * (cc + e >= lo + r ? xe : 0.0);
           }
         }
       }
     }
-    // blocks in flight, kdone .. k - 1 (at most GMAX - 1): their factor entries and this
-    // block's inverse diagonal block are loaded first; then wave 0 polls their solutions
-    // (one round trip when they are done) and passes them on through LDS
-    const int nfl = (int)(k - kdone);
-    T pf[GMAX - 1][RPW], dd[DL];
+    // blocks in flight, kdone .. kc - 1 (at most step - 1), up to FL at a time, the last
+    // ones together: their factor entries (and, before the last, this block's inverse
+    // diagonal block) are loaded first; then wave 0 polls their solutions (one round trip
+    // when they are done) and passes them on through LDS
+    T dd[DL];
+    int kf = kdone;
+#pragma unroll 1
+    for (;;) {
+      const int rest = kc - kf;
+      const int nfl = (int)(rest > FL ? (rest - 1) % FL + 1 : rest);
+      T pf[FL][RPW];
 #pragma unroll
-    for (int o = 0; o < GMAX - 1; ++o) {
-      const int64_t cc = min<int64_t>(kdone + o, max<int64_t>(k - 1, 0)) * SB + lane;
+      for (int o = 0; o < FL; ++o) {
+        const int cc = min<int>(kf + o, max<int>(kc - 1, 0)) * SB;
 #pragma unroll
-      for (int r = 0; r < RPW; ++r) pf[o][r] = rp[r][cc];
-    }
+        for (int r = 0; r < RPW; ++r) pf[o][r] = (rp[r] + cc)[(uint32_t)lane];
+      }
+      if (rest <= FL)
 #pragma unroll
-    for (int u = 0; u < DL; ++u) dd[u] = dv[k * SB * SB + threadIdx.x + SOLVE_THREADS * u];
-    if (nfl > 0) {
-      if (wave == 0) {
-        double xo[GMAX - 1];
-        int64_t spins = 0;
-        for (;;) {
-          bool ok = true;
+        for (int u = 0; u < DL; ++u)
+          dd[u] = (dv + (int64_t)min(k, ncb - 1) * SB * SB)[threadIdx.x + SOLVE_THREADS * u];
+      if (nfl > 0) {
+        if (wave == 0) {
+          double xo[FL];
+          int64_t spins = 0;
+          for (;;) {
+            bool ok = true;
 #pragma unroll
-          for (int o = 0; o < GMAX - 1; ++o) {
-            xo[o] = poll_load(y + min<int64_t>(kdone + o, k - 1) * SB + lane);
-            ok = ok && !is_mark(xo[o]);
+            for (int o = 0; o < FL; ++o) {
+              xo[o] = poll_load((y + min(kf + o, kf + nfl - 1) * SB) + (uint32_t)lane);
+              ok = ok && !is_mark(xo[o]);
+            }
+            if (__all(ok) || poll_give_up(spins, err)) break;
           }
-          if (__all(ok) || poll_give_up(spins, err)) break;
+#pragma unroll
+          for (int o = 0; o < FL; ++o) xs[o][lane] = xo[o];
         }
+        __syncthreads();
+        double xo[FL];
 #pragma unroll
-        for (int o = 0; o < GMAX - 1; ++o) xs[o][lane] = xo[o];
+        for (int o = 0; o < FL; ++o) xo[o] = xs[o][lane];
+#pragma unroll
+        for (int o = 0; o < FL; ++o) {
+          if (o >= nfl) break;
+          const int cc = (kf + o) * SB + lane;
+#pragma unroll
+          for (int r = 0; r < RPW; ++r)
+            s[r] += (double)pf[o][r] * (cc >= ifirst + r - B ? xo[o] : 0.0);
+        }
       }
-      __syncthreads();
-      double xo[GMAX - 1];
-#pragma unroll
-      for (int o = 0; o < GMAX - 1; ++o) xo[o] = xs[o][lane];
-#pragma unroll
-      for (int o = 0; o < GMAX - 1; ++o) {
-        if (o >= nfl) break;
-        const int64_t cc = (kdone + o) * SB + lane;
-#pragma unroll
-        for (int r = 0; r < RPW; ++r)
-          s[r] += (double)pf[o][r] * (cc >= ifirst + r - B ? xo[o] : 0.0);
-      }
+      if (rest <= FL) break;
+      kf += nfl;
+      __syncthreads();                             // xs is taken again
     }
     const double tot = reduce_rows8(s, lane);
+    if (k >= ncb) {                                // separator rows of a lower part
+      if (own) hand_over(y + i0 + ii, tot);
+      __syncthreads();
+      continue;
+    }
+    if (i0 >= sep && own) {                       // the lower part's share of these rows
+      int64_t spins = 0;
+      double t = poll_load(mate - (i0 + ii));
+      while (is_mark(t) && !poll_give_up(spins, err)) t = poll_load(mate - (i0 + ii));
+      bval -= t;
+    }
     if ((lane & 7) == 0) acc[ii] = own ? bval - tot : 0.0;
     __syncthreads();
     // y = Di acc: thread (wave, lane) holds Di[wave + 8 u][lane] (u < 8) from the prefetch,
@@ -1136,46 +1296,64 @@ __device__ __forceinline__ void band_solve_1_mat(int64_t n, int64_t B, int64_t l
     }
     __syncthreads();
   }
+  }
   // ---- backward: lanes own the block's 64 columns, waves split the band rows below it;
   // entry (r, c) = cb[r * rs + c]
+#pragma unroll 1
+  for (int seg = split ? 1 : 0; seg >= 0; --seg) {
+  if (seg && gs < 0) continue;
+  if (!seg && split) {                             // the separator's solution
+    use(own);
+    const int r0 = lower ? cols : sep;
+    for (int r = r0 + threadIdx.x; r < n; r += SOLVE_THREADS) {
+      int64_t spins = 0;
+      while (is_mark(poll_load(lower ? mate - r : z + r)) && !poll_give_up(spins, err)) {}
+    }
+    __syncthreads();
+  }
+  // blocks of the segment: all from kbeg to kend
+  const int kbeg = seg ? sep / SB : 0;
+  const int kend = seg || !split || lower ? (cols + SB - 1) / SB : sep / SB;
+  const int step = seg ? GS : G;
   const T* cb = base + B;
-  const int64_t rs = ld - 1;
-  for (int64_t t = g; t < nblk; t += G) {
-    const int64_t kb = nblk - 1 - t;
-    const int64_t i0 = kb * SB;
-    const int nb = (int)min<int64_t>(SB, n - i0);
-    const int64_t rend = min(min<int64_t>(n, i0 + nb + B), lrb[kb]);   // envelope end
-    const int64_t kdone = kb + G;                  // row blocks >= kdone complete
-    const int64_t done_beg = min<int64_t>(rend, kdone * SB);
-    const int64_t cidx = i0 + lane;
+  for (int kb = kend - 1 - (seg ? gs : g); kb >= kbeg; kb -= step) {
+    const int i0 = kb * SB;
+    const int nb = (int)min<int>(SB, cols - i0);
+    const int rend = min(min<int>(n, i0 + nb + B), (int)lrb[kb]);   // envelope end
+    const int kdone = min(kb + step, kend);    // row blocks >= kdone complete
+    const int done_beg = min<int>(rend, kdone * SB);
+    const int cidx = i0 + lane;
     double sacc = 0.0;
     {
       // lane l loads the V adjacent columns from V (l mod 64 / V) of the rows
       // r0 + 8 (V v + l / (64 / V)) (16 bytes, aligned as above), so one load covers V
       // rows; the row groups' sums are then added and handed to the lanes of their columns
-      constexpr int V = 16 / sizeof(T);
+      constexpr int V = 16 / (int)sizeof(T);
       constexpr int LPR = 64 / V;                   // lanes per row
       typedef T TV __attribute__((ext_vector_type(V)));
       const int pr = lane % LPR, hf = lane / LPR;
-      const int64_t cv = i0 + V * pr;
       double sv[V];
 #pragma unroll
       for (int e = 0; e < V; ++e) sv[e] = 0.0;
-      for (int64_t r0 = done_beg + wave; r0 < rend; r0 += SW * UB) {
+      const uint32_t rs32 = (uint32_t)rs, cv = V * pr;
+      const int lo = (int)(B + i0) + V * pr;         // row r reaches the columns from r - lo on
+      for (int r0 = done_beg + wave; r0 < rend; r0 += SW * UB) {
         TV l[UB / V];
-        const double xz = poll_load(z + min<int64_t>(r0 + SW * (lane % UB), rend - 1));
+        const int left = (int)(rend - 1 - r0);       // rows below r0 inside the envelope
+        const int rz = r0 + min<int>(SW * (lane % UB), left);
+        const double xz = poll_load(rz < cols ? z + rz : mate - rz);
+        const T* cr = cb + r0 * rs + i0;             // (scalar; the lanes' offsets are 32-bit)
+#pragma unroll
+        for (int v = 0; v < UB / V; ++v)
+          l[v] = *reinterpret_cast<const TV*>(
+              cr + ((uint32_t)min<int>(SW * (V * v + hf), left) * rs32 + cv));
 #pragma unroll
         for (int v = 0; v < UB / V; ++v) {
-          const int64_t rr = min<int64_t>(r0 + SW * (V * v + hf), rend - 1);
-          l[v] = *reinterpret_cast<const TV*>(cb + rr * rs + cv);
-        }
-#pragma unroll
-        for (int v = 0; v < UB / V; ++v) {
-          const int64_t rr = r0 + SW * (V * v + hf);
+          const int rr = SW * (V * v + hf);
           const double xu = __shfl(xz, V * v + hf);
 #pragma unroll
           for (int e = 0; e < V; ++e)
-            sv[e] += (double)l[v][e] * ((rr < rend && rr - B <= cv + e) ? xu : 0.0);
+            sv[e] += (double)l[v][e] * ((rr <= left && (int)r0 + rr <= lo + e) ? xu : 0.0);
         }
       }
 #pragma unroll
@@ -1188,57 +1366,69 @@ __device__ __forceinline__ void band_solve_1_mat(int64_t n, int64_t B, int64_t l
         if (lane % V == e) sacc = t;
       }
     }
-    // row blocks in flight, kb + 1 .. kin (at most GMAX - 1): factor entries and the
-    // inverse diagonal block first, then the polls of their final solutions (rows inside
-    // the band only) together with this block's forward solution
-    const int64_t kin = min<int64_t>(kdone - 1, (rend - 1) / SB);   // last row block in flight
-    const int nfl = (int)max<int64_t>(kin - kb, 0);
-    T pf[GMAX - 1][RPW], dd[DL];
-#pragma unroll
-    for (int o = 0; o < GMAX - 1; ++o)
-#pragma unroll
-      for (int r = 0; r < RPW; ++r)
-        pf[o][r] = cb[min<int64_t>((kb + 1 + o) * SB + wave + SW * r, n - 1) * rs + cidx];
-#pragma unroll
-    for (int u = 0; u < DL; ++u) dd[u] = dv[kb * SB * SB + threadIdx.x + SOLVE_THREADS * u];
-    // wave 0 polls this block's forward solution and the final solutions of the rows in
-    // flight (lane l: row l of each block), and passes them on through LDS
+    // row blocks in flight, kb + 1 .. kin (at most step - 1), up to FL at a time from the
+    // far end, the nearest together: factor entries and, before the last, the inverse
+    // diagonal block first, then the polls of their final solutions (rows inside the band
+    // only), the last together with this block's forward solution
+    const int kin = min<int>(kdone - 1, (rend - 1) / SB);   // last row block in flight
+    T dd[DL];
     double yown = 0.0;
-    if (wave == 0) {
-      double xo[GMAX - 1];
-      int64_t spins = 0;
-      for (;;) {
-        bool ok = true;
-        if (lane < nb) {
-          yown = poll_load(y + cidx);
-          ok = !is_mark(yown);
+    int kl = max(kin, kb);                     // the farthest one not yet taken
+#pragma unroll 1
+    for (;;) {
+      const int rest = kl - kb;
+      const int nfl = (int)(rest > FL ? (rest - 1) % FL + 1 : rest);
+      const int kf = kl - nfl + 1;             // blocks kf .. kl
+      const bool lastc = rest <= FL;
+      T pf[FL][RPW];
+#pragma unroll
+      for (int o = 0; o < FL; ++o)
+#pragma unroll
+        for (int r = 0; r < RPW; ++r)
+          pf[o][r] = cb[min<int>((kf + o) * SB + wave + SW * r, n - 1) * rs + cidx];
+      if (lastc)
+#pragma unroll
+        for (int u = 0; u < DL; ++u) dd[u] = (dv + (int64_t)kb * SB * SB)[threadIdx.x + SOLVE_THREADS * u];
+      // wave 0 polls (lane l: row l of each block) and passes the values on through LDS
+      if (wave == 0) {
+        double xo[FL];
+        int64_t spins = 0;
+        for (;;) {
+          bool ok = true;
+          if (lastc && lane < nb) {
+            yown = poll_load(y + cidx);
+            ok = !is_mark(yown);
+          }
+#pragma unroll
+          for (int o = 0; o < FL; ++o) {
+            const int rr = (kf + o) * SB + lane;
+            const bool need = o < nfl && rr < rend;
+            xo[o] = poll_load(z + min<int>(rr, rend - 1));
+            ok = ok && (!need || !is_mark(xo[o]));
+          }
+          if (__all(ok) || poll_give_up(spins, err)) break;
         }
 #pragma unroll
-        for (int o = 0; o < GMAX - 1; ++o) {
-          const int64_t rr = (kb + 1 + o) * SB + lane;
-          const bool need = o < nfl && rr < rend;
-          xo[o] = poll_load(z + min<int64_t>(rr, rend - 1));
-          ok = ok && (!need || !is_mark(xo[o]));
+        for (int o = 0; o < FL; ++o) xs[o][lane] = xo[o];
+      }
+      __syncthreads();
+      double xr[FL][RPW];
+#pragma unroll
+      for (int o = 0; o < FL; ++o)
+#pragma unroll
+        for (int r = 0; r < RPW; ++r) xr[o][r] = xs[o][wave + SW * r];
+#pragma unroll
+      for (int o = 0; o < FL; ++o) {
+        if (o >= nfl) break;
+#pragma unroll
+        for (int r = 0; r < RPW; ++r) {
+          const int rr = (kf + o) * SB + wave + SW * r;
+          sacc += (double)pf[o][r] * ((rr < rend && rr - B <= cidx) ? xr[o][r] : 0.0);
         }
-        if (__all(ok) || poll_give_up(spins, err)) break;
       }
-#pragma unroll
-      for (int o = 0; o < GMAX - 1; ++o) xs[o][lane] = xo[o];
-    }
-    __syncthreads();
-    double xr[GMAX - 1][RPW];
-#pragma unroll
-    for (int o = 0; o < GMAX - 1; ++o)
-#pragma unroll
-      for (int r = 0; r < RPW; ++r) xr[o][r] = xs[o][wave + SW * r];
-#pragma unroll
-    for (int o = 0; o < GMAX - 1; ++o) {
-      if (o >= nfl) break;
-#pragma unroll
-      for (int r = 0; r < RPW; ++r) {
-        const int64_t rr = (kb + 1 + o) * SB + wave + SW * r;
-        sacc += (double)pf[o][r] * ((rr < rend && rr - B <= cidx) ? xr[o][r] : 0.0);
-      }
+      if (lastc) break;
+      kl -= nfl;
+      __syncthreads();                             // xs is taken again
     }
     part[wave][lane] = sacc;
     if (wave == 0) acc[lane] = lane < nb ? yown : 0.0;
@@ -1267,55 +1457,110 @@ __device__ __forceinline__ void band_solve_1_mat(int64_t n, int64_t B, int64_t l
     }
     __syncthreads();
   }
+  }
 }
 
-// Matrices j of one band set: work-group (g, j) at blockIdx.x = g * n_pad + j.
+// Work-groups of one class (blockIdx mod 8, hence of one XCD) take their places in a list of
+// (matrix, group, part) in the order they start, from a counter that the marker fill resets.
+// The two parts of a matrix wait for each other, and so do the groups of a part: a matrix's
+// work-groups are neighbours in the list, so those running are a prefix of it, every
+// complete matrix of the prefix finishes, and its slots go to the next ones - no launch
+// waits for ever, however few of its work-groups are resident at a time.
+__device__ inline int take_place(int* counter) {
+  __shared__ int q;
+  if (threadIdx.x == 0) q = atomicAdd(counter, 1);
+  __syncthreads();
+  return __builtin_amdgcn_readfirstlane(q);
+}
+
+// A work-group-uniform table entry, into scalar registers (read after an atomic, the
+// compiler would otherwise keep its fields, and all that follows from them, per lane).
+template <class V>
+__device__ inline V uniform_load(const V* p) {
+  static_assert(sizeof(V) % 4 == 0, "whole words");
+  V out;
+  int w[sizeof(V) / 4];
+#pragma unroll
+  for (size_t i = 0; i < sizeof(V) / 4; ++i)
+    w[i] = __builtin_amdgcn_readfirstlane(reinterpret_cast<const int*>(p)[i]);
+  __builtin_memcpy(&out, w, sizeof(V));
+  return out;
+}
+
+// (part, group) of this work-group in a launch over one band set of n_mat matrices, G groups
+// per part, both parts of a matrix (PP = 2 if the set has split matrices) in turn; part -1:
+// none
+__device__ inline int2 set_place(const int32_t* part_of, int n_mat, int G, int PP,
+                                 int* counters) {
+  const int x = blockIdx.x & 7, q = take_place(counters + x);
+  const int j = q / (G * PP) * 8 + x, m = q % (G * PP);
+  if (j >= n_mat) return {-1, 0};
+  return {uniform_load(part_of + 2 * j + m % PP), m / PP};
+}
+
+// The parts of one band set (set_place)
 template <class T, bool COARSE>
 __global__ void __launch_bounds__(SOLVE_THREADS) k_band_solve_1(
-    BandArgs a, const T* v, const T* dinv, const int64_t* boff, const int64_t* xoff,
-    const double* xall, double* yall, double* zall, const int64_t* yoff, int G, int n_pad,
-    int n_mat, int* err) {
-  const int g = blockIdx.x / n_pad, j = blockIdx.x % n_pad;
-  if (j >= n_mat || g >= G) return;
-  const int64_t n = a.n[j], B = a.B[j], ld = a.ld[j];
-  if (n == 0) return;
-  band_solve_1_mat<T>(n, B, ld, v + a.off[j], dinv + boff[j], a.fcb + a.eoff[j],
-                      a.lrb + a.eoff[j], xall + xoff[j], yall + yoff[j], zall + yoff[j], g, G,
+    BandArgs a, const int32_t* part_of, const T* v, const T* dinv, const int64_t* xoff,
+    const double* xall, double* yall, double* zall, int G, int PP, int n_mat, int* err) {
+  const int2 pg = set_place(part_of, n_mat, G, PP, err + 1);
+  if (pg.x < 0) return;
+  auto load = [&](int i) -> Solve1<T> {
+    const BandPart P = uniform_load(a.part + i);
+    const int mp = P.kind == PART_WHOLE ? i
+                                        : uniform_load(part_of + 2 * P.mat + (P.kind == PART_UPPER));
+    const int64_t mo = uniform_load(&a.part[mp].yoff);
+    return {P.rows, P.cols, P.kind == PART_UPPER ? P.sep : P.rows, P.N, P.B, P.ld, P.kind,
+            v + P.off, dinv + P.boff, a.fcb + P.eoff, a.lrb + P.eoff,
+            xall + uniform_load(xoff + P.mat), yall + P.yoff, zall + P.yoff,
+            (P.kind == PART_LOWER ? zall : yall) + mo};
+  };
+  const BandPart P = uniform_load(a.part + pg.x);
+  if (P.rows == 0) return;
+  band_solve_1_mat<T>(load, pg.x,
+                      P.kind == PART_WHOLE ? -1 : uniform_load(part_of + 2 * P.mat), pg.y, G,
                       err);
 }
 
-// The matrices of several band sets in one launch (all of one precision): work-group i
-// takes group work[2 i + 1] of matrix work[2 i] (none if negative); matrix j's rows,
-// bandwidth, group count, factor, inverse diagonal blocks, right-hand side and scratch
-// come from tab[j].
+// The parts of several band sets in one launch (all of one precision): the q-th work-group
+// of class x to start takes group work[2 i + 1] of part work[2 i], i = q n_class + x (none
+// if negative).
 template <class T>
-__global__ void __launch_bounds__(SOLVE_THREADS) k_band_solve_1_multi(const BandPtrs* tab,
-                                                                       const int32_t* work,
-                                                                       int* err) {
-  const int j = work[2 * blockIdx.x], g = work[2 * blockIdx.x + 1];
+__global__ void __launch_bounds__(SOLVE_THREADS) k_band_solve_1_multi(const BandPtrs* __restrict__ tab,
+                                                                       const int32_t* __restrict__ work,
+                                                                       int n_class, int* err) {
+  const int x = blockIdx.x % n_class;
+  const int i = take_place(err + 1 + x) * n_class + x;
+  const int j = uniform_load(work + 2 * i), g = uniform_load(work + 2 * i + 1);
   if (j < 0) return;
-  const BandPtrs t = tab[j];
+  auto load = [&](int p) -> Solve1<T> {
+    const BandPtrs t = uniform_load(tab + p);
+    return {t.n, t.cols, t.sep, t.N, t.B, t.B + 1, (int)t.kind, static_cast<const T*>(t.v),
+            static_cast<const T*>(t.dinv), t.fcb, t.lrb, t.x, t.y, t.z, t.mate};
+  };
+  const BandPtrs t = uniform_load(tab + j);
   if (t.n == 0) return;
-  band_solve_1_mat<T>(t.n, t.B, t.B + 1, static_cast<const T*>(t.v),
-                      static_cast<const T*>(t.dinv), t.fcb, t.lrb, t.x, t.y, t.z, g, (int)t.G,
-                      err);
+  // (an upper part stands right before its lower part in the table)
+  const int upper = t.kind == PART_WHOLE ? -1 : t.kind == PART_UPPER ? j : j - 1;
+  band_solve_1_mat<T>(load, j, upper, g, (int)t.G, err);
 }
 
-// y and z scratch of every matrix of a multi-set solve back to the marker
-__global__ void k_fill_mark_multi(const BandPtrs* tab) {
+// y and z scratch of every part of a multi-set solve back to the marker, its counters to 0
+__global__ void k_fill_mark_multi(const BandPtrs* tab, int* counters) {
   const BandPtrs t = tab[blockIdx.y];
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (blockIdx.y == 0 && i < 8) counters[i] = 0;
   if (i < (t.n + SB - 1) / SB * SB) {
     t.y[i] = __longlong_as_double((long long)YMARK);
     t.z[i] = __longlong_as_double((long long)YMARK);
   }
 }
 
-// x_j <- z_j for every matrix of a multi-set solve
+// x <- z for every part of a multi-set solve
 __global__ void k_copy_out_multi(const BandPtrs* tab) {
   const BandPtrs t = tab[blockIdx.y];
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < t.n) t.x[i] = t.z[i];
+  if (i < t.cols) t.x[t.kind == PART_LOWER ? t.N - 1 - i : i] = t.z[i];
 }
 
 // ---- M right-hand sides per matrix (M a multiple of 8, at most MC; row-major, row
@@ -1341,9 +1586,9 @@ constexpr int AL = SB * SB / MT;                  // band-chunk entries per thre
 
 template <class T, int M>
 __global__ void __launch_bounds__(MT) k_band_solve_m(
-    BandArgs a, const T* v, const T* dinv, const int64_t* boff, const int64_t* xoff,
-    const double* xall, T* yall, T* zall, const int64_t* yoff, int G, int n_pad,
-    int n_mat, const int32_t* active, int* err) {
+    BandArgs a, const int32_t* part_of, const T* v, const T* dinv, const int64_t* xoff,
+    const double* xall, T* yall, T* zall, int G, int PP, int n_mat, const int32_t* active,
+    int* err) {
   typedef Mfma<T> MF;
   typedef typename MF::S S;
   typedef T Y;                                    // hand-over scratch: the factor's precision
@@ -1352,24 +1597,44 @@ __global__ void __launch_bounds__(MT) k_band_solve_m(
   constexpr int YL = SB * M / MT;                 // solution-chunk entries per thread
   __shared__ S Ab[2][SB][SB + 1];                 // band chunks (double buffer); buffer 0
   __shared__ S Yc[2][SB * MP];                    // holds the inverse block in finish
-  const int g = blockIdx.x / n_pad, j = blockIdx.x % n_pad;
-  if (j >= n_mat || g >= G) return;
-  if (active && !active[j]) return;
-  const int64_t n = a.n[j], B = a.B[j], ld = a.ld[j];
+  const int2 pg = set_place(part_of, n_mat, G, PP, err + 1);
+  const int g = pg.y;
+  if (pg.x < 0) return;
+  int64_t n, B, rs, n1, ncb, sep;                 // n1: last row of the matrix; ncb: blocks
+  const T *cb, *dv;                               // with columns of their own
+  const int64_t *fcb, *lrb;
+  const double* x;
+  Y *y, *z;
+  const Y* mate;                                  // the other part's scratch, row r at n1 - r
+  bool lower;
+  const int mat = uniform_load(&a.part[pg.x].mat);
+  if (active && !uniform_load(active + mat)) return;
+  auto use = [&](int part) {
+    const BandPart P = uniform_load(a.part + part);
+    n = P.rows, B = P.B, rs = P.ld - 1, n1 = P.N - 1;
+    ncb = (P.cols + SB - 1) / SB;
+    sep = P.kind == PART_UPPER ? P.sep : P.rows;
+    lower = P.kind == PART_LOWER;
+    cb = v + P.off + B;                           // entry (r, c) = cb[r * rs + c]
+    dv = dinv + P.boff;
+    fcb = a.fcb + P.eoff;
+    lrb = a.lrb + P.eoff;
+    x = xall + uniform_load(xoff + mat);
+    y = yall + P.yoff * M;
+    z = zall + P.yoff * M;
+    const int mp = P.kind == PART_WHOLE ? part : uniform_load(part_of + 2 * mat + !lower);
+    mate = (lower ? zall : yall) + uniform_load(&a.part[mp].yoff) * M;
+  };
+  use(pg.x);
   if (n == 0) return;
-  const T* cb = v + a.off[j] + B;                 // entry (r, c) = cb[r * rs + c]
-  const int64_t rs = ld - 1;
-  const T* dv = dinv + boff[j];
-  const int64_t* fcb = a.fcb + a.eoff[j];
-  const int64_t* lrb = a.lrb + a.eoff[j];
-  const double* x = xall + xoff[j];
-  Y* y = yall + yoff[j] * M;
-  Y* z = zall + yoff[j] * M;
+  // the separator of a split matrix is swept by the work-groups of both parts (see
+  // band_solve_1_mat); the polls of every chunk are all the waiting it needs
+  const bool own_lower = lower, split = lower || sep < n;
+  const int upper = uniform_load(part_of + 2 * mat);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int rt = wave & 3, ct = wave >> 2;        // this wave's row and column tile
   const bool tile = ct < NCT;                      // waves past the column tiles only stage
   const int li = lane & 15, lk = lane >> 4;
-  const int64_t nblk = (n + SB - 1) / SB;
   if constexpr (MP > M)
     for (int idx = threadIdx.x; idx < 2 * SB * (MP - M); idx += MT) {
       const int e = idx % (SB * (MP - M));
@@ -1378,21 +1643,26 @@ __global__ void __launch_bounds__(MT) k_band_solve_m(
   // forward chunk kk of block i0: band rows i0.., columns 64 kk..; backward chunk kk:
   // band rows 64 kk.., columns i0..; both with solution rows 64 kk..  Thread t stages band
   // rows t / 64 + 8 u at column t % 64.
+  // entry idx of the solution rows of chunk kk: the part's own, or the separator's from the
+  // upper part's backward solutions
+  auto sol = [&](bool bwd, int64_t kk, int64_t idx) -> const Y* {
+    if (bwd && kk >= ncb) return mate + (n1 - kk * SB - idx / M) * M + idx % M;
+    return (bwd ? z : y) + kk * SB * M + idx;
+  };
   auto fetch = [&](bool bwd, int64_t i0, int64_t kk, T (&fa)[AL], Y (&fy)[YL]) {
     const int64_t r0 = (bwd ? kk * SB : i0) + wave;
     const int64_t c = (bwd ? i0 : kk * SB) + lane;
 #pragma unroll
     for (int u = 0; u < AL; ++u) fa[u] = cb[min<int64_t>(r0 + 8 * u, n - 1) * rs + c];
     const int64_t yend = min<int64_t>((int64_t)SB * M, (n - kk * SB) * M);   // rows < n
-    const Y* xs = (bwd ? z : y) + kk * SB * M;
 #pragma unroll
-    for (int u = 0; u < YL; ++u) fy[u] = poll_load(xs + min<int64_t>(threadIdx.x + MT * u, yend - 1));
+    for (int u = 0; u < YL; ++u)
+      fy[u] = poll_load(sol(bwd, kk, min<int64_t>(threadIdx.x + MT * u, yend - 1)));
   };
   auto stage = [&](int buf, bool bwd, int64_t i0, int nb, int64_t kk, const T (&fa)[AL],
                    Y (&fy)[YL]) {
     {                                              // until every needed entry is handed over
       const int64_t yend = min<int64_t>((int64_t)SB * M, (n - kk * SB) * M);
-      const Y* xs = (bwd ? z : y) + kk * SB * M;
       // the first test on the values already loaded is straight-line code, so the wait
       // before it covers only this chunk's loads, not the prefetch of the next one; the
       // polling loop is the slow path of a chunk still in flight
@@ -1405,7 +1675,7 @@ __global__ void __launch_bounds__(MT) k_band_solve_m(
           if (poll_give_up(spins, err)) break;
 #pragma unroll
           for (int u = 0; u < YL; ++u)
-            fy[u] = poll_load(xs + min<int64_t>(threadIdx.x + MT * u, yend - 1));
+            fy[u] = poll_load(sol(bwd, kk, min<int64_t>(threadIdx.x + MT * u, yend - 1)));
           bool again = false;
 #pragma unroll
           for (int u = 0; u < YL; ++u)
@@ -1491,7 +1761,23 @@ __global__ void __launch_bounds__(MT) k_band_solve_m(
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int64_t row = min<int64_t>(i0 + 16 * rt + MF::row(r, lk), n - 1);
-        bb[r] = x[row * M + cc];
+        bb[r] = x[(lower ? n1 - row : row) * M + cc];
+      }
+      if (i0 >= sep) {                             // the lower part's share of these rows
+        int64_t spins = 0;
+        Y tb[4];
+        for (;;) {
+          bool ok = true;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int ii = 16 * rt + MF::row(r, lk);
+            tb[r] = poll_load(mate + (n1 - i0 - min(ii, nb - 1)) * M + cc);
+            ok = ok && (!tile || ii >= nb || !is_mark(tb[r]));
+          }
+          if (__all(ok) || poll_give_up(spins, err)) break;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) bb[r] -= (double)tb[r];
       }
     } else {
       int64_t spins = 0;
@@ -1532,38 +1818,58 @@ __global__ void __launch_bounds__(MT) k_band_solve_m(
     __syncthreads();
   };
   // ---- forward: chunks in increasing order; those from kdone on are still in flight
-  for (int64_t k = g; k < nblk; k += G) {
-    const int64_t i0 = k * SB;
-    const int nb = (int)min<int64_t>(SB, n - i0);
-    const int64_t kfirst = max(max<int64_t>(i0 - B, 0), fcb[k]) / SB;   // envelope start
-    T dd[AL];
+#pragma unroll 1
+  for (int seg = 0; seg < (split ? 2 : 1); ++seg) {
+    if (seg) use(upper);
+    const int64_t kend = seg || !split || lower ? (n + SB - 1) / SB : sep / SB;
+    for (int64_t k = seg ? sep / SB + 2 * g + own_lower : g; k < kend; k += seg ? 2 * G : G) {
+      const int64_t i0 = k * SB;
+      const int nb = (int)min<int64_t>(SB, n - i0);
+      const int64_t kfirst = max(max<int64_t>(i0 - B, 0), fcb[k]) / SB;   // envelope start
+      T dd[AL];
 #pragma unroll
-    for (int u = 0; u < AL; ++u) dd[u] = dv[k * SB * SB + threadIdx.x + MT * u];
-    typename MF::V acc = {0, 0, 0, 0};
-    sweep(false, i0, nb, kfirst, k - kfirst, 1, acc);
-    finish(false, i0, nb, dd, acc);
+      for (int u = 0; u < AL; ++u) dd[u] = dv[min(k, ncb - 1) * SB * SB + threadIdx.x + MT * u];
+      typename MF::V acc = {0, 0, 0, 0};
+      sweep(false, i0, nb, kfirst, min(k, ncb) - kfirst, 1, acc);
+      if (k < ncb) {
+        finish(false, i0, nb, dd, acc);
+      } else {                                     // separator rows of a lower part
+        if (tile)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int ii = 16 * rt + MF::row(r, lk), col = 16 * ct + li;
+            if (ii < nb && col < M) hand_over(y + (i0 + ii) * M + col, (Y)acc[r]);
+          }
+        __syncthreads();
+      }
+    }
   }
   // ---- backward: chunks from the far end of the band inwards
-  for (int64_t t = g; t < nblk; t += G) {
-    const int64_t kb = nblk - 1 - t;
-    const int64_t i0 = kb * SB;
-    const int nb = (int)min<int64_t>(SB, n - i0);
-    const int64_t klast = (min(min<int64_t>(n, i0 + nb + B), lrb[kb]) - 1) / SB;   // last row block
-    T dd[AL];
+#pragma unroll 1
+  for (int seg = split ? 1 : 0; seg >= 0; --seg) {
+    if (!seg && split) use(pg.x);
+    const int64_t kbeg = seg ? sep / SB : 0;
+    const int64_t kend = seg || !split || lower ? ncb : sep / SB;
+    for (int64_t kb = kend - 1 - (seg ? 2 * g + own_lower : g); kb >= kbeg;
+         kb -= seg ? 2 * G : G) {
+      const int64_t i0 = kb * SB;
+      const int nb = (int)min<int64_t>(SB, n - i0);
+      const int64_t klast = (min(min<int64_t>(n, i0 + nb + B), lrb[kb]) - 1) / SB;   // last row block
+      T dd[AL];
 #pragma unroll
-    for (int u = 0; u < AL; ++u) dd[u] = dv[kb * SB * SB + threadIdx.x + MT * u];
-    typename MF::V acc = {0, 0, 0, 0};
-    sweep(true, i0, nb, klast, klast - kb, -1, acc);
-    finish(true, i0, nb, dd, acc);
+      for (int u = 0; u < AL; ++u) dd[u] = dv[kb * SB * SB + threadIdx.x + MT * u];
+      typename MF::V acc = {0, 0, 0, 0};
+      sweep(true, i0, nb, klast, klast - kb, -1, acc);
+      finish(true, i0, nb, dd, acc);
+    }
   }
 }
 
-// Work-groups per matrix: as many as keep every work-group of the launch resident at once
-// (the waits rely on it); at most GMAX for one right-hand side, 8 for several.  The solves
-// of one context are stream-ordered, so a launch may count on the whole machine (other
-// kernels can only delay the dispatch of its groups, not block them).  When several
-// contexts solve concurrently (share > 1) each gets an equal part of three quarters of it,
-// so that all their launches fit together.
+// Work-groups per part: as many as keep every work-group of the launch resident at once (a
+// part waits at the pace of its slowest group); at most GMAX for one right-hand side, 8 for
+// several.  The solves of one context are stream-ordered, so a launch may count on the
+// whole machine.  When several contexts solve concurrently (share > 1) each gets an equal
+// part of three quarters of it, so that all their launches fit together.
 static int solve_groups(BandSet& bs, const void* kernel, int which) {
   if (bs.solve_groups[which] > 0) return bs.solve_groups[which];
   int dev = 0, cus = 0, per_cu = 0;
@@ -1577,7 +1883,7 @@ static int solve_groups(BandSet& bs, const void* kernel, int which) {
   int G = 1;
   const int top = bs.force_groups[which] > 0 ? std::min(bs.force_groups[which], cap) : cap;
   for (int c = top; c >= 2; --c)
-    if ((int64_t)bs.n_mat * c <= capacity && bs.max_n >= (int64_t)2 * SB * c) {
+    if ((int64_t)bs.n_part * c <= capacity && bs.max_cols >= (int64_t)2 * SB * c) {
       G = c;
       break;
     }
@@ -1585,62 +1891,57 @@ static int solve_groups(BandSet& bs, const void* kernel, int which) {
   return G;
 }
 
-// The launch's error word (raised by a poll that timed out), zero until a check clears it
-static int* solve_err(BandSet& bs, hipStream_t st, int& n_pad) {
-  n_pad = (bs.n_mat + 7) / 8 * 8;                  // all groups of a matrix on one XCD
+// The launch's error word (raised by a poll that timed out), zero until a check clears it;
+// the counters of take_place follow it
+static int* solve_err(BandSet& bs, hipStream_t st) {
   if (!bs.err.n) {
-    bs.err.alloc(1);
+    bs.err.alloc(1 + 8);
     zero(bs.err, st);
   }
   return bs.err.p;
 }
+static int solve_parts(const BandSet& bs) { return bs.split ? 2 : 1; }
+static unsigned solve_grid(const BandSet& bs, int G) {
+  return (unsigned)((bs.n_mat + 7) / 8 * 8 * G * solve_parts(bs));
+}
 
-__global__ void k_fill_mark(double* p, int64_t n) {
+__global__ void k_fill_mark(double* p, int64_t n, int* counters) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < 8) counters[i] = 0;
   if (i < n) p[i] = __longlong_as_double((long long)YMARK);
 }
 
 // The forward and backward solution scratch of the single-right-hand-side solve (y, then
 // z, 64-aligned segments per matrix), reset to the marker by a fill kernel on the stream
 // (so the launch can be captured in a graph).
-static void alloc_solve1_scratch(BandSet& bs, hipStream_t st) {
-  if (bs.d_yoff.n) return;
-  std::vector<int64_t> yo(bs.n_mat + 1, 0);
-  for (int j = 0; j < bs.n_mat; ++j) yo[j + 1] = yo[j] + (bs.n[j] + SB - 1) / SB * SB;
-  bs.ybuf.alloc(2 * std::max<int64_t>(yo[bs.n_mat], 1));
-  bs.d_yoff.alloc(bs.n_mat + 1);
-  to_dev(bs.d_yoff.p, yo.data(), bs.n_mat + 1, st);
-  GX_HIP(hipStreamSynchronize(st));                // yo is a local host vector
+static void alloc_solve1_scratch(BandSet& bs) {
+  if (!bs.ybuf.n) bs.ybuf.alloc(2 * std::max<int64_t>(bs.rows, 8));
 }
 
 static double* solve1_scratch(BandSet& bs, hipStream_t st) {
-  alloc_solve1_scratch(bs, st);
+  alloc_solve1_scratch(bs);
   hipLaunchKernelGGL(k_fill_mark, dim3(nblocks((int64_t)bs.ybuf.n, 256)), dim3(256), 0, st,
-                     bs.ybuf.p, (int64_t)bs.ybuf.n);
+                     bs.ybuf.p, (int64_t)bs.ybuf.n, solve_err(bs, st) + 1);
   return bs.ybuf.p;
 }
 
-// x_j <- z_j for every matrix (the solutions out of the scratch)
-__global__ void k_copy_out(const int64_t* nrows, const int64_t* xoff, const int64_t* yoff,
-                           const double* z, double* x) {
-  const int j = blockIdx.y;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < nrows[j]) x[xoff[j] + i] = z[yoff[j] + i];
-}
-
-__global__ void k_fill_mark32(float* p, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = __uint_as_float(YMARK32);
-}
-
-// z_j -> x_j for the active matrices (n_j rows of w columns)
+// The solutions out of the scratch: rows of each part's own columns, w right-hand sides, of
+// the active matrices
 template <class Y>
-__global__ void k_copy_out_m(const int64_t* nrows, const int64_t* xoff, const int64_t* yoff,
-                             int w, const Y* z, double* x, const int32_t* active) {
-  const int j = blockIdx.y;
-  if (active && !active[j]) return;
+__global__ void k_copy_out(const BandPart* part, const int64_t* xoff, int w, const Y* z,
+                           double* x, const int32_t* active) {
+  const BandPart& P = part[blockIdx.y];
+  if (active && !active[P.mat]) return;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < nrows[j] * w) x[xoff[j] + i] = (double)z[yoff[j] * w + i];
+  if (i >= P.cols * w) return;
+  const int64_t r = i / w, o = P.kind == PART_LOWER ? (P.N - 1 - r) * w + (i - r * w) : i;
+  x[xoff[P.mat] + o] = (double)z[P.yoff * w + i];
+}
+
+__global__ void k_fill_mark32(float* p, int64_t n, int* counters) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < 8) counters[i] = 0;
+  if (i < n) p[i] = __uint_as_float(YMARK32);
 }
 
 template <int M>
@@ -1648,33 +1949,32 @@ static void launch_m(BandSet& bs, const BandArgs& a, const int64_t* d_xoff, doub
                      hipStream_t st, const int32_t* active) {
   const int G = bs.fp32 ? solve_groups(bs, reinterpret_cast<const void*>(&k_band_solve_m<float, M>), 1)
                         : solve_groups(bs, reinterpret_cast<const void*>(&k_band_solve_m<double, M>), 1);
-  int n_pad = 0;
-  int* err = solve_err(bs, st, n_pad);
-  // y and z scratch of M columns: segments at yoff[j] * M rows (64-aligned row offsets)
-  if (!bs.d_yoff.n) (void)solve1_scratch(bs, st);
-  const int64_t rows = (int64_t)bs.ybuf.n / 2;     // padded rows of all matrices
+  const int PP = solve_parts(bs);
+  int* err = solve_err(bs, st);
+  // y and z scratch of M columns: segments at yoff * M (64-aligned row offsets)
+  const int64_t rows = std::max<int64_t>(bs.rows, 8);
   if (bs.mbuf.n < (size_t)(2 * rows * MC)) bs.mbuf.alloc(2 * rows * MC);
-  const dim3 cgrid(nblocks(bs.max_n * M, 256), bs.n_mat);
+  const dim3 cgrid(nblocks(bs.max_cols * M, 256), bs.n_part);
   if (bs.fp32) {                                   // FP32 scratch in the same buffer
     float* y = reinterpret_cast<float*>(bs.mbuf.p);
     float* z = y + rows * M;
     hipLaunchKernelGGL(k_fill_mark32, dim3(nblocks(2 * rows * M, 256)), dim3(256), 0, st, y,
-                       2 * rows * M);
-    hipLaunchKernelGGL((k_band_solve_m<float, M>), dim3(G * n_pad), dim3(MT), 0, st, a, bs.v32.p,
-                       bs.dinv32.p, bs.d_boff.p, d_xoff, x, y, z, bs.d_yoff.p, G, n_pad,
-                       bs.n_mat, active, err);
-    hipLaunchKernelGGL(k_copy_out_m<float>, cgrid, dim3(256), 0, st, bs.d_n.p, d_xoff,
-                       bs.d_yoff.p, M, z, x, active);
+                       2 * rows * M, err + 1);
+    hipLaunchKernelGGL((k_band_solve_m<float, M>), dim3(solve_grid(bs, G)), dim3(MT), 0, st, a,
+                       bs.d_part_of.p, bs.v32.p, bs.dinv32.p, d_xoff, x, y, z, G, PP, bs.n_mat,
+                       active, err);
+    hipLaunchKernelGGL(k_copy_out<float>, cgrid, dim3(256), 0, st, bs.d_part.p, d_xoff, M, z, x,
+                       active);
   } else {
     double* y = bs.mbuf.p;
     double* z = bs.mbuf.p + rows * M;
     hipLaunchKernelGGL(k_fill_mark, dim3(nblocks(2 * rows * M, 256)), dim3(256), 0, st, y,
-                       2 * rows * M);
-    hipLaunchKernelGGL((k_band_solve_m<double, M>), dim3(G * n_pad), dim3(MT), 0, st, a,
-                       bs.v64.p, bs.dinv64.p, bs.d_boff.p, d_xoff, x, y, z, bs.d_yoff.p, G,
-                       n_pad, bs.n_mat, active, err);
-    hipLaunchKernelGGL(k_copy_out_m<double>, cgrid, dim3(256), 0, st, bs.d_n.p, d_xoff,
-                       bs.d_yoff.p, M, z, x, active);
+                       2 * rows * M, err + 1);
+    hipLaunchKernelGGL((k_band_solve_m<double, M>), dim3(solve_grid(bs, G)), dim3(MT), 0, st, a,
+                       bs.d_part_of.p, bs.v64.p, bs.dinv64.p, d_xoff, x, y, z, G, PP, bs.n_mat,
+                       active, err);
+    hipLaunchKernelGGL(k_copy_out<double>, cgrid, dim3(256), 0, st, bs.d_part.p, d_xoff, M, z, x,
+                       active);
   }
 }
 
@@ -1721,30 +2021,30 @@ void band_solve(BandSet& bs, const int64_t* d_xoff, double* x, hipStream_t st, i
     GX_HIP(hipGetLastError());
     return;
   }
-  BandArgs a{bs.d_n.p, bs.d_B.p, bs.d_ld.p, bs.d_off.p, bs.d_eoff.p, bs.d_fcb.p, bs.d_lrb.p};
-  int n_pad = 0;
+  const BandArgs a{bs.d_part.p, bs.d_fcb.p, bs.d_lrb.p, 0};
   if (ncol == 1 && !active) {
     const void* kf = bs.fp32 ? reinterpret_cast<const void*>(&k_band_solve_1<float, false>)
                    : bs.coarse ? reinterpret_cast<const void*>(&k_band_solve_1<double, true>)
                                : reinterpret_cast<const void*>(&k_band_solve_1<double, false>);
-    const int G = solve_groups(bs, kf, 0);
-    int* err = solve_err(bs, st, n_pad);
+    const int G = solve_groups(bs, kf, 0), PP = solve_parts(bs);
+    const dim3 grid(solve_grid(bs, G));
+    int* err = solve_err(bs, st);
     double* y = solve1_scratch(bs, st);
     double* z = y + bs.ybuf.n / 2;
     if (bs.fp32)
-      hipLaunchKernelGGL((k_band_solve_1<float, false>), dim3(G * n_pad), dim3(SOLVE_THREADS), 0,
-                         st, a, bs.v32.p, bs.dinv32.p, bs.d_boff.p, d_xoff, x, y, z,
-                         bs.d_yoff.p, G, n_pad, bs.n_mat, err);
+      hipLaunchKernelGGL((k_band_solve_1<float, false>), grid, dim3(SOLVE_THREADS), 0, st, a,
+                         bs.d_part_of.p, bs.v32.p, bs.dinv32.p, d_xoff, x, y, z, G, PP,
+                         bs.n_mat, err);
     else if (bs.coarse)
-      hipLaunchKernelGGL((k_band_solve_1<double, true>), dim3(G * n_pad), dim3(SOLVE_THREADS), 0,
-                         st, a, bs.v64.p, bs.dinv64.p, bs.d_boff.p, d_xoff, x, y, z,
-                         bs.d_yoff.p, G, n_pad, bs.n_mat, err);
+      hipLaunchKernelGGL((k_band_solve_1<double, true>), grid, dim3(SOLVE_THREADS), 0, st, a,
+                         bs.d_part_of.p, bs.v64.p, bs.dinv64.p, d_xoff, x, y, z, G, PP,
+                         bs.n_mat, err);
     else
-      hipLaunchKernelGGL((k_band_solve_1<double, false>), dim3(G * n_pad), dim3(SOLVE_THREADS), 0,
-                         st, a, bs.v64.p, bs.dinv64.p, bs.d_boff.p, d_xoff, x, y, z,
-                         bs.d_yoff.p, G, n_pad, bs.n_mat, err);
-    hipLaunchKernelGGL(k_copy_out, dim3(nblocks(bs.max_n, 256), bs.n_mat), dim3(256), 0, st,
-                       bs.d_n.p, d_xoff, bs.d_yoff.p, z, x);
+      hipLaunchKernelGGL((k_band_solve_1<double, false>), grid, dim3(SOLVE_THREADS), 0, st, a,
+                         bs.d_part_of.p, bs.v64.p, bs.dinv64.p, d_xoff, x, y, z, G, PP,
+                         bs.n_mat, err);
+    hipLaunchKernelGGL(k_copy_out<double>, dim3(nblocks(bs.max_cols, 256), bs.n_part), dim3(256),
+                       0, st, bs.d_part.p, d_xoff, 1, z, x, (const int32_t*)nullptr);
   } else {
     switch (ncol) {
       case 8: launch_m<8>(bs, a, d_xoff, x, st, active); break;
@@ -1783,39 +2083,53 @@ void multi_solve_plan(MultiSolve& m, const std::vector<BandSet*>& sets,
   m.fp32 = sets[0]->fp32;
   m.host.clear();
   m.max_n = 0;
+  std::vector<int> mats;                           // first part of each matrix in the table
   for (size_t k = 0; k < sets.size(); ++k) {
     BandSet& bs = *sets[k];
     GX_REQUIRE(bs.fp32 == m.fp32 && !bs.coarse && x[k] && xoff[k],
                "multi-set solve: band sets of one precision with right-hand sides");
-    alloc_solve1_scratch(bs, st);
-    const int64_t half = (int64_t)bs.ybuf.n / 2;
-    int64_t yo = 0;
+    alloc_solve1_scratch(bs);
+    double *y = bs.ybuf.p, *z = y + bs.ybuf.n / 2;
     for (int j = 0; j < bs.n_mat; ++j) {
-      BandPtrs t;
-      t.v = m.fp32 ? static_cast<const void*>(bs.v32.p + bs.off[j])
-                   : static_cast<const void*>(bs.v64.p + bs.off[j]);
-      t.dinv = m.fp32 ? static_cast<const void*>(bs.dinv32.p + bs.boff[j])
-                      : static_cast<const void*>(bs.dinv64.p + bs.boff[j]);
-      t.x = x[k] + xoff[k][j];
-      t.y = bs.ybuf.p + yo;
-      t.z = bs.ybuf.p + half + yo;
-      t.n = bs.n[j];
-      t.B = bs.B[j];
-      t.fcb = bs.d_fcb.p + bs.eoff[j];
-      t.lrb = bs.d_lrb.p + bs.eoff[j];
-      yo += (bs.n[j] + SB - 1) / SB * SB;
-      m.max_n = std::max(m.max_n, bs.n[j]);
-      m.host.push_back(t);
+      mats.push_back((int)m.host.size());
+      for (int h = 0; h < 2; ++h) {
+        const int ip = bs.part_of[2 * j + h];
+        if (ip < 0) continue;
+        const BandPart& p = bs.part[ip];
+        const BandPart& o = bs.part[bs.part_of[2 * j + 1 - h] < 0 ? ip : bs.part_of[2 * j + 1 - h]];
+        BandPtrs t;
+        t.v = m.fp32 ? static_cast<const void*>(bs.v32.p + p.off)
+                     : static_cast<const void*>(bs.v64.p + p.off);
+        t.dinv = m.fp32 ? static_cast<const void*>(bs.dinv32.p + p.boff)
+                        : static_cast<const void*>(bs.dinv64.p + p.boff);
+        t.x = x[k] + xoff[k][j];
+        t.y = y + p.yoff;
+        t.z = z + p.yoff;
+        t.mate = (p.kind == PART_LOWER ? z : y) + o.yoff;
+        t.n = p.rows;
+        t.cols = p.cols;
+        t.sep = p.kind == PART_UPPER ? p.sep : p.rows;
+        t.N = p.N;
+        t.B = p.B;
+        t.fcb = bs.d_fcb.p + p.eoff;
+        t.lrb = bs.d_lrb.p + p.eoff;
+        t.G = 1;
+        t.kind = p.kind;
+        m.max_n = std::max(m.max_n, p.rows);
+        m.host.push_back(t);
+      }
     }
   }
-  m.n_mat = (int)m.host.size();
-  GX_REQUIRE(m.n_mat > 0 && m.n_mat <= 65535, "multi-set solve: 1 to 65535 matrices");
-  // Work-groups per matrix.  The waits between the groups of a matrix need them all
-  // resident, and work-group i runs on XCD i mod NX (each with its share of the resident
-  // capacity).  Matrices go to XCDs largest first, each to the least loaded one with a
-  // free slot; the spare slots of an XCD then go one at a time to its matrix with the most
-  // factor entries per group (at most GMAX, at least two blocks of rows per group).  If
-  // there are more matrices than slots every matrix gets one group (no waits at all).
+  const int nm = (int)mats.size();
+  m.n_part = (int)m.host.size();
+  mats.push_back(m.n_part);
+  GX_REQUIRE(m.n_part > 0 && m.n_part <= 65535, "multi-set solve: 1 to 65535 parts");
+  // Work-groups per part.  A matrix waits at the pace of its slowest group, so all of them
+  // are to be resident, and work-group i runs on XCD i mod NX (each with its share of the
+  // resident capacity).  Matrices go to XCDs largest first, each to the least loaded one
+  // with free slots; the spare slots of an XCD then go to its matrices with the most factor
+  // entries per group (one more group for each part, at most GMAX, at least two blocks of
+  // rows per group).  If there are more parts than slots every part gets one group.
   int dev = 0, cus = 0, per_cu = 0;
   GX_HIP(hipGetDevice(&dev));
   GX_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
@@ -1824,46 +2138,52 @@ void multi_solve_plan(MultiSolve& m, const std::vector<BandSet*>& sets,
   GX_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kf, SOLVE_THREADS, 0));
   const int NX = cus % 8 == 0 ? 8 : 1;             // XCDs (MI355X: 8 of 32 CUs)
   const int64_t per_x = (int64_t)cus / NX * std::max(per_cu, 1);
-  const int nm = m.n_mat;
   std::vector<int> xcd(nm, 0);
   std::vector<double> wk(nm);
-  for (int j = 0; j < nm; ++j) {
-    wk[j] = (double)m.host[j].n * (double)(m.host[j].B + 1);
-    m.host[j].G = 1;
-  }
+  auto parts = [&](int j) { return mats[j + 1] - mats[j]; };
+  auto first = [&](int j) -> BandPtrs& { return m.host[mats[j]]; };
+  for (int j = 0; j < nm; ++j) wk[j] = (double)first(j).N * (double)(first(j).B + 1) / parts(j);
   std::vector<int> order(nm);
   for (int j = 0; j < nm; ++j) order[j] = j;
-  std::sort(order.begin(), order.end(), [&](int a, int b) { return wk[a] > wk[b]; });
+  std::sort(order.begin(), order.end(),
+            [&](int a, int b) { return wk[a] * parts(a) > wk[b] * parts(b); });
   std::vector<double> load(NX, 0.0);
   std::vector<int64_t> used(NX, 0);
-  const bool fits = nm <= per_x * NX;
+  bool fits = true;
   for (int r = 0; r < nm; ++r) {
     const int j = order[r];
     int best = -1;
-    for (int x = 0; x < NX; ++x)
-      if ((!fits || used[x] < per_x) && (best < 0 || load[x] < load[best])) best = x;
+    for (int pass = 0; pass < 2 && best < 0; ++pass)
+      for (int x = 0; x < NX; ++x)
+        if ((pass || used[x] + parts(j) <= per_x) && (best < 0 || load[x] < load[best])) best = x;
     xcd[j] = best;
-    load[best] += wk[j];
-    ++used[best];
+    load[best] += wk[j] * parts(j);
+    used[best] += parts(j);
+    fits = fits && used[best] <= per_x;
   }
   if (fits)
     for (int x = 0; x < NX; ++x)
-      for (; used[x] < per_x; ++used[x]) {
+      for (;;) {
         int pick = -1;
         for (int j = 0; j < nm; ++j) {
-          const BandPtrs& t = m.host[j];
-          if (xcd[j] != x || t.G >= GMAX || t.n < (int64_t)2 * SB * (t.G + 1)) continue;
-          if (pick < 0 || wk[j] / (double)t.G > wk[pick] / (double)m.host[pick].G) pick = j;
+          const BandPtrs& t = first(j);
+          if (xcd[j] != x || t.G >= GMAX || t.cols < (int64_t)2 * SB * (t.G + 1) ||
+              used[x] + parts(j) > per_x)
+            continue;
+          if (pick < 0 || wk[j] / (double)t.G > wk[pick] / (double)first(pick).G) pick = j;
         }
         if (pick < 0) break;
-        ++m.host[pick].G;
+        used[x] += parts(pick);
+        for (int q = mats[pick]; q < mats[pick + 1]; ++q) ++m.host[q].G;
       }
+  // a matrix's work-groups are neighbours in its XCD's list (take_place)
   std::vector<std::vector<int32_t>> lists(NX);
   for (int j = 0; j < nm; ++j)
-    for (int g = 0; g < (int)m.host[j].G; ++g) {
-      lists[xcd[j]].push_back(j);
-      lists[xcd[j]].push_back(g);
-    }
+    for (int g = 0; g < (int)first(j).G; ++g)
+      for (int q = mats[j]; q < mats[j + 1]; ++q) {
+        lists[xcd[j]].push_back(q);
+        lists[xcd[j]].push_back(g);
+      }
   size_t slots = 0;
   for (auto& l : lists) slots = std::max(slots, l.size() / 2);
   std::vector<int32_t> wl(2 * slots * NX, -1);
@@ -1873,12 +2193,13 @@ void multi_solve_plan(MultiSolve& m, const std::vector<BandSet*>& sets,
       wl[2 * (q * NX + x) + 1] = lists[x][2 * q + 1];
     }
   m.n_wg = (int)(slots * NX);
+  m.n_class = NX;
   if (m.tab.n < m.host.size()) m.tab.alloc(m.host.size());
   to_dev(m.tab.p, m.host.data(), m.host.size(), st);
   if (m.work.n < wl.size()) m.work.alloc(wl.size());
   to_dev(m.work.p, wl.data(), wl.size(), st);
   if (!m.err.n) {
-    m.err.alloc(1);
+    m.err.alloc(1 + 8);
     zero(m.err, st);
   }
   GX_HIP(hipStreamSynchronize(st));                // wl and host are read by the copies
@@ -1886,16 +2207,16 @@ void multi_solve_plan(MultiSolve& m, const std::vector<BandSet*>& sets,
 
 // Solves every matrix of the table in place (marker fill, solve, copy-out on st).
 void multi_solve(MultiSolve& m, hipStream_t st) {
-  GX_REQUIRE(m.n_mat > 0, "multi-set solve: no table");
-  const unsigned nm = (unsigned)m.n_mat;
+  GX_REQUIRE(m.n_part > 0, "multi-set solve: no table");
+  const unsigned nm = (unsigned)m.n_part;
   hipLaunchKernelGGL(k_fill_mark_multi, dim3(nblocks((m.max_n + SB - 1) / SB * SB, 256), nm),
-                     dim3(256), 0, st, m.tab.p);
+                     dim3(256), 0, st, m.tab.p, m.err.p + 1);
   if (m.fp32)
     hipLaunchKernelGGL(k_band_solve_1_multi<float>, dim3((unsigned)m.n_wg), dim3(SOLVE_THREADS),
-                       0, st, m.tab.p, m.work.p, m.err.p);
+                       0, st, m.tab.p, m.work.p, m.n_class, m.err.p);
   else
     hipLaunchKernelGGL(k_band_solve_1_multi<double>, dim3((unsigned)m.n_wg), dim3(SOLVE_THREADS),
-                       0, st, m.tab.p, m.work.p, m.err.p);
+                       0, st, m.tab.p, m.work.p, m.n_class, m.err.p);
   hipLaunchKernelGGL(k_copy_out_multi, dim3(nblocks(m.max_n, 256), nm), dim3(256), 0, st,
                      m.tab.p);
   GX_HIP(hipGetLastError());
@@ -1923,18 +2244,18 @@ void band_solve_check(BandSet& bs, hipStream_t st) {
   }
 }
 
-// zero the entries between one matrix's storage and the next (the line alignment of the
-// starts leaves up to A - 1 of them); the fills write only the matrices' own rows, and a
-// load left of a row's band, masked by a factor 0, must not meet a NaN there
-template <class T>
-__global__ void k_zero_gaps(int n_mat, int A, const int64_t* off, const int64_t* nn,
-                            const int64_t* ld, int64_t total, T* v) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t j = i / A, k = i % A;
-  if (j >= n_mat) return;
-  const int64_t e = off[j] + nn[j] * ld[j] + k;
-  const int64_t next = j + 1 < n_mat ? off[j + 1] : total;
-  if (e < next) v[e] = (T)0;
+// Rows n1 of the upper part's own and n2 of the lower part's own columns of a matrix of
+// order n and half bandwidth B eliminated from both ends (n1 = n2 = 0: not split).  Both are
+// multiples of the 64-row block and leave a separator of at least B rows between them.  The
+// chain of a split matrix has (n + B) / 2 rows instead of n, so there is little to gain
+// below three bandwidths, and nothing below a few blocks; thousands of matrices fill the
+// device as they are.
+static void split_rows(int64_t n, int64_t B, size_t n_mat, int64_t* n1, int64_t* n2) {
+  *n1 = *n2 = 0;
+  if (n < 3 * B || n < 6 * SB || n_mat > 4096) return;
+  const int64_t b = (n - std::max<int64_t>(B, 1)) / SB;    // blocks outside the separator
+  *n1 = b / 2 * SB;
+  *n2 = (b - b / 2) * SB;
 }
 
 void band_layout(BandSet& bs, const std::vector<int64_t>& n, const std::vector<int64_t>& B,
@@ -1942,119 +2263,158 @@ void band_layout(BandSet& bs, const std::vector<int64_t>& n, const std::vector<i
   bs.n_mat = (int)n.size();
   bs.n = n;
   bs.B = B;
-  bs.ld.resize(n.size());
-  bs.off.resize(n.size());
   bs.fp32 = fp32;
-  int64_t o = 0;
-  bs.max_n = 0;
   bs.panel.release();
   bs.d_poff.release();
   bs.ybuf.release();
-  bs.d_yoff.release();
   bs.mbuf.release();
-  bs.max_B = 0;
+  bs.max_n = bs.max_B = 0;
+  bs.max_cols = 0;
+  bs.total = bs.stored = bs.rows = bs.n_inv = 0;
+  bs.split = false;
+  bs.part.clear();
+  bs.part_of.assign(2 * n.size(), -1);
+  int64_t nblk = 0;                                // 64-row blocks of all parts
   // the stored half-bandwidth is B rounded up to a multiple of A, the entries of a 128-byte
-  // line, and every matrix starts on a multiple of A: entry (r, c) then sits at an offset
+  // line, and every part starts on a multiple of A: entry (r, c) then sits at an offset
   // congruent to c modulo A, so a row's entries from any multiple of A on fill whole
   // lines.  The extra band entries left of the band are zeros (outside the envelope).
   const int64_t A = fp32 ? 32 : 16;
   for (size_t j = 0; j < n.size(); ++j) {
     bs.B[j] = (B[j] + A - 1) / A * A;
-    bs.ld[j] = bs.B[j] + 1;
-    o = (o + A - 1) / A * A;
-    bs.off[j] = o;
-    o += n[j] * bs.ld[j];
+    bs.total = (bs.total + A - 1) / A * A + n[j] * (bs.B[j] + 1);
     bs.max_n = std::max<int64_t>(bs.max_n, n[j]);
     bs.max_B = std::max<int64_t>(bs.max_B, bs.B[j]);
+    int64_t n1 = 0, n2 = 0;
+    split_rows(n[j], B[j], n.size(), &n1, &n2);
+    for (int h = 0; h < (n2 ? 2 : 1); ++h) {
+      BandPart p{};
+      p.mat = (int)j;
+      p.kind = n2 == 0 ? PART_WHOLE : h == 0 ? PART_UPPER : PART_LOWER;
+      p.N = n[j];
+      p.rows = h == 0 ? n[j] - n2 : n[j] - n1;
+      p.cols = h == 0 ? p.rows : n2;
+      p.sep = n2 == 0 ? p.rows : h == 0 ? n1 : n2;
+      p.B = bs.B[j];
+      p.ld = p.B + 1;
+      p.fe[0] = p.sep;
+      p.fb[1] = p.sep;
+      p.fe[1] = p.cols;
+      bs.stored = (bs.stored + A - 1) / A * A;
+      p.off = bs.stored;
+      bs.stored += p.rows * p.ld;
+      p.yoff = bs.rows;
+      bs.rows += (p.rows + SB - 1) / SB * SB;
+      p.boff = bs.n_inv;
+      bs.n_inv += (p.cols + SB - 1) / SB * SB * SB;
+      p.eoff = nblk;
+      nblk += (p.rows + SB - 1) / SB;
+      bs.max_cols = std::max(bs.max_cols, p.cols);
+      bs.part_of[2 * j + h] = (int32_t)bs.part.size();
+      bs.part.push_back(p);
+    }
+    bs.split = bs.split || n2 > 0;
   }
-  bs.total = o;
+  bs.n_part = (int)bs.part.size();
   // the envelope: row r from its first column f(r) (3 x its node's first coupled node, or
   // r - B) to the diagonal; env counts its entries, env_flops the Cholesky flops over it
-  // (column c: h^2 + 2 h + 1 with h the rows below c that reach it), fcb / lrb its tables
-  bs.eoff.assign(n.size() + 1, 0);
-  for (size_t j = 0; j < n.size(); ++j) bs.eoff[j + 1] = bs.eoff[j] + (n[j] + SB - 1) / SB;
-  std::vector<int64_t> fcb(std::max<int64_t>(bs.eoff[n.size()], 1)), lrb(fcb.size());
+  // (column c: h^2 + 2 h + 1 with h the rows below c that reach it)
   bs.env.assign(n.size(), 0);
   bs.env_flops = 0.0;
-  size_t node0 = 0;
+  std::vector<int64_t> node0(n.size() + 1, 0);     // first node of each matrix in first_node
   for (size_t j = 0; j < n.size(); ++j) {
-    const int64_t nj = n[j], Bj = B[j], nbk = (nj + SB - 1) / SB;
-    GX_REQUIRE(!first_node || (nj % 3 == 0 && node0 + nj / 3 <= first_node->size()),
-               "band layout: a first node for every node of every matrix");
-    int64_t* fj = fcb.data() + bs.eoff[j];
-    int64_t* lj = lrb.data() + bs.eoff[j];
-    std::vector<int64_t> reach(nbk, 0), diff(nj + 1, 0);
-    for (int64_t b = 0; b < nbk; ++b) fj[b] = nj;
+    const int64_t nj = n[j];
+    node0[j + 1] = node0[j] + nj / 3;
+    GX_REQUIRE(!first_node || (nj % 3 == 0 && 2 * node0[j + 1] <= (int64_t)first_node->size()),
+               "band layout: a first and a last node for every node of every matrix");
+  }
+  const int32_t* fn = first_node ? first_node->data() : nullptr;
+  const int32_t* ln = first_node ? fn + node0[n.size()] : nullptr;
+  for (size_t j = 0; j < n.size(); ++j) {
+    const int64_t nj = n[j], Bj = B[j];
+    std::vector<int64_t> diff(nj + 1, 0);
     for (int64_t r = 0; r < nj; ++r) {
-      int64_t f = first_node ? 3 * (int64_t)(*first_node)[node0 + r / 3] : r - Bj;
+      int64_t f = fn ? 3 * (int64_t)fn[node0[j] + r / 3] : r - Bj;
       f = std::min(std::max(f, std::max<int64_t>(r - Bj, 0)), r);
-      fj[r / SB] = std::min(fj[r / SB], f);
-      reach[f / SB] = std::max(reach[f / SB], r + 1);
       bs.env[j] += r - f + 1;
       ++diff[f];
       --diff[r];
     }
-    int64_t run = 0, h = 0;
-    for (int64_t b = 0; b < nbk; ++b) {
-      run = std::max(run, reach[b]);
-      lj[b] = std::max(run, std::min(nj, (b + 1) * SB));
-    }
+    int64_t h = 0;
     for (int64_t c = 0; c < nj; ++c) {
       h += diff[c];
       bs.env_flops += (double)h * h + 2.0 * h + 1.0;
     }
-    if (first_node) node0 += nj / 3;
   }
-  bs.d_eoff.alloc(n.size() + 1);
+  // its tables by 64-row blocks, per part.  Rows of a lower part start at the last node that
+  // their node couples to, and the separator's window in an upper part is filled by both
+  // parts: its rows start at the window's start, or at their band's.
+  std::vector<int64_t> fcb(std::max<int64_t>(nblk, 1)), lrb(fcb.size());
+  for (const BandPart& p : bs.part) {
+    const int64_t nbk = (p.rows + SB - 1) / SB, Bj = B[p.mat], nd = node0[p.mat];
+    int64_t* fj = fcb.data() + p.eoff;
+    int64_t* lj = lrb.data() + p.eoff;
+    std::vector<int64_t> reach(nbk, 0);
+    for (int64_t b = 0; b < nbk; ++b) fj[b] = p.rows;
+    for (int64_t r = 0; r < p.rows; ++r) {
+      int64_t f = r - Bj;
+      if (fn && p.kind == PART_LOWER)
+        f = p.N - 3 - 3 * (int64_t)ln[nd + (p.N - 1 - r) / 3];
+      else if (fn)
+        f = 3 * (int64_t)fn[nd + r / 3];
+      f = std::min(std::max(f, std::max<int64_t>(r - Bj, 0)), r);
+      if (p.kind == PART_UPPER && r >= p.sep) f = std::min(f, std::max(p.sep, r - Bj));
+      fj[r / SB] = std::min(fj[r / SB], f);
+      reach[f / SB] = std::max(reach[f / SB], r + 1);
+    }
+    int64_t run = 0;
+    for (int64_t b = 0; b < nbk; ++b) {
+      run = std::max(run, reach[b]);
+      lj[b] = std::max(run, std::min(p.rows, (b + 1) * SB));
+    }
+  }
   bs.d_fcb.alloc(fcb.size());
   bs.d_lrb.alloc(lrb.size());
-  to_dev(bs.d_eoff.p, bs.eoff.data(), n.size() + 1, st);
   to_dev(bs.d_fcb.p, fcb.data(), fcb.size(), st);
   to_dev(bs.d_lrb.p, lrb.data(), lrb.size(), st);
   bs.d_n.alloc(n.size());
-  bs.d_B.alloc(n.size());
-  bs.d_ld.alloc(n.size());
-  bs.d_off.alloc(n.size());
   to_dev(bs.d_n.p, bs.n.data(), n.size(), st);
-  to_dev(bs.d_B.p, bs.B.data(), n.size(), st);
-  to_dev(bs.d_ld.p, bs.ld.data(), n.size(), st);
-  to_dev(bs.d_off.p, bs.off.data(), n.size(), st);
-  bs.boff.assign(n.size() + 1, 0);
-  for (size_t j = 0; j < n.size(); ++j)
-    bs.boff[j + 1] = bs.boff[j] + (n[j] + SB - 1) / SB * SB * SB;
-  bs.d_boff.alloc(n.size() + 1);
-  to_dev(bs.d_boff.p, bs.boff.data(), n.size() + 1, st);
+  bs.d_part.alloc(bs.part.size());
+  to_dev(bs.d_part.p, bs.part.data(), bs.part.size(), st);
+  bs.d_part_of.alloc(bs.part_of.size());
+  to_dev(bs.d_part_of.p, bs.part_of.data(), bs.part_of.size(), st);
   if (fp32) {
     bs.v64.release();
     bs.dinv64.release();
-    bs.v32.alloc(o + band_pad(bs.max_B));
-    GX_HIP(hipMemsetAsync(bs.v32.p + o, 0, band_pad(bs.max_B) * sizeof(float), st));
-    hipLaunchKernelGGL(k_zero_gaps<float>, dim3(nblocks((int64_t)n.size() * A, 256)), dim3(256),
-                       0, st, bs.n_mat, (int)A, bs.d_off.p, bs.d_n.p, bs.d_ld.p, o, bs.v32.p);
-    bs.dinv32.alloc(bs.boff[n.size()]);
+    bs.v32.alloc(bs.stored + band_pad(bs.max_B));
+    bs.dinv32.alloc(bs.n_inv);
   } else {
     bs.v32.release();
     bs.dinv32.release();
-    bs.v64.alloc(o + band_pad(bs.max_B));
-    GX_HIP(hipMemsetAsync(bs.v64.p + o, 0, band_pad(bs.max_B) * sizeof(double), st));
-    hipLaunchKernelGGL(k_zero_gaps<double>, dim3(nblocks((int64_t)n.size() * A, 256)), dim3(256),
-                       0, st, bs.n_mat, (int)A, bs.d_off.p, bs.d_n.p, bs.d_ld.p, o, bs.v64.p);
-    bs.dinv64.alloc(bs.boff[n.size()]);
+    bs.v64.alloc(bs.stored + band_pad(bs.max_B));
+    bs.dinv64.alloc(bs.n_inv);
   }
   bs.solve_groups[0] = bs.solve_groups[1] = 0;
   GX_HIP(hipStreamSynchronize(st));
 }
 
+// All of the set's storage, with the gaps between the parts and the padding: a load outside
+// a row's band, masked by a factor 0, must not meet a NaN there.
+void band_zero(BandSet& bs, hipStream_t st) {
+  if (bs.fp32)
+    zero(bs.v32, st);
+  else
+    zero(bs.v64, st);
+}
 
 // ---------------------------------------------------------------------------------------
 // Stand-alone factor-and-solve of caller-supplied band matrices (exposed for testing the
 // subdomain solver in isolation).
-// caller band entry e (bandwidth bw[j], rows of bw[j] + 1 entries) into the set's storage
-// (bandwidth sB[j], offsets soff[j]), which is zero beforehand
+// caller band entry e (bandwidth bw[j], rows of bw[j] + 1 entries) into the set's storage,
+// which is zero beforehand
 __global__ void k_band_import(int64_t total, const double* src, const double* dscale,
-                              const int64_t* off, const int64_t* nn, const int64_t* bw,
-                              const int64_t* doff, int n_mat, const int64_t* soff,
-                              const int64_t* sB, float* d32, double* d64) {
+                              const int64_t* off, const int64_t* bw, const int64_t* doff,
+                              int n_mat, BandView bv, float* d32, double* d64) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= total) return;
   int j = 0;
@@ -2063,13 +2423,14 @@ __global__ void k_band_import(int64_t total, const double* src, const double* ds
   if (c < 0) return;                               // left of the first column: none
   double v = src[e];
   if (dscale) v *= dscale[doff[j] + r] * dscale[doff[j] + c];
-  const int64_t d = soff[j] + r * (sB[j] + 1) + (c - r + sB[j]);
+  const int64_t d = band_pos(bv.part[bv.part_of[2 * j]],
+                             bv.part[max(bv.part_of[2 * j + 1], 0)], r, c);
   if (d32) d32[d] = (float)v;
   else d64[d] = v;
 }
 
 __global__ void k_band_diag(int64_t rows, const double* src, const int64_t* off,
-                            const int64_t* nn, const int64_t* bw, const int64_t* doff, int n_mat,
+                            const int64_t* bw, const int64_t* doff, int n_mat,
                             double* dscale) {
   const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (q >= rows) return;
@@ -2111,10 +2472,7 @@ extern "C" gx_status gx_band_factor_solve(gx_ctx* c, int32_t n_mat, const int64_
   BandSet bs;
   band_layout(bs, nv, bv, fp32, s);
   bs.force_groups[0] = bs.force_groups[1] = groups;
-  if (fp32)
-    zero(bs.v32, s);
-  else
-    zero(bs.v64, s);
+  band_zero(bs, s);
   DevBuf<int64_t> d_off(n_mat + 1), d_doff(n_mat + 1), d_xoff(n_mat), d_bw(n_mat);
   to_dev(d_off.p, off.data(), n_mat + 1, s);
   to_dev(d_bw.p, bv.data(), n_mat, s);
@@ -2124,12 +2482,11 @@ extern "C" gx_status gx_band_factor_solve(gx_ctx* c, int32_t n_mat, const int64_
   if (fp32) {
     dsc.alloc(doff[n_mat]);
     hipLaunchKernelGGL(k_band_diag, dim3(nblocks(doff[n_mat], 256)), dim3(256), 0, s,
-                       doff[n_mat], band, d_off.p, bs.d_n.p, d_bw.p, d_doff.p, n_mat, dsc.p);
+                       doff[n_mat], band, d_off.p, d_bw.p, d_doff.p, n_mat, dsc.p);
   }
   hipLaunchKernelGGL(k_band_import, dim3(nblocks(off[n_mat], 256)), dim3(256), 0, s,
-                     off[n_mat], band, fp32 ? dsc.p : nullptr, d_off.p, bs.d_n.p, d_bw.p,
-                     d_doff.p, n_mat, bs.d_off.p, bs.d_B.p, fp32 ? bs.v32.p : nullptr,
-                     fp32 ? nullptr : bs.v64.p);
+                     off[n_mat], band, fp32 ? dsc.p : nullptr, d_off.p, d_bw.p, d_doff.p, n_mat,
+                     band_view(bs), fp32 ? bs.v32.p : nullptr, fp32 ? nullptr : bs.v64.p);
   GX_HIP(hipGetLastError());
   band_factor(c, bs, s, "the given band matrices");
   if (fp32)

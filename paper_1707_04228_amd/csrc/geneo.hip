@@ -100,8 +100,8 @@ __global__ void __launch_bounds__(64) k_neumann_fill(GeneoDev g, const int32_t* 
   const int64_t ln = blockIdx.x;
   if (ln >= g.nD[j]) return;
   const int64_t n = g.D_nodes[g.offD[j] + ln];
-  const int64_t B = bv.B[j], ld = bv.ld[j];
-  T* base = v + bv.off[j];
+  const BandPart& up = bv.part[bv.part_of[2 * j]];
+  const BandPart& lo_p = bv.part[max(bv.part_of[2 * j + 1], 0)];
   const int rb = rp[n], len = rp[n + 1] - rb;
   if (len > NROW) {
     if (threadIdx.x == 0) atomicOr(err, 1);
@@ -137,12 +137,12 @@ __global__ void __launch_bounds__(64) k_neumann_fill(GeneoDev g, const int32_t* 
     const int64_t lm = g.D_loc[(int64_t)j * g.N + m];
     if (lm < 0) continue;
     const int64_t row = 3 * ln + i, col = 3 * lm + kk;
-    const int64_t o = col - row + B;
+    const int64_t o = band_pos(up, lo_p, row, col);
     if (col > row || o < 0) continue;
     double val = rv[idx];
     if (g.fixed[3 * n + i] || g.fixed[3 * m + kk]) val = (row == col) ? 1.0 : 0.0;
     if (dM) val /= sqrt(dM[doff[j] + row] * dM[doff[j] + col]);
-    base[row * ld + o] = (T)val;
+    v[o] = (T)val;
   }
 }
 
@@ -959,19 +959,19 @@ void geneo_coarse(gx_ctx* c, const gx_geneo_opts* o, const std::function<void()>
     Mb.force_groups[0] = c->tune[0];
     Mb.force_groups[1] = c->tune[1];
     c->neumann_entries = Mb.total;
-    BandView bv{Mb.d_B.p, Mb.d_ld.p, Mb.d_off.p};
+    BandView bv = band_view(Mb);
     DevBuf<int> ferr(1);
     zero(ferr, s);
     if (fp32) {
       dM.alloc(doff[n_sub]);
       hipLaunchKernelGGL(k_neumann_diag, dim3(nblocks(maxD, 256), n_sub), dim3(256), 0, s, g,
                          sigma, d_doff.p, dM.p);
-      GX_HIP(hipMemsetAsync(Mb.v32.p, 0, Mb.total * sizeof(float), s));
+      band_zero(Mb, s);
       hipLaunchKernelGGL(k_neumann_fill<float>, dim3((unsigned)maxD, n_sub), dim3(64), 0, s, g,
                          c->row_ptr.p, c->col.p, sigma, bv, d_doff.p, (const double*)dM.p,
                          Mb.v32.p, ferr.p);
     } else {
-      GX_HIP(hipMemsetAsync(Mb.v64.p, 0, Mb.total * sizeof(double), s));
+      band_zero(Mb, s);
       hipLaunchKernelGGL(k_neumann_fill<double>, dim3((unsigned)maxD, n_sub), dim3(64), 0, s, g,
                          c->row_ptr.p, c->col.p, sigma, bv, d_doff.p, (const double*)nullptr,
                          Mb.v64.p, ferr.p);
@@ -987,8 +987,8 @@ void geneo_coarse(gx_ctx* c, const gx_geneo_opts* o, const std::function<void()>
       // an FP32 factor broke down: this matrix set is refactored in FP64 (reported)
       c->fp64_fallbacks |= 2;
       band_layout(Mb, n3, B, false, s, &first);
-      bv = BandView{Mb.d_B.p, Mb.d_ld.p, Mb.d_off.p};
-      GX_HIP(hipMemsetAsync(Mb.v64.p, 0, Mb.total * sizeof(double), s));
+      bv = band_view(Mb);
+      band_zero(Mb, s);
       hipLaunchKernelGGL(k_neumann_fill<double>, dim3((unsigned)maxD, n_sub), dim3(64), 0, s, g,
                          c->row_ptr.p, c->col.p, sigma, bv, d_doff.p, (const double*)nullptr,
                          Mb.v64.p, ferr.p);
@@ -1266,9 +1266,9 @@ void geneo_coarse(gx_ctx* c, const gx_geneo_opts* o, const std::function<void()>
                      sw.Z.p, Vc.p, d_vco.p, n0, K0.p);
   band_layout(sw.C, {n0}, {n0 - 1}, false, s);
   sw.C.coarse = true;
-  zero(sw.C.v64, s);
+  band_zero(sw.C, s);
   hipLaunchKernelGGL(k_coarse_fill, dim3(nblocks(n0 * n0, 256)), dim3(256), 0, s, n0, K0.p,
-                     sw.C.B[0], sw.C.ld[0], sw.C.v64.p);
+                     sw.C.B[0], sw.C.B[0] + 1, sw.C.v64.p);
   GX_HIP(hipGetLastError());
   band_factor(c, sw.C, s, "the coarse matrix K0 (near-dependent coarse vectors?)");
   const int64_t zero64 = 0;

@@ -202,69 +202,103 @@ __device__ inline double wave_sum_d(double s) {
   return s;
 }
 
-struct BandView {
-  const int64_t* B;
-  const int64_t* ld;
-  const int64_t* off;
+// A part of a band matrix: what one elimination chain works on.  A matrix whose order is
+// several times its bandwidth is eliminated from both ends at once (BandSet): the upper part
+// holds rows 0 .. n1 + ns - 1 in order, the lower part rows N - 1 .. n1 in reverse order, and
+// the ns rows from n1 on, the separator, lie at the end of both.  The lower part eliminates
+// its own n2 = N - n1 - ns columns; what that leaves in the separator's window is added to
+// the upper part's, which then eliminates the separator too.  Row r of the lower part is
+// row N - 1 - r of the matrix.
+enum { PART_WHOLE = 0, PART_UPPER = 1, PART_LOWER = 2 };
+struct BandPart {
+  int32_t mat, kind;                           // matrix; PART_*
+  int64_t rows, cols;                          // stored rows; columns the part eliminates
+  int64_t sep;                                 // first separator row (rows if none)
+  int64_t N;                                   // order of the matrix
+  int64_t B, ld;                               // stored half bandwidth, row stride
+  int64_t off, boff, eoff, yoff;               // storage, inverse blocks, tables, scratch
+  // columns of the two phases of the factorisation: up to the separator, then the separator
+  int64_t fb[2], fe[2];
 };
+
+// Where the fill kernels put entry (r, c), c <= r, of matrix j
+struct BandView {
+  const BandPart* part;
+  const int32_t* part_of;                      // parts of matrix j: 2 j, 2 j + 1 (-1: none)
+};
+// Address of the entry relative to the set's storage, -1 left of the band
+__device__ inline int64_t band_pos(const BandPart& u, const BandPart& l, int64_t r, int64_t c) {
+  if (r - c > u.B) return -1;
+  if (r < u.rows) return u.off + r * u.ld + (c - r + u.B);
+  return l.off + (l.N - 1 - c) * l.ld + (c - r + l.B);
+}
 
 // ------------------------------------------------------------------------------------
 // Decomposition and preconditioner state.
 struct BandSet {
-  // Banded lower factors of a batch of SPD matrices, row-major band storage:
-  // entry (r, c), r - B <= c <= r, of matrix j lives at off[j] + r * ld[j] + (c - r + B).
-  int n_mat = 0;
-  std::vector<int64_t> n, B, ld, off;          // host copies
+  // Banded lower factors of a batch of SPD matrices in parts (BandPart), row-major band
+  // storage: entry (r, c), r - B <= c <= r, of a part lives at off + r * ld + (c - r + B).
+  int n_mat = 0, n_part = 0;
+  bool split = false;                          // some matrix has two parts
+  std::vector<int64_t> n, B;                   // of the matrices
+  std::vector<BandPart> part;
+  std::vector<int32_t> part_of;                // parts of matrix j: 2 j, 2 j + 1 (-1: none)
+  DevBuf<BandPart> d_part;
+  DevBuf<int32_t> d_part_of;
   // envelope (profile) entries of each matrix's lower triangle, diagonal included: the
   // entries from each row's first nonzero column to the diagonal (Cholesky creates no fill
   // outside it).  band_layout sets it to the band itself; callers that know the matrices'
   // profile replace it.
   std::vector<int64_t> env;
   double env_flops = 0.0;                      // Cholesky flops over the envelope
-  // the envelope by 64-row blocks (block b of matrix j at eoff[j] + b): fcb, the first
+  // the envelope by 64-row blocks (block b of a part at its eoff + b): fcb, the first
   // column any row of the block reaches; lrb, one past the last row that reaches a column
   // of the block.  From each row's first column when band_layout is given it, otherwise
   // from the band.  The kernels skip the 64-column steps outside it (exact zeros: Cholesky
   // creates no fill outside the envelope).
-  std::vector<int64_t> eoff;
-  DevBuf<int64_t> d_eoff, d_fcb, d_lrb;
-  DevBuf<int64_t> d_n, d_B, d_ld, d_off;       // device copies
-  int64_t total = 0;                           // stored entries
+  DevBuf<int64_t> d_fcb, d_lrb;
+  DevBuf<int64_t> d_n;                         // orders of the matrices
+  int64_t total = 0;                           // band entries of the matrices
+  int64_t stored = 0;                          // entries of the parts' storage (gaps included)
+  int64_t rows = 0;                            // 64-aligned rows of all parts
   int max_n = 0, max_B = 0;
+  int64_t max_cols = 0;                        // of a part
   DevBuf<double> v64;                          // FP64 storage (precision FP64)
   DevBuf<float> v32;                           // FP32 storage (mixed precision)
   // inverses of the 64x64 diagonal blocks of the factors (row-major, identity-padded past
-  // the end of a matrix), block b of matrix j at boff[j] + 4096 b; same precision as v
-  std::vector<int64_t> boff;
-  DevBuf<int64_t> d_boff;
+  // the end of a part), block b of a part at its boff + 4096 b; same precision as v
+  int64_t n_inv = 0;
   DevBuf<double> dinv64;
   DevBuf<float> dinv32;
   bool fp32 = false;
   int solve_groups[2] = {0, 0};                // work-groups per matrix: 1-RHS, m-RHS solve
   int force_groups[2] = {0, 0};                // requested (0: automatic, capped by residency)
   int share = 1;                               // contexts whose solves may run concurrently
-  DevBuf<int> err;                             // error word of the solves (poll time-out)
+  DevBuf<int> err;                             // error word of the solves (poll time-out),
+                                               // then their eight work-group counters
   bool coarse = false;                         // the coarse matrix (own solve kernel name)
   // column panels of solves with more right-hand sides than one launch takes
   DevBuf<double> panel;
   DevBuf<int64_t> d_poff;
-  // forward solutions of the single-right-hand-side solve (64-aligned segment per matrix)
+  // forward solutions of the single-right-hand-side solve (64-aligned segment per part)
   DevBuf<double> ybuf;
-  DevBuf<int64_t> d_yoff;
   DevBuf<double> mbuf;                         // the same for up to 32 right-hand sides
 };
 
-// Addresses of one matrix in a solve over the factors of several band sets in one launch
+// One part in a single-right-hand-side solve over the factors of several band sets
 struct BandPtrs {
   const void* v;                               // factor (precision of the launch)
   const void* dinv;                            // inverse 64x64 diagonal blocks
-  double* x;                                   // right-hand side in, solution out
+  double* x;                                   // right-hand side in, solution out (matrix)
   double* y;                                   // forward-solution scratch (64-aligned length)
   double* z;                                   // backward-solution scratch
-  int64_t n, B;                                // rows, half-bandwidth
+  const double* mate;                          // upper part: y of the lower, lower: z of the
+                                               // upper part (row r at N - 1 - r)
+  int64_t n, cols, sep, N, B;                  // as in BandPart
   const int64_t* fcb;                          // envelope by 64-row blocks (see BandSet)
   const int64_t* lrb;
-  int64_t G;                                   // work-groups sharing the matrix
+  int64_t G;                                   // work-groups sharing the part
+  int64_t kind;
 };
 
 // The single-right-hand-side solves of several band sets of one precision on one device in
@@ -273,9 +307,9 @@ struct MultiSolve {
   std::vector<BandSet*> sets;                  // in table order
   std::vector<BandPtrs> host;
   DevBuf<BandPtrs> tab;
-  DevBuf<int32_t> work;                        // (matrix, group) per work-group, -1: none
-  DevBuf<int> err;                             // time-out word of the launches
-  int n_mat = 0, n_wg = 0;
+  DevBuf<int32_t> work;                        // (part, group) per work-group, -1: none
+  DevBuf<int> err;                             // time-out word of the launches, counters
+  int n_part = 0, n_wg = 0, n_class = 1;       // work-group i is of class i mod n_class
   int64_t max_n = 0;
   bool fp32 = false;
 };
@@ -387,10 +421,13 @@ std::vector<int64_t> list_bandwidth(gx_ctx* c, const int32_t* list, const int64_
                                     std::vector<int32_t>* first_out = nullptr);
 double interior_refactor_ms(gx_ctx* c);
 // first_node (optional): for each matrix's nodes in order (n_j / 3 each, concatenated),
-// the first node its rows couple to; it gives the envelope (env, env_flops, the block
-// tables), otherwise the band itself is taken
+// the first node its rows couple to, then, for all nodes again, the last one; they give the
+// envelope (env, env_flops, the block tables), otherwise the band itself is taken.  The
+// storage is left unset: the caller zeroes all of it (band_zero) before it fills it.
 void band_layout(BandSet& bs, const std::vector<int64_t>& n, const std::vector<int64_t>& B,
                  bool fp32, hipStream_t st, const std::vector<int32_t>* first_node = nullptr);
+void band_zero(BandSet& bs, hipStream_t st);
+inline BandView band_view(const BandSet& bs) { return {bs.d_part.p, bs.d_part_of.p}; }
 void band_factor(gx_ctx* c, BandSet& bs, hipStream_t st, const char* what);
 // one of the context's set-up streams, created if it is not there
 hipStream_t aux_stream(hipStream_t& st);
@@ -424,7 +461,7 @@ void band_factor_finish(FactorJob& job);
 // The interior factorisation as a job that can run on a side stream (see schwarz.hip).
 struct InteriorJob {
   std::vector<int64_t> n, B, env;
-  std::vector<int32_t> first;                  // first coupled node of every node
+  std::vector<int32_t> first;                  // first, then last coupled node of every node
   int64_t maxI = 0;
   bool fp32 = false;
   FactorJob factor;

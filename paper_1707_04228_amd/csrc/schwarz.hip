@@ -210,22 +210,27 @@ void dd_build(gx_ctx* c, const int32_t* part, int n_sub, int overlap) {
 // and including their diagonals.  Integer sums: the result does not depend on the order.
 __global__ void k_band_width(const int32_t* rp, const int32_t* col, const int32_t* list,
                              const int64_t* loff, const int64_t* lcnt, const int32_t* loc,
-                             int64_t N, int32_t* bw, unsigned long long* env, int32_t* first) {
+                             int64_t N, int32_t* bw, unsigned long long* env, int32_t* first,
+                             int32_t* last) {
   const int j = blockIdx.y;
   const int64_t ln = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (ln >= lcnt[j]) return;
   const int n = list[loff[j] + ln];
   const int32_t* lj = loc + (int64_t)j * N;
-  int mn = (int)ln;
+  int mn = (int)ln, mx = (int)ln;
   for (int k = rp[n]; k < rp[n + 1]; ++k) {
     const int lm = lj[col[k]];
     if (lm >= 0 && lm < mn) mn = lm;
+    mx = max(mx, lm);
   }
   atomicMax(&bw[j], (int)ln - mn);
   atomicAdd(&env[j], (unsigned long long)(9 * ((int64_t)ln - mn) + 6));
   first[loff[j] + ln] = mn;
+  last[loff[j] + ln] = mx;
 }
 
+// The blocks of K on the lists' nodes into the (zeroed) band storage, the lower triangle of
+// each matrix, with the symmetric diagonal scaling when dg is given.
 template <class T>
 __global__ void __launch_bounds__(64) k_band_fill(const int32_t* rp, const int32_t* col,
                                                   const double* val, const double* dg,
@@ -237,10 +242,8 @@ __global__ void __launch_bounds__(64) k_band_fill(const int32_t* rp, const int32
   if (ln >= lcnt[j]) return;
   const int n = list[loff[j] + ln];
   const int32_t* lj = loc + (int64_t)j * N;
-  const int64_t B = bv.B[j], ld = bv.ld[j];
-  T* base = v + bv.off[j];
-  for (int64_t i = threadIdx.x; i < 3 * ld; i += 64) base[3 * ln * ld + i] = (T)0;
-  __syncthreads();
+  const BandPart& up = bv.part[bv.part_of[2 * j]];
+  const BandPart& lo = bv.part[max(bv.part_of[2 * j + 1], 0)];
   for (int k = rp[n] + threadIdx.x; k < rp[n + 1]; k += 64) {
     const int m = col[k];
     const int lm = lj[m];
@@ -251,7 +254,7 @@ __global__ void __launch_bounds__(64) k_band_fill(const int32_t* rp, const int32
         if (cc > r) continue;
         double x = val[(int64_t)k * 9 + 3 * a + b];
         if (dg) x /= sqrt(dg[3 * (int64_t)n + a] * dg[3 * (int64_t)m + b]);
-        base[r * ld + (cc - r + B)] = (T)x;
+        v[band_pos(up, lo, r, cc)] = (T)x;
       }
   }
 }
@@ -277,20 +280,18 @@ std::vector<int64_t> list_bandwidth(gx_ctx* c, const int32_t* list, const int64_
   for (int64_t v : cnt) mx = std::max(mx, v);
   std::vector<int64_t> hoff(n_sub + 1);
   to_host(hoff.data(), d_off, n_sub + 1, s);
-  DevBuf<int32_t> bw(n_sub), first(std::max<int64_t>(hoff[n_sub], 1));
+  const int64_t tot = hoff[n_sub];
+  DevBuf<int32_t> bw(n_sub), first(std::max<int64_t>(2 * tot, 1));
   DevBuf<unsigned long long> env(n_sub);
   zero(bw, s);
   zero(env, s);
   hipLaunchKernelGGL(k_band_width, dim3(nblocks(mx, 256), n_sub), dim3(256), 0, s,
                      c->row_ptr.p, c->col.p, list, d_off, d_cnt, loc, c->n_nodes, bw.p, env.p,
-                     first.p);
+                     first.p, first.p + tot);
   GX_HIP(hipGetLastError());
-  if (first_out) {                                  // the matrices' nodes in order
-    std::vector<int32_t> all(hoff[n_sub]);
-    to_host(all.data(), first.p, all.size(), s);
-    first_out->clear();
-    for (int j = 0; j < n_sub; ++j)
-      first_out->insert(first_out->end(), all.begin() + hoff[j], all.begin() + hoff[j] + cnt[j]);
+  if (first_out) {                                  // the lists' nodes in order, twice
+    first_out->resize(2 * tot);
+    to_host(first_out->data(), first.p, first_out->size(), s);
   }
   std::vector<int32_t> hb(n_sub);
   std::vector<unsigned long long> he(n_sub);
@@ -300,6 +301,22 @@ std::vector<int64_t> list_bandwidth(gx_ctx* c, const int32_t* list, const int64_
   for (int j = 0; j < n_sub; ++j) B[j] = 3 * (int64_t)hb[j] + 2;
   if (env_out) env_out->assign(he.begin(), he.end());
   return B;
+}
+
+// The interior matrices into their (laid out) band storage, on s.
+static void interior_fill(gx_ctx* c, int64_t maxI, hipStream_t s) {
+  Schwarz& sw = c->sw;
+  band_zero(sw.A, s);
+  const BandView bv = band_view(sw.A);
+  if (sw.A.fp32)
+    hipLaunchKernelGGL(k_band_fill<float>, dim3((unsigned)maxI, sw.n_sub), dim3(64), 0, s,
+                       c->row_ptr.p, c->col.p, c->val.p, sw.dg.p, sw.I_nodes.p, sw.d_offI.p,
+                       sw.d_nI.p, sw.I_loc.p, c->n_nodes, bv, sw.A.v32.p);
+  else
+    hipLaunchKernelGGL(k_band_fill<double>, dim3((unsigned)maxI, sw.n_sub), dim3(64), 0, s,
+                       c->row_ptr.p, c->col.p, c->val.p, (const double*)nullptr, sw.I_nodes.p,
+                       sw.d_offI.p, sw.d_nI.p, sw.I_loc.p, c->n_nodes, bv, sw.A.v64.p);
+  GX_HIP(hipGetLastError());
 }
 
 // Fills the interior band matrices and enqueues their factorisation on s (which may be a
@@ -324,16 +341,7 @@ void interior_factors_prepare(gx_ctx* c, int precision, hipStream_t s, InteriorJ
     hipLaunchKernelGGL(k_diag, dim3(nblocks(N, 256)), dim3(256), 0, s, c->row_ptr.p,
                        c->col.p, c->val.p, N, sw.dg.p);
   }
-  BandView bv{sw.A.d_B.p, sw.A.d_ld.p, sw.A.d_off.p};
-  if (job.fp32)
-    hipLaunchKernelGGL(k_band_fill<float>, dim3((unsigned)job.maxI, n_sub), dim3(64), 0, s,
-                       c->row_ptr.p, c->col.p, c->val.p, sw.dg.p, sw.I_nodes.p, sw.d_offI.p,
-                       sw.d_nI.p, sw.I_loc.p, N, bv, sw.A.v32.p);
-  else
-    hipLaunchKernelGGL(k_band_fill<double>, dim3((unsigned)job.maxI, n_sub), dim3(64), 0, s,
-                       c->row_ptr.p, c->col.p, c->val.p, (const double*)nullptr, sw.I_nodes.p,
-                       sw.d_offI.p, sw.d_nI.p, sw.I_loc.p, N, bv, sw.A.v64.p);
-  GX_HIP(hipGetLastError());
+  interior_fill(c, job.maxI, s);
 }
 
 void interior_factors_launch(gx_ctx* c, hipStream_t s, InteriorJob& job, bool threaded) {
@@ -351,7 +359,6 @@ void interior_factors_start(gx_ctx* c, int precision, hipStream_t s, InteriorJob
 void interior_factors_finish(gx_ctx* c, InteriorJob& job) {
   Schwarz& sw = c->sw;
   hipStream_t s = c->stream;
-  const int64_t N = c->n_nodes;
   const int n_sub = sw.n_sub;
   try {
     band_factor_finish(job.factor);
@@ -359,11 +366,7 @@ void interior_factors_finish(gx_ctx* c, InteriorJob& job) {
     if (!job.fp32 || e.code != GX_ENOTSPD) throw;
     c->fp64_fallbacks |= 1;
     band_layout(sw.A, job.n, job.B, false, s, &job.first);
-    BandView bv64{sw.A.d_B.p, sw.A.d_ld.p, sw.A.d_off.p};
-    hipLaunchKernelGGL(k_band_fill<double>, dim3((unsigned)job.maxI, n_sub), dim3(64), 0, s,
-                       c->row_ptr.p, c->col.p, c->val.p, (const double*)nullptr, sw.I_nodes.p,
-                       sw.d_offI.p, sw.d_nI.p, sw.I_loc.p, N, bv64, sw.A.v64.p);
-    GX_HIP(hipGetLastError());
+    interior_fill(c, job.maxI, s);
     band_factor(c, sw.A, s, "the subdomain matrices");
     sw.precision = GX_FP64;
   }
@@ -389,20 +392,9 @@ void interior_factors(gx_ctx* c, int precision) {
 double interior_refactor_ms(gx_ctx* c) {
   Schwarz& sw = c->sw;
   hipStream_t s = c->stream;
-  const int64_t N = c->n_nodes;
-  const int n_sub = sw.n_sub;
   int64_t maxI = 0;
-  for (int j = 0; j < n_sub; ++j) maxI = std::max(maxI, sw.nI[j]);
-  BandView bv{sw.A.d_B.p, sw.A.d_ld.p, sw.A.d_off.p};
-  if (sw.A.fp32)
-    hipLaunchKernelGGL(k_band_fill<float>, dim3((unsigned)maxI, n_sub), dim3(64), 0, s,
-                       c->row_ptr.p, c->col.p, c->val.p, sw.dg.p, sw.I_nodes.p, sw.d_offI.p,
-                       sw.d_nI.p, sw.I_loc.p, N, bv, sw.A.v32.p);
-  else
-    hipLaunchKernelGGL(k_band_fill<double>, dim3((unsigned)maxI, n_sub), dim3(64), 0, s,
-                       c->row_ptr.p, c->col.p, c->val.p, (const double*)nullptr, sw.I_nodes.p,
-                       sw.d_offI.p, sw.d_nI.p, sw.I_loc.p, N, bv, sw.A.v64.p);
-  GX_HIP(hipGetLastError());
+  for (int j = 0; j < sw.n_sub; ++j) maxI = std::max(maxI, sw.nI[j]);
+  interior_fill(c, maxI, s);
   EventPair ev;
   GX_HIP(hipEventRecord(ev.a, s));
   {
