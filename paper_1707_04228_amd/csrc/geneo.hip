@@ -452,72 +452,116 @@ __global__ void k_copy_active(int64_t n_rows_max, const int64_t* nrows, int m,
   dst[voff[j] + r] = src[voff[j] + r];
 }
 
-// Gram partials G_U[a][b] = sum_i U[i][a] V1[i][b] and G_2 = sum_i U[i][a] V2[i][b] over a
-// chunk of rows; chunk partials are reduced in a fixed order afterwards
-constexpr int GCH = 4096;
-constexpr int GROWS = 32;
+// ---- the eigensolver's dense work on blocks of m columns (row-major), on the FP64 matrix
+// instruction 16x16x4: lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16] and holds
+// D[4 q + l / 16][l % 16] in accumulator register q.  A work-group takes a chunk of rows of
+// one subdomain; what it sums over rows goes to a slot of its own, and the slots are added in
+// a fixed order afterwards.
+typedef double v4d __attribute__((ext_vector_type(4)));
+typedef double v2d __attribute__((ext_vector_type(2)));
+__device__ inline v4d mma64(double a, double b, v4d c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
+// Rows per chunk: about 2048 work-groups over all subdomains, so that small blocks still
+// spread over the device and large ones do not write more slots than they need (a multiple
+// of the 64 rows that the four waves take at a time).
+static int64_t chunk_rows(const std::vector<int64_t>& nodes) {
+  int64_t rows = 0;
+  for (int64_t n : nodes) rows += 3 * n;
+  return std::min<int64_t>(4096, std::max<int64_t>(256, (rows / 2048 + 63) / 64 * 64));
+}
+
+// Gram partials G_1 = U^T V1 and G_2 = U^T V2.  Bound by the three blocks' bytes: a step of
+// a wave takes four rows, 128 bytes of each row and tile per load, straight from memory into
+// the operands.  16 subdomains of 116k rows, 32 columns: 1.37 -> 0.39 ms against scalar
+// products from LDS (3.6 TB/s); 4 of 4.5k rows: 0.60 -> 0.02 ms.
+template <int NT>
 __global__ void __launch_bounds__(256) k_gram(const int64_t* nrows, int m, const int64_t* voff,
                                               const int32_t* active, const double* U,
-                                              const double* V1, const double* V2,
+                                              const double* V1, const double* V2, int64_t gch,
                                               int64_t nch_max, double* part) {
-  __shared__ double su[GROWS][MAXM], s1[GROWS][MAXM], s2[GROWS][MAXM];
+  __shared__ double red[2][16 * NT][16 * NT + 1];
   const int j = blockIdx.y;
   if (!active[j]) return;
   const int64_t n3 = 3 * nrows[j];
-  const int64_t r0 = (int64_t)blockIdx.x * GCH;
-  constexpr int EPT = (MAXM * MAXM + 255) / 256;
-  double a1[EPT], a2[EPT];
+  const int64_t r0 = (int64_t)blockIdx.x * gch, rend = min(n3, r0 + gch);
+  if (r0 >= n3) return;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
+  v4d a1[NT][NT], a2[NT][NT];
 #pragma unroll
-  for (int q = 0; q < EPT; ++q) a1[q] = a2[q] = 0.0;
-  const double* Uj = U + voff[j];
-  const double* V1j = V1 + voff[j];
-  const double* V2j = V2 + voff[j];
-  for (int64_t rb = r0; rb < min(n3, r0 + GCH); rb += GROWS) {
-    for (int t = threadIdx.x; t < GROWS * m; t += 256) {
-      const int rr = t / m, cc = t % m;
-      const int64_t row = rb + rr;
-      const bool ok = row < n3;
-      su[rr][cc] = ok ? Uj[row * m + cc] : 0.0;
-      s1[rr][cc] = ok ? V1j[row * m + cc] : 0.0;
-      s2[rr][cc] = ok ? V2j[row * m + cc] : 0.0;
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int u = 0; u < NT; ++u) a1[t][u] = a2[t][u] = v4d{0, 0, 0, 0};
+  const double *Uj = U + voff[j], *V1j = V1 + voff[j], *V2j = V2 + voff[j];
+#pragma unroll 2
+  for (int64_t r = r0 + 4 * w; r < rend; r += 16) {
+    const int64_t row = min(r + lk, rend - 1) * m;
+    double fu[NT], f1[NT], f2[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const int c = min(16 * t + li, m - 1);
+      fu[t] = Uj[row + c];
+      f1[t] = V1j[row + c];
+      f2[t] = V2j[row + c];
     }
-    __syncthreads();
 #pragma unroll
-    for (int q = 0; q < EPT; ++q) {
-      const int e = threadIdx.x + 256 * q;
-      if (e < m * m) {
-        const int a = e / m, b = e % m;
-        double t1 = 0, t2 = 0;
-        for (int rr = 0; rr < GROWS; ++rr) {
-          t1 += su[rr][a] * s1[rr][b];
-          t2 += su[rr][a] * s2[rr][b];
-        }
-        a1[q] += t1;
-        a2[q] += t2;
+    for (int t = 0; t < NT; ++t)                    // rows past the chunk: zero in one operand
+      fu[t] = r + lk < rend ? fu[t] : 0.0;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int u = 0; u < NT; ++u) {
+        a1[t][u] = mma64(fu[t], f1[u], a1[t][u]);
+        a2[t][u] = mma64(fu[t], f2[u], a2[t][u]);
       }
-    }
+  }
+  for (int q = 0; q < 4; ++q) {                     // the waves' sums, in wave order
+    if (w == q)
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int u = 0; u < NT; ++u)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            double* p1 = &red[0][16 * t + 4 * e + lk][16 * u + li];
+            double* p2 = &red[1][16 * t + 4 * e + lk][16 * u + li];
+            *p1 = (q ? *p1 : 0.0) + a1[t][u][e];
+            *p2 = (q ? *p2 : 0.0) + a2[t][u][e];
+          }
     __syncthreads();
   }
   double* pj = part + ((int64_t)j * nch_max + blockIdx.x) * 2 * MAXM * MAXM;
-#pragma unroll
-  for (int q = 0; q < EPT; ++q) {
-    const int e = threadIdx.x + 256 * q;
-    if (e < m * m) {
-      pj[e] = a1[q];
-      pj[MAXM * MAXM + e] = a2[q];
-    }
+  for (int e = threadIdx.x; e < m * m; e += 256) {
+    pj[e] = red[0][e / m][e % m];
+    pj[MAXM * MAXM + e] = red[1][e / m][e % m];
   }
 }
 
-__global__ void k_gram_sum(const int64_t* nrows, int m, const int32_t* active,
+// sum over k < n of p[k * stride], four at a time (a fixed order; the loads of a round are
+// independent)
+__device__ inline double slot_sum(const double* p, int64_t n, int64_t stride) {
+  double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+  int64_t k = 0;
+  for (; k + 4 <= n; k += 4) {
+    s0 += p[k * stride];
+    s1 += p[(k + 1) * stride];
+    s2 += p[(k + 2) * stride];
+    s3 += p[(k + 3) * stride];
+  }
+  for (; k < n; ++k) s0 += p[k * stride];
+  return (s0 + s1) + (s2 + s3);
+}
+
+__global__ void k_gram_sum(const int64_t* nrows, int m, const int32_t* active, int64_t gch,
                            int64_t nch_max, const double* part, double* G) {
   const int j = blockIdx.y;
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (!active[j] || e >= 2 * MAXM * MAXM) return;
-  const int64_t nch = (3 * nrows[j] + GCH - 1) / GCH;
-  double s = 0.0;
-  for (int64_t k = 0; k < nch; ++k) s += part[((int64_t)j * nch_max + k) * 2 * MAXM * MAXM + e];
-  G[(int64_t)j * 2 * MAXM * MAXM + e] = s;
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (!active[j] || i >= 2 * m * m) return;
+  const int e = i < m * m ? i : MAXM * MAXM + i - m * m;
+  G[(int64_t)j * 2 * MAXM * MAXM + e] =
+      slot_sum(part + (int64_t)j * nch_max * 2 * MAXM * MAXM + e, (3 * nrows[j] + gch - 1) / gch,
+               2 * MAXM * MAXM);
 }
 
 // Small dense Rayleigh-Ritz per subdomain: G_B c = mu G_M c, largest mu first.
@@ -530,7 +574,7 @@ __global__ void __launch_bounds__(256) k_rayleigh_ritz(int m, const int32_t* act
       V[MAXM][MAXM + 1];
   __shared__ double dsc[MAXM], rc[MAXM / 2 + 1], rs[MAXM / 2 + 1], mu[MAXM];
   __shared__ int rp[MAXM / 2 + 1], rq[MAXM / 2 + 1], perm[MAXM];
-  __shared__ double offn;
+  __shared__ double offs[4][2];
   const int j = blockIdx.x;
   if (!active[j]) return;
   const int t = threadIdx.x;
@@ -592,21 +636,30 @@ __global__ void __launch_bounds__(256) k_rayleigh_ritz(int m, const int32_t* act
     V[a][b] = (a == b) ? 1.0 : 0.0;
   }
   __syncthreads();
-  // parallel cyclic Jacobi, round-robin pairing (one index is a dummy when m is odd)
+  // parallel cyclic Jacobi, round-robin pairing (one index is a dummy when m is odd).  A
+  // round is a chain of two barriers: the rotations, then every 2 x 2 block (pair k's rows,
+  // pair l's columns) turned from both sides by the thread that owns it, and V's columns.
+  // (One subdomain's chain of dependent steps is all there is: 32 columns 0.69 -> 0.29 ms
+  // with the sums over H and the ordering taken off a single thread.)
   const int me = m + (m & 1);
   const int np = me / 2;
   for (int sweep = 0; sweep < 40; ++sweep) {
-    if (t == 0) {
-      double off = 0.0, all = 0.0;
-      for (int a = 0; a < m; ++a)
-        for (int b = 0; b < m; ++b) {
-          all += H[a][b] * H[a][b];
-          if (a != b) off += H[a][b] * H[a][b];
-        }
-      offn = (off <= 1e-30 * all) ? 1.0 : 0.0;
+    double off = 0.0, all = 0.0;
+    for (int e = t; e < m * m; e += 256) {
+      const double h = H[e / m][e % m];
+      all += h * h;
+      if (e / m != e % m) off += h * h;
+    }
+    off = wave_sum_d(off);
+    all = wave_sum_d(all);
+    if ((t & 63) == 0) {
+      offs[t >> 6][0] = off;
+      offs[t >> 6][1] = all;
     }
     __syncthreads();
-    if (offn != 0.0) break;
+    off = offs[0][0] + offs[1][0] + offs[2][0] + offs[3][0];
+    all = offs[0][1] + offs[1][1] + offs[2][1] + offs[3][1];
+    if (off <= 1e-30 * all) break;                  // the same in every thread
     for (int round = 0; round < me - 1; ++round) {
       if (t < np) {
         int p, q;
@@ -631,24 +684,35 @@ __global__ void __launch_bounds__(256) k_rayleigh_ritz(int m, const int32_t* act
         rs[t] = s;
       }
       __syncthreads();
-      for (int e = t; e < np * m; e += 256) {      // rows: H <- P^T H
-        const int k = e / m, col = e % m;
-        const int p = rp[k], q = rq[k];
-        if (p == q) continue;
-        const double c = rc[k], s = rs[k];
-        const double hp = H[p][col], hq = H[q][col];
-        H[p][col] = c * hp - s * hq;
-        H[q][col] = s * hp + c * hq;
+      for (int e = t; e < np * np; e += 256) {     // H <- P^T H P, rows first
+        const int k = e / np, l = e % np;
+        const int p = rp[k], q = rq[k], x = rp[l], y = rq[l];
+        const double c = rc[k], s = rs[k], d = rc[l], f = rs[l];
+        double hpx = H[p][x], hpy = H[p][y], hqx = H[q][x], hqy = H[q][y];
+        if (p != q) {
+          const double a0 = c * hpx - s * hqx, a1 = c * hpy - s * hqy;
+          hqx = s * hpx + c * hqx;
+          hqy = s * hpy + c * hqy;
+          hpx = a0;
+          hpy = a1;
+        }
+        if (x != y) {
+          H[p][x] = d * hpx - f * hpy;
+          H[p][y] = f * hpx + d * hpy;
+          if (p != q) {
+            H[q][x] = d * hqx - f * hqy;
+            H[q][y] = f * hqx + d * hqy;
+          }
+        } else {
+          H[p][x] = hpx;
+          if (p != q) H[q][x] = hqx;
+        }
       }
-      __syncthreads();
-      for (int e = t; e < np * m; e += 256) {      // columns: H <- H P, V <- V P
+      for (int e = t; e < np * m; e += 256) {      // V <- V P
         const int k = e / m, row = e % m;
         const int p = rp[k], q = rq[k];
         if (p == q) continue;
         const double c = rc[k], s = rs[k];
-        const double hp = H[row][p], hq = H[row][q];
-        H[row][p] = c * hp - s * hq;
-        H[row][q] = s * hp + c * hq;
         const double vp = V[row][p], vq = V[row][q];
         V[row][p] = c * vp - s * vq;
         V[row][q] = s * vp + c * vq;
@@ -656,19 +720,13 @@ __global__ void __launch_bounds__(256) k_rayleigh_ritz(int m, const int32_t* act
       __syncthreads();
     }
   }
-  // order by decreasing mu
-  if (t == 0) {
-    for (int a = 0; a < m; ++a) {
-      mu[a] = H[a][a];
-      perm[a] = a;
-    }
-    for (int a = 0; a < m; ++a)
-      for (int b = a + 1; b < m; ++b)
-        if (mu[perm[b]] > mu[perm[a]]) {
-          const int tmp = perm[a];
-          perm[a] = perm[b];
-          perm[b] = tmp;
-        }
+  // order by decreasing mu (ties: the lower column first)
+  if (t < m) mu[t] = H[t][t];
+  __syncthreads();
+  if (t < m) {
+    int rank = 0;
+    for (int a = 0; a < m; ++a) rank += mu[a] > mu[t] || (mu[a] == mu[t] && a < t);
+    perm[rank] = t;
   }
   __syncthreads();
   // c = D L^-T V (column b = Ritz vector of the b-th largest mu)
@@ -688,91 +746,124 @@ __global__ void __launch_bounds__(256) k_rayleigh_ritz(int m, const int32_t* act
   }
 }
 
-// out[i][b] = sum_a in[i][a] c[a][b] (row-major blocks of m columns).  A work-group takes
-// ROT_ROWS rows, so that the m x m matrix it stages in LDS serves many of them; each wave
-// forms four rows at a time (lane = column).
-constexpr int ROT_ROWS = 64;
-__global__ void __launch_bounds__(256) k_rotate(const int64_t* nrows, int m,
-                                                const int64_t* voff, const int32_t* active,
-                                                const double* Cm, const double* in,
-                                                double* out) {
-  __shared__ double c[MAXM][MAXM];
+// X = Y C, M X = (M Y) C, B X = (B Y) C and, per column, the partial sums of
+// ||M X - theta B X||^2, ||M X||^2 and ||X||^2 in one pass over the blocks.  A wave takes 16
+// rows at a time and forms out^T = C^T in^T: its share of C stays in registers.  Which
+// reduction index a lane group takes in a step, and which column an operand row stands for,
+// is free: a group takes 4 NT adjacent entries of a row, and a lane ends with 4 adjacent
+// columns, so loads and stores are 16 bytes wide.  A wave reads its rows of all three
+// blocks before it writes any, so outputs may be inputs.  Bound by six passes over the
+// blocks (eleven in three rotations, the residuals and two copies): 16 subdomains of 116k
+// rows, 32 columns, 2.9 -> 0.81 ms; 4 of 4.5k rows, 0.34 -> 0.02 ms.  MX or BX2 (a second copy of B X,
+// the next solve's right-hand side) may be null.
+template <int NT>
+__global__ void __launch_bounds__(256) k_rotate(const int64_t* nrows, int m, const int64_t* voff,
+                                                const int32_t* active, const double* Cm,
+                                                const double* theta, const double* Yin,
+                                                const double* MYin, const double* BYin,
+                                                double* X, double* MX, double* BX, double* BX2,
+                                                int64_t gch, int64_t nch_max, double* part) {
+  __shared__ double red[4][3][16 * NT];
+  constexpr int KS = 4 * NT;
   const int j = blockIdx.y;
   if (!active[j]) return;
   const int64_t n3 = 3 * nrows[j];
-  const int64_t r0 = (int64_t)blockIdx.x * ROT_ROWS;
+  const int64_t r0 = (int64_t)blockIdx.x * gch, rend = min(n3, r0 + gch);
   if (r0 >= n3) return;
-  for (int e = threadIdx.x; e < m * m; e += 256) c[e / m][e % m] = Cm[(int64_t)j * MAXM * MAXM + e];
-  __syncthreads();
-  const int b = threadIdx.x % 64, w = threadIdx.x / 64;
-  const int bb = min(b, m - 1);
-  const int64_t rend = min(n3, r0 + ROT_ROWS);
-  const double* base = in + voff[j];
-  for (int64_t row = r0 + w; row < rend; row += 16) {   // rows row + 4 q, q < 4
-    // lane a loads entry a of each row (one coalesced load per row); the products take
-    // entry a from lane a (a wave-uniform lane read into a scalar operand)
-    double xv[4];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
+  // C[k][b], k = KS lk + ks, b = 16 t + 4 (li % 4) + li / 4; zero past m
+  double ca[NT][KS], th[NT][4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) xv[q] = base[min(row + 4 * q, rend - 1) * m + bb];
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int a = 0; a < m; ++a) {
-      const double ca = c[a][bb];
+  for (int t = 0; t < NT; ++t) {
+    const int b = 16 * t + 4 * (li & 3) + (li >> 2);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) acc[q] += lane_value(xv[q], a) * ca;
+    for (int ks = 0; ks < KS; ++ks) {
+      const int k = KS * lk + ks;
+      ca[t][ks] = k < m && b < m ? Cm[(int64_t)j * MAXM * MAXM + min(k, m - 1) * m + min(b, m - 1)]
+                                 : 0.0;
     }
-    if (b < m)
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
-        if (row + 4 * q < rend) out[voff[j] + (row + 4 * q) * m + b] = acc[q];
+    for (int q = 0; q < 4; ++q)
+      th[t][q] = theta[(int64_t)j * MAXM + min(16 * t + 4 * lk + q, m - 1)];
+  }
+  double sr[NT][4], sm[NT][4], sx[NT][4];
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) sr[t][q] = sm[t][q] = sx[t][q] = 0.0;
+  auto turn = [&](const double* in, int64_t row, v4d (&out)[NT]) {
+    double v[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ks += 2) {
+      const int k = KS * lk + ks;
+      const v2d x = *reinterpret_cast<const v2d*>(in + voff[j] + row * m + min(k, m - 2));
+      v[ks] = k < m ? x[0] : 0.0;
+      v[ks + 1] = k < m ? x[1] : 0.0;
+    }
+#pragma unroll
+    for (int t = 0; t < NT; ++t) out[t] = v4d{0, 0, 0, 0};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+      for (int t = 0; t < NT; ++t) out[t] = mma64(ca[t][ks], v[ks], out[t]);
+  };
+  for (int64_t rb = r0 + 16 * w; rb < rend; rb += 64) {
+    const int64_t row = min(rb + li, rend - 1);
+    v4d x[NT], mx[NT], bx[NT];
+    turn(Yin, row, x);
+    turn(MYin, row, mx);
+    turn(BYin, row, bx);
+    if (rb + li < rend) {
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const int b = 16 * t + 4 * lk;
+        if (b >= m) continue;
+        const int64_t o = voff[j] + row * m + b;
+        auto put = [&](double* p, const v4d& v) {
+          *reinterpret_cast<v2d*>(p + o) = v2d{v[0], v[1]};
+          *reinterpret_cast<v2d*>(p + o + 2) = v2d{v[2], v[3]};
+        };
+        put(X, x[t]);
+        if (MX) put(MX, mx[t]);
+        put(BX, bx[t]);
+        if (BX2) put(BX2, bx[t]);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const double d = mx[t][q] - th[t][q] * bx[t][q];
+          sr[t][q] += d * d;
+          sm[t][q] += mx[t][q] * mx[t][q];
+          sx[t][q] += x[t][q] * x[t][q];
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      double v[3] = {sr[t][q], sm[t][q], sx[t][q]};
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        for (int o = 1; o < 16; o <<= 1) v[i] += __shfl_xor(v[i], o);
+        if (li == 0) red[w][i][16 * t + 4 * lk + q] = v[i];
+      }
+    }
+  __syncthreads();
+  double* pj = part + ((int64_t)j * nch_max + blockIdx.x) * 3 * MAXM;
+  for (int e = threadIdx.x; e < 3 * m; e += 256) {
+    const int i = e / m, b = e % m;
+    pj[i * MAXM + b] = red[0][i][b] + red[1][i][b] + red[2][i][b] + red[3][i][b];
   }
 }
 
-// per column: ||MX - theta BX||^2, ||MX||^2 and ||X||^2 (chunk partials, then fixed-order
-// sums)
-__global__ void __launch_bounds__(256) k_resid(const int64_t* nrows, int m,
-                                               const int64_t* voff, const int32_t* active,
-                                               const double* theta, const double* MX,
-                                               const double* BX, const double* X,
-                                               int64_t nch_max, double* part) {
-  __shared__ double red[4][3][64];
-  const int j = blockIdx.y;
-  if (!active[j]) return;
-  const int64_t n3 = 3 * nrows[j];
-  const int b = threadIdx.x % 64, rg = threadIdx.x / 64;
-  double r2 = 0, m2 = 0, x2 = 0;
-  if (b < m) {
-    const double th = theta[(int64_t)j * MAXM + b];
-    const int64_t r0 = (int64_t)blockIdx.x * GCH;
-    for (int64_t row = r0 + rg; row < min(n3, r0 + GCH); row += 4) {
-      const int64_t e = voff[j] + row * m + b;
-      const double mx = MX[e];
-      const double d = mx - th * BX[e];
-      r2 += d * d;
-      m2 += mx * mx;
-      x2 += X[e] * X[e];
-    }
-  }
-  red[rg][0][b] = r2;
-  red[rg][1][b] = m2;
-  red[rg][2][b] = x2;
-  __syncthreads();
-  if (rg == 0 && b < m) {
-    double* pj = part + ((int64_t)j * nch_max + blockIdx.x) * 3 * MAXM;
-#pragma unroll
-    for (int q = 0; q < 3; ++q)
-      pj[q * MAXM + b] = red[0][q][b] + red[1][q][b] + red[2][q][b] + red[3][q][b];
-  }
-}
-
-__global__ void k_resid_sum(const int64_t* nrows, const int32_t* active, int64_t nch_max,
-                            const double* part, double* out) {
+__global__ void k_resid_sum(const int64_t* nrows, const int32_t* active, int m, int64_t gch,
+                            int64_t nch_max, const double* part, double* out) {
   const int j = blockIdx.x;
   const int e = threadIdx.x;
-  if (!active[j] || e >= 3 * MAXM) return;
-  const int64_t nch = (3 * nrows[j] + GCH - 1) / GCH;
-  double s = 0.0;
-  for (int64_t k = 0; k < nch; ++k) s += part[((int64_t)j * nch_max + k) * 3 * MAXM + e];
-  out[(int64_t)j * 3 * MAXM + e] = s;
+  if (!active[j] || e >= 3 * MAXM || e % MAXM >= m) return;
+  out[(int64_t)j * 3 * MAXM + e] =
+      slot_sum(part + (int64_t)j * nch_max * 3 * MAXM + e, (3 * nrows[j] + gch - 1) / gch,
+               3 * MAXM);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -850,46 +941,79 @@ __global__ void k_pair_adjacency(const uint64_t* nand, const uint64_t* nor, int 
   }
 }
 
-// K_0 block (k, j) = sum over nodes in I_k and D_j of Z_k^T V_j
-__global__ void __launch_bounds__(256) k_coarse_pair(GeneoDev g, CoarseDev cd, int n_sub,
-                                                     const int32_t* adj, const double* Z,
+// K_0 block (k, j) = sum over nodes in I_k and D_j of Z_k^T V_j, partial sums over a chunk of
+// I_k's nodes (blockIdx.y) into a slot of its own, added by k_coarse_sum.  Each wave looks up
+// 64 nodes at a time and takes those in D_j in turn, a node's three rows in one step of the
+// matrix instruction (the fourth is zero): most nodes of a neighbouring pair are skipped at
+// the look-up.  16 subdomains of 30k nodes: 16 to 26 -> 1.1 ms against one work-group per pair
+// that scanned all nodes with scalar products.
+constexpr int CPT = (MAXM + 15) / 16;
+__global__ void __launch_bounds__(256) k_coarse_pair(GeneoDev g, CoarseDev cd,
+                                                     const int32_t* pairs, const double* Z,
                                                      const double* Vc, const int64_t* vcoff,
-                                                     int64_t n0, double* K0) {
-  const int k = blockIdx.x, j = blockIdx.y;
-  if (!adj[(int64_t)k * n_sub + j]) return;
+                                                     int64_t nodes, int64_t slot, double* part) {
+  __shared__ double red[16 * CPT][16 * CPT + 1];
+  const int k = pairs[2 * blockIdx.x], j = pairs[2 * blockIdx.x + 1];
   const int mk = cd.nev[k], mj = cd.nev[j];
   if (mk == 0 || mj == 0) return;
-  constexpr int EPT = (MAXM * MAXM + 255) / 256;
-  double acc[EPT];
-#pragma unroll
-  for (int q = 0; q < EPT; ++q) acc[q] = 0.0;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
   const int64_t nIk = cd.nI[k], n3k = 3 * nIk;
+  const int64_t end = min(nIk, ((int64_t)blockIdx.y + 1) * nodes);
   const double* Zk = Z + cd.zoff[k];
   const double* Vj = Vc + vcoff[j];
-  for (int64_t ln = 0; ln < nIk; ++ln) {
-    const int64_t n = cd.I_nodes[cd.offI[k] + ln];
-    const int64_t ldj = g.D_loc[(int64_t)j * g.N + n];
-    if (ldj < 0) continue;
+  const int tk = (mk + 15) / 16, tj = (mj + 15) / 16;
+  v4d acc[CPT][CPT];
 #pragma unroll
-    for (int q = 0; q < EPT; ++q) {
-      const int e = threadIdx.x + 256 * q;
-      if (e < mk * mj) {
-        const int b = e / mj, a = e % mj;
-        double s = 0.0;
-        for (int c = 0; c < 3; ++c)
-          s += Zk[(int64_t)b * n3k + 3 * ln + c] * Vj[(3 * ldj + c) * mj + a];
-        acc[q] += s;
+  for (int t = 0; t < CPT; ++t)
+#pragma unroll
+    for (int u = 0; u < CPT; ++u) acc[t][u] = v4d{0, 0, 0, 0};
+  for (int64_t l0 = blockIdx.y * nodes + 64 * w; l0 < end; l0 += 256) {
+    int ld = -1;                                   // this lane's node in D_j
+    if (l0 + lane < end)
+      ld = g.D_loc[(int64_t)j * g.N + cd.I_nodes[cd.offI[k] + l0 + lane]];
+    for (uint64_t todo = __ballot(ld >= 0); todo; todo &= todo - 1) {
+      const int b = __ffsll((unsigned long long)todo) - 1;
+      const int64_t rz = 3 * (l0 + b) + min(lk, 2);
+      const int64_t rv = 3 * (int64_t)__builtin_amdgcn_readlane(ld, b) + min(lk, 2);
+      double fz[CPT], fv[CPT];
+#pragma unroll
+      for (int t = 0; t < CPT; ++t) {
+        fz[t] = t < tk ? Zk[(int64_t)min(16 * t + li, mk - 1) * n3k + rz] : 0.0;
+        fv[t] = t < tj ? Vj[rv * mj + min(16 * t + li, mj - 1)] : 0.0;
       }
-    }
-  }
 #pragma unroll
-  for (int q = 0; q < EPT; ++q) {
-    const int e = threadIdx.x + 256 * q;
-    if (e < mk * mj) {
-      const int b = e / mj, a = e % mj;
-      K0[(int64_t)(cd.coff[k] + b) * n0 + cd.coff[j] + a] = acc[q];
+      for (int t = 0; t < CPT; ++t) fz[t] = lk < 3 ? fz[t] : 0.0;
+#pragma unroll
+      for (int t = 0; t < CPT; ++t)
+#pragma unroll
+        for (int u = 0; u < CPT; ++u)
+          if (t < tk && u < tj) acc[t][u] = mma64(fz[t], fv[u], acc[t][u]);
     }
   }
+  for (int q = 0; q < 4; ++q) {                     // the waves' sums, in wave order
+    if (w == q)
+#pragma unroll
+      for (int t = 0; t < CPT; ++t)
+#pragma unroll
+        for (int u = 0; u < CPT; ++u)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            double* p = &red[16 * t + 4 * e + lk][16 * u + li];
+            *p = (q ? *p : 0.0) + acc[t][u][e];
+          }
+    __syncthreads();
+  }
+  double* pj = part + ((int64_t)blockIdx.x * gridDim.y + blockIdx.y) * slot;
+  for (int e = threadIdx.x; e < mk * mj; e += 256) pj[e] = red[e / mj][e % mj];
+}
+
+__global__ void k_coarse_sum(CoarseDev cd, const int32_t* pairs, int n_chunk, int64_t slot,
+                             const double* part, int64_t n0, double* K0) {
+  const int k = pairs[2 * blockIdx.x], j = pairs[2 * blockIdx.x + 1];
+  const int mk = cd.nev[k], mj = cd.nev[j];
+  for (int e = threadIdx.x; e < mk * mj; e += blockDim.x)
+    K0[(int64_t)(cd.coff[k] + e / mj) * n0 + cd.coff[j] + e % mj] =
+        slot_sum(part + (int64_t)blockIdx.x * n_chunk * slot + e, n_chunk, slot);
 }
 
 // symmetrise K_0 into full band storage (B = n0 - 1, ld = n0)
@@ -1069,13 +1193,12 @@ void geneo_coarse(gx_ctx* c, const gx_geneo_opts* o, const std::function<void()>
   d_voff.alloc(n_sub + 1);
   to_dev(d_voff.p, voff.data(), n_sub + 1, s);
   X.alloc(tot);
-  DevBuf<double> BX(tot), Y(tot), BY(tot), T(tot), MYb(m32 ? tot : 0);
+  DevBuf<double> BX(tot), Y(tot), BY(tot), T(m32 ? tot : 0), MYb(m32 ? tot : 0);
   double* MY = m32 ? MYb.p : BX.p;                 // M Y (= B X for exact FP64 solves)
   DevBuf<int32_t> active(n_sub);
   std::vector<int32_t> act(n_sub, 1);
   to_dev(active.p, act.data(), n_sub, s);
-  int64_t nch_max = 0;
-  for (int j = 0; j < n_sub; ++j) nch_max = std::max(nch_max, (3 * sw.nD[j] + GCH - 1) / GCH);
+  const int64_t gch_rows = chunk_rows(sw.nD), nch_max = (3 * maxD + gch_rows - 1) / gch_rows;
   DevBuf<double> gpart((size_t)n_sub * nch_max * 2 * MAXM * MAXM), G((size_t)n_sub * 2 * MAXM * MAXM);
   DevBuf<double> Cm((size_t)n_sub * MAXM * MAXM), theta((size_t)n_sub * MAXM);
   DevBuf<double> rpart((size_t)n_sub * nch_max * 3 * MAXM), rsum((size_t)n_sub * 3 * MAXM);
@@ -1083,7 +1206,6 @@ void geneo_coarse(gx_ctx* c, const gx_geneo_opts* o, const std::function<void()>
   zero(err, s);
   const dim3 growD((unsigned)maxD, n_sub);
   const dim3 gvec(nblocks(3 * maxD * m, 256), n_sub);
-  const dim3 grows(nblocks(3 * maxD, ROT_ROWS), n_sub);
   const dim3 gch((unsigned)nch_max, n_sub);
   hipLaunchKernelGGL(k_rand_init, gvec, dim3(256), 0, s, g, m, d_voff.p, X.p);
   if (m_prev)                                      // warm start: the previous block first
@@ -1122,8 +1244,9 @@ void geneo_coarse(gx_ctx* c, const gx_geneo_opts* o, const std::function<void()>
         hipLaunchKernelGGL(k_sub_block, gvec, dim3(256), 0, s, sw.d_nD.p, m, d_voff.p,
                            active.p, X.p, T.p, Y.p);
     } else {
-      hipLaunchKernelGGL(k_copy_active, gvec, dim3(256), 0, s, 3 * maxD * m, sw.d_nD.p, m,
-                         d_voff.p, active.p, BX.p, Y.p);
+      if (itm == 0)                                // later the rotation leaves B X in Y
+        hipLaunchKernelGGL(k_copy_active, gvec, dim3(256), 0, s, 3 * maxD * m, sw.d_nD.p, m,
+                           d_voff.p, active.p, BX.p, Y.p);
       GX_HIP(hipEventRecord(ev.a, s));
       band_solve(Mb, d_voff.p, Y.p, s, m, active.p);
       GX_HIP(hipEventRecord(ev.b, s));
@@ -1133,25 +1256,22 @@ void geneo_coarse(gx_ctx* c, const gx_geneo_opts* o, const std::function<void()>
     if (m32)
       hipLaunchKernelGGL(k_amul_rows, growD, dim3(64), 0, s, g, crowA.p, clocA.p, cbvA.p, m,
                          d_voff.p, active.p, Y.p, BY.p, sigma, MY);
-    hipLaunchKernelGGL(k_gram, gch, dim3(256), 0, s, sw.d_nD.p, m, d_voff.p, active.p, Y.p,
-                       MY, BY.p, nch_max, gpart.p);
-    hipLaunchKernelGGL(k_gram_sum, dim3(nblocks(2 * MAXM * MAXM, 256), n_sub), dim3(256), 0,
-                       s, sw.d_nD.p, m, active.p, nch_max, gpart.p, G.p);
+    const int nt = (m + 15) / 16;                  // column tiles
+    auto gram = nt == 1 ? k_gram<1> : nt == 2 ? k_gram<2> : k_gram<3>;
+    hipLaunchKernelGGL(gram, gch, dim3(256), 0, s, sw.d_nD.p, m, d_voff.p, active.p, Y.p, MY,
+                       BY.p, gch_rows, nch_max, gpart.p);
+    hipLaunchKernelGGL(k_gram_sum, dim3(nblocks(2 * m * m, 256), n_sub), dim3(256), 0, s,
+                       sw.d_nD.p, m, active.p, gch_rows, nch_max, gpart.p, G.p);
     hipLaunchKernelGGL(k_rayleigh_ritz, dim3(n_sub), dim3(256), 0, s, m, active.p, G.p, Cm.p,
                        theta.p, err.p);
-    hipLaunchKernelGGL(k_rotate, grows, dim3(256), 0, s, sw.d_nD.p, m, d_voff.p, active.p,
-                       Cm.p, Y.p, T.p);             // new X
-    hipLaunchKernelGGL(k_rotate, grows, dim3(256), 0, s, sw.d_nD.p, m, d_voff.p, active.p,
-                       Cm.p, MY, Y.p);              // M X_new
-    hipLaunchKernelGGL(k_rotate, grows, dim3(256), 0, s, sw.d_nD.p, m, d_voff.p, active.p,
-                       Cm.p, BY.p, BX.p);           // B X_new
-    hipLaunchKernelGGL(k_resid, gch, dim3(256), 0, s, sw.d_nD.p, m, d_voff.p, active.p,
-                       theta.p, Y.p, BX.p, T.p, nch_max, rpart.p);
-    hipLaunchKernelGGL(k_resid_sum, dim3(n_sub), dim3(3 * MAXM), 0, s, sw.d_nD.p, active.p,
-                       nch_max, rpart.p, rsum.p);
-    // new X into X for the active subdomains
-    hipLaunchKernelGGL(k_copy_active, gvec, dim3(256), 0, s, 3 * maxD * m, sw.d_nD.p, m,
-                       d_voff.p, active.p, T.p, X.p);
+    // new X, M X (kept in Y for the mixed path's next residuals) and B X, for the active
+    // subdomains; in FP64 the next solve's right-hand side B X goes to Y as well
+    auto rotate = nt == 1 ? k_rotate<1> : nt == 2 ? k_rotate<2> : k_rotate<3>;
+    hipLaunchKernelGGL(rotate, gch, dim3(256), 0, s, sw.d_nD.p, m, d_voff.p, active.p, Cm.p,
+                       theta.p, Y.p, MY, BY.p, X.p, m32 ? Y.p : nullptr, BX.p,
+                       m32 ? nullptr : Y.p, gch_rows, nch_max, rpart.p);
+    hipLaunchKernelGGL(k_resid_sum, dim3(n_sub), dim3(3 * MAXM), 0, s, sw.d_nD.p, active.p, m,
+                       gch_rows, nch_max, rpart.p, rsum.p);
     GX_HIP(hipGetLastError());
     to_host(h_theta.data(), theta.p, h_theta.size(), s);
     to_host(h_res.data(), rsum.p, h_res.size(), s);
@@ -1262,8 +1382,32 @@ void geneo_coarse(gx_ctx* c, const gx_geneo_opts* o, const std::function<void()>
   const int64_t n0 = sw.n0;
   DevBuf<double> K0(n0 * n0);
   zero(K0, s);
-  hipLaunchKernelGGL(k_coarse_pair, dim3(n_sub, n_sub), dim3(256), 0, s, g, cd, n_sub, adj.p,
-                     sw.Z.p, Vc.p, d_vco.p, n0, K0.p);
+  {
+    std::vector<int32_t> hadj((size_t)n_sub * n_sub), hp;   // the pairs that touch
+    to_host(hadj.data(), adj.p, hadj.size(), s);
+    for (int k = 0; k < n_sub; ++k)
+      for (int j = 0; j < n_sub; ++j)
+        if (hadj[(size_t)k * n_sub + j]) {
+          hp.push_back(k);
+          hp.push_back(j);
+        }
+    const unsigned n_pair = (unsigned)(hp.size() / 2);
+    DevBuf<int32_t> pairs(hp.size());
+    to_dev(pairs.p, hp.data(), hp.size(), s);
+    // chunks of nodes per pair: about 4096 work-groups in all, 256 nodes or more each
+    const int n_chunk = (int)std::max<int64_t>(
+        1, std::min<int64_t>((maxI + 255) / 256, 4096 / (int64_t)n_pair));
+    const int64_t nodes = (maxI + n_chunk - 1) / n_chunk;
+    int64_t top = 1;
+    for (int j = 0; j < n_sub; ++j) top = std::max<int64_t>(top, sw.nev[j]);
+    DevBuf<double> kpart((size_t)n_pair * n_chunk * top * top);
+    hipLaunchKernelGGL(k_coarse_pair, dim3(n_pair, n_chunk), dim3(256), 0, s, g, cd, pairs.p,
+                       sw.Z.p, Vc.p, d_vco.p, nodes, top * top, kpart.p);
+    hipLaunchKernelGGL(k_coarse_sum, dim3(n_pair), dim3(256), 0, s, cd, pairs.p, n_chunk,
+                       top * top, kpart.p, n0, K0.p);
+    GX_HIP(hipStreamSynchronize(s));                // hp is read by its copy
+    GX_HIP(hipGetLastError());
+  }
   band_layout(sw.C, {n0}, {n0 - 1}, false, s);
   sw.C.coarse = true;
   band_zero(sw.C, s);
