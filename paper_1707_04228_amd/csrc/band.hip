@@ -29,6 +29,7 @@ namespace gx {
 constexpr int NB = 64;          // factorisation block
 constexpr int TS = 64;          // trailing-update tile
 constexpr int SB = 64;          // solve block (one wavefront)
+static_assert(SB == NB, "solve blocks are the factorisation's");
 constexpr int SOLVE_THREADS = 512;
 
 typedef double v4d __attribute__((ext_vector_type(4)));
@@ -958,6 +959,47 @@ void band_factor_finish(FactorJob& job) {
                 "non-positive pivot in the banded Cholesky factorisation of " + job.what);
 }
 
+// The links of every block: D_b L(b, b - 1) and D_b^T L(b + 1, b)^T, 64 x 64 products on the
+// FP64 matrix instruction.  A solve's step from block to block then takes one product on the
+// path from one hand-over to the next: D_b (rhs - older blocks) is formed while the
+// neighbour's solution is awaited, and only its link follows (in place of the neighbour's
+// own block, so the solve reads no more).  Work-group (block, part); each wave forms two of
+// the 16 tiles of either product, its operands straight from LDS.
+template <class T>
+__global__ void __launch_bounds__(512) k_link(const BandPart* part, const T* v, const T* dinv,
+                                              T* link) {
+  __shared__ double D[SB][SB + 1], L[2][SB][SB + 1];
+  const BandPart& P = part[blockIdx.y];
+  const int64_t n = P.rows, ncb = (P.cols + SB - 1) / SB, b = blockIdx.x;
+  if (b >= ncb) return;
+  const int64_t i0 = b * SB, rs = P.ld - 1;
+  const T* cb = v + P.off + P.B;
+  const T* d = dinv + P.boff + b * SB * SB;
+  for (int e = threadIdx.x; e < SB * SB; e += 512) {
+    const int i = e / SB, c = e % SB;
+    D[i][c] = (double)d[e];
+    const int64_t r0 = i0 + i, c0 = i0 - SB + c, r1 = i0 + SB + i, c1 = i0 + c;
+    L[0][i][c] = b > 0 && r0 < n && r0 - c0 <= P.B ? (double)cb[r0 * rs + c0] : 0.0;
+    L[1][i][c] = r1 < n && c1 < n && r1 - c1 <= P.B ? (double)cb[r1 * rs + c1] : 0.0;
+  }
+  __syncthreads();
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
+  T* out = link + 2 * P.boff + 2 * b * SB * SB;
+  for (int q = 0; q < 4; ++q) {
+    const int which = q >> 1, tile = w + 8 * (q & 1), rt = tile >> 2, ct = tile & 3;
+    v4d acc = {0, 0, 0, 0};
+#pragma unroll
+    for (int k = 0; k < SB; k += 4) {
+      const double fa = which ? D[k + lk][16 * rt + li] : D[16 * rt + li][k + lk];
+      const double fb = which ? L[1][16 * ct + li][k + lk] : L[0][k + lk][16 * ct + li];
+      acc = Mfma<double>::mma(fa, fb, acc);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      out[(int64_t)which * SB * SB + (16 * rt + 4 * e + lk) * SB + 16 * ct + li] = (T)acc[e];
+  }
+}
+
 void band_factor(gx_ctx* c, BandSet& bs, hipStream_t st, const char* what) {
   FactorJob job;
   band_factor_start(bs, st, aux_stream(c->look[0]), job, what);
@@ -979,16 +1021,16 @@ void band_factor(gx_ctx* c, BandSet& bs, hipStream_t st, const char* what) {
 // every wave always reaches the end of the kernel.
 //
 // What bounds the one-right-hand-side solve: a work-group streams about 22 GB/s however idle
-// the device is, and a hand-over costs 2.5 to 3 us, so few matrices need many groups, and
-// the chain of (n + B) / 128 hand-overs per sweep is the rest.  Per solve, unsplit with four
-// groups -> split with up to eight (FP64 but where noted): 4 matrices of n = 3,500, B = 370:
-// 0.29 -> 0.18 ms; 6 of 16,000, 1,020: 1.77 -> 0.73 ms; 16 of 37,000, 1,220 (9.5 GB): 4.85 ->
-// 2.03 ms; 5 of 45,000, 2,080, FP32: 6.12 -> 2.03 ms; 16 of 91,000, 1,630 (26 GB): 15.1 -> 5.8
-// ms.  64 of those fill the device with one group per compute unit and stay where they
+// the device is, so few matrices need many groups; then the chain of (n + B) / 128 hand-overs
+// per sweep, which the links (k_link) and lane sums in registers shorten.  Per solve, one
+// chain per matrix and four groups -> now (FP64 but where noted): 4 matrices of n = 3,500, B =
+// 370: 0.29 -> 0.13 ms; 6 of 16,000, 1,020: 1.77 -> 0.59 ms; 16 of 37,000, 1,220 (9.5 GB): 4.85
+// -> 1.98 ms; 5 of 45,000, 2,080, FP32: 6.12 -> 1.38 ms; 16 of 91,000, 1,630 (26 GB): 15.1 ->
+// 5.65 ms.  64 of those fill the device with one group per compute unit and stay where they
 // were (118 GB in 22 to 23 ms, FP32 59 GB in 12.9 ms).
 constexpr int SW = SOLVE_THREADS / 64;           // waves per work-group (8)
 constexpr int RPW = SB / SW;                      // forward rows per wave (8)
-constexpr int GMAX = 8;                           // work-groups per part, 1-RHS solve
+constexpr int GMAX = 16;                          // work-groups per part, 1-RHS solve
 constexpr int FL = 3;                             // blocks in flight taken at a time
 constexpr int DL = SB * SB / SOLVE_THREADS;       // inverse-block entries per thread (8)
 static_assert(DL == RPW, "the inverse-block products reuse the 8-row lane reduction");
@@ -1009,24 +1051,49 @@ __device__ inline T band_raw(const T* base, int64_t n, int64_t B, int64_t ld, in
   return base[rc * ld + o];
 }
 
-// s[r] summed over the 64 lanes; lane l receives the total of row l >> 3
+// The 32-bit halves of a double through a lane operation
+template <class F>
+__device__ inline double by_halves(double v, F f) {
+  const uint64_t u = (uint64_t)__double_as_longlong(v);
+  return __longlong_as_double(
+      (long long)((uint64_t)f((uint32_t)(u >> 32)) << 32 | f((uint32_t)u)));
+}
+// lane i's value of a DPP move within its row of 16 lanes (CTRL 0x100 + k: from lane i + k,
+// 0x120 + 8: from lane i xor 8)
+template <int CTRL>
+__device__ inline double row_move(double v) {
+  return by_halves(v, [](uint32_t w) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, CTRL, 0xf, 0xf, true);
+  });
+}
+// a + b after the odd 32-lane halves (16-lane rows) of a and the even ones of b have changed
+// places: a summed over the pairs of halves (rows) in the even ones, b in the odd ones
+template <int LANES>
+__device__ inline double swap_add(double a, double b) {
+  const uint64_t ua = (uint64_t)__double_as_longlong(a), ub = (uint64_t)__double_as_longlong(b);
+  auto swap = [](uint32_t x, uint32_t y) {
+    if constexpr (LANES == 32) return __builtin_amdgcn_permlane32_swap(x, y, false, false);
+    else return __builtin_amdgcn_permlane16_swap(x, y, false, false);
+  };
+  const auto lo = swap((uint32_t)ua, (uint32_t)ub), hi = swap((uint32_t)(ua >> 32), (uint32_t)(ub >> 32));
+  return __longlong_as_double((long long)((uint64_t)hi[0] << 32 | lo[0])) +
+         __longlong_as_double((long long)((uint64_t)hi[1] << 32 | lo[1]));
+}
+
+// s[r] summed over the 64 lanes; lane l (a multiple of 8) receives the total of row l >> 3.
+// In registers throughout (lane swaps and DPP moves, no LDS): the sum is on the path from one
+// hand-over to the next.
 __device__ inline double reduce_rows8(const double (&s)[RPW], int lane) {
   double t4[4], t2[2];
-  const bool b5 = lane & 32, b4 = lane & 16, b3 = lane & 8;
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const double send = b5 ? s[r] : s[r + 4];
-    t4[r] = (b5 ? s[r + 4] : s[r]) + __shfl_xor(send, 32);
-  }
+  for (int r = 0; r < 4; ++r) t4[r] = swap_add<32>(s[r], s[r + 4]);
 #pragma unroll
-  for (int r = 0; r < 2; ++r) {
-    const double send = b4 ? t4[r] : t4[r + 2];
-    t2[r] = (b4 ? t4[r + 2] : t4[r]) + __shfl_xor(send, 16);
-  }
-  double t = (b3 ? t2[1] : t2[0]) + __shfl_xor(b3 ? t2[0] : t2[1], 8);
-  t += __shfl_xor(t, 4);
-  t += __shfl_xor(t, 2);
-  t += __shfl_xor(t, 1);
+  for (int r = 0; r < 2; ++r) t2[r] = swap_add<16>(t4[r], t4[r + 2]);
+  const bool b3 = lane & 8;
+  double t = (b3 ? t2[1] : t2[0]) + row_move<0x128>(b3 ? t2[0] : t2[1]);
+  t += row_move<0x104>(t);
+  t += row_move<0x102>(t);
+  t += row_move<0x101>(t);
   return t;
 }
 
@@ -1091,6 +1158,7 @@ struct Solve1 {
   int kind;
   const T* base;
   const T* dv;
+  const T* link;
   const int64_t* fcb;
   const int64_t* lrb;
   const double* x;
@@ -1111,7 +1179,7 @@ template <class T, class Load>
 __device__ __forceinline__ void band_solve_1_mat(Load load, int own, int upper, int g, int G,
                                                  int* err) {
   int n, cols, sep, B, rs, N;                       // (a part has less than 2^31 entries)
-  const T *base, *dv;
+  const T *base, *dv, *link;
   const int64_t *fcb, *lrb;
   const double *x, *mate;                           // row r at x[dx r], mate[-r]
   double *y, *z;
@@ -1121,7 +1189,7 @@ __device__ __forceinline__ void band_solve_1_mat(Load load, int own, int upper, 
     const Solve1<T> S = load(part);
     n = (int)S.n, cols = (int)S.cols, sep = (int)S.sep, B = (int)S.B, rs = (int)S.ld - 1;
     N = (int)S.N;
-    base = S.base, dv = S.dv, fcb = S.fcb, lrb = S.lrb;
+    base = S.base, dv = S.dv, link = S.link, fcb = S.fcb, lrb = S.lrb;
     lower = S.kind == PART_LOWER;
     x = lower ? S.x + N - 1 : S.x;
     dx = lower ? -1 : 1;
@@ -1215,15 +1283,18 @@ __device__ __forceinline__ void band_solve_1_mat(Load load, int own, int upper, 
         }
       }
     }
-    // blocks in flight, kdone .. kc - 1 (at most step - 1), up to FL at a time, the last
-    // ones together: their factor entries (and, before the last, this block's inverse
-    // diagonal block) are loaded first; then wave 0 polls their solutions (one round trip
-    // when they are done) and passes them on through LDS
-    T dd[DL];
+    // blocks in flight, kdone .. kc - 1 (at most step - 1), the nearest of them left to the
+    // link below; up to FL at a time, the last ones together: their factor entries (and,
+    // before the last, this block's inverse diagonal block and link) are loaded first; then
+    // wave 0 polls their solutions (one round trip when they are done) and passes them on
+    // through LDS
+    const bool linked = link && k < ncb && kdone < k;
+    const int kin = linked ? kc - 1 : kc;
+    T dd[DL], lm[DL];
     int kf = kdone;
 #pragma unroll 1
     for (;;) {
-      const int rest = kc - kf;
+      const int rest = kin - kf;
       const int nfl = (int)(rest > FL ? (rest - 1) % FL + 1 : rest);
       T pf[FL][RPW];
 #pragma unroll
@@ -1232,10 +1303,14 @@ __device__ __forceinline__ void band_solve_1_mat(Load load, int own, int upper, 
 #pragma unroll
         for (int r = 0; r < RPW; ++r) pf[o][r] = (rp[r] + cc)[(uint32_t)lane];
       }
-      if (rest <= FL)
+      if (rest <= FL) {
+        const int64_t kd = min(k, ncb - 1);
 #pragma unroll
-        for (int u = 0; u < DL; ++u)
-          dd[u] = (dv + (int64_t)min(k, ncb - 1) * SB * SB)[threadIdx.x + SOLVE_THREADS * u];
+        for (int u = 0; u < DL; ++u) {
+          dd[u] = (dv + kd * SB * SB)[threadIdx.x + SOLVE_THREADS * u];
+          if (linked) lm[u] = (link + 2 * kd * SB * SB)[threadIdx.x + SOLVE_THREADS * u];
+        }
+      }
       if (nfl > 0) {
         if (wave == 0) {
           double xo[FL];
@@ -1290,7 +1365,19 @@ __device__ __forceinline__ void band_solve_1_mat(Load load, int own, int upper, 
       double pr[RPW];
 #pragma unroll
       for (int u = 0; u < DL; ++u) pr[u] = (double)dd[u] * av;
-      const double yr = reduce_rows8(pr, lane);
+      double yr = reduce_rows8(pr, lane);
+      if (linked) {                                // - D L(k, k - 1) y(k - 1): every wave polls
+        const double* yp = y + i0 - SB;            // for itself, no barrier on this path
+        int64_t spins = 0;
+        double yv;
+        for (;;) {
+          yv = poll_load(yp + (uint32_t)lane);
+          if (!__any(is_mark(yv)) || poll_give_up(spins, err)) break;
+        }
+#pragma unroll
+        for (int u = 0; u < DL; ++u) pr[u] = (double)lm[u] * yv;
+        yr -= reduce_rows8(pr, lane);
+      }
       const int row = wave + SW * (lane >> 3);
       if ((lane & 7) == 0 && row < nb) hand_over(y + i0 + row, yr);
     }
@@ -1366,17 +1453,19 @@ __device__ __forceinline__ void band_solve_1_mat(Load load, int own, int upper, 
         if (lane % V == e) sacc = t;
       }
     }
-    // row blocks in flight, kb + 1 .. kin (at most step - 1), up to FL at a time from the
-    // far end, the nearest together: factor entries and, before the last, the inverse
+    // row blocks in flight, kb + 1 .. kin (at most step - 1), the nearest of them left to
+    // the link below; up to FL at a time from the far end, the nearest together: factor entries and, before the last, the inverse
     // diagonal block first, then the polls of their final solutions (rows inside the band
     // only), the last together with this block's forward solution
     const int kin = min<int>(kdone - 1, (rend - 1) / SB);   // last row block in flight
-    T dd[DL];
+    const bool linked = link && kb + 1 < kdone && rend > (kb + 1) * SB;
+    const int kn = linked ? kb + 1 : kb;
+    T dd[DL], lm[DL];
     double yown = 0.0;
-    int kl = max(kin, kb);                     // the farthest one not yet taken
+    int kl = max(kin, kn);                         // the farthest one not yet taken
 #pragma unroll 1
     for (;;) {
-      const int rest = kl - kb;
+      const int rest = kl - kn;
       const int nfl = (int)(rest > FL ? (rest - 1) % FL + 1 : rest);
       const int kf = kl - nfl + 1;             // blocks kf .. kl
       const bool lastc = rest <= FL;
@@ -1388,7 +1477,11 @@ __device__ __forceinline__ void band_solve_1_mat(Load load, int own, int upper, 
           pf[o][r] = cb[min<int>((kf + o) * SB + wave + SW * r, n - 1) * rs + cidx];
       if (lastc)
 #pragma unroll
-        for (int u = 0; u < DL; ++u) dd[u] = (dv + (int64_t)kb * SB * SB)[threadIdx.x + SOLVE_THREADS * u];
+        for (int u = 0; u < DL; ++u) {
+          dd[u] = (dv + (int64_t)kb * SB * SB)[threadIdx.x + SOLVE_THREADS * u];
+          if (linked)
+            lm[u] = (link + (2 * (int64_t)kb + 1) * SB * SB)[threadIdx.x + SOLVE_THREADS * u];
+        }
       // wave 0 polls (lane l: row l of each block) and passes the values on through LDS
       if (wave == 0) {
         double xo[FL];
@@ -1449,11 +1542,32 @@ __device__ __forceinline__ void band_solve_1_mat(Load load, int own, int upper, 
       part[wave][lane] = pc;
     }
     __syncthreads();
-    if (wave == 0) {
-      double zs = 0.0;
+    if (!linked) {
+      if (wave == 0) {
+        double zs = 0.0;
 #pragma unroll
-      for (int w = 0; w < SW; ++w) zs += part[w][lane];
-      if (lane < nb) hand_over(z + cidx, zs);
+        for (int w = 0; w < SW; ++w) zs += part[w][lane];
+        if (lane < nb) hand_over(z + cidx, zs);
+      }
+    } else {                                       // - D^T L(kb + 1, kb)^T z(kb + 1), as above
+      const int row = wave + SW * (lane >> 3);
+      double zr = 0.0;
+#pragma unroll
+      for (int w = 0; w < SW; ++w) zr += part[w][row];
+      const double* zp = z + i0 + SB;
+      const bool in = i0 + SB + lane < n;
+      int64_t spins = 0;
+      double zv;
+      for (;;) {
+        zv = poll_load(zp + (uint32_t)lane);
+        if (!__any(in && is_mark(zv)) || poll_give_up(spins, err)) break;
+      }
+      if (!in) zv = 0.0;
+      double pr2[DL];
+#pragma unroll
+      for (int u = 0; u < DL; ++u) pr2[u] = (double)lm[u] * zv;
+      zr -= reduce_rows8(pr2, lane);
+      if ((lane & 7) == 0 && row < nb) hand_over(z + i0 + row, zr);
     }
     __syncthreads();
   }
@@ -1501,8 +1615,9 @@ __device__ inline int2 set_place(const int32_t* part_of, int n_mat, int G, int P
 // The parts of one band set (set_place)
 template <class T, bool COARSE>
 __global__ void __launch_bounds__(SOLVE_THREADS) k_band_solve_1(
-    BandArgs a, const int32_t* part_of, const T* v, const T* dinv, const int64_t* xoff,
-    const double* xall, double* yall, double* zall, int G, int PP, int n_mat, int* err) {
+    BandArgs a, const int32_t* part_of, const T* v, const T* dinv, const T* link,
+    const int64_t* xoff, const double* xall, double* yall, double* zall, int G, int PP, int n_mat,
+    int* err) {
   const int2 pg = set_place(part_of, n_mat, G, PP, err + 1);
   if (pg.x < 0) return;
   auto load = [&](int i) -> Solve1<T> {
@@ -1511,7 +1626,8 @@ __global__ void __launch_bounds__(SOLVE_THREADS) k_band_solve_1(
                                         : uniform_load(part_of + 2 * P.mat + (P.kind == PART_UPPER));
     const int64_t mo = uniform_load(&a.part[mp].yoff);
     return {P.rows, P.cols, P.kind == PART_UPPER ? P.sep : P.rows, P.N, P.B, P.ld, P.kind,
-            v + P.off, dinv + P.boff, a.fcb + P.eoff, a.lrb + P.eoff,
+            v + P.off, dinv + P.boff, link ? link + 2 * P.boff : nullptr,
+            a.fcb + P.eoff, a.lrb + P.eoff,
             xall + uniform_load(xoff + P.mat), yall + P.yoff, zall + P.yoff,
             (P.kind == PART_LOWER ? zall : yall) + mo};
   };
@@ -1536,7 +1652,7 @@ __global__ void __launch_bounds__(SOLVE_THREADS) k_band_solve_1_multi(const Band
   auto load = [&](int p) -> Solve1<T> {
     const BandPtrs t = uniform_load(tab + p);
     return {t.n, t.cols, t.sep, t.N, t.B, t.B + 1, (int)t.kind, static_cast<const T*>(t.v),
-            static_cast<const T*>(t.dinv), t.fcb, t.lrb, t.x, t.y, t.z, t.mate};
+            static_cast<const T*>(t.dinv), static_cast<const T*>(t.link), t.fcb, t.lrb, t.x, t.y, t.z, t.mate};
   };
   const BandPtrs t = uniform_load(tab + j);
   if (t.n == 0) return;
@@ -1891,6 +2007,38 @@ static int solve_groups(BandSet& bs, const void* kernel, int which) {
   return G;
 }
 
+// Whether the links pay in a solve with G groups per part: they shorten the step from one
+// hand-over to the next (2.7 -> 1.8 us) but give every work-group a second wait, product and
+// reduction per block, so they pay where a step is bound by the hand-over and not by a
+// group's share of the stream (64 B w / G bytes at about 22 GB/s).  Measured with eight
+// groups, unlinked -> linked, at B w / G bytes: 370: 182 -> 141 us, 1,020: 727 -> 652 us,
+// 1,040: 2,033 -> 1,831 us, 1,220: 2,032 -> 2,072 us, 1,630: 5,767 -> 5,907 us.
+static bool link_pays(int64_t B, bool fp32, int G) {
+  return G > 1 && B * (fp32 ? 4 : 8) <= 1100 * (int64_t)G;
+}
+
+static const void* solve1_kernel(const BandSet& bs) {
+  return bs.fp32     ? reinterpret_cast<const void*>(&k_band_solve_1<float, false>)
+         : bs.coarse ? reinterpret_cast<const void*>(&k_band_solve_1<double, true>)
+                     : reinterpret_cast<const void*>(&k_band_solve_1<double, false>);
+}
+
+// The links of a factored set whose one-right-hand-side solves will use them.
+void band_link(BandSet& bs, hipStream_t st) {
+  if (!link_pays(bs.max_B, bs.fp32, solve_groups(bs, solve1_kernel(bs), 0))) return;
+  const dim3 grid(nblocks(bs.max_cols, SB), bs.n_part);
+  if (bs.fp32) {
+    bs.link32.alloc(2 * bs.n_inv);
+    hipLaunchKernelGGL(k_link<float>, grid, dim3(512), 0, st, bs.d_part.p, bs.v32.p, bs.dinv32.p,
+                       bs.link32.p);
+  } else {
+    bs.link64.alloc(2 * bs.n_inv);
+    hipLaunchKernelGGL(k_link<double>, grid, dim3(512), 0, st, bs.d_part.p, bs.v64.p,
+                       bs.dinv64.p, bs.link64.p);
+  }
+  GX_HIP(hipGetLastError());
+}
+
 // The launch's error word (raised by a poll that timed out), zero until a check clears it;
 // the counters of take_place follow it
 static int* solve_err(BandSet& bs, hipStream_t st) {
@@ -2023,25 +2171,25 @@ void band_solve(BandSet& bs, const int64_t* d_xoff, double* x, hipStream_t st, i
   }
   const BandArgs a{bs.d_part.p, bs.d_fcb.p, bs.d_lrb.p, 0};
   if (ncol == 1 && !active) {
-    const void* kf = bs.fp32 ? reinterpret_cast<const void*>(&k_band_solve_1<float, false>)
-                   : bs.coarse ? reinterpret_cast<const void*>(&k_band_solve_1<double, true>)
-                               : reinterpret_cast<const void*>(&k_band_solve_1<double, false>);
-    const int G = solve_groups(bs, kf, 0), PP = solve_parts(bs);
+    const int G = solve_groups(bs, solve1_kernel(bs), 0), PP = solve_parts(bs);
+    const bool linked = link_pays(bs.max_B, bs.fp32, G);
+    const float* link32 = linked ? bs.link32.p : nullptr;
+    const double* link64 = linked ? bs.link64.p : nullptr;
     const dim3 grid(solve_grid(bs, G));
     int* err = solve_err(bs, st);
     double* y = solve1_scratch(bs, st);
     double* z = y + bs.ybuf.n / 2;
     if (bs.fp32)
       hipLaunchKernelGGL((k_band_solve_1<float, false>), grid, dim3(SOLVE_THREADS), 0, st, a,
-                         bs.d_part_of.p, bs.v32.p, bs.dinv32.p, d_xoff, x, y, z, G, PP,
+                         bs.d_part_of.p, bs.v32.p, bs.dinv32.p, link32, d_xoff, x, y, z, G, PP,
                          bs.n_mat, err);
     else if (bs.coarse)
       hipLaunchKernelGGL((k_band_solve_1<double, true>), grid, dim3(SOLVE_THREADS), 0, st, a,
-                         bs.d_part_of.p, bs.v64.p, bs.dinv64.p, d_xoff, x, y, z, G, PP,
+                         bs.d_part_of.p, bs.v64.p, bs.dinv64.p, link64, d_xoff, x, y, z, G, PP,
                          bs.n_mat, err);
     else
       hipLaunchKernelGGL((k_band_solve_1<double, false>), grid, dim3(SOLVE_THREADS), 0, st, a,
-                         bs.d_part_of.p, bs.v64.p, bs.dinv64.p, d_xoff, x, y, z, G, PP,
+                         bs.d_part_of.p, bs.v64.p, bs.dinv64.p, link64, d_xoff, x, y, z, G, PP,
                          bs.n_mat, err);
     hipLaunchKernelGGL(k_copy_out<double>, dim3(nblocks(bs.max_cols, 256), bs.n_part), dim3(256),
                        0, st, bs.d_part.p, d_xoff, 1, z, x, (const int32_t*)nullptr);
@@ -2102,6 +2250,9 @@ void multi_solve_plan(MultiSolve& m, const std::vector<BandSet*>& sets,
                      : static_cast<const void*>(bs.v64.p + p.off);
         t.dinv = m.fp32 ? static_cast<const void*>(bs.dinv32.p + p.boff)
                         : static_cast<const void*>(bs.dinv64.p + p.boff);
+        t.link = bs.link32.n   ? static_cast<const void*>(bs.link32.p + 2 * p.boff)
+                 : bs.link64.n ? static_cast<const void*>(bs.link64.p + 2 * p.boff)
+                               : nullptr;
         t.x = x[k] + xoff[k][j];
         t.y = y + p.yoff;
         t.z = z + p.yoff;
@@ -2176,6 +2327,8 @@ void multi_solve_plan(MultiSolve& m, const std::vector<BandSet*>& sets,
         used[x] += parts(pick);
         for (int q = mats[pick]; q < mats[pick + 1]; ++q) ++m.host[q].G;
       }
+  for (BandPtrs& t : m.host)
+    if (!link_pays(t.B, m.fp32, (int)t.G)) t.link = nullptr;
   // a matrix's work-groups are neighbours in its XCD's list (take_place)
   std::vector<std::vector<int32_t>> lists(NX);
   for (int j = 0; j < nm; ++j)
@@ -2268,6 +2421,8 @@ void band_layout(BandSet& bs, const std::vector<int64_t>& n, const std::vector<i
   bs.d_poff.release();
   bs.ybuf.release();
   bs.mbuf.release();
+  bs.link64.release();
+  bs.link32.release();
   bs.max_n = bs.max_B = 0;
   bs.max_cols = 0;
   bs.total = bs.stored = bs.rows = bs.n_inv = 0;
@@ -2489,6 +2644,7 @@ extern "C" gx_status gx_band_factor_solve(gx_ctx* c, int32_t n_mat, const int64_
                      band_view(bs), fp32 ? bs.v32.p : nullptr, fp32 ? nullptr : bs.v64.p);
   GX_HIP(hipGetLastError());
   band_factor(c, bs, s, "the given band matrices");
+  if (nrhs == 1) band_link(bs, s);
   if (fp32)
     hipLaunchKernelGGL(k_scale_rhs, dim3(nblocks(doff[n_mat] * nrhs, 256)), dim3(256), 0, s,
                        doff[n_mat], nrhs, dsc.p, x);

@@ -1415,6 +1415,7 @@ void geneo_coarse(gx_ctx* c, const gx_geneo_opts* o, const std::function<void()>
                      sw.C.B[0], sw.C.B[0] + 1, sw.C.v64.p);
   GX_HIP(hipGetLastError());
   band_factor(c, sw.C, s, "the coarse matrix K0 (near-dependent coarse vectors?)");
+  band_link(sw.C, s);
   const int64_t zero64 = 0;
   sw.d_c_xoff.alloc(1);
   to_dev(sw.d_c_xoff.p, &zero64, 1, s);

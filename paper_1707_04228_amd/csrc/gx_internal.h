@@ -270,6 +270,10 @@ struct BandSet {
   int64_t n_inv = 0;
   DevBuf<double> dinv64;
   DevBuf<float> dinv32;
+  // for the one-right-hand-side solves (band_link): block b's links to its neighbours at
+  // 2 boff + 8192 b, D_b L(b, b - 1) and then D_b^T L(b + 1, b)^T with D_b its inverse block
+  DevBuf<double> link64;
+  DevBuf<float> link32;
   bool fp32 = false;
   int solve_groups[2] = {0, 0};                // work-groups per matrix: 1-RHS, m-RHS solve
   int force_groups[2] = {0, 0};                // requested (0: automatic, capped by residency)
@@ -289,6 +293,7 @@ struct BandSet {
 struct BandPtrs {
   const void* v;                               // factor (precision of the launch)
   const void* dinv;                            // inverse 64x64 diagonal blocks
+  const void* link;                            // links between neighbouring blocks
   double* x;                                   // right-hand side in, solution out (matrix)
   double* y;                                   // forward-solution scratch (64-aligned length)
   double* z;                                   // backward-solution scratch
@@ -458,6 +463,8 @@ void band_factor_start(BandSet& bs, hipStream_t st, hipStream_t la, FactorJob& j
                        const char* what,
                        bool threaded = false);
 void band_factor_finish(FactorJob& job);
+// the links of a factored set's blocks, before its one-right-hand-side solves
+void band_link(BandSet& bs, hipStream_t st);
 // The interior factorisation as a job that can run on a side stream (see schwarz.hip).
 struct InteriorJob {
   std::vector<int64_t> n, B, env;
