@@ -294,11 +294,11 @@ static int64_t scan_impl(T* data, int64_t n, int64_t* tmp, hipStream_t s) {
   return (int64_t)lastx + (int64_t)last;
 }
 
+void exclusive_scan32_async(int32_t* data, int64_t n, int64_t* tmp, hipStream_t s) {
+  scan_rec<int32_t>(data, n, tmp, s);
+}
 int64_t exclusive_scan(int64_t* data, int64_t n, int64_t* tmp, hipStream_t s) {
   return scan_impl<int64_t>(data, n, tmp, s);
-}
-int64_t exclusive_scan32(int32_t* data, int64_t n, int64_t* tmp, hipStream_t s) {
-  return scan_impl<int32_t>(data, n, tmp, s);
 }
 
 }  // namespace gx

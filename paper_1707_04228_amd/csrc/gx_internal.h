@@ -195,7 +195,8 @@ __device__ inline double lane_value(double v, int l) {
 // scan_tmp_size(n) elements.
 size_t scan_tmp_size(int64_t n);
 int64_t exclusive_scan(int64_t* data, int64_t n, int64_t* tmp, hipStream_t s);
-int64_t exclusive_scan32(int32_t* data, int64_t n, int64_t* tmp, hipStream_t s);
+// the same for int32 values, without waiting for the total
+void exclusive_scan32_async(int32_t* data, int64_t n, int64_t* tmp, hipStream_t s);
 
 __device__ inline double wave_sum_d(double s) {
   for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
@@ -408,7 +409,6 @@ struct gx_ctx {
 
 namespace gx {
 // implemented in the respective .hip files
-void build_node_elem(gx_ctx* c);
 void spmv(gx_ctx* c, const double* x, double* y);
 void geneo_setup(gx_ctx* c, const gx_geneo_opts* o, int32_t* nev_out, int64_t* n0_out);
 void precond_apply(gx_ctx* c, const double* r, double* z);
