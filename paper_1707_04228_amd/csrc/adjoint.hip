@@ -374,35 +374,112 @@ __global__ void k_layer_dC(int n_layers, const double* eng, const double* C, dou
     }
 }
 
-// fixed-order sums: out[k] = sum of v[e] over the elements with key[e] == k (key null: k = 0)
-__global__ void k_keyed_sum(int64_t n, const double* v, const int32_t* key, int n_keys,
-                            double* out) {
-  __shared__ double red[256];
-  const int k = blockIdx.x;
-  double acc = 0.0;
-  for (int64_t i = threadIdx.x; i < n; i += 256)
-    if (!key || key[i] == k) acc += v[i];
-  red[threadIdx.x] = acc;
+// J per element (zero outside the region): sigma'_3 = C[2][0..2] . normal strains in the ply's
+// axes at the 27 Gauss points.  Two elements per wavefront, lanes 0-26 and 32-58, the
+// reference gradients in LDS; elements outside the region cost one store.  (The sensitivity
+// kernel, which carries the adjoint field and gradients along and takes every element, needed
+// 262 us for the 33,600 elements of a strip whose arc is a tenth of it; this one 17 us.)
+constexpr int OW = 4;                              // wavefronts per work-group
+__global__ void __launch_bounds__(64 * OW) k_objective(SensArgs A, int64_t n_elems, double* jv) {
+  __shared__ double dNr[27][20][3], X[2 * OW][20][3], U[2 * OW][20][3];
+  ref_gradients(dNr);
   __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, hl = lane & 31;
+  const int s = 2 * w + (lane >> 5);               // this half-wave's element slot
+  for (int64_t e0 = (int64_t)blockIdx.x * 2 * OW; e0 < n_elems;
+       e0 += (int64_t)gridDim.x * 2 * OW) {
+    const int64_t e = e0 + s;
+    const bool in = e < n_elems && A.region[e];
+    if (!__any(in)) {
+      if (hl == 0 && e < n_elems) jv[e] = 0.0;
+      continue;
+    }
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);       // (one wavefront: LDS accesses in order)
+    __builtin_amdgcn_wave_barrier();
+    if (in)
+      for (int t = hl; t < 60; t += 32) {
+        const int a = t / 3, i = t % 3;
+        const int64_t nd = A.conn[20 * e + a];
+        X[s][a][i] = node_coord(A.xyz, nd, i, A.P, e, a);
+        U[s][a][i] = A.u[3 * nd + i];
+      }
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_wave_barrier();
+    double jq = 0.0;
+    if (in && hl < 27) {
+      double det, H[3][3], E[3][3];
+      point_state(X[s], U[s], dNr[hl], &det, H, E);
+      const int L = A.elayer[e];
+      const double an = A.ang[L] * (M_PI / 180.0), ca = cos(an), sa = sin(an);
+      const double* C = A.Cl + 36 * L + 12;
+      double sig = 0.0;
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        double q[3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+          q[i] = k == 0 ? ca * E[0][i] + sa * E[1][i]
+                 : k == 1 ? ca * E[1][i] - sa * E[0][i] : E[2][i];
+        double eps = 0.0;
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+          for (int j = 0; j < 3; ++j) eps += q[i] * H[i][j] * q[j];
+        sig += C[k] * eps;
+      }
+      double x, wq, wy, wz;
+      gauss3(hl % 3, &x, &wq);
+      gauss3((hl / 3) % 3, &x, &wy);
+      gauss3(hl / 9, &x, &wz);
+      jq = sig * sig * (det * (wq * wy * wz));
+    }
+    for (int o = 16; o > 0; o >>= 1) jq += __shfl_xor(jq, o);   // within the half-wave
+    if (hl == 0 && e < n_elems) jv[e] = jq;
   }
-  if (threadIdx.x == 0 && k < n_keys) out[k] = red[0];
 }
 
-// sum of v[0..n) in a fixed order, through the one-value device buffer o
+// fixed-order sums: out[k] = sum of v[i] over the i of slice k (of gridDim.x), or with keys
+// over those with key[i] == k
+__global__ void __launch_bounds__(1024) k_keyed_sum(int64_t n, const double* v,
+                                                    const int32_t* key, double* out) {
+  __shared__ double red[16];
+  const int k = blockIdx.x, t = threadIdx.x;
+  const int64_t len = key ? n : (n + gridDim.x - 1) / gridDim.x;
+  const int64_t beg = key ? 0 : k * len, end = min(n, beg + len);
+  double s[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int64_t i = beg + t; i < end; i += 4096)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t q = i + 1024 * u, c = min(q, end - 1);
+      const double x = v[c];
+      s[u] += q < end && (!key || key[c] == k) ? x : 0.0;
+    }
+  double a = wave_sum_d((s[0] + s[1]) + (s[2] + s[3]));
+  if ((t & 63) == 0) red[t >> 6] = a;
+  __syncthreads();
+  if (t < 64) {
+    a = wave_sum_d(t < 16 ? red[t] : 0.0);
+    if (t == 0) out[k] = a;
+  }
+}
+
+// sum of v[0..n) in a fixed order, through the SUM_SLOTS-value device buffer o: one
+// work-group takes up to 16k values in a few rounds; more go through SUM_SLOTS partial sums
+constexpr int SUM_SLOTS = 32;
 static double dev_sum_into(const double* v, int64_t n, double* o, hipStream_t st) {
-  hipLaunchKernelGGL(k_keyed_sum, dim3(1), dim3(256), 0, st, n, v, (const int32_t*)nullptr, 1,
-                     o);
+  const bool one = n <= 16384;
+  hipLaunchKernelGGL(k_keyed_sum, dim3(one ? 1 : SUM_SLOTS), dim3(1024), 0, st, n, v,
+                     (const int32_t*)nullptr, o);
   GX_HIP(hipGetLastError());
-  double h = 0.0;
-  to_host(&h, o, 1, st);
-  return h;
+  double h[SUM_SLOTS];
+  to_host(h, o, one ? 1 : SUM_SLOTS, st);
+  double s = 0.0;
+  for (int i = 0; i < (one ? 1 : SUM_SLOTS); ++i) s += h[i];
+  return s;
 }
 
 static double dev_sum(const double* v, int64_t n, hipStream_t st) {
-  DevBuf<double> o(1);
+  DevBuf<double> o(SUM_SLOTS);
   return dev_sum_into(v, n, o.p, st);
 }
 
@@ -426,7 +503,7 @@ static void check_objective_laminate(gx_ctx* c, const gx_laminate* lam) {
 }
 
 // J and (grad != null) dJ/du [3 n_nodes], with the caller's buffers: region [n_elems] (the
-// element mask), jv [n_elems] (J per element), sum [1] and, with grad, ge [60 n_elems]
+// element mask), jv [n_elems] (J per element), sum [SUM_SLOTS] and, with grad, ge [60 n_elems]
 static double objective_into(gx_ctx* c, const gx_laminate* lam, int32_t region_kind,
                              const double* u, uint8_t* region, double* jv, double* sum,
                              double* ge, double* grad) {
@@ -439,15 +516,18 @@ static double objective_into(gx_ctx* c, const gx_laminate* lam, int32_t region_k
   } else {
     laminate_region(lam, region, st);
   }
-  hipLaunchKernelGGL(k_sens<double>, dim3(sens_grid(E)), dim3(64), sizeof(SensSmem), st,
-                     sens_args(c, u, nullptr, nullptr, nullptr, region), E, (double*)nullptr,
-                     jv, (double*)nullptr, ge);
-  GX_HIP(hipGetLastError());
   if (grad) {
+    hipLaunchKernelGGL(k_sens<double>, dim3(sens_grid(E)), dim3(64), sizeof(SensSmem), st,
+                       sens_args(c, u, nullptr, nullptr, nullptr, region), E, (double*)nullptr,
+                       jv, (double*)nullptr, ge);
     hipLaunchKernelGGL(k_grad_gather, dim3(nblocks(c->n_nodes, 256)), dim3(256), 0, st,
                        c->n_nodes, c->ne_ptr.p, c->ne_idx.p, c->conn.p, ge, c->fixed.p, grad);
-    GX_HIP(hipGetLastError());
+  } else {
+    hipLaunchKernelGGL(k_objective, dim3((unsigned)std::min<int64_t>(nblocks(E, 2 * OW), 2048)),
+                       dim3(64 * OW), 0, st, sens_args(c, u, nullptr, nullptr, nullptr, region),
+                       E, jv);
   }
+  GX_HIP(hipGetLastError());
   return dev_sum_into(jv, E, sum, st);
 }
 
@@ -456,7 +536,7 @@ static double objective(gx_ctx* c, const gx_laminate* lam, int32_t region_kind, 
   check_objective_laminate(c, lam);
   const int64_t E = c->n_elems;
   region.alloc(E);
-  DevBuf<double> jv(E), sum(1), ge(grad ? 60 * E : 0);
+  DevBuf<double> jv(E), sum(SUM_SLOTS), ge(grad ? 60 * E : 0);
   return objective_into(c, lam, region_kind, u, region.p, jv.p, sum.p, ge.p, grad);
 }
 
@@ -512,7 +592,8 @@ gx_status gx_objective_noalloc(gx_ctx* c, const gx_laminate* lam, int32_t region
   if (c->matrix_only) throw Error(GX_ESTATE, "needs an assembled mesh, not a loaded matrix");
   GX_REQUIRE(lam && u && J_out && (region == 0 || region == 1), "bad objective arguments");
   check_objective_laminate(c, lam);
-  // layout: the sum at 0, J per element at 256, the region mask after it
+  // layout: the partial sums at 0, J per element at 256, the region mask after it
+  static_assert(SUM_SLOTS * sizeof(double) <= 256, "the partial sums fit before J");
   const int64_t E = c->n_elems;
   const size_t need = 256 + 8 * (size_t)E + (size_t)E;
   if (need > NOALLOC_BYTES)
@@ -578,8 +659,8 @@ gx_status gx_adjoint(gx_ctx* c, const gx_laminate* lam, int32_t region, const do
   hipLaunchKernelGGL(k_sens<Dual>, dim3(sens_grid(E)), dim3(64), sizeof(SensSmem), st,
                      sens_args(c, u, lamv.p, nullptr, dC.p, mask.p), E, s.p, (double*)nullptr,
                      jd.p, (double*)nullptr);
-  hipLaunchKernelGGL(k_keyed_sum, dim3(nl), dim3(256), 0, st, E, s.p, c->elayer.p, nl, dK.p);
-  hipLaunchKernelGGL(k_keyed_sum, dim3(nl), dim3(256), 0, st, E, jd.p, c->elayer.p, nl, dJ.p);
+  hipLaunchKernelGGL(k_keyed_sum, dim3(nl), dim3(1024), 0, st, E, s.p, c->elayer.p, dK.p);
+  hipLaunchKernelGGL(k_keyed_sum, dim3(nl), dim3(1024), 0, st, E, jd.p, c->elayer.p, dJ.p);
   GX_HIP(hipGetLastError());
   std::vector<double> hK(nl), hJ(nl);
   to_host(hK.data(), dK.p, nl, st);

@@ -61,6 +61,75 @@ static __device__ inline double node_coord(const double* xyz, int64_t nd, int i,
   return x;
 }
 
+static __device__ inline void gauss3(int i, double* x, double* w) {
+  const double s = 0.7745966692414833770358531;  // sqrt(3/5)
+  *x = (i == 0) ? -s : ((i == 1) ? 0.0 : s);
+  *w = (i == 1) ? 8.0 / 9.0 : 5.0 / 9.0;
+}
+
+// Reference gradients of the 20 nodes at the 27 Gauss points (q = i + 3 j + 9 k), by all
+// threads of a work-group
+static __device__ inline void ref_gradients(double (*dNr)[20][3]) {
+  for (int idx = threadIdx.x; idx < 27 * 20; idx += blockDim.x) {
+    const int q = idx / 20, a = idx % 20;
+    double x0, x1, x2, w, N, d[3];
+    gauss3(q % 3, &x0, &w);
+    gauss3((q / 3) % 3, &x1, &w);
+    gauss3(q / 9, &x2, &w);
+    shape_one(a, x0, x1, x2, &N, d);
+    for (int j = 0; j < 3; ++j) dNr[q][a][j] = d[j];
+  }
+}
+
+// What the stress kernels need of one Gauss point of one element: the Jacobian (J[i][j] =
+// dx_i / dxi_j), its determinant, the displacement gradient H[i][j] = du_i / dx_j and the
+// geometric frame (rows of E: e1 along dx/dxi, e2 from dx/deta, e3 = e1 x e2).
+static __device__ inline void point_state(const double (*X)[3], const double (*U)[3],
+                                          const double (*dN)[3], double* det, double (&H)[3][3],
+                                          double (&E)[3][3]) {
+  double J[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}}, G[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
+#pragma unroll 4
+  for (int a = 0; a < 20; ++a)
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        J[i][j] += X[a][i] * dN[a][j];
+        G[i][j] += U[a][i] * dN[a][j];             // du_i / dxi_j
+      }
+  *det = J[0][0] * (J[1][1] * J[2][2] - J[1][2] * J[2][1]) -
+         J[0][1] * (J[1][0] * J[2][2] - J[1][2] * J[2][0]) +
+         J[0][2] * (J[1][0] * J[2][1] - J[1][1] * J[2][0]);
+  const double id = 1.0 / *det;
+  double Ji[3][3];                               // Ji[j][i] = dxi_j / dx_i
+  Ji[0][0] = (J[1][1] * J[2][2] - J[1][2] * J[2][1]) * id;
+  Ji[0][1] = (J[0][2] * J[2][1] - J[0][1] * J[2][2]) * id;
+  Ji[0][2] = (J[0][1] * J[1][2] - J[0][2] * J[1][1]) * id;
+  Ji[1][0] = (J[1][2] * J[2][0] - J[1][0] * J[2][2]) * id;
+  Ji[1][1] = (J[0][0] * J[2][2] - J[0][2] * J[2][0]) * id;
+  Ji[1][2] = (J[0][2] * J[1][0] - J[0][0] * J[1][2]) * id;
+  Ji[2][0] = (J[1][0] * J[2][1] - J[1][1] * J[2][0]) * id;
+  Ji[2][1] = (J[0][1] * J[2][0] - J[0][0] * J[2][1]) * id;
+  Ji[2][2] = (J[0][0] * J[1][1] - J[0][1] * J[1][0]) * id;
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+      H[i][j] = G[i][0] * Ji[0][j] + G[i][1] * Ji[1][j] + G[i][2] * Ji[2][j];
+  const double n1 = sqrt(J[0][0] * J[0][0] + J[1][0] * J[1][0] + J[2][0] * J[2][0]);
+#pragma unroll
+  for (int i = 0; i < 3; ++i) E[0][i] = J[i][0] / n1;
+  const double pr = J[0][1] * E[0][0] + J[1][1] * E[0][1] + J[2][1] * E[0][2];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) E[1][i] = J[i][1] - pr * E[0][i];
+  const double n2 = sqrt(E[1][0] * E[1][0] + E[1][1] * E[1][1] + E[1][2] * E[1][2]);
+#pragma unroll
+  for (int i = 0; i < 3; ++i) E[1][i] /= n2;
+  E[2][0] = E[0][1] * E[1][2] - E[0][2] * E[1][1];
+  E[2][1] = E[0][2] * E[1][0] - E[0][0] * E[1][2];
+  E[2][2] = E[0][0] * E[1][1] - E[0][1] * E[1][0];
+}
+
 // the context's description (defined where gx_ctx is complete)
 template <class Ctx>
 inline Periodic periodic_of(const Ctx* c) {
@@ -69,12 +138,5 @@ inline Periodic periodic_of(const Ctx* c) {
   for (int i = 0; i < 3; ++i) P.p[i] = c->period[i];
   return P;
 }
-
-static __device__ inline void gauss3(int i, double* x, double* w) {
-  const double s = 0.7745966692414833770358531;  // sqrt(3/5)
-  *x = (i == 0) ? -s : ((i == 1) ? 0.0 : s);
-  *w = (i == 1) ? 8.0 / 9.0 : 5.0 / 9.0;
-}
-
 
 }  // namespace gx

@@ -12,10 +12,10 @@
 // displacement: the strain of u_e, rotated into the material axes (the geometric frame
 // e1 = unit dx/dxi, e2 = dx/deta made orthogonal, e3 = e1 x e2, turned by the ply angle
 // about e3, as in the assembly), times the layer stiffness, then turned back by the ply
-// angle into the frame (s, l, r) = (e1, e2, e3).  One 64-lane work-group per element, lane q
-// at Gauss point q; the element's maximum goes to a per-element slot, and one work-group
-// reduces those in a fixed order (ties go to the lower element, then the lower point), so
-// the result is the same on every run.
+// angle into the frame (s, l, r) = (e1, e2, e3).  Two elements per wavefront, lane q of a half
+// at Gauss point q; the element's maximum goes to a per-element slot, and those are reduced
+// in a fixed order (ties go to the lower element, then the lower point), so the result is
+// the same on every run.
 #include <cmath>
 
 #include "element.h"
@@ -23,112 +23,80 @@
 
 namespace gx {
 
-struct FailSmem {
-  double X[20][3];
-  double U[20][3];
-  double F[64];
-  double S[64][6];
-};
-
-__global__ void __launch_bounds__(64) k_failure(Periodic P, int64_t n_elems, const double* xyz,
-                                                const int32_t* conn, const int32_t* elayer,
-                                                const double* Cl, const double* ang,
-                                                const uint8_t* sel, const double* u,
-                                                double s33, double s13, double* Fq,
-                                                double* Fe, int32_t* qe, double* Se) {
-  __shared__ FailSmem sm;
-  const int t = threadIdx.x;
-  for (int64_t e = blockIdx.x; e < n_elems; e += gridDim.x) {
-    const int layer = elayer[e];
-    if (!sel[layer]) {                           // uniform per work-group
-      if (t < 27 && Fq) Fq[27 * e + t] = 0.0;
-      if (t == 0) {
+constexpr int FW = 4;                              // wavefronts per work-group
+// The reference gradients sit in LDS (forming them anew at every point was most of the work:
+// 92 -> 30 us for 33,600 elements, 11 of 35 element layers selected); what is left is the
+// F values written and the layers' elements read.
+__global__ void __launch_bounds__(64 * FW) k_failure(Periodic P, int64_t n_elems,
+                                                     const double* xyz, const int32_t* conn,
+                                                     const int32_t* elayer, const double* Cl,
+                                                     const double* ang, const uint8_t* sel,
+                                                     const double* u, double s33, double s13,
+                                                     double* Fq, double* Fe, int32_t* qe,
+                                                     double* Se) {
+  __shared__ double dNr[27][20][3], X[2 * FW][20][3], U[2 * FW][20][3];
+  ref_gradients(dNr);
+  __syncthreads();
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, hl = lane & 31;
+  const int s = 2 * w + (lane >> 5);               // this half-wave's element slot
+  for (int64_t e0 = (int64_t)blockIdx.x * 2 * FW; e0 < n_elems;
+       e0 += (int64_t)gridDim.x * 2 * FW) {
+    const int64_t e = e0 + s;
+    const int layer = e < n_elems ? elayer[e] : 0;
+    const bool in = e < n_elems && sel[layer];
+    if (e < n_elems && !in) {
+      if (hl < 27 && Fq) Fq[27 * e + hl] = 0.0;
+      if (hl == 0) {
         Fe[e] = 0.0;
         qe[e] = 0;
       }
-      if (t < 6) Se[6 * e + t] = 0.0;
-      continue;
+      if (hl < 6) Se[6 * e + hl] = 0.0;
     }
-    __syncthreads();
-    if (t < 60) {
-      const int a = t / 3, i = t % 3;
-      const int64_t nd = conn[20 * e + a];
-      sm.X[a][i] = node_coord(xyz, nd, i, P, e, a);
-      sm.U[a][i] = u[3 * nd + i];
-    }
-    __syncthreads();
+    if (!__any(in)) continue;
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);       // (one wavefront: LDS accesses in order)
+    __builtin_amdgcn_wave_barrier();
+    if (in)
+      for (int t = hl; t < 60; t += 32) {
+        const int a = t / 3, i = t % 3;
+        const int64_t nd = conn[20 * e + a];
+        X[s][a][i] = node_coord(xyz, nd, i, P, e, a);
+        U[s][a][i] = u[3 * nd + i];
+      }
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_wave_barrier();
     double F = -1.0, loc[6] = {0, 0, 0, 0, 0, 0};
-    if (t < 27) {
-      double p0, p1, p2, w;
-      gauss3(t % 3, &p0, &w);
-      gauss3((t / 3) % 3, &p1, &w);
-      gauss3(t / 9, &p2, &w);
-      double J[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
-      for (int a = 0; a < 20; ++a) {
-        double N, d[3];
-        shape_one(a, p0, p1, p2, &N, d);
-        for (int i = 0; i < 3; ++i)
-          for (int j = 0; j < 3; ++j) J[i][j] += sm.X[a][i] * d[j];
-      }
-      const double det = J[0][0] * (J[1][1] * J[2][2] - J[1][2] * J[2][1]) -
-                         J[0][1] * (J[1][0] * J[2][2] - J[1][2] * J[2][0]) +
-                         J[0][2] * (J[1][0] * J[2][1] - J[1][1] * J[2][0]);
-      const double id = 1.0 / det;
-      double Ji[3][3];                           // Ji[j][i] = dxi_j / dx_i
-      Ji[0][0] = (J[1][1] * J[2][2] - J[1][2] * J[2][1]) * id;
-      Ji[0][1] = (J[0][2] * J[2][1] - J[0][1] * J[2][2]) * id;
-      Ji[0][2] = (J[0][1] * J[1][2] - J[0][2] * J[1][1]) * id;
-      Ji[1][0] = (J[1][2] * J[2][0] - J[1][0] * J[2][2]) * id;
-      Ji[1][1] = (J[0][0] * J[2][2] - J[0][2] * J[2][0]) * id;
-      Ji[1][2] = (J[0][2] * J[1][0] - J[0][0] * J[1][2]) * id;
-      Ji[2][0] = (J[1][0] * J[2][1] - J[1][1] * J[2][0]) * id;
-      Ji[2][1] = (J[0][1] * J[2][0] - J[0][0] * J[2][1]) * id;
-      Ji[2][2] = (J[0][0] * J[1][1] - J[0][1] * J[1][0]) * id;
-      // displacement gradient H[i][j] = du_i / dx_j
-      double H[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
-      for (int a = 0; a < 20; ++a) {
-        double N, d[3];
-        shape_one(a, p0, p1, p2, &N, d);
-        double g[3];
-        for (int i = 0; i < 3; ++i) g[i] = d[0] * Ji[0][i] + d[1] * Ji[1][i] + d[2] * Ji[2][i];
-        for (int i = 0; i < 3; ++i)
-          for (int j = 0; j < 3; ++j) H[i][j] += sm.U[a][i] * g[j];
-      }
-      // geometric frame (rows of E) and material axes (rows of Q)
-      double E[3][3];
-      {
-        double n1 = sqrt(J[0][0] * J[0][0] + J[1][0] * J[1][0] + J[2][0] * J[2][0]);
-        for (int i = 0; i < 3; ++i) E[0][i] = J[i][0] / n1;
-        const double pr = J[0][1] * E[0][0] + J[1][1] * E[0][1] + J[2][1] * E[0][2];
-        for (int i = 0; i < 3; ++i) E[1][i] = J[i][1] - pr * E[0][i];
-        const double n2 = sqrt(E[1][0] * E[1][0] + E[1][1] * E[1][1] + E[1][2] * E[1][2]);
-        for (int i = 0; i < 3; ++i) E[1][i] /= n2;
-        E[2][0] = E[0][1] * E[1][2] - E[0][2] * E[1][1];
-        E[2][1] = E[0][2] * E[1][0] - E[0][0] * E[1][2];
-        E[2][2] = E[0][0] * E[1][1] - E[0][1] * E[1][0];
-      }
+    if (in && hl < 27) {
+      double det, H[3][3], E[3][3];
+      point_state(X[s], U[s], dNr[hl], &det, H, E);
       const double an = ang[layer] * (M_PI / 180.0), ca = cos(an), sa = sin(an);
       double Q[3][3];
+#pragma unroll
       for (int i = 0; i < 3; ++i) {
         Q[0][i] = ca * E[0][i] + sa * E[1][i];
         Q[1][i] = -sa * E[0][i] + ca * E[1][i];
         Q[2][i] = E[2][i];
       }
       // strain in the material axes, eps' = Q sym(H) Q^T, engineering Voigt vector
-      double em[3][3];
+      double T[3][3], em[3][3];
+#pragma unroll
+      for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int b = 0; b < 3; ++b)
+          T[i][b] = 0.5 * ((H[i][0] + H[0][i]) * Q[b][0] + (H[i][1] + H[1][i]) * Q[b][1] +
+                           (H[i][2] + H[2][i]) * Q[b][2]);
+#pragma unroll
       for (int a = 0; a < 3; ++a)
-        for (int b = 0; b < 3; ++b) {
-          double acc = 0.0;
-          for (int i = 0; i < 3; ++i)
-            for (int j = 0; j < 3; ++j) acc += Q[a][i] * 0.5 * (H[i][j] + H[j][i]) * Q[b][j];
-          em[a][b] = acc;
-        }
+#pragma unroll
+        for (int b = 0; b < 3; ++b)
+          em[a][b] = Q[a][0] * T[0][b] + Q[a][1] * T[1][b] + Q[a][2] * T[2][b];
       const double ev[6] = {em[0][0], em[1][1], em[2][2], 2.0 * em[1][2], 2.0 * em[0][2],
                             2.0 * em[0][1]};
       const double* C = Cl + 36 * layer;
       double sv[6];
+#pragma unroll
       for (int I = 0; I < 6; ++I) {
         double acc = 0.0;
+#pragma unroll
         for (int K = 0; K < 6; ++K) acc += C[6 * I + K] * ev[K];
         sv[I] = acc;
       }
@@ -136,14 +104,17 @@ __global__ void __launch_bounds__(64) k_failure(Periodic P, int64_t n_elems, con
       // angle about e3 (Rp[a][m] = e_a . q_m)
       const double Sm[3][3] = {{sv[0], sv[5], sv[4]}, {sv[5], sv[1], sv[3]}, {sv[4], sv[3], sv[2]}};
       const double Rp[3][3] = {{ca, -sa, 0.0}, {sa, ca, 0.0}, {0.0, 0.0, 1.0}};
-      double Sg[3][3];
+      double R1[3][3], Sg[3][3];
+#pragma unroll
       for (int a = 0; a < 3; ++a)
-        for (int b = 0; b < 3; ++b) {
-          double acc = 0.0;
-          for (int m = 0; m < 3; ++m)
-            for (int k = 0; k < 3; ++k) acc += Rp[a][m] * Sm[m][k] * Rp[b][k];
-          Sg[a][b] = acc;
-        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+          R1[a][k] = Rp[a][0] * Sm[0][k] + Rp[a][1] * Sm[1][k] + Rp[a][2] * Sm[2][k];
+#pragma unroll
+      for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int b = 0; b < 3; ++b)
+          Sg[a][b] = R1[a][0] * Rp[b][0] + R1[a][1] * Rp[b][1] + R1[a][2] * Rp[b][2];
       loc[0] = Sg[0][0];
       loc[1] = Sg[1][1];
       loc[2] = Sg[2][2];
@@ -153,36 +124,40 @@ __global__ void __launch_bounds__(64) k_failure(Periodic P, int64_t n_elems, con
       const double sr = loc[2] > 0.0 ? loc[2] / s33 : 0.0;
       const double trs = loc[4] / s13, trl = loc[3] / s13;
       F = sqrt(sr * sr + trs * trs + trl * trl);
-      if (Fq) Fq[27 * e + t] = F;
+      if (Fq) Fq[27 * e + hl] = F;
     }
-    sm.F[t] = F;
-    for (int k = 0; k < 6; ++k) sm.S[t][k] = loc[k];
-    __syncthreads();
-    if (t == 0) {
-      int best = 0;
-      for (int q = 1; q < 27; ++q)
-        if (sm.F[q] > sm.F[best]) best = q;
-      Fe[e] = sm.F[best];
-      qe[e] = best;
-      for (int k = 0; k < 6; ++k) Se[6 * e + k] = sm.S[best][k];
+    // the half-wave's largest F (the lower point on a tie) and who holds it, as a scan from
+    // the first point on finds it: a NaN there stays, one further on is passed over
+    double best = hl > 0 && F != F ? -1.0 : F;
+    int at = hl;
+    for (int o = 1; o < 32; o <<= 1) {
+      const double ob = __shfl_down(best, o, 32);
+      const int oa = __shfl_down(at, o, 32);
+      if (hl + o < 27 && ob > best) {
+        best = ob;
+        at = oa;
+      }
+    }
+    at = __shfl(at, 0, 32);
+    if (in && hl == at) {
+      Fe[e] = F;
+      qe[e] = at;
+#pragma unroll
+      for (int k = 0; k < 6; ++k) Se[6 * e + k] = loc[k];
     }
   }
 }
 
-// The largest F over all elements (ties: the lower element index) by one work-group in a
-// fixed order: each thread scans a strided set of elements, then a tree over the threads.
-__global__ void __launch_bounds__(256) k_failure_max(int64_t n_elems, const double* Fe,
-                                                     int64_t* best_e) {
-  __shared__ double v[256];
-  __shared__ int64_t ix[256];
+// The largest F over all elements (ties: the lower element index): every work-group takes a
+// slice, then one takes the slices' results in order and packs what the host reads.
+struct FailPick {
+  double F, stress[6];
+  int64_t elem;
+  int32_t gauss, layer;
+};
+constexpr int FSLICE = 64;
+__device__ inline void fail_reduce(double& bv, int64_t& bi, double* v, int64_t* ix) {
   const int t = threadIdx.x;
-  double bv = -1.0;
-  int64_t bi = -1;
-  for (int64_t e = t; e < n_elems; e += 256)
-    if (Fe[e] > bv) {
-      bv = Fe[e];
-      bi = e;
-    }
   v[t] = bv;
   ix[t] = bi;
   __syncthreads();
@@ -197,7 +172,43 @@ __global__ void __launch_bounds__(256) k_failure_max(int64_t n_elems, const doub
     }
     __syncthreads();
   }
-  if (t == 0) *best_e = ix[0];
+  bv = v[0];
+  bi = ix[0];
+}
+__global__ void __launch_bounds__(256) k_failure_max(int64_t n_elems, const double* Fe,
+                                                     double* pv, int64_t* pi) {
+  __shared__ double v[256];
+  __shared__ int64_t ix[256];
+  const int64_t len = (n_elems + FSLICE - 1) / FSLICE, end = min(n_elems, (blockIdx.x + 1) * len);
+  double bv = -1.0;
+  int64_t bi = -1;
+  for (int64_t e = blockIdx.x * len + threadIdx.x; e < end; e += 256)
+    if (Fe[e] > bv) {
+      bv = Fe[e];
+      bi = e;
+    }
+  fail_reduce(bv, bi, v, ix);
+  if (threadIdx.x == 0) {
+    pv[blockIdx.x] = bv;
+    pi[blockIdx.x] = bi;
+  }
+}
+__global__ void __launch_bounds__(256) k_failure_pick(const double* pv, const int64_t* pi,
+                                                      const int32_t* elayer, const int32_t* qe,
+                                                      const double* Se, FailPick* out) {
+  __shared__ double v[256];
+  __shared__ int64_t ix[256];
+  const int t = threadIdx.x;
+  double bv = t < FSLICE ? pv[t] : -1.0;
+  int64_t bi = t < FSLICE ? pi[t] : -1;
+  fail_reduce(bv, bi, v, ix);
+  if (t != 0) return;
+  out->F = bv;
+  out->elem = bi;
+  if (bi < 0) return;
+  out->gauss = qe[bi];
+  out->layer = elayer[bi];
+  for (int k = 0; k < 6; ++k) out->stress[k] = Se[6 * bi + k];
 }
 
 }  // namespace gx
@@ -226,29 +237,29 @@ extern "C" gx_status gx_failure(gx_ctx* c, const double* u, const int32_t* layer
   to_dev(sel.p, hs.data(), nl, st);
   DevBuf<double> fe, se;
   DevBuf<int32_t> qe(E);
-  DevBuf<int64_t> be(1);
+  DevBuf<int64_t> pi(FSLICE);
+  DevBuf<double> pv(FSLICE);
+  DevBuf<FailPick> pick(1);
   double* Fe = F_elem;
   if (!Fe) {
     fe.alloc(E);
     Fe = fe.p;
   }
   se.alloc(6 * E);
-  hipLaunchKernelGGL(k_failure, dim3((unsigned)std::min<int64_t>(E, 256 * 64)), dim3(64), 0, st,
-                     periodic_of(c), E, c->xyz.p, c->conn.p, c->elayer.p, c->Cl.p, c->ang.p, sel.p, u, s33, s13,
-                     F_gauss, Fe, qe.p, se.p);
-  hipLaunchKernelGGL(k_failure_max, dim3(1), dim3(256), 0, st, E, Fe, be.p);
+  hipLaunchKernelGGL(k_failure, dim3((unsigned)std::min<int64_t>(nblocks(E, 2 * FW), 2048)),
+                     dim3(64 * FW), 0, st, periodic_of(c), E, c->xyz.p, c->conn.p, c->elayer.p,
+                     c->Cl.p, c->ang.p, sel.p, u, s33, s13, F_gauss, Fe, qe.p, se.p);
+  hipLaunchKernelGGL(k_failure_max, dim3(FSLICE), dim3(256), 0, st, E, Fe, pv.p, pi.p);
+  hipLaunchKernelGGL(k_failure_pick, dim3(1), dim3(256), 0, st, pv.p, pi.p, c->elayer.p, qe.p,
+                     se.p, pick.p);
   GX_HIP(hipGetLastError());
-  int64_t e = -1;
-  to_host(&e, be.p, 1, st);
-  GX_REQUIRE(e >= 0 && e < E, "no element of the selected layers");
-  int32_t q = 0;
-  int32_t layer = 0;
-  to_host(&out->F_max, Fe + e, 1, st);
-  to_host(&q, qe.p + e, 1, st);
-  to_host(&layer, c->elayer.p + e, 1, st);
-  to_host(out->stress, se.p + 6 * e, 6, st);
-  out->elem = e;
-  out->gauss = q;
-  out->layer = layer;
+  FailPick h{};
+  to_host(&h, pick.p, 1, st);
+  GX_REQUIRE(h.elem >= 0 && h.elem < E, "no element of the selected layers");
+  out->F_max = h.F;
+  out->elem = h.elem;
+  out->gauss = h.gauss;
+  out->layer = h.layer;
+  for (int k = 0; k < 6; ++k) out->stress[k] = h.stress[k];
   GX_API_END(c)
 }
