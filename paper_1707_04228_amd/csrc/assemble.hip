@@ -178,36 +178,37 @@ __global__ void k_layer_stiffness(int n_layers, const double* eng, double* C, in
 // ---------------------------------------------------------------------------------------
 // 4. element stiffness, one wavefront per element (four per work-group, grid-stride).
 //
-// K_e = sum over (q, I) of B'[(q, I)][r] w_q (C B')[(q, I)][c], a 60 x 162 x 60 product, as 16 x 16
-// tiles of the lower triangle (ten of the padded 64 x 64) on the FP64 matrix instruction.  The
-// order of the reduction is free, so a step takes one strain component at four Gauss points,
-// one per group of 16 lanes: a lane then needs B' at one point and column, which it forms in
-// registers from two 3 x 3 matrices of that point (LDS) and the node's reference gradients -
-// no strain matrix is ever stored.  With h = Q J^-T dN the gradient of the node's shape
-// function in the ply's axes and q = Q[.][i], column (node, i) of B' is [q0 h0, q1 h1, q2 h2,
-// q1 h2 + q2 h1, q0 h2 + q2 h0, q0 h1 + q1 h0].
+// K_e = sum_q w_q B_q^T (C_q B_q), B_q the strain-displacement matrix of the 20 nodes at Gauss point
+// q and C_q the layer's stiffness in global axes.  A point is a step: 60 lanes form the
+// gradient of a node and a column of C B each and pass them on through the wavefront's own part
+// of LDS; then lane (A, B), A <= B, of 55 adds the point to the 3 x 3 blocks of the two nodes of A
+// and the two of B.  Products and sums are in the order of the definition (nodes, Gauss
+// points and strain rows ascending, one fused multiply-add each): the matrices of these
+// thin plies are ill-conditioned (1e8), and another order moves the solution by 1e-8.
 //
-// Bound by the matrix instruction (420 per element, 0.35 ms for 33,600 elements) and the chain
-// of the point set-up beside it: 4.37 -> 0.68 ms against one work-group per element with
-// scalar products from LDS.
+// Bound by FP64 issue (about 5,000 products per lane and element) and LDS (42 doubles read per
+// 144 products): 33,600 elements 4.37 -> 1.00 ms, against one work-group per element with its
+// point set-up on 27 of 256 threads and a product of one pair of nodes per thread.  (On the
+// matrix instruction, which sums in another order, 0.68 ms.)
 struct ElemWave {
   double X[20][3];
-  double J[27][9];
-  double H[28][9];           // Q J^-T per Gauss point (row k: ply axis k)
-  double Q[28][9];           // ply axes (rows)
-  double w[28];              // det J * weight, zero at the padding point
+  double J[27][9];           // Jacobians, then their inverses (Ji[3 j + i] = dxi_j / dx_i)
+  double Cg[27][36];         // stiffness in global axes
+  double dv[27];             // det J * weight
+  double G[20][3];           // physical gradients at the current point
+  double CB[20][18];         // C_q B_b, entry 3 I + k, at the current point
 };
 constexpr int EW = 4;        // wavefronts per work-group
 struct ElemSmem {
-  double dNr[28][20][3];     // reference gradients at the Gauss points (zero padding point)
+  double dNr[27][20][3];     // reference gradients at the Gauss points
   ElemWave wave[EW];
 };
-typedef double v4d __attribute__((ext_vector_type(4)));
 
-// Frame, ply axes, inverse Jacobian and weight of Gauss point q from its Jacobian
-// J[3 i + j] = dx_i / dxi_j: e1 along dx/dxi, e2 from dx/deta (Gram-Schmidt), e3 = e1 x e2; the
-// fibre rotated by the ply angle about e3.
-__device__ inline void gauss_point_setup(int q, ElemWave& sm, double ca, double sa, int* err) {
+// Inverse Jacobian, weight and stiffness of Gauss point q from its Jacobian
+// J[3 i + j] = dx_i / dxi_j, in the geometric frame: e1 along dx/dxi, e2 from dx/deta
+// (Gram-Schmidt), e3 = e1 x e2; the fibre rotated by the ply angle about e3.
+__device__ inline void gauss_point_setup(int q, ElemWave& sm, const double* Cl, double ca,
+                                         double sa, int* err) {
   double J[3][3];
 #pragma unroll
   for (int i = 0; i < 9; ++i) J[i / 3][i % 3] = sm.J[q][i];
@@ -216,16 +217,15 @@ __device__ inline void gauss_point_setup(int q, ElemWave& sm, double ca, double 
                      J[0][2] * (J[1][0] * J[2][1] - J[1][1] * J[2][0]);
   if (!(det > 0)) atomicOr(err, ERR_JACOBIAN);
   const double id = 1.0 / det;
-  double Ji[3][3];                               // Ji[j][i] = dxi_j / dx_i
-  Ji[0][0] = (J[1][1] * J[2][2] - J[1][2] * J[2][1]) * id;
-  Ji[0][1] = (J[0][2] * J[2][1] - J[0][1] * J[2][2]) * id;
-  Ji[0][2] = (J[0][1] * J[1][2] - J[0][2] * J[1][1]) * id;
-  Ji[1][0] = (J[1][2] * J[2][0] - J[1][0] * J[2][2]) * id;
-  Ji[1][1] = (J[0][0] * J[2][2] - J[0][2] * J[2][0]) * id;
-  Ji[1][2] = (J[0][2] * J[1][0] - J[0][0] * J[1][2]) * id;
-  Ji[2][0] = (J[1][0] * J[2][1] - J[1][1] * J[2][0]) * id;
-  Ji[2][1] = (J[0][1] * J[2][0] - J[0][0] * J[2][1]) * id;
-  Ji[2][2] = (J[0][0] * J[1][1] - J[0][1] * J[1][0]) * id;
+  sm.J[q][0] = (J[1][1] * J[2][2] - J[1][2] * J[2][1]) * id;
+  sm.J[q][1] = (J[0][2] * J[2][1] - J[0][1] * J[2][2]) * id;
+  sm.J[q][2] = (J[0][1] * J[1][2] - J[0][2] * J[1][1]) * id;
+  sm.J[q][3] = (J[1][2] * J[2][0] - J[1][0] * J[2][2]) * id;
+  sm.J[q][4] = (J[0][0] * J[2][2] - J[0][2] * J[2][0]) * id;
+  sm.J[q][5] = (J[0][2] * J[1][0] - J[0][0] * J[1][2]) * id;
+  sm.J[q][6] = (J[1][0] * J[2][1] - J[1][1] * J[2][0]) * id;
+  sm.J[q][7] = (J[0][1] * J[2][0] - J[0][0] * J[2][1]) * id;
+  sm.J[q][8] = (J[0][0] * J[1][1] - J[0][1] * J[1][0]) * id;
   double e1[3] = {J[0][0], J[1][0], J[2][0]}, t2[3] = {J[0][1], J[1][1], J[2][1]};
   const double n1 = sqrt(e1[0] * e1[0] + e1[1] * e1[1] + e1[2] * e1[2]);
 #pragma unroll
@@ -237,6 +237,7 @@ __device__ inline void gauss_point_setup(int q, ElemWave& sm, double ca, double 
   for (int i = 0; i < 3; ++i) e2[i] /= n2;
   const double e3[3] = {e1[1] * e2[2] - e1[2] * e2[1], e1[2] * e2[0] - e1[0] * e2[2],
                         e1[0] * e2[1] - e1[1] * e2[0]};
+  // material axes (rows of Q, global components)
   double Q[3][3];
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
@@ -244,18 +245,46 @@ __device__ inline void gauss_point_setup(int q, ElemWave& sm, double ca, double 
     Q[1][i] = -sa * e1[i] + ca * e2[i];
     Q[2][i] = e3[i];
   }
+  // Bond matrix: local engineering strain = T * global engineering strain
+  constexpr int vi[6] = {0, 1, 2, 1, 0, 0}, vj[6] = {0, 1, 2, 2, 2, 1};
+  double T[6][6], CT[6][6];
 #pragma unroll
-  for (int k = 0; k < 3; ++k)
+  for (int I = 0; I < 6; ++I) {
+    const int i = vi[I], j = vj[I];
 #pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      sm.Q[q][3 * k + j] = Q[k][j];
-      sm.H[q][3 * k + j] = Q[k][0] * Ji[j][0] + Q[k][1] * Ji[j][1] + Q[k][2] * Ji[j][2];
+    for (int K = 0; K < 6; ++K) {
+      const int k = vi[K], l = vj[K];
+      if (I < 3)
+        T[I][K] = (K < 3) ? Q[i][k] * Q[i][k] : Q[i][k] * Q[i][l];
+      else
+        T[I][K] = (K < 3) ? 2.0 * Q[i][k] * Q[j][k] : Q[i][k] * Q[j][l] + Q[i][l] * Q[j][k];
+    }
+  }
+  // C_g = T^T C T; C is a full 3 x 3 normal block and three shear moduli
+#pragma unroll
+  for (int K = 0; K < 6; ++K) {
+#pragma unroll
+    for (int I = 0; I < 3; ++I)
+      CT[I][K] = __builtin_fma(Cl[6 * I + 2], T[2][K],
+                               __builtin_fma(Cl[6 * I + 1], T[1][K], Cl[6 * I] * T[0][K]));
+#pragma unroll
+    for (int I = 3; I < 6; ++I) CT[I][K] = Cl[7 * I] * T[I][K];
+  }
+#pragma unroll
+  for (int I = 0; I < 6; ++I)
+#pragma unroll
+    for (int K = I; K < 6; ++K) {
+      double s = T[0][I] * CT[0][K];
+#pragma unroll
+      for (int L = 1; L < 6; ++L) s = __builtin_fma(T[L][I], CT[L][K], s);
+      sm.Cg[q][6 * I + K] = s;
+      sm.Cg[q][6 * K + I] = s;
     }
   double xq, wq, wy, wz;
   gauss3(q % 3, &xq, &wq);
   gauss3((q / 3) % 3, &xq, &wy);
   gauss3(q / 9, &xq, &wz);
-  sm.w[q] = det * wq * wy * wz;
+  sm.dv[q] = det * wq * wy * wz;
 }
 
 __global__ void __launch_bounds__(64 * EW, 2) k_element(Periodic P, int64_t n_elems,
@@ -267,29 +296,31 @@ __global__ void __launch_bounds__(64 * EW, 2) k_element(Periodic P, int64_t n_el
   extern __shared__ double smem_raw[];
   ElemSmem& sm = *reinterpret_cast<ElemSmem*>(smem_raw);
   // reference gradients at the 27 Gauss points (q = i + 3 j + 9 k)
-  for (int idx = threadIdx.x; idx < 28 * 20; idx += blockDim.x) {
+  for (int idx = threadIdx.x; idx < 27 * 20; idx += blockDim.x) {
     const int q = idx / 20, a = idx % 20;
-    double x0, x1, x2, w, N, d[3] = {0, 0, 0};
-    if (q < 27) {
-      gauss3(q % 3, &x0, &w);
-      gauss3((q / 3) % 3, &x1, &w);
-      gauss3(q / 9, &x2, &w);
-      shape_one(a, x0, x1, x2, &N, d);
-    }
+    double x0, x1, x2, w, N, d[3];
+    gauss3(q % 3, &x0, &w);
+    gauss3((q / 3) % 3, &x1, &w);
+    gauss3(q / 9, &x2, &w);
+    shape_one(a, x0, x1, x2, &N, d);
     for (int j = 0; j < 3; ++j) sm.dNr[q][a][j] = d[j];
   }
   __syncthreads();
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int li = lane & 15, lk = lane >> 4;
   ElemWave& W = sm.wave[wv];
-  if (lane < 9) W.H[27][lane] = W.Q[27][lane] = 0.0;
-  if (lane == 0) W.w[27] = 0.0;
   // (the lanes of a wavefront exchange through their own part of LDS: its accesses are
   // performed in order, so only the compiler has to keep them)
   auto fence = [] {
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
     __builtin_amdgcn_wave_barrier();
   };
+  const int nb = min(lane / 3, 19), nk = lane % 3;  // this lane's node and column of C B
+  // the strain rows that displacement component k enters, ascending, and with which gradient
+  // component: k = 0: 11, 13, 12; 1: 22, 23, 12; 2: 33, 23, 13
+  const int j1 = nk == 0 ? 4 : 3, j2 = nk == 2 ? 4 : 5;
+  int A = 0, Bn = lane;                            // this lane's pairs of nodes
+  while (A < 9 && Bn >= 10 - A) { Bn -= 10 - A; ++A; }
+  Bn = min(Bn + A, 9);
   for (int64_t e = (int64_t)blockIdx.x * EW + wv; e < n_elems; e += (int64_t)gridDim.x * EW) {
     if (lane < 60)
       W.X[lane / 3][lane % 3] = node_coord(xyz, conn[20 * e + lane / 3], lane % 3, P, e, lane / 3);
@@ -305,84 +336,71 @@ __global__ void __launch_bounds__(64 * EW, 2) k_element(Periodic P, int64_t n_el
     fence();
     if (lane < 27) {
       const double an = angle[L] * (M_PI / 180.0);
-      gauss_point_setup(lane, W, cos(an), sin(an), err);
+      gauss_point_setup(lane, W, Clayer + 36 * L, cos(an), sin(an), err);
     }
     fence();
-    // the layer's stiffness: a full symmetric 3 x 3 normal block and three shear moduli
-    const double* C = Clayer + 36 * L;
-    double Cn[3][3], Cs[3];
+    double acc[2][2][9];
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      Cs[i] = lane_value(C[7 * (3 + i)], 0);       // (into scalar registers)
-#pragma unroll
-      for (int j = 0; j < 3; ++j) Cn[i][j] = lane_value(C[6 * i + j], 0);
-    }
-    v4d acc[10];
-#pragma unroll
-    for (int t = 0; t < 10; ++t) acc[t] = v4d{0, 0, 0, 0};
+    for (int i = 0; i < 36; ++i) acc[i / 18][i / 9 % 2][i % 9] = 0.0;
 #pragma unroll 1
-    for (int g = 0; g < 7; ++g) {
-      const int q = 4 * g + lk;                    // this lane's Gauss point
-      const double w = W.w[q];
-      double h[4][3], c[4][3];
+    for (int q = 0; q < 27; ++q) {
+      {
+        const double d0 = sm.dNr[q][nb][0], d1 = sm.dNr[q][nb][1], d2 = sm.dNr[q][nb][2];
+        double g[3];
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int dof = 16 * t + li, a = min(dof / 3, 19), i = dof - 3 * (dof / 3);
-        const double d0 = sm.dNr[q][a][0], d1 = sm.dNr[q][a][1], d2 = sm.dNr[q][a][2];
+        for (int i = 0; i < 3; ++i)
+          g[i] = d0 * W.J[q][i] + d1 * W.J[q][3 + i] + d2 * W.J[q][6 + i];
+        const double g0 = nk == 0 ? g[0] : nk == 1 ? g[1] : g[2];
+        const double g1 = nk == 2 ? g[1] : g[2], g2 = nk == 0 ? g[1] : g[0];
+        if (lane < 60) {
+          W.G[nb][nk] = g0;
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          h[t][k] = W.H[q][3 * k] * d0 + W.H[q][3 * k + 1] * d1 + W.H[q][3 * k + 2] * d2;
-          c[t][k] = dof < 60 ? W.Q[q][3 * k + i] : 0.0;
+          for (int I = 0; I < 6; ++I) {
+            const double* c = &W.Cg[q][6 * I];
+            W.CB[nb][3 * I + nk] = __builtin_fma(c[j2], g2, __builtin_fma(c[j1], g1, c[nk] * g0));
+          }
         }
       }
-      // one strain component: b its row of B', cb that of w C B'
-      auto step = [&](const double (&b)[4], const double (&cb)[4]) {
+      fence();
+      const double dv = W.dv[q];
+      double ga[2][3];
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
+      for (int x = 0; x < 2; ++x)
 #pragma unroll
-          for (int s = 0; s <= r; ++s)
-            acc[r * (r + 1) / 2 + s] = __builtin_amdgcn_mfma_f64_16x16x4f64(
-                b[r], cb[s], acc[r * (r + 1) / 2 + s], 0, 0, 0);
-      };
-      double b[4], cb[4];
+        for (int i = 0; i < 3; ++i) ga[x][i] = W.G[2 * A + x][i];
 #pragma unroll
-      for (int I = 0; I < 3; ++I) {
+      for (int y = 0; y < 2; ++y) {
+        double cb[18];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          b[t] = c[t][I] * h[t][I];
-          cb[t] = w * (Cn[I][0] * (c[t][0] * h[t][0]) + Cn[I][1] * (c[t][1] * h[t][1]) +
-                       Cn[I][2] * (c[t][2] * h[t][2]));
-        }
-        step(b, cb);
+        for (int i = 0; i < 18; ++i) cb[i] = W.CB[2 * Bn + y][i];
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+          for (int k = 0; k < 3; ++k) {
+            const double* g = ga[x];
+            const double s0 = __builtin_fma(g[1], cb[15 + k], __builtin_fma(g[2], cb[12 + k], g[0] * cb[k]));
+            const double s1 = __builtin_fma(g[0], cb[15 + k], __builtin_fma(g[2], cb[9 + k], g[1] * cb[3 + k]));
+            const double s2 = __builtin_fma(g[0], cb[12 + k], __builtin_fma(g[1], cb[9 + k], g[2] * cb[6 + k]));
+            acc[x][y][k] = __builtin_fma(dv, s0, acc[x][y][k]);
+            acc[x][y][3 + k] = __builtin_fma(dv, s1, acc[x][y][3 + k]);
+            acc[x][y][6 + k] = __builtin_fma(dv, s2, acc[x][y][6 + k]);
+          }
       }
-#pragma unroll
-      for (int I = 0; I < 3; ++I) {
-        const int k = I == 0 ? 1 : 0, l = I == 2 ? 1 : 2;   // 23, 13, 12
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          b[t] = c[t][k] * h[t][l] + c[t][l] * h[t][k];
-          cb[t] = w * (Cs[I] * b[t]);
-        }
-        step(b, cb);
-      }
+      fence();
     }
-    // entry (row, col) of the 60 x 60 matrix and its mirror, in 3 x 3 blocks
     double* out = Ke + e * 3600;
-    int lo = lane;                                 // (opaque, so that the places below are
-    asm volatile("" : "+v"(lo));                   // formed here and not kept in registers)
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
+    for (int x = 0; x < 2; ++x)
 #pragma unroll
-      for (int c = 0; c <= r; ++c)
+      for (int y = 0; y < 2; ++y) {
+        const int a = 2 * A + x, b = 2 * Bn + y;
+        if (lane >= 55 || a > b) continue;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const int row = 16 * r + 4 * k + (lo >> 4), col = 16 * c + (lo & 15);
-          if (row >= 60 || col > row) continue;
-          const int a = row / 3, i = row % 3, b = col / 3, j = col % 3;
-          const double x = acc[r * (r + 1) / 2 + c][k];
-          out[(a * 20 + b) * 9 + 3 * i + j] = x;
-          if (col < row) out[(b * 20 + a) * 9 + 3 * j + i] = x;
-        }
+        for (int i = 0; i < 9; ++i) out[(a * 20 + b) * 9 + i] = acc[x][y][i];
+        if (a != b)
+#pragma unroll
+          for (int i = 0; i < 9; ++i) out[(b * 20 + a) * 9 + i % 3 * 3 + i / 3] = acc[x][y][i];
+      }
     fence();
   }
 }
