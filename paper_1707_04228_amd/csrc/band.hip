@@ -1602,11 +1602,11 @@ __device__ inline V uniform_load(const V* p) {
 }
 
 // (part, group) of this work-group in a launch over one band set of n_mat matrices, G groups
-// per part, both parts of a matrix (PP = 2 if the set has split matrices) in turn; part -1:
-// none
-__device__ inline int2 set_place(const int32_t* part_of, int n_mat, int G, int PP,
+// per part, both parts of a matrix (PP = 2 if the set has split matrices) in turn, matrix j on
+// XCD (j + xcd0) mod 8; part -1: none
+__device__ inline int2 set_place(const int32_t* part_of, int n_mat, int G, int PP, int xcd0,
                                  int* counters) {
-  const int x = blockIdx.x & 7, q = take_place(counters + x);
+  const int x = (blockIdx.x - xcd0) & 7, q = take_place(counters + x);
   const int j = q / (G * PP) * 8 + x, m = q % (G * PP);
   if (j >= n_mat) return {-1, 0};
   return {uniform_load(part_of + 2 * j + m % PP), m / PP};
@@ -1616,9 +1616,9 @@ __device__ inline int2 set_place(const int32_t* part_of, int n_mat, int G, int P
 template <class T, bool COARSE>
 __global__ void __launch_bounds__(SOLVE_THREADS) k_band_solve_1(
     BandArgs a, const int32_t* part_of, const T* v, const T* dinv, const T* link,
-    const int64_t* xoff, const double* xall, double* yall, double* zall, int G, int PP, int n_mat,
+    const int64_t* xoff, const double* xall, double* yall, double* zall, int G, int PP, int xcd0, int n_mat,
     int* err) {
-  const int2 pg = set_place(part_of, n_mat, G, PP, err + 1);
+  const int2 pg = set_place(part_of, n_mat, G, PP, xcd0, err + 1);
   if (pg.x < 0) return;
   auto load = [&](int i) -> Solve1<T> {
     const BandPart P = uniform_load(a.part + i);
@@ -1703,7 +1703,7 @@ constexpr int AL = SB * SB / MT;                  // band-chunk entries per thre
 template <class T, int M>
 __global__ void __launch_bounds__(MT) k_band_solve_m(
     BandArgs a, const int32_t* part_of, const T* v, const T* dinv, const int64_t* xoff,
-    const double* xall, T* yall, T* zall, int G, int PP, int n_mat, const int32_t* active,
+    const double* xall, T* yall, T* zall, int G, int PP, int xcd0, int n_mat, const int32_t* active,
     int* err) {
   typedef Mfma<T> MF;
   typedef typename MF::S S;
@@ -1713,7 +1713,7 @@ __global__ void __launch_bounds__(MT) k_band_solve_m(
   constexpr int YL = SB * M / MT;                 // solution-chunk entries per thread
   __shared__ S Ab[2][SB][SB + 1];                 // band chunks (double buffer); buffer 0
   __shared__ S Yc[2][SB * MP];                    // holds the inverse block in finish
-  const int2 pg = set_place(part_of, n_mat, G, PP, err + 1);
+  const int2 pg = set_place(part_of, n_mat, G, PP, xcd0, err + 1);
   const int g = pg.y;
   if (pg.x < 0) return;
   int64_t n, B, rs, n1, ncb, sep;                 // n1: last row of the matrix; ncb: blocks
@@ -1983,9 +1983,14 @@ __global__ void __launch_bounds__(MT) k_band_solve_m(
 
 // Work-groups per part: as many as keep every work-group of the launch resident at once (a
 // part waits at the pace of its slowest group); at most GMAX for one right-hand side, 8 for
-// several.  The solves of one context are stream-ordered, so a launch may count on the
-// whole machine.  When several contexts solve concurrently (share > 1) each gets an equal
-// part of three quarters of it, so that all their launches fit together.
+// several.  A matrix's work-groups run on one XCD (set_place), so it is the parts on the
+// fullest XCD that are counted, against its eighth of the machine: counted together, 14
+// matrices of 24 parts would put 40 work-groups on an XCD's 32 slots.  The solves of one
+// context are stream-ordered, so a launch may count on the whole machine.  When several
+// contexts solve concurrently (share > 1) their launches together get three quarters of it;
+// their matrices go round the XCDs one after another (xcd0), so an XCD holds at most
+// `together` parts - or, where that is not known or contexts wait for their turn, share times
+// one context's.
 static int solve_groups(BandSet& bs, const void* kernel, int which) {
   if (bs.solve_groups[which] > 0) return bs.solve_groups[which];
   int dev = 0, cus = 0, per_cu = 0;
@@ -1993,13 +1998,17 @@ static int solve_groups(BandSet& bs, const void* kernel, int which) {
   GX_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
   GX_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel,
                                                       which == 0 ? SOLVE_THREADS : MT, 0));
-  const int64_t full = (int64_t)cus * std::max(per_cu, 0);
-  const int64_t capacity = bs.share > 1 ? full * 3 / 4 / bs.share : full;
+  const int64_t full = (int64_t)cus * std::max(per_cu, 0) / 8;   // of an XCD
+  const int64_t capacity = bs.share > 1 ? full * 3 / 4 : full;
+  std::vector<int64_t> parts(8, 0);
+  for (const BandPart& p : bs.part) ++parts[p.mat & 7];
+  int64_t most = *std::max_element(parts.begin(), parts.end()) * std::max(bs.share, 1);
+  if (bs.together > 0) most = std::min<int64_t>(most, bs.together);
   const int cap = which == 0 ? GMAX : 8;
   int G = 1;
   const int top = bs.force_groups[which] > 0 ? std::min(bs.force_groups[which], cap) : cap;
   for (int c = top; c >= 2; --c)
-    if ((int64_t)bs.n_part * c <= capacity && bs.max_cols >= (int64_t)2 * SB * c) {
+    if (most * c <= capacity && bs.max_cols >= (int64_t)2 * SB * c) {
       G = c;
       break;
     }
@@ -2109,7 +2118,7 @@ static void launch_m(BandSet& bs, const BandArgs& a, const int64_t* d_xoff, doub
     hipLaunchKernelGGL(k_fill_mark32, dim3(nblocks(2 * rows * M, 256)), dim3(256), 0, st, y,
                        2 * rows * M, err + 1);
     hipLaunchKernelGGL((k_band_solve_m<float, M>), dim3(solve_grid(bs, G)), dim3(MT), 0, st, a,
-                       bs.d_part_of.p, bs.v32.p, bs.dinv32.p, d_xoff, x, y, z, G, PP, bs.n_mat,
+                       bs.d_part_of.p, bs.v32.p, bs.dinv32.p, d_xoff, x, y, z, G, PP, bs.xcd0, bs.n_mat,
                        active, err);
     hipLaunchKernelGGL(k_copy_out<float>, cgrid, dim3(256), 0, st, bs.d_part.p, d_xoff, M, z, x,
                        active);
@@ -2119,7 +2128,7 @@ static void launch_m(BandSet& bs, const BandArgs& a, const int64_t* d_xoff, doub
     hipLaunchKernelGGL(k_fill_mark, dim3(nblocks(2 * rows * M, 256)), dim3(256), 0, st, y,
                        2 * rows * M, err + 1);
     hipLaunchKernelGGL((k_band_solve_m<double, M>), dim3(solve_grid(bs, G)), dim3(MT), 0, st, a,
-                       bs.d_part_of.p, bs.v64.p, bs.dinv64.p, d_xoff, x, y, z, G, PP, bs.n_mat,
+                       bs.d_part_of.p, bs.v64.p, bs.dinv64.p, d_xoff, x, y, z, G, PP, bs.xcd0, bs.n_mat,
                        active, err);
     hipLaunchKernelGGL(k_copy_out<double>, cgrid, dim3(256), 0, st, bs.d_part.p, d_xoff, M, z, x,
                        active);
@@ -2182,15 +2191,15 @@ void band_solve(BandSet& bs, const int64_t* d_xoff, double* x, hipStream_t st, i
     if (bs.fp32)
       hipLaunchKernelGGL((k_band_solve_1<float, false>), grid, dim3(SOLVE_THREADS), 0, st, a,
                          bs.d_part_of.p, bs.v32.p, bs.dinv32.p, link32, d_xoff, x, y, z, G, PP,
-                         bs.n_mat, err);
+                         bs.xcd0, bs.n_mat, err);
     else if (bs.coarse)
       hipLaunchKernelGGL((k_band_solve_1<double, true>), grid, dim3(SOLVE_THREADS), 0, st, a,
                          bs.d_part_of.p, bs.v64.p, bs.dinv64.p, link64, d_xoff, x, y, z, G, PP,
-                         bs.n_mat, err);
+                         bs.xcd0, bs.n_mat, err);
     else
       hipLaunchKernelGGL((k_band_solve_1<double, false>), grid, dim3(SOLVE_THREADS), 0, st, a,
                          bs.d_part_of.p, bs.v64.p, bs.dinv64.p, link64, d_xoff, x, y, z, G, PP,
-                         bs.n_mat, err);
+                         bs.xcd0, bs.n_mat, err);
     hipLaunchKernelGGL(k_copy_out<double>, dim3(nblocks(bs.max_cols, 256), bs.n_part), dim3(256),
                        0, st, bs.d_part.p, d_xoff, 1, z, x, (const int32_t*)nullptr);
   } else {
