@@ -111,6 +111,384 @@ __device__ inline void chain_wait(const int* f, int epoch, int* err) {
   atomicOr(err, 2);
 }
 
+// One launch per group for the group's own rows: the GP x GP triangle of 64-row blocks from
+// the diagonal block of the first panel down.  Work-group (t, j) owns row block t of matrix
+// j, the 64 rows [k0 + 64 t, + 64), and keeps its t + 1 blocks in registers from the start:
+//   1. Panel by panel, q < t: L(t, q) = A(t, q) Li(q)^T once the inverse Li(q) of that panel's
+//      diagonal block is handed over (FP64 instruction); the block is stored.
+//   2. Its products are taken off the row's other blocks at once, with the matrix instruction
+//      in the factor's precision: A(t, t) -= L(t, q) L(t, q)^T, and for q < m < t
+//      A(t, m) -= L(t, q) L(m, q)^T with row block m's result.
+//   3. Cholesky of A(t, t) and the inverse of its factor; the inverse is handed to the
+//      work-groups of the later row blocks and kept for the triangular solves.
+// The launch is a chain of GP diagonal blocks, on one work-group at a time.  What lies
+// between two of them is one hand-over (the inverse; a row block's own products never leave
+// its work-group), two 64^3 products and the factorisation itself; everything else runs
+// beside it.  With a work-group per block a step was two hand-overs and the reload of all
+// earlier panels, and one wave factored and inverted the diagonal block: 33 us a step, now 17,
+// of which 4 x 2.7 us are the four block columns of step 3.  Per launch: 131 -> 77 us (8 parts, B =
+// 370, FP64), 160 -> 94 (FP32, B = 540), 218 -> 151 (32 parts, B = 1,630, beside the update).
+// Work-groups are numbered by row block, then matrix, and take their number from a counter
+// of the launch when they start, not from their position in the grid; a work-group waits for
+// lower row blocks of its matrix only, so every wait is for a work-group that is already
+// running: the launch cannot deadlock, whatever order the hardware dispatches its
+// work-groups in and whatever else occupies the device.
+// A non-positive pivot raises bit 1 of the error word (and may leave NaNs behind it).
+template <class T>
+__global__ void __launch_bounds__(CT, 2) k_chain(BandArgs a, T* v, int64_t kg, int n_mat,
+                                              int* flags, int* ticket, int epoch, double* inv,
+                                              T* dinv, int* err) {
+  typedef Mfma<T> MT;
+  typedef typename MT::S S;
+  constexpr int XS = sizeof(S) == 8 ? NB + 1 : NB + 4;   // LDS stride of a finished block
+  __shared__ double D[NB][NB + 1];               // a block of A; the diagonal block's factor
+  __shared__ double Li[NB][NB + 1];              // the inverse of a diagonal block
+  __shared__ double Wd[NB / 16][16][17];         // inverses of the 16x16 diagonal blocks
+  __shared__ double rd[NB];                      // reciprocals of the pivots
+  __shared__ int tk;
+  static_assert(NB * XS * sizeof(S) <= sizeof(D), "finished blocks fit in the block buffers");
+  S* X = reinterpret_cast<S*>(&D[0][0]);         // L(t, q) (aliases D)
+  S* Y = reinterpret_cast<S*>(&Li[0][0]);        // L(m, q) (aliases Li)
+  if (threadIdx.x == 0) tk = atomicAdd(ticket, 1);
+  __syncthreads();
+  const int b = __builtin_amdgcn_readfirstlane(tk), t = b / n_mat, j = b - t * n_mat;
+  const BandPart& P = a.part[j];
+  const int64_t k0l = P.fb[a.phase] + kg;
+  if (k0l >= P.fe[a.phase] || k0l + NB * t >= P.rows) return;
+  const int n = (int)P.rows, B = (int)P.B, rs = (int)P.ld - 1;
+  const int k0 = (int)k0l, ce = (int)P.fe[a.phase], r0 = k0 + NB * t;
+  const int np = min(t, (ce - k0 + NB - 1) / NB);  // panels left of the row's diagonal block
+  const bool diag = r0 < ce;                       // the row block has a panel
+  auto reach = [&](int rb, int q) { return NB * (rb - q) <= NB - 1 + B; };  // block not empty
+  T* base = v + P.off;
+  auto at = [&](int r, int c) { return (uint32_t)(r * rs + B + c); };     // entry (r, c)
+  int* fj = flags + (int64_t)j * GP * GP;          // flag of block (m, q): fj[GP m + q]
+  int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int li = lane & 15, lk = lane >> 4;
+  // Behind this the compiler takes the lane's place for new: the conditions and addresses
+  // of one step, kept for the next, would not fit in the registers.
+  auto forget = [&]() { asm volatile("" : "+v"(lane), "+v"(li), "+v"(lk)); };
+  const int wr = 32 * (w & 1), wc = 32 * (w >> 1);
+  // The row's blocks, in the matrix instruction's result layout (entries outside the matrix
+  // or the band are 0; the diagonal block keeps its lower triangle): av[d] is A(t, q + d).
+  double av[GP - 1][2][4][2], ad[2][4][2];
+  auto inside = [&](int q, bool low, int rl, int cl) {
+    const int r = r0 + rl, c = k0 + NB * q + cl;
+    return r < n && c < ce && c >= r - B && (!low || cl <= rl);
+  };
+  // The loads of all blocks are issued before the first is used; outside entries load
+  // entry (0, 0) and are zeroed by a second look at the conditions.
+  auto load = [&](double (&x)[2][4][2], int q, bool low) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int jj = 0; jj < 2; ++jj) {
+          const int rl = wr + 16 * i + MT::row(e, lk), cl = wc + 16 * jj + li;
+          x[i][e][jj] = base[inside(q, low, rl, cl) ? at(r0 + rl, k0 + NB * q + cl) : (uint32_t)B];
+        }
+  };
+  auto clip = [&](double (&x)[2][4][2], int q, bool low) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int jj = 0; jj < 2; ++jj)
+          if (!inside(q, low, wr + 16 * i + MT::row(e, lk), wc + 16 * jj + li)) x[i][e][jj] = 0.0;
+  };
+#pragma unroll
+  for (int q = 0; q < GP - 1; ++q)
+    if (q < np) load(av[q], q, false);
+  if (diag) load(ad, t, true);
+  forget();
+#pragma unroll
+  for (int q = 0; q < GP - 1; ++q)
+    if (q < np) clip(av[q], q, false);
+  if (diag) clip(ad, t, true);
+  // x -= U V^T with finished blocks in LDS
+  auto update = [&](double (&x)[2][4][2], const S* U, const S* V) {
+    typename MT::V acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int jj = 0; jj < 2; ++jj) acc[i][jj] = typename MT::V{0, 0, 0, 0};
+#pragma unroll 4
+    for (int k = 0; k < NB; k += 4) {
+      S fa[2], fb[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) fa[i] = U[(wr + 16 * i + li) * XS + k + lk];
+#pragma unroll
+      for (int jj = 0; jj < 2; ++jj) fb[jj] = V[(wc + 16 * jj + li) * XS + k + lk];
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int jj = 0; jj < 2; ++jj) acc[i][jj] = MT::mma(fa[i], fb[jj], acc[i][jj]);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int jj = 0; jj < 2; ++jj) x[i][e][jj] -= (double)acc[i][jj][e];
+  };
+  auto to_D = [&](const double (&x)[2][4][2]) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int jj = 0; jj < 2; ++jj)
+          D[wr + 16 * i + MT::row(e, lk)][wc + 16 * jj + li] = x[i][e][jj];
+  };
+#pragma unroll 1
+  for (int q = 0; q < np; ++q) {
+    if (reach(t, q)) {
+      forget();
+      // 1.
+      const int c0 = k0 + NB * q;
+      to_D(av[0]);
+      if (threadIdx.x == 0) chain_wait(fj + GP * q + q, epoch, err);
+      __syncthreads();
+      const double* iq = inv + ((int64_t)j * GP + q) * NB * NB;
+      double lv[NB * NB / CT];                     // all loads issued before any is used
+#pragma unroll
+      for (int u = 0; u < NB * NB / CT; ++u) lv[u] = co_load(iq + threadIdx.x + CT * u);
+#pragma unroll
+      for (int u = 0; u < NB * NB / CT; ++u)
+        Li[w + CT / NB * u][lane] = lv[u];
+      __syncthreads();
+      v4d x[2][2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int jj = 0; jj < 2; ++jj) x[i][jj] = v4d{0, 0, 0, 0};
+#pragma unroll 4
+      for (int k = 0; k < NB; k += 4) {
+        double fa[2], fb[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) fa[i] = D[wr + 16 * i + li][k + lk];
+#pragma unroll
+        for (int jj = 0; jj < 2; ++jj) fb[jj] = Li[wc + 16 * jj + li][k + lk];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int jj = 0; jj < 2; ++jj) x[i][jj] = Mfma<double>::mma(fa[i], fb[jj], x[i][jj]);
+      }
+      __syncthreads();                             // D and Li are read
+      forget();
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int jj = 0; jj < 2; ++jj) {
+            const int rl = wr + 16 * i + Mfma<double>::row(e, lk), cl = wc + 16 * jj + li;
+            const int r = r0 + rl, c = c0 + cl;
+            const bool ok = r < n && c < ce && c >= r - B;
+            if (ok) co_store(base + at(r, c), (T)x[i][jj][e]);
+            X[rl * XS + cl] = ok ? (S)(T)x[i][jj][e] : (S)0;
+          }
+      __syncthreads();
+      // 2.
+      if (diag) update(ad, X, X);
+      chain_signal(fj + GP * t + q, epoch);        // (the stores drained beside the product)
+#pragma unroll
+      for (int d = 1; d < GP - 1; ++d) {
+        const int m = q + d;
+        if (m >= np || !reach(m, q)) continue;
+        if (threadIdx.x == 0) chain_wait(fj + GP * m + q, epoch, err);
+        __syncthreads();
+        // (the rows are inside the matrix; outside the band they read entry (0, 0))
+        T yv[NB * NB / CT];
+        const int lo = NB * d + w - B;             // first column of the block's row w
+#pragma unroll
+        for (int u = 0; u < NB * NB / CT; ++u)
+          yv[u] = co_load(base + (lane >= lo + CT / NB * u
+                                      ? at(k0 + NB * m + w + CT / NB * u, c0 + lane)
+                                      : (uint32_t)B));
+        forget();
+#pragma unroll
+        for (int u = 0; u < NB * NB / CT; ++u)
+          Y[(w + CT / NB * u) * XS + lane] = lane >= lo + CT / NB * u ? (S)yv[u] : (S)0;
+        __syncthreads();
+        update(av[d], X, Y);
+        __syncthreads();                           // Y is read
+      }
+    }
+#pragma unroll
+    for (int d = 0; d + 1 < GP - 1; ++d)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int jj = 0; jj < 2; ++jj) av[d][i][e][jj] = av[d + 1][i][e][jj];
+    __syncthreads();                               // X is read
+  }
+  if (!diag) return;
+  forget();
+  const int nb = min(NB, ce - r0);                 // columns of the panel inside the matrix
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int jj = 0; jj < 2; ++jj) {
+        const int rl = wr + 16 * i + MT::row(e, lk), cl = wc + 16 * jj + li;
+        if (rl == cl && rl >= nb) ad[i][e][jj] = 1.0;   // padding of a short last panel
+      }
+  to_D(ad);
+  __syncthreads();
+  // 3. Cholesky of the diagonal block and its inverse, in 16-column blocks.  Stage kb: wave 0
+  // factors block column kb for all the rows below it in registers (lane r holds row r;
+  // pivots and column entries come from other lanes by reads of their registers), wave 1
+  // extends the inverse by block row kb - 1, waves 2 and 3 take column kb - 1's products off
+  // the tiles right of column kb; then column kb's products are taken off column kb + 1, a
+  // tile to a wave.  With L the factor and W_i the inverses of its diagonal tiles, block row
+  // i of the inverse is W_i and -W_i S(i, j), S(i, j) = sum_{j <= k < i} L(i, k) Li(k, j):
+  // after the last stage only W_3 and one product are left.
+  typedef Mfma<double> M64;
+  // scratch tile of wave-local products and of S(3, j): above D's diagonal, read by nothing
+  auto tmp = [&](int i, int j2, int l) -> double& { return D[i][16 * (j2 + 1) + l]; };
+  auto invert_tile = [&](int i) {                  // W_i, lane c: column c
+    const int b0 = 16 * i, c16 = lane & 15;
+    double x[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) x[k] = k == c16 ? 1.0 : 0.0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      x[k] *= rd[b0 + k];
+#pragma unroll
+      for (int l = k + 1; l < 16; ++l) x[l] -= D[b0 + l][b0 + k] * x[k];
+    }
+    if (lane < 16)
+#pragma unroll
+      for (int k = 0; k < 16; ++k) Wd[i][k][c16] = x[k];
+  };
+  auto row_sum = [&](int i, int j2) {              // S(i, j2) into the scratch tile j2
+    v4d acc = v4d{0, 0, 0, 0};
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)                 // k = j2: Li(j2, j2) = W_j2
+      acc = M64::mma(D[16 * i + li][16 * j2 + 4 * ks + lk], Wd[j2][4 * ks + lk][li], acc);
+#pragma unroll 1
+    for (int k = j2 + 1; k < i; ++k)
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks)
+        acc = M64::mma(D[16 * i + li][16 * k + 4 * ks + lk],
+                       Li[16 * k + 4 * ks + lk][16 * j2 + li], acc);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) tmp(M64::row(e, lk), j2, li) = acc[e];
+  };
+  auto row_inverse = [&](int i, int j2) {          // Li(i, j2) = -W_i S(i, j2)
+    v4d acc = v4d{0, 0, 0, 0};
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+      acc = M64::mma(Wd[i][li][4 * ks + lk], tmp(4 * ks + lk, j2, li), acc);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) Li[16 * i + M64::row(e, lk)][16 * j2 + li] = -acc[e];
+  };
+  auto tile_update = [&](int ti, int tj, int kb) {  // A(ti, tj) -= L(ti, kb) L(tj, kb)^T
+    v4d acc = v4d{0, 0, 0, 0};
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+      acc = M64::mma(D[16 * ti + li][16 * kb + 4 * ks + lk], D[16 * tj + li][16 * kb + 4 * ks + lk],
+                     acc);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) D[16 * ti + M64::row(e, lk)][16 * tj + li] -= acc[e];
+  };
+#pragma unroll 1
+  for (int kb = 0; kb < 4; ++kb) {
+    const int b0 = 16 * kb;
+    if (w == 0) {
+      double f[16], u[16], piv = 1.0, g = 0.0;     // piv: pivot i in lane b0 + i
+#pragma unroll
+      for (int c = 0; c < 16; ++c) f[c] = lane >= b0 + c ? D[lane][b0 + c] : 0.0;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        // column i is left unscaled and enters the later ones as (f_i / d) f_i^T: the chain
+        // from pivot to pivot is one reciprocal (the hardware's estimate r, then
+        // r (1 + e + e^2), e = 1 - d r: full FP64 precision), a product and a
+        // subtraction; the square roots follow for all 16 at once.  Column i - 1's
+        // products for the columns after i are taken off meanwhile.
+        const double d = lane_value(f[i], b0 + i);
+        piv = lane == b0 + i ? d : piv;
+        double r = __builtin_amdgcn_rcp(d);
+        const double e = 1.0 - d * r;
+        r += r * (e + e * e);
+#pragma unroll
+        for (int c = i + 1; c < 16; ++c) {
+          if (i > 0) f[c] -= g * u[c];
+          u[c] = lane_value(f[i], b0 + c);
+        }
+        g = f[i] * r;
+        if (i < 15) f[i + 1] -= g * u[i + 1];
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      // 1 / sqrt: the hardware's estimate, then two Newton steps q <- q (3 - d q^2) / 2
+      const bool bad = !(piv > 0.0);
+      if (__any(bad) && lane == 0) atomicOr(err, 1);
+      if (bad) piv = 1.0;
+      double q = __builtin_amdgcn_rsq(piv);
+      q = q * (1.5 - 0.5 * piv * q * q);
+      q = q * (1.5 - 0.5 * piv * q * q);
+      const double dl = bad ? 1.0 : piv * q;
+      if (lane >= b0 && lane < b0 + 16) rd[lane] = q;
+#pragma unroll
+      for (int c = 0; c < 16; ++c) f[c] *= lane_value(q, b0 + c);
+      if (lane >= b0)
+#pragma unroll
+        for (int c = 0; c < 16; ++c)
+          D[lane][b0 + c] = lane > b0 + c ? f[c] : lane == b0 + c ? dl : 0.0;
+    } else if (w == 1) {
+      if (kb > 0) {
+        invert_tile(kb - 1);
+#pragma unroll 1
+        for (int j2 = 0; j2 < kb - 1; ++j2) {
+          row_sum(kb - 1, j2);
+          __builtin_amdgcn_wave_barrier();
+          row_inverse(kb - 1, j2);
+          __builtin_amdgcn_wave_barrier();
+        }
+        if (kb == 3)
+#pragma unroll 1
+          for (int j2 = 0; j2 < 3; ++j2) row_sum(3, j2);
+      }
+    } else if (kb > 0 && kb < 3) {
+      int id = w;                                  // dealt to waves 2 and 3 in turn
+      for (int tj = kb + 1; tj < 4; ++tj)
+        for (int ti = tj; ti < 4; ++ti, ++id)
+          if ((id & 1) == 0) tile_update(ti, tj, kb - 1);
+    }
+    if (kb == 3) break;
+    __syncthreads();
+    if (kb + 1 + w < 4) tile_update(kb + 1 + w, kb + 1, kb);
+    __syncthreads();
+  }
+  if (w == 0) invert_tile(3);
+  __syncthreads();
+  if (w < 3) row_inverse(3, w);
+  __syncthreads();
+  // the inverse first, then what nothing waits for in this launch
+  auto inverse = [&](int i, int l) {
+    return l > i ? 0.0 : (i >> 4) == (l >> 4) ? Wd[i >> 4][i & 15][l & 15] : Li[i][l];
+  };
+  double* it = inv + ((int64_t)j * GP + t) * NB * NB;
+#pragma unroll 4
+  for (int idx = threadIdx.x; idx < NB * NB; idx += CT)
+    co_store(it + idx, inverse(idx / NB, idx % NB));
+  chain_signal(fj + GP * t + t, epoch);
+  T* dj = dinv + P.boff + (int64_t)(r0 / NB) * NB * NB;
+#pragma unroll 4
+  for (int idx = threadIdx.x; idx < NB * NB; idx += CT) {
+    const int i = idx / NB, l = idx % NB;
+    dj[idx] = (T)inverse(i, l);
+    if (i < nb && l <= i && i - l <= B) base[at(r0 + i, r0 + l)] = (T)D[i][l];
+  }
+}
+
 template <class S>
 struct Chunk;                                     // reduction chunk: KC columns, LDS stride KS
 template <>
@@ -122,342 +500,12 @@ struct Chunk<float> {
   static constexpr int KC = 64, KS = 68;
 };
 
-// One launch per group for the group's own rows.  Work-group (p, j, t) owns the 64 rows
-// [c0 + 64 t, c0 + 64 t + 64) of panel p (columns [c0, c0 + 64), c0 = k0 + 64 p) of matrix
-// j; t = 0 is the diagonal block; blocks below the group (p + t >= GP) are k_far's and only
-// raise their flags.  Work-groups are numbered: panel 0's diagonal blocks (all matrices),
-// then panel by panel and matrix by matrix the blocks t >= 1, with the next panel's
-// diagonal block right after block t = 1 (the last one it needs), so that the next
-// factorisation runs while the rest of the panel is dispatched.  A work-group takes its number from a counter of the
-// launch when it starts, not from its position in the grid, so every wait is for a
-// work-group that is already running: the launch cannot deadlock, whatever order the
-// hardware dispatches its work-groups in and whatever else occupies the device.
-//   1. The block is brought up to date by this group's earlier panels (the earlier groups'
-//      updates are done before the launch): A -= L[rows][K] L[panel rows][K]^T, after
-//      waiting for the work-groups that produced them, with the matrix instruction in the
-//      factor's precision.
-//   2. t = 0: Cholesky of the 64x64 block and the inverse of its factor by one wave, in
-//      16-column blocks (step 2a below); the inverse is handed to the panel's other
-//      work-groups and kept for the triangular solves.
-//      t > 0: waits for the inverse and forms L[rows][panel] = A Li^T (FP64 instruction).
-//   3. The flag of (p, j, t) is raised.
-// A non-positive pivot raises bit 1 of the error word and is replaced by 1.
-template <class T>
-__global__ void __launch_bounds__(CT) k_chain(BandArgs a, T* v, int64_t kg, int NR, int n_mat,
-                                              int* flags, int* ticket, int epoch, double* inv,
-                                              T* dinv, int* err) {
-  typedef Mfma<T> MT;
-  typedef typename MT::S S;
-  constexpr int KC = Chunk<S>::KC, KS = Chunk<S>::KS;
-  constexpr int RP = CT / KC;                    // rows staged per pass
-  constexpr int PER = NB / RP;                   // staged entries per thread and operand
-  __shared__ double D[NB][NB + 1];               // the block; the factor (t = 0)
-  __shared__ double Li[NB][NB + 1];              // the inverse of the diagonal block
-  __shared__ double Wd[NB / 16][16][17];         // inverses of the 16x16 diagonal blocks
-  __shared__ double Tt[16][17];                  // one tile of the inverse's assembly
-  static_assert(NB * KS * sizeof(S) <= sizeof(D), "staging fits in the block buffers");
-  S* Pr = reinterpret_cast<S*>(&D[0][0]);        // staging of step 1 (aliases D and Li)
-  S* Ps = reinterpret_cast<S*>(&Li[0][0]);
-  int p, j, t;
-  {
-    __shared__ int tk;
-    if (threadIdx.x == 0) tk = atomicAdd(ticket, 1);
-    __syncthreads();
-    int b = tk;
-    if (b < n_mat || NR == 1) {                  // panel 0's diagonal blocks
-      p = b / n_mat;
-      j = b - p * n_mat;
-      t = 0;
-    } else {
-      b -= n_mat;
-      for (p = 0; p < GP; ++p) {                 // section of panel p
-        const int m = NR - 1 + (p + 1 < GP);
-        if (b < n_mat * m) break;
-        b -= n_mat * m;
-      }
-      j = b / (NR - 1 + (p + 1 < GP));
-      const int o = b - j * (NR - 1 + (p + 1 < GP));
-      if (o == 0) {
-        t = 1;
-      } else if (p + 1 < GP && o == 1) {         // the next panel's diagonal block
-        p += 1;
-        t = 0;
-      } else {
-        t = p + 1 < GP ? o : o + 1;
-      }
-    }
-  }
-  const int tr = p + t;                          // row block, counted from k0
-  const int NRT = NR + GP - 1;
-  int* fj = flags + (int64_t)j * GP * NRT;       // flag of (q, j, row block b): fj[q NRT + b]
-  const BandPart& P = a.part[j];
-  const int64_t n = P.rows, B = P.B, ld = P.ld;
-  const int64_t k0 = P.fb[a.phase] + kg, ce = P.fe[a.phase];
-  const int64_t c0 = k0 + (int64_t)NB * p, r0 = c0 + (int64_t)NB * t;
-  // no entries, or rows below the group (k_far's): only the flag
-  if (c0 >= ce || r0 >= n || r0 > c0 + NB - 1 + B || tr >= GP) {
-    if (threadIdx.x == 0) __hip_atomic_store(fj + p * NRT + tr, epoch, __ATOMIC_RELEASE,
-                                             __HIP_MEMORY_SCOPE_AGENT);
-    return;
-  }
-  T* base = v + P.off;
-  const int64_t rs = ld - 1;                     // entry (r, c) at r * rs + B + c
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int li = lane & 15, lk = lane >> 4;
-  const int wr = 32 * (w & 1), wc = 32 * (w >> 1);
-  const int kc_t = threadIdx.x % KC, i0 = threadIdx.x / KC;
-  // the block's entries, loaded now and used after step 1 (entries outside the matrix or
-  // the band read as 0; the diagonal block keeps its lower triangle)
-  const int nb = (int)min<int64_t>(NB, ce - c0); // columns of the panel inside the matrix
-  double av[2][4][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int jj = 0; jj < 2; ++jj) {
-        const int rl = wr + 16 * i + MT::row(q, lk), cl = wc + 16 * jj + li;
-        const int64_t r = r0 + rl, c = c0 + cl;
-        av[i][q][jj] = (r < n && cl < nb && c >= r - B && (t > 0 || cl <= rl))
-                           ? (double)base[r * rs + B + c] : 0.0;
-      }
-  // 1. A -= L[rows][K] L[panel rows][K]^T over this group's earlier panels K = [k0, c0),
-  // once the work-groups that produced them are done; the next chunk is fetched while
-  // the current one is multiplied
-  typename MT::V acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int jj = 0; jj < 2; ++jj) acc[i][jj] = typename MT::V{0, 0, 0, 0};
-  if (p > 0) {
-    if (threadIdx.x == 0)
-      for (int q = 0; q < p; ++q) {               // blocks past a panel's reach have none
-        if (tr - q < NR) chain_wait(fj + q * NRT + tr, epoch, err);
-        if (p - q < NR) chain_wait(fj + q * NRT + p, epoch, err);
-      }
-    __syncthreads();
-    // the first chunk with an entry inside the envelope of the block's rows
-    const int64_t lo = max(r0 - B, a.fcb[P.eoff + r0 / NB]);
-    const int64_t kstart = lo > k0 ? k0 + (lo - k0) / KC * KC : k0;
-    S xr[PER], xs[PER];
-    // 32-bit terms relative to the block: row i of a block is inside the matrix if
-    // i < lim, and panel column q (counted from k0) is inside the band of that row if
-    // q - i >= lo; rows' band origins are 32-bit offsets from the matrix start
-    const int lim_r = (int)min<int64_t>(n - r0, NB), lim_s = (int)min<int64_t>(n - c0, NB);
-    const int lo_r = (int)(r0 - B - k0), lo_s = (int)(c0 - B - k0), qend = (int)(c0 - k0);
-    const uint32_t or0 = (uint32_t)(min(r0 + i0, n - 1) * rs + B + k0 + kc_t);
-    const uint32_t os0 = (uint32_t)(min(c0 + i0, n - 1) * rs + B + k0 + kc_t);
-    const uint32_t ostep = (uint32_t)(RP * rs);
-    auto fetch = [&](int64_t kc) {
-      const int qq = (int)(kc - k0) + kc_t;
-      const uint32_t kd = (uint32_t)(kc - k0);
-#pragma unroll
-      for (int u = 0; u < PER; ++u) {
-        const int i = i0 + RP * u;
-        const bool okr = qq < qend && i < lim_r && qq - i >= lo_r;
-        const bool oks = qq < qend && i < lim_s && qq - i >= lo_s;
-        xr[u] = okr ? (S)co_load(base + (or0 + u * ostep + kd)) : (S)0;
-        xs[u] = oks ? (S)co_load(base + (os0 + u * ostep + kd)) : (S)0;
-      }
-    };
-    if (kstart < c0) fetch(kstart);
-    for (int64_t kc = kstart; kc < c0; kc += KC) {
-#pragma unroll
-      for (int u = 0; u < PER; ++u) {
-        Pr[(i0 + RP * u) * KS + kc_t] = xr[u];
-        Ps[(i0 + RP * u) * KS + kc_t] = xs[u];
-      }
-      __syncthreads();
-      if (kc + KC < c0) fetch(kc + KC);
-#pragma unroll
-      for (int k = 0; k < KC; k += 4) {
-        S fa[2], fb[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) fa[i] = Pr[(wr + 16 * i + li) * KS + k + lk];
-#pragma unroll
-        for (int jj = 0; jj < 2; ++jj) fb[jj] = Ps[(wc + 16 * jj + li) * KS + k + lk];
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int jj = 0; jj < 2; ++jj) acc[i][jj] = MT::mma(fa[i], fb[jj], acc[i][jj]);
-      }
-      __syncthreads();
-    }
-  }
-  // the updated block into D
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int jj = 0; jj < 2; ++jj) {
-        const int rl = wr + 16 * i + MT::row(q, lk), cl = wc + 16 * jj + li;
-        double x = av[i][q][jj] - (double)acc[i][jj][q];
-        if (t == 0 && rl == cl && rl >= nb) x = 1.0;       // padding of a short last panel
-        D[rl][cl] = x;
-      }
-  __syncthreads();
-  double* invj = inv + ((int64_t)j * GP + p) * NB * NB;
-  if (t == 0) {
-    // 2a. Cholesky of the diagonal block and its inverse, by wave 0 alone (no barriers), in
-    // 16-column blocks: the 16x16 diagonal block is factored in registers (lane r holds
-    // row r; pivots and column entries come from other lanes by reads of their registers)
-    // and inverted by forward substitution (lane c: column c); the panel below it is
-    // L = A W^T with W that inverse, and the trailing triangle takes -= L L^T, both as
-    // 16x16 tiles on the FP64 matrix instruction.  The inverse of the 64x64 factor is then
-    // built tile by tile: Li(i, i) = W_i, Li(i, j) = -W_i sum_{j <= k < i} L(i, k) Li(k, j).
-    if (w == 0) {
-      typedef Mfma<double> M64;
-      const int r16 = lane & 15;
-      for (int kb = 0; kb < 4; ++kb) {
-        const int b0 = 16 * kb;
-        double f[16], rdg[16];                     // rdg: reciprocals of the pivots
-#pragma unroll
-        for (int c = 0; c < 16; ++c) f[c] = c <= r16 ? D[b0 + r16][b0 + c] : 0.0;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const double dii = lane_value(f[i], i);
-          const bool ok = dii > 0.0;
-          if (!ok && lane == 0) atomicOr(err, 1);
-          // 1 / sqrt(dii): the hardware estimate, then two Newton steps
-          // r <- r (3 - dii r^2) / 2, which bring it to full FP64 precision
-          double r = 1.0;
-          if (ok) {
-            r = __builtin_amdgcn_rsq(dii);
-            r = r * (1.5 - 0.5 * dii * r * r);
-            r = r * (1.5 - 0.5 * dii * r * r);
-          }
-          rdg[i] = r;
-          f[i] = r16 == i ? (ok ? dii * r : 1.0) : f[i] * r;
-#pragma unroll
-          for (int s2 = i + 1; s2 < 16; ++s2) f[s2] -= f[i] * lane_value(f[i], s2);
-        }
-        if (lane < 16)
-#pragma unroll
-          for (int c = 0; c < 16; ++c) D[b0 + r16][b0 + c] = c <= r16 ? f[c] : 0.0;
-        double xi[16];                             // column r16 of the block's inverse
-        // (the factor's entries L(i, k) are read back from LDS, the same address in every
-        // lane, rather than from lane i's registers: they do not depend on xi, so the
-        // reads are issued ahead, and they take no scalar registers)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          double sum = i == r16 ? 1.0 : 0.0;
-#pragma unroll
-          for (int k = 0; k < i; ++k) sum -= D[b0 + i][b0 + k] * xi[k];
-          xi[i] = sum * rdg[i];
-        }
-        if (lane < 16)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) Wd[kb][i][r16] = xi[i];
-        for (int ti = kb + 1; ti < 4; ++ti) {      // panel tiles: L = A W^T
-          v4d acc = v4d{0, 0, 0, 0};
-#pragma unroll
-          for (int ks = 0; ks < 4; ++ks)
-            acc = M64::mma(D[16 * ti + li][b0 + 4 * ks + lk], Wd[kb][li][4 * ks + lk], acc);
-#pragma unroll
-          for (int q = 0; q < 4; ++q) D[16 * ti + M64::row(q, lk)][b0 + li] = acc[q];
-        }
-        for (int tj = kb + 1; tj < 4; ++tj)        // trailing tiles: -= L L^T
-          for (int ti = tj; ti < 4; ++ti) {
-            v4d acc = v4d{0, 0, 0, 0};
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks)
-              acc = M64::mma(D[16 * ti + li][b0 + 4 * ks + lk], D[16 * tj + li][b0 + 4 * ks + lk],
-                             acc);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) D[16 * ti + M64::row(q, lk)][16 * tj + li] -= acc[q];
-          }
-      }
-      // Li is assembled below the diagonal tiles only: its diagonal tiles are the W_i (read
-      // from Wd) and it is zero above them
-      for (int dd = 1; dd < 4; ++dd)
-        for (int ti = dd; ti < 4; ++ti) {
-          const int tj = ti - dd;
-          v4d acc = v4d{0, 0, 0, 0};
-#pragma unroll
-          for (int ks = 0; ks < 4; ++ks)              // kt = tj: Li(tj, tj) = W_tj
-            acc = M64::mma(D[16 * ti + li][16 * tj + 4 * ks + lk], Wd[tj][4 * ks + lk][li], acc);
-          for (int kt = tj + 1; kt < ti; ++kt)
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks)
-              acc = M64::mma(D[16 * ti + li][16 * kt + 4 * ks + lk],
-                             Li[16 * kt + 4 * ks + lk][16 * tj + li], acc);
-#pragma unroll
-          for (int q = 0; q < 4; ++q) Tt[M64::row(q, lk)][li] = acc[q];
-          v4d o = v4d{0, 0, 0, 0};
-#pragma unroll
-          for (int ks = 0; ks < 4; ++ks)
-            o = M64::mma(Wd[ti][li][4 * ks + lk], Tt[4 * ks + lk][li], o);
-#pragma unroll
-          for (int q = 0; q < 4; ++q) Li[16 * ti + M64::row(q, lk)][16 * tj + li] = -o[q];
-        }
-    }
-    __syncthreads();
-    T* dj = dinv + P.boff + (c0 / NB) * NB * NB;
-    for (int idx = threadIdx.x; idx < NB * NB; idx += CT) {
-      const int i = idx / NB, l = idx % NB;
-      const double lv = (i >> 4) > (l >> 4)    ? Li[i][l]
-                        : (i >> 4) == (l >> 4) ? Wd[i >> 4][i & 15][l & 15]
-                                               : 0.0;
-      co_store(invj + idx, lv);
-      dj[idx] = (T)lv;
-      if (i < nb && l <= i && i - l <= B) base[(c0 + i) * rs + B + c0 + l] = (T)D[i][l];
-    }
-  } else {
-    // 2b. L[rows][panel] = A Li^T with the inverse of the diagonal block
-    if (threadIdx.x == 0) chain_wait(fj + p * NRT + p, epoch, err);
-    __syncthreads();
-    {
-      double lv[NB * NB / CT];                   // all loads issued before any is used
-#pragma unroll
-      for (int u = 0; u < NB * NB / CT; ++u) lv[u] = co_load(invj + threadIdx.x + CT * u);
-#pragma unroll
-      for (int u = 0; u < NB * NB / CT; ++u) {
-        const int idx = threadIdx.x + CT * u;
-        Li[idx / NB][idx % NB] = lv[u];
-      }
-    }
-    __syncthreads();
-    v4d x[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int jj = 0; jj < 2; ++jj) x[i][jj] = v4d{0, 0, 0, 0};
-#pragma unroll 4
-    for (int k = 0; k < NB; k += 4) {
-      double fa[2], fb[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) fa[i] = D[wr + 16 * i + li][k + lk];
-#pragma unroll
-      for (int jj = 0; jj < 2; ++jj) fb[jj] = Li[wc + 16 * jj + li][k + lk];
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int jj = 0; jj < 2; ++jj) x[i][jj] = Mfma<double>::mma(fa[i], fb[jj], x[i][jj]);
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int jj = 0; jj < 2; ++jj) {
-          const int rl = wr + 16 * i + Mfma<double>::row(q, lk), cl = wc + 16 * jj + li;
-          const int64_t r = r0 + rl, c = c0 + cl;
-          if (r < n && cl < nb && c >= r - B) co_store(base + r * rs + B + c, (T)x[i][jj][q]);
-        }
-  }
-  // 3.
-  chain_signal(fj + p * NRT + tr, epoch);
-}
-
 // The rows below a group (row blocks GP, GP + 1, .. counted from k0) for all of the
 // group's panels, once k_chain has factored the group's own rows: work-group (j, f) owns
-// the 64 rows [k0 + 64 (GP + f), + 64) of matrix j and takes the panels in turn, each as
-// k_chain's steps 1 and 2 for a block t > 0 - the update by the group's earlier panels
-// (from its own results and the group's rows), then the product with the inverse of the
-// panel's diagonal block.  Everything it reads was written by earlier launches or by
-// itself, so nothing is waited for and plain loads suffice; the products are the same,
-// in the same order, as k_chain's.
+// the 64 rows [k0 + 64 (GP + f), + 64) of matrix j and takes the panels in turn: the update
+// by the group's earlier panels (from its own results and the group's rows), then the product
+// with the inverse of the panel's diagonal block.  Everything it reads was written by earlier
+// launches or by itself, so nothing is waited for and plain loads suffice.
 template <class T>
 __global__ void __launch_bounds__(CT, 2) k_far(BandArgs a, T* v, int64_t kg, int NF, int n_mat,
                                                const double* inv) {
@@ -824,9 +872,7 @@ void band_factor_t(BandSet& bs, T* v, T* dinv, hipStream_t st, FactorJob& job, b
     GX_REQUIRE((p.rows + T2) * p.ld + 64 < ((int64_t)1 << 31),
                "a band matrix of 2^31 entries or more exceeds the update's 32-bit offsets");
   const int NR = (int)((bs.max_B + NB - 1) / NB) + 1;   // row blocks of a panel
-  // k_chain takes the group's own rows (GP row blocks per panel, those below the group
-  // exit at once), k_far the NF row blocks below the group
-  const int NRC = GP, NRT = NRC + GP - 1, NF = NR - 1;
+  const int NF = NR - 1;                          // row blocks below a group: k_far's
   const int n_part = bs.n_part, n_mat = bs.n_mat;
   job.inv.alloc((size_t)n_part * GP * NB * NB);
   // columns of the longest part in each phase, and the largest separator
@@ -837,13 +883,13 @@ void band_factor_t(BandSet& bs, T* v, T* dinv, hipStream_t st, FactorJob& job, b
   }
   int64_t n_groups = 0;
   for (int h = 0; h < 2; ++h) n_groups += (span[h] + GP * NB - 1) / (GP * NB);
-  job.flags.alloc((size_t)n_part * GP * NRT + n_groups);   // then one ticket counter per launch
+  job.flags.alloc((size_t)n_part * GP * GP + n_groups);   // then one ticket counter per launch
   zero(job.flags, st);
-  int* tickets = job.flags.p + (int64_t)n_part * GP * NRT;
+  int* tickets = job.flags.p + (int64_t)n_part * GP * GP;
   const int64_t nt2 = (bs.max_B + T2 - 1) / T2;
   const int64_t per_rest = wide_tiles(bs.max_B, NEXT_TS, nt2), tot_rest = per_rest * n_part;
   const int64_t per_next = wide_tiles(bs.max_B, 0, NEXT_TS), tot_next = per_next * n_part;
-  const unsigned chain_blocks = (unsigned)((int64_t)GP * n_part * NRC);
+  const unsigned chain_blocks = (unsigned)((int64_t)GP * n_part);
   const unsigned far_blocks = (unsigned)((int64_t)n_part * NF);
   // group g on st: the update of its columns by group g - 1 (after the update of the same
   // columns by group g - 2, which ran on the second stream), then its k_chain and k_far;
@@ -880,7 +926,7 @@ void band_factor_t(BandSet& bs, T* v, T* dinv, hipStream_t st, FactorJob& job, b
                              k0 - GP * NB, (int64_t)GP * NB, (int64_t)0, NEXT_TS, per_next,
                              tot_next);
         if (last) break;
-        hipLaunchKernelGGL(k_chain<T>, dim3(chain_blocks), dim3(CT), 0, st, a, v, k0, NRC,
+        hipLaunchKernelGGL(k_chain<T>, dim3(chain_blocks), dim3(CT), 0, st, a, v, k0,
                            n_part, flags, tickets + g, g + 1, inv, dinv, err);
         if (far_blocks)
           hipLaunchKernelGGL(k_far<T>, dim3(far_blocks), dim3(CT), 0, st, a, v, k0, NF, n_part,

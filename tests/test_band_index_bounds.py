@@ -325,3 +325,26 @@ def test_factorisation_waits_are_for_earlier_numbers(n_mat, NR):
         for f in _chain_waits(p, j, t, NR):
             assert f in raised, (b, f)
             assert raised[f] < b, (b, (p, j, t), f, raised[f])
+
+
+@pytest.mark.parametrize("n_mat,B", [(1, 0), (3, 16), (2, 63), (5, 128), (64, 512), (4096, 200)])
+def test_row_block_waits_are_for_earlier_numbers(n_mat, B):
+    """k_chain with a work-group per 64-row block: numbers go row block by row block, and a
+    block (m, q) that another row block t > m waits for (the inverse (q, q), or (m, q) with
+    q < m < t) is not empty, so its flag is raised, by a work-group with a lower number."""
+    def number(t, j):
+        return t * n_mat + j
+
+    def reach(t, q):
+        return 64 * (t - q) <= 63 + B
+
+    for j in {0, n_mat // 2, n_mat - 1}:
+        for t in range(GP):
+            for q in range(t):
+                if not reach(t, q):
+                    continue
+                waits = [(q, q)] + [(m, q) for m in range(q + 1, t) if reach(m, q)]
+                # A(t, m) takes L(t, q) L(m, q)^T for every m between: none is left out
+                assert [m for m, _ in waits[1:]] == list(range(q + 1, t))
+                for m, _ in waits:
+                    assert reach(m, q) and number(m, j) < number(t, j)
