@@ -78,6 +78,17 @@ constexpr int GP = 4;                             // panels per group
 constexpr int CT = 256;                           // threads of a panel work-group
 constexpr int64_t SPIN_LIMIT = (int64_t)1 << 22;  // polls before a wait gives up
 
+// Counters, flags and error words that the next launch takes its numbers from or polls are
+// cleared by a kernel, ordered on the stream like the launches themselves.
+__global__ void k_clear(int* p, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) p[i] = 0;
+}
+static void clear(DevBuf<int>& b, hipStream_t st) {
+  hipLaunchKernelGGL(k_clear, dim3(nblocks((int64_t)b.n, 256)), dim3(256), 0, st, b.p,
+                     (int64_t)b.n);
+}
+
 // Loads and stores of data handed between the work-groups of one launch: agent-scope
 // relaxed atomics, which bypass the per-XCD caches, so a reader sees the writer's values
 // without a cache flush or invalidate on either side.
@@ -884,7 +895,7 @@ void band_factor_t(BandSet& bs, T* v, T* dinv, hipStream_t st, FactorJob& job, b
   int64_t n_groups = 0;
   for (int h = 0; h < 2; ++h) n_groups += (span[h] + GP * NB - 1) / (GP * NB);
   job.flags.alloc((size_t)n_part * GP * GP + n_groups);   // then one ticket counter per launch
-  zero(job.flags, st);
+  clear(job.flags, st);
   int* tickets = job.flags.p + (int64_t)n_part * GP * GP;
   const int64_t nt2 = (bs.max_B + T2 - 1) / T2;
   const int64_t per_rest = wide_tiles(bs.max_B, NEXT_TS, nt2), tot_rest = per_rest * n_part;
@@ -984,7 +995,7 @@ void band_factor_start(BandSet& bs, hipStream_t st, hipStream_t la, FactorJob& j
   job.la = la;
   job.what = what;
   job.err.alloc(1);
-  zero(job.err, st);
+  clear(job.err, st);
   if (bs.fp32)
     band_factor_t<float>(bs, bs.v32.p, bs.dinv32.p, st, job, threaded);
   else
@@ -2099,7 +2110,7 @@ void band_link(BandSet& bs, hipStream_t st) {
 static int* solve_err(BandSet& bs, hipStream_t st) {
   if (!bs.err.n) {
     bs.err.alloc(1 + 8);
-    zero(bs.err, st);
+    clear(bs.err, st);
   }
   return bs.err.p;
 }
@@ -2408,7 +2419,7 @@ void multi_solve_plan(MultiSolve& m, const std::vector<BandSet*>& sets,
   to_dev(m.work.p, wl.data(), wl.size(), st);
   if (!m.err.n) {
     m.err.alloc(1 + 8);
-    zero(m.err, st);
+    clear(m.err, st);
   }
   GX_HIP(hipStreamSynchronize(st));                // wl and host are read by the copies
 }
@@ -2436,7 +2447,7 @@ void multi_solve_check(MultiSolve& m, hipStream_t st) {
   int h = 0;
   to_host(&h, m.err.p, 1, st);
   if (h) {
-    zero(m.err, st);
+    clear(m.err, st);
     throw Error(GX_EHIP, "banded solve: a work-group timed out waiting for a block");
   }
 }
@@ -2447,7 +2458,7 @@ void band_solve_check(BandSet& bs, hipStream_t st) {
   int h = 0;
   to_host(&h, bs.err.p, 1, st);
   if (h) {
-    zero(bs.err, st);
+    clear(bs.err, st);
     throw Error(GX_EHIP, "banded solve: a work-group timed out waiting for a block");
   }
 }
