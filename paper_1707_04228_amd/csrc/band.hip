@@ -2039,8 +2039,11 @@ __global__ void __launch_bounds__(MT) k_band_solve_m(
 }
 
 // Work-groups per part: as many as keep every work-group of the launch resident at once (a
-// part waits at the pace of its slowest group); at most GMAX for one right-hand side, 8 for
-// several.  A matrix's work-groups run on one XCD (set_place), so it is the parts on the
+// part waits at the pace of its slowest group); at most GMAX for one right-hand side.  For
+// several a group has B / 64 chunks per block, 2 to 3 us each, and the chain passes a block in
+// about 7 us, so B / 128 groups (8 at least) keep up with it and more only poll: with 16 in place of
+// 8 groups 5 matrices of n = 45,000, B = 2,080 (FP32) 5.60 -> 3.92 ms, but 6 of 16,000, 1,020
+// 1.92 -> 1.98 and 4 of 3,500, 370 0.51 -> 0.53 ms.  A matrix's work-groups run on one XCD (set_place), so it is the parts on the
 // fullest XCD that are counted, against its eighth of the machine: counted together, 14
 // matrices of 24 parts would put 40 work-groups on an XCD's 32 slots.  The solves of one
 // context are stream-ordered, so a launch may count on the whole machine.  When several
@@ -2061,7 +2064,8 @@ static int solve_groups(BandSet& bs, const void* kernel, int which) {
   for (const BandPart& p : bs.part) ++parts[p.mat & 7];
   int64_t most = *std::max_element(parts.begin(), parts.end()) * std::max(bs.share, 1);
   if (bs.together > 0) most = std::min<int64_t>(most, bs.together);
-  const int cap = which == 0 ? GMAX : 8;
+  const int cap = which == 0 ? GMAX
+                             : (int)std::min<int64_t>(GMAX, std::max<int64_t>(8, bs.max_B / 128));
   int G = 1;
   const int top = bs.force_groups[which] > 0 ? std::min(bs.force_groups[which], cap) : cap;
   for (int c = top; c >= 2; --c)
