@@ -1086,6 +1086,9 @@ void band_factor(gx_ctx* c, BandSet& bs, hipStream_t st, const char* what) {
 // 5.65 ms.  64 of those fill the device with one group per compute unit and stay where they
 // were (118 GB in 22 to 23 ms, FP32 59 GB in 12.9 ms).
 constexpr int SW = SOLVE_THREADS / 64;           // waves per work-group (8)
+constexpr int CL = 32;                            // words from one place counter to the next
+                                                  // (and to the error word): a line of its
+                                                  // own for each XCD
 constexpr int RPW = SB / SW;                      // forward rows per wave (8)
 constexpr int GMAX = 16;                          // work-groups per part, 1-RHS solve
 constexpr int FL = 3;                             // blocks in flight taken at a time
@@ -1663,7 +1666,7 @@ __device__ inline V uniform_load(const V* p) {
 // XCD (j + xcd0) mod 8; part -1: none
 __device__ inline int2 set_place(const int32_t* part_of, int n_mat, int G, int PP, int xcd0,
                                  int* counters) {
-  const int x = (blockIdx.x - xcd0) & 7, q = take_place(counters + x);
+  const int x = (blockIdx.x - xcd0) & 7, q = take_place(counters + CL * x);
   const int j = q / (G * PP) * 8 + x, m = q % (G * PP);
   if (j >= n_mat) return {-1, 0};
   return {uniform_load(part_of + 2 * j + m % PP), m / PP};
@@ -1675,7 +1678,7 @@ __global__ void __launch_bounds__(SOLVE_THREADS) k_band_solve_1(
     BandArgs a, const int32_t* part_of, const T* v, const T* dinv, const T* link,
     const int64_t* xoff, const double* xall, double* yall, double* zall, int G, int PP, int xcd0, int n_mat,
     int* err) {
-  const int2 pg = set_place(part_of, n_mat, G, PP, xcd0, err + 1);
+  const int2 pg = set_place(part_of, n_mat, G, PP, xcd0, err + CL);
   if (pg.x < 0) return;
   auto load = [&](int i) -> Solve1<T> {
     const BandPart P = uniform_load(a.part + i);
@@ -1703,7 +1706,7 @@ __global__ void __launch_bounds__(SOLVE_THREADS) k_band_solve_1_multi(const Band
                                                                        const int32_t* __restrict__ work,
                                                                        int n_class, int* err) {
   const int x = blockIdx.x % n_class;
-  const int i = take_place(err + 1 + x) * n_class + x;
+  const int i = take_place(err + CL * (1 + x)) * n_class + x;
   const int j = uniform_load(work + 2 * i), g = uniform_load(work + 2 * i + 1);
   if (j < 0) return;
   auto load = [&](int p) -> Solve1<T> {
@@ -1722,7 +1725,7 @@ __global__ void __launch_bounds__(SOLVE_THREADS) k_band_solve_1_multi(const Band
 __global__ void k_fill_mark_multi(const BandPtrs* tab, int* counters) {
   const BandPtrs t = tab[blockIdx.y];
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (blockIdx.y == 0 && i < 8) counters[i] = 0;
+  if (blockIdx.y == 0 && i < 8) counters[CL * i] = 0;
   if (i < (t.n + SB - 1) / SB * SB) {
     t.y[i] = __longlong_as_double((long long)YMARK);
     t.z[i] = __longlong_as_double((long long)YMARK);
@@ -1770,7 +1773,7 @@ __global__ void __launch_bounds__(MT) k_band_solve_m(
   constexpr int YL = SB * M / MT;                 // solution-chunk entries per thread
   __shared__ S Ab[2][SB][SB + 1];                 // band chunks (double buffer); buffer 0
   __shared__ S Yc[2][SB * MP];                    // holds the inverse block in finish
-  const int2 pg = set_place(part_of, n_mat, G, PP, xcd0, err + 1);
+  const int2 pg = set_place(part_of, n_mat, G, PP, xcd0, err + CL);
   const int g = pg.y;
   if (pg.x < 0) return;
   int64_t n, B, rs, n1, ncb, sep;                 // n1: last row of the matrix; ncb: blocks
@@ -2113,7 +2116,7 @@ void band_link(BandSet& bs, hipStream_t st) {
 // the counters of take_place follow it
 static int* solve_err(BandSet& bs, hipStream_t st) {
   if (!bs.err.n) {
-    bs.err.alloc(1 + 8);
+    bs.err.alloc(CL * (1 + 8));
     clear(bs.err, st);
   }
   return bs.err.p;
@@ -2125,7 +2128,7 @@ static unsigned solve_grid(const BandSet& bs, int G) {
 
 __global__ void k_fill_mark(double* p, int64_t n, int* counters) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < 8) counters[i] = 0;
+  if (i < 8) counters[CL * i] = 0;
   if (i < n) p[i] = __longlong_as_double((long long)YMARK);
 }
 
@@ -2139,7 +2142,7 @@ static void alloc_solve1_scratch(BandSet& bs) {
 static double* solve1_scratch(BandSet& bs, hipStream_t st) {
   alloc_solve1_scratch(bs);
   hipLaunchKernelGGL(k_fill_mark, dim3(nblocks((int64_t)bs.ybuf.n, 256)), dim3(256), 0, st,
-                     bs.ybuf.p, (int64_t)bs.ybuf.n, solve_err(bs, st) + 1);
+                     bs.ybuf.p, (int64_t)bs.ybuf.n, solve_err(bs, st) + CL);
   return bs.ybuf.p;
 }
 
@@ -2158,7 +2161,7 @@ __global__ void k_copy_out(const BandPart* part, const int64_t* xoff, int w, con
 
 __global__ void k_fill_mark32(float* p, int64_t n, int* counters) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < 8) counters[i] = 0;
+  if (i < 8) counters[CL * i] = 0;
   if (i < n) p[i] = __uint_as_float(YMARK32);
 }
 
@@ -2177,7 +2180,7 @@ static void launch_m(BandSet& bs, const BandArgs& a, const int64_t* d_xoff, doub
     float* y = reinterpret_cast<float*>(bs.mbuf.p);
     float* z = y + rows * M;
     hipLaunchKernelGGL(k_fill_mark32, dim3(nblocks(2 * rows * M, 256)), dim3(256), 0, st, y,
-                       2 * rows * M, err + 1);
+                       2 * rows * M, err + CL);
     hipLaunchKernelGGL((k_band_solve_m<float, M>), dim3(solve_grid(bs, G)), dim3(MT), 0, st, a,
                        bs.d_part_of.p, bs.v32.p, bs.dinv32.p, d_xoff, x, y, z, G, PP, bs.xcd0, bs.n_mat,
                        active, err);
@@ -2187,7 +2190,7 @@ static void launch_m(BandSet& bs, const BandArgs& a, const int64_t* d_xoff, doub
     double* y = bs.mbuf.p;
     double* z = bs.mbuf.p + rows * M;
     hipLaunchKernelGGL(k_fill_mark, dim3(nblocks(2 * rows * M, 256)), dim3(256), 0, st, y,
-                       2 * rows * M, err + 1);
+                       2 * rows * M, err + CL);
     hipLaunchKernelGGL((k_band_solve_m<double, M>), dim3(solve_grid(bs, G)), dim3(MT), 0, st, a,
                        bs.d_part_of.p, bs.v64.p, bs.dinv64.p, d_xoff, x, y, z, G, PP, bs.xcd0, bs.n_mat,
                        active, err);
@@ -2422,7 +2425,7 @@ void multi_solve_plan(MultiSolve& m, const std::vector<BandSet*>& sets,
   if (m.work.n < wl.size()) m.work.alloc(wl.size());
   to_dev(m.work.p, wl.data(), wl.size(), st);
   if (!m.err.n) {
-    m.err.alloc(1 + 8);
+    m.err.alloc(CL * (1 + 8));
     clear(m.err, st);
   }
   GX_HIP(hipStreamSynchronize(st));                // wl and host are read by the copies
@@ -2433,7 +2436,7 @@ void multi_solve(MultiSolve& m, hipStream_t st) {
   GX_REQUIRE(m.n_part > 0, "multi-set solve: no table");
   const unsigned nm = (unsigned)m.n_part;
   hipLaunchKernelGGL(k_fill_mark_multi, dim3(nblocks((m.max_n + SB - 1) / SB * SB, 256), nm),
-                     dim3(256), 0, st, m.tab.p, m.err.p + 1);
+                     dim3(256), 0, st, m.tab.p, m.err.p + CL);
   if (m.fp32)
     hipLaunchKernelGGL(k_band_solve_1_multi<float>, dim3((unsigned)m.n_wg), dim3(SOLVE_THREADS),
                        0, st, m.tab.p, m.work.p, m.n_class, m.err.p);
