@@ -1756,6 +1756,14 @@ __global__ void k_copy_out_multi(const BandPtrs* tab) {
 // chunk reads): solution entries are loaded with agent-scope relaxed atomics, and a chunk
 // is staged only once none of the entries it needs is a marker (a chunk still in flight
 // is polled again until then).
+// What bounds it: the latency of a chunk's stages (2.9 us with one work-group per compute
+// unit; leaving out the solution rows, the band or the products takes about a quarter off
+// each), and for narrow bands the hand-overs.  So what a block needs besides its chunks, its
+// right-hand side and its inverse block, is loaded before the sweep and waits in registers
+// and in LDS buffers of its own: per solve of 32 columns, 8 matrices of n = 3,500, B = 370
+// 0.51 -> 0.46 ms, 6 of 16,000, 1,020 1.92 -> 1.66, 16 of 91,000, 1,630 18.7 -> 17.4 and, FP32, 5 of
+// 45,000, 2,080 3.92 -> 3.25 ms.  (Half the waves with the band straight in registers, no LDS
+// for it: 2.11 and 21.1 ms in the second and third.)
 constexpr int MC = 32;                            // right-hand sides per launch, at most
 constexpr int MT = 512;                           // threads per work-group
 constexpr int AL = SB * SB / MT;                  // band-chunk entries per thread (8)
@@ -1771,12 +1779,12 @@ __global__ void __launch_bounds__(MT) k_band_solve_m(
   constexpr int NCT = (M + 15) / 16;              // column tiles (1 or 2)
   constexpr int MP = 16 * NCT;                    // LDS row stride (zero columns past M)
   constexpr int YL = SB * M / MT;                 // solution-chunk entries per thread
-  __shared__ S Ab[2][SB][SB + 1];                 // band chunks (double buffer); buffer 0
-  __shared__ S Yc[2][SB * MP];                    // holds the inverse block in finish
+  __shared__ S Ab[3][SB][SB + 1];                 // band chunks (double buffer), and the
+  __shared__ S Yc[3][SB * MP];                    // inverse block and its right-hand side
   const int2 pg = set_place(part_of, n_mat, G, PP, xcd0, err + CL);
   const int g = pg.y;
   if (pg.x < 0) return;
-  int64_t n, B, rs, n1, ncb, sep;                 // n1: last row of the matrix; ncb: blocks
+  int n, B, rs, n1, ncb, sep;                     // n1: last row of the matrix; ncb: blocks
   const T *cb, *dv;                               // with columns of their own
   const int64_t *fcb, *lrb;
   const double* x;
@@ -1787,9 +1795,9 @@ __global__ void __launch_bounds__(MT) k_band_solve_m(
   if (active && !uniform_load(active + mat)) return;
   auto use = [&](int part) {
     const BandPart P = uniform_load(a.part + part);
-    n = P.rows, B = P.B, rs = P.ld - 1, n1 = P.N - 1;
-    ncb = (P.cols + SB - 1) / SB;
-    sep = P.kind == PART_UPPER ? P.sep : P.rows;
+    n = (int)P.rows, B = (int)P.B, rs = (int)P.ld - 1, n1 = (int)P.N - 1;
+    ncb = (int)(P.cols + SB - 1) / SB;            // (a part has less than 2^31 entries)
+    sep = (int)(P.kind == PART_UPPER ? P.sep : P.rows);
     lower = P.kind == PART_LOWER;
     cb = v + P.off + B;                           // entry (r, c) = cb[r * rs + c]
     dv = dinv + P.boff;
@@ -1812,7 +1820,7 @@ __global__ void __launch_bounds__(MT) k_band_solve_m(
   const bool tile = ct < NCT;                      // waves past the column tiles only stage
   const int li = lane & 15, lk = lane >> 4;
   if constexpr (MP > M)
-    for (int idx = threadIdx.x; idx < 2 * SB * (MP - M); idx += MT) {
+    for (int idx = threadIdx.x; idx < 3 * SB * (MP - M); idx += MT) {
       const int e = idx % (SB * (MP - M));
       Yc[idx / (SB * (MP - M))][(e / (MP - M)) * MP + M + e % (MP - M)] = (S)0;
     }
@@ -1821,54 +1829,54 @@ __global__ void __launch_bounds__(MT) k_band_solve_m(
   // rows t / 64 + 8 u at column t % 64.
   // entry idx of the solution rows of chunk kk: the part's own, or the separator's from the
   // upper part's backward solutions
-  auto sol = [&](bool bwd, int64_t kk, int64_t idx) -> const Y* {
-    if (bwd && kk >= ncb) return mate + (n1 - kk * SB - idx / M) * M + idx % M;
-    return (bwd ? z : y) + kk * SB * M + idx;
+  auto sol = [&](bool bwd, int kk, int idx) -> const Y* {
+    if (bwd && kk >= ncb) return mate + ((int64_t)(n1 - kk * SB - idx / M) * M + idx % M);
+    return (bwd ? z : y) + (int64_t)(kk * SB) * M + (uint32_t)idx;
   };
-  auto fetch = [&](bool bwd, int64_t i0, int64_t kk, T (&fa)[AL], Y (&fy)[YL]) {
-    const int64_t r0 = (bwd ? kk * SB : i0) + wave;
-    const int64_t c = (bwd ? i0 : kk * SB) + lane;
+  auto fetch = [&](bool bwd, int i0, int kk, T (&fa)[AL], Y (&fy)[YL]) {
+    const int r0 = (bwd ? kk * SB : i0) + wave;
+    const int c = (bwd ? i0 : kk * SB) + lane;
 #pragma unroll
-    for (int u = 0; u < AL; ++u) fa[u] = cb[min<int64_t>(r0 + 8 * u, n - 1) * rs + c];
-    const int64_t yend = min<int64_t>((int64_t)SB * M, (n - kk * SB) * M);   // rows < n
+    for (int u = 0; u < AL; ++u) fa[u] = cb[min(r0 + 8 * u, n - 1) * rs + c];
+    const int yend = min(SB, n - kk * SB) * M;   // rows < n
 #pragma unroll
     for (int u = 0; u < YL; ++u)
-      fy[u] = poll_load(sol(bwd, kk, min<int64_t>(threadIdx.x + MT * u, yend - 1)));
+      fy[u] = poll_load(sol(bwd, kk, min((int)threadIdx.x + MT * u, yend - 1)));
   };
-  auto stage = [&](int buf, bool bwd, int64_t i0, int nb, int64_t kk, const T (&fa)[AL],
+  auto stage = [&](int buf, bool bwd, int i0, int nb, int kk, const T (&fa)[AL],
                    Y (&fy)[YL]) {
     {                                              // until every needed entry is handed over
-      const int64_t yend = min<int64_t>((int64_t)SB * M, (n - kk * SB) * M);
+      const int yend = min(SB, n - kk * SB) * M;
       // the first test on the values already loaded is straight-line code, so the wait
       // before it covers only this chunk's loads, not the prefetch of the next one; the
       // polling loop is the slow path of a chunk still in flight
       bool ok = true;
 #pragma unroll
-      for (int u = 0; u < YL; ++u) ok = ok && (threadIdx.x + MT * u >= yend || !is_mark(fy[u]));
+      for (int u = 0; u < YL; ++u) ok = ok && ((int)threadIdx.x + MT * u >= yend || !is_mark(fy[u]));
       if (!__all(ok)) {
         int64_t spins = 0;
         for (;;) {
           if (poll_give_up(spins, err)) break;
 #pragma unroll
           for (int u = 0; u < YL; ++u)
-            fy[u] = poll_load(sol(bwd, kk, min<int64_t>(threadIdx.x + MT * u, yend - 1)));
+            fy[u] = poll_load(sol(bwd, kk, min((int)threadIdx.x + MT * u, yend - 1)));
           bool again = false;
 #pragma unroll
           for (int u = 0; u < YL; ++u)
-            again = again || (threadIdx.x + MT * u < yend && is_mark(fy[u]));
+            again = again || ((int)threadIdx.x + MT * u < yend && is_mark(fy[u]));
           if (!__any(again)) break;
         }
       }
     }
-    const int64_t r0 = (bwd ? kk * SB : i0) + wave;
-    const int64_t c = (bwd ? i0 : kk * SB) + lane;
+    const int r0 = (bwd ? kk * SB : i0) + wave;
+    const int c = (bwd ? i0 : kk * SB) + lane;
 #pragma unroll
     for (int u = 0; u < AL; ++u) {
-      const int64_t r = r0 + 8 * u;
+      const int r = r0 + 8 * u;
       const bool in = r < n && c <= r && c >= r - B && (!bwd || lane < nb);
       Ab[buf][wave + 8 * u][lane] = in ? (S)fa[u] : (S)0;
     }
-    const int64_t yend = min<int64_t>((int64_t)SB * M, (n - kk * SB) * M);   // rows < n
+    const int yend = min(SB, n - kk * SB) * M;   // rows < n
 #pragma unroll
     for (int u = 0; u < YL; ++u) {
       const int idx = threadIdx.x + MT * u;
@@ -1898,24 +1906,38 @@ __global__ void __launch_bounds__(MT) k_band_solve_m(
   // chunk q + 1 into the other buffer right after its product of chunk q, so one barrier
   // per chunk separates the staging of a buffer from its readers (the product two chunks
   // back, and the next product)
-  auto sweep = [&](bool bwd, int64_t i0, int nb, int64_t first, int64_t count, int step,
+  // (dd, the block's inverse diagonal block, arrives meanwhile and goes to LDS after the first
+  // product)
+  auto keep = [&](const T (&dd)[AL]) {
+#pragma unroll
+    for (int u = 0; u < AL; ++u) {
+      const int idx = threadIdx.x + MT * u;
+      Ab[2][idx >> 6][idx & 63] = (S)dd[u];
+    }
+  };
+  auto sweep = [&](bool bwd, int i0, int nb, int first, int count, int step, const T (&dd)[AL],
                    typename MF::V& acc) {
-    if (count <= 0) return;
+    if (count <= 0) {
+      __syncthreads();                             // finish of the last block read buffer 2
+      keep(dd);
+      return;
+    }
     T fa0[AL], fa1[AL];
     Y fy0[YL], fy1[YL];
     // chunk q, clamped to the last one: every prefetch is issued unconditionally (a chunk
     // past the end repeats the last, never used), which keeps the loads in flight the same
     // on every path and lets each wait count only the chunk it needs
-    const int64_t qmax = count - 1;
-    auto kk_of = [&](int64_t q) { return first + step * min(q, qmax); };
+    const int qmax = count - 1;
+    auto kk_of = [&](int q) { return first + step * min(q, qmax); };
     fetch(bwd, i0, kk_of(0), fa0, fy0);
     fetch(bwd, i0, kk_of(1), fa1, fy1);
-    __syncthreads();                               // finish of the last block read buffer 0
+    __syncthreads();                               // the last block's readers are done
     stage(0, bwd, i0, nb, kk_of(0), fa0, fy0);
-    for (int64_t q = 0; q < count; q += 2) {
+    for (int q = 0; q < count; q += 2) {
       __syncthreads();
       fetch(bwd, i0, kk_of(q + 2), fa0, fy0);
       mma(0, bwd, acc);
+      if (q == 0) keep(dd);
       if (q + 1 >= count) break;
       stage(1, bwd, i0, nb, kk_of(q + 1), fa1, fy1);
       __syncthreads();
@@ -1924,97 +1946,92 @@ __global__ void __launch_bounds__(MT) k_band_solve_m(
       stage(0, bwd, i0, nb, kk_of(q + 2), fa0, fy0);
     }
   };
-  // Yc <- rhs - accumulated sums (rows >= nb zero), Ab <- inverse block; the product with
-  // it is the block's solution, handed over.  The right-hand side is x forward and the
-  // block's forward solution (polled) backward.
-  // (dd: the block's inverse diagonal block, loaded before the sweep so that its latency
-  // stays off the chain of hand-overs)
-  auto finish = [&](bool bwd, int64_t i0, int nb, const T (&dd)[AL],
-                    const typename MF::V& acc) {
-    double bb[4];
+  // The right-hand side of a block, x forward and the block's forward solution backward, in
+  // the layout of the sums; true if some of it is still to come.
+  auto rhs = [&](bool bwd, int i0, int nb, double (&bb)[4]) -> bool {
     const int cc = min(16 * ct + li, M - 1);
-    if (!bwd) {
+    bool missing = false;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int64_t row = min<int64_t>(i0 + 16 * rt + MF::row(r, lk), n - 1);
-        bb[r] = x[(lower ? n1 - row : row) * M + cc];
+    for (int r = 0; r < 4; ++r) {
+      const int row = i0 + min(16 * rt + MF::row(r, lk), nb - 1);
+      if (!bwd) {
+        bb[r] = x[(int64_t)(lower ? n1 - row : row) * M + cc];
+      } else {
+        const Y yb = poll_load(y + ((int64_t)row * M + cc));
+        bb[r] = (double)yb;
+        missing = missing || (tile && is_mark(yb));
       }
-      if (i0 >= sep) {                             // the lower part's share of these rows
-        int64_t spins = 0;
-        Y tb[4];
-        for (;;) {
-          bool ok = true;
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int ii = 16 * rt + MF::row(r, lk);
-            tb[r] = poll_load(mate + (n1 - i0 - min(ii, nb - 1)) * M + cc);
-            ok = ok && (!tile || ii >= nb || !is_mark(tb[r]));
-          }
-          if (__all(ok) || poll_give_up(spins, err)) break;
-        }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) bb[r] -= (double)tb[r];
-      }
-    } else {
+    }
+    return missing;
+  };
+  // Yc <- rhs - accumulated sums (rows >= nb zero); the product of the inverse block with it
+  // is the block's solution, handed over.
+  // (bb, the block's right-hand side, and its inverse block are loaded before the sweep so
+  // that their latency stays off the chain of hand-overs)
+  auto finish = [&](bool bwd, int i0, int nb, double (&bb)[4], bool missing,
+                    const typename MF::V& acc) {
+    if (__any(missing)) {
       int64_t spins = 0;
+      while (__any(rhs(bwd, i0, nb, bb)) && !poll_give_up(spins, err)) {}
+    }
+    if (!bwd && i0 >= sep) {                       // the lower part's share of these rows
+      const int cc = min(16 * ct + li, M - 1);
+      int64_t spins = 0;
+      Y tb[4];
       for (;;) {
         bool ok = true;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int ii = 16 * rt + MF::row(r, lk);
-          const Y yb = poll_load(y + (i0 + min(ii, nb - 1)) * M + cc);
-          bb[r] = (double)yb;
-          ok = ok && (!tile || ii >= nb || !is_mark(yb));
+          tb[r] = poll_load(mate + ((int64_t)(n1 - i0 - min(ii, nb - 1)) * M + cc));
+          ok = ok && (!tile || ii >= nb || !is_mark(tb[r]));
         }
         if (__all(ok) || poll_give_up(spins, err)) break;
       }
-    }
-    __syncthreads();
 #pragma unroll
-    for (int u = 0; u < AL; ++u) {
-      const int idx = threadIdx.x + MT * u;
-      Ab[0][idx >> 6][idx & 63] = (S)dd[u];
+      for (int r = 0; r < 4; ++r) bb[r] -= (double)tb[r];
     }
     if (tile)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int ii = 16 * rt + MF::row(r, lk), col = 16 * ct + li;
-        if (col < M) Yc[0][ii * MP + col] = ii < nb ? (S)(bb[r] - (double)acc[r]) : (S)0;
+        if (col < M) Yc[2][ii * MP + col] = ii < nb ? (S)(bb[r] - (double)acc[r]) : (S)0;
       }
     __syncthreads();
     typename MF::V yv = {0, 0, 0, 0};
-    mma(0, bwd, yv);
+    mma(2, bwd, yv);
     Y* dst = bwd ? z : y;
     if (tile)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int ii = 16 * rt + MF::row(r, lk), col = 16 * ct + li;
-        if (ii < nb && col < M) hand_over(dst + (i0 + ii) * M + col, (Y)yv[r]);
+        if (ii < nb && col < M) hand_over(dst + ((int64_t)(i0 + ii) * M + col), (Y)yv[r]);
       }
-    __syncthreads();
   };
   // ---- forward: chunks in increasing order; those from kdone on are still in flight
 #pragma unroll 1
   for (int seg = 0; seg < (split ? 2 : 1); ++seg) {
     if (seg) use(upper);
-    const int64_t kend = seg || !split || lower ? (n + SB - 1) / SB : sep / SB;
-    for (int64_t k = seg ? sep / SB + 2 * g + own_lower : g; k < kend; k += seg ? 2 * G : G) {
-      const int64_t i0 = k * SB;
-      const int nb = (int)min<int64_t>(SB, n - i0);
-      const int64_t kfirst = max(max<int64_t>(i0 - B, 0), fcb[k]) / SB;   // envelope start
+    const int kend = seg || !split || lower ? (n + SB - 1) / SB : sep / SB;
+    for (int k = seg ? sep / SB + 2 * g + own_lower : g; k < kend; k += seg ? 2 * G : G) {
+      const int i0 = k * SB;
+      const int nb = (int)min(SB, n - i0);
+      const int kfirst = max(max(i0 - B, 0), (int)fcb[k]) / SB;   // envelope start
       T dd[AL];
 #pragma unroll
-      for (int u = 0; u < AL; ++u) dd[u] = dv[min(k, ncb - 1) * SB * SB + threadIdx.x + MT * u];
+      for (int u = 0; u < AL; ++u) dd[u] = dv[(int64_t)min(k, ncb - 1) * SB * SB + threadIdx.x + MT * u];
       typename MF::V acc = {0, 0, 0, 0};
-      sweep(false, i0, nb, kfirst, min(k, ncb) - kfirst, 1, acc);
+      double bb[4];
+      if (k < ncb) rhs(false, i0, nb, bb);
+      sweep(false, i0, nb, kfirst, min(k, ncb) - kfirst, 1, dd, acc);
       if (k < ncb) {
-        finish(false, i0, nb, dd, acc);
+        finish(false, i0, nb, bb, false, acc);
       } else {                                     // separator rows of a lower part
         if (tile)
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             const int ii = 16 * rt + MF::row(r, lk), col = 16 * ct + li;
-            if (ii < nb && col < M) hand_over(y + (i0 + ii) * M + col, (Y)acc[r]);
+            if (ii < nb && col < M) hand_over(y + ((int64_t)(i0 + ii) * M + col), (Y)acc[r]);
           }
         __syncthreads();
       }
@@ -2024,19 +2041,21 @@ __global__ void __launch_bounds__(MT) k_band_solve_m(
 #pragma unroll 1
   for (int seg = split ? 1 : 0; seg >= 0; --seg) {
     if (!seg && split) use(pg.x);
-    const int64_t kbeg = seg ? sep / SB : 0;
-    const int64_t kend = seg || !split || lower ? ncb : sep / SB;
-    for (int64_t kb = kend - 1 - (seg ? 2 * g + own_lower : g); kb >= kbeg;
+    const int kbeg = seg ? sep / SB : 0;
+    const int kend = seg || !split || lower ? ncb : sep / SB;
+    for (int kb = kend - 1 - (seg ? 2 * g + own_lower : g); kb >= kbeg;
          kb -= seg ? 2 * G : G) {
-      const int64_t i0 = kb * SB;
-      const int nb = (int)min<int64_t>(SB, n - i0);
-      const int64_t klast = (min(min<int64_t>(n, i0 + nb + B), lrb[kb]) - 1) / SB;   // last row block
+      const int i0 = kb * SB;
+      const int nb = (int)min(SB, n - i0);
+      const int klast = (min(min(n, i0 + nb + B), (int)lrb[kb]) - 1) / SB;   // last row block
       T dd[AL];
 #pragma unroll
-      for (int u = 0; u < AL; ++u) dd[u] = dv[kb * SB * SB + threadIdx.x + MT * u];
+      for (int u = 0; u < AL; ++u) dd[u] = dv[(int64_t)kb * SB * SB + threadIdx.x + MT * u];
       typename MF::V acc = {0, 0, 0, 0};
-      sweep(true, i0, nb, klast, klast - kb, -1, acc);
-      finish(true, i0, nb, dd, acc);
+      double bb[4];
+      const bool missing = rhs(true, i0, nb, bb);
+      sweep(true, i0, nb, klast, klast - kb, -1, dd, acc);
+      finish(true, i0, nb, bb, missing, acc);
     }
   }
 }
@@ -2046,11 +2065,11 @@ __global__ void __launch_bounds__(MT) k_band_solve_m(
 // several a group has B / 64 chunks per block, 2 to 3 us each, and the chain passes a block in
 // about 7 us, so B / 128 groups (8 at least) keep up with it and more only poll: with 16 in place of
 // 8 groups 5 matrices of n = 45,000, B = 2,080 (FP32) 5.60 -> 3.92 ms, but 6 of 16,000, 1,020
-// 1.92 -> 1.98 and 4 of 3,500, 370 0.51 -> 0.53 ms.  A matrix's work-groups run on one XCD (set_place), so it is the parts on the
-// fullest XCD that are counted, against its eighth of the machine: counted together, 14
-// matrices of 24 parts would put 40 work-groups on an XCD's 32 slots.  The solves of one
-// context are stream-ordered, so a launch may count on the whole machine.  When several
-// contexts solve concurrently (share > 1) their launches together get three quarters of it;
+// 1.92 -> 1.98 and 4 of 3,500, 370 0.51 -> 0.53 ms.  A matrix's work-groups run on one XCD
+// (set_place), so it is the parts on the fullest XCD that are counted, against its eighth of
+// the machine: counted together, 14 matrices of 24 parts would put 40 work-groups on an XCD's
+// 32 slots.  The solves of one context are stream-ordered, so a launch may count on the whole
+// machine.  When several contexts solve concurrently (share > 1) their launches together get three quarters of it;
 // their matrices go round the XCDs one after another (xcd0), so an XCD holds at most
 // `together` parts - or, where that is not known or contexts wait for their turn, share times
 // one context's.
