@@ -262,8 +262,8 @@ gx_status gx_geneo_setup(gx_ctx* ctx, const gx_geneo_opts* opts, int32_t* nev_ou
 /* Set-up of many contexts (extension: many laminates at once): gx_geneo_setup(ctxs[i],
  * opts[i], nev_out[i], n0_out + i) for every i, up to `concurrent` of them at a time on
  * host threads of the library, each context on its own stream.  While they run, the
- * contexts' multi-work-group launches together take at most 3/4 of the device's resident
- * capacity, so that concurrent launches stay resident together.  Set-ups are
+ * contexts' multi-work-group launches are sized so that all of them stay resident together
+ * whichever XCDs they fall on.  Set-ups are
  * chains of small launches on a few streams each, so they overlap only as far as the
  * process has hardware queues (GPU_MAX_HW_QUEUES, read when the HIP runtime starts;
  * HIP's default is 4).  Each

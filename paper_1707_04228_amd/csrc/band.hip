@@ -1662,11 +1662,10 @@ __device__ inline V uniform_load(const V* p) {
 }
 
 // (part, group) of this work-group in a launch over one band set of n_mat matrices, G groups
-// per part, both parts of a matrix (PP = 2 if the set has split matrices) in turn, matrix j on
-// XCD (j + xcd0) mod 8; part -1: none
-__device__ inline int2 set_place(const int32_t* part_of, int n_mat, int G, int PP, int xcd0,
+// per part, both parts of a matrix (PP = 2 if the set has split matrices) in turn; part -1: none
+__device__ inline int2 set_place(const int32_t* part_of, int n_mat, int G, int PP,
                                  int* counters) {
-  const int x = (blockIdx.x - xcd0) & 7, q = take_place(counters + CL * x);
+  const int x = blockIdx.x & 7, q = take_place(counters + CL * x);
   const int j = q / (G * PP) * 8 + x, m = q % (G * PP);
   if (j >= n_mat) return {-1, 0};
   return {uniform_load(part_of + 2 * j + m % PP), m / PP};
@@ -1676,9 +1675,9 @@ __device__ inline int2 set_place(const int32_t* part_of, int n_mat, int G, int P
 template <class T, bool COARSE>
 __global__ void __launch_bounds__(SOLVE_THREADS) k_band_solve_1(
     BandArgs a, const int32_t* part_of, const T* v, const T* dinv, const T* link,
-    const int64_t* xoff, const double* xall, double* yall, double* zall, int G, int PP, int xcd0, int n_mat,
+    const int64_t* xoff, const double* xall, double* yall, double* zall, int G, int PP, int n_mat,
     int* err) {
-  const int2 pg = set_place(part_of, n_mat, G, PP, xcd0, err + CL);
+  const int2 pg = set_place(part_of, n_mat, G, PP, err + CL);
   if (pg.x < 0) return;
   auto load = [&](int i) -> Solve1<T> {
     const BandPart P = uniform_load(a.part + i);
@@ -1771,7 +1770,7 @@ constexpr int AL = SB * SB / MT;                  // band-chunk entries per thre
 template <class T, int M>
 __global__ void __launch_bounds__(MT) k_band_solve_m(
     BandArgs a, const int32_t* part_of, const T* v, const T* dinv, const int64_t* xoff,
-    const double* xall, T* yall, T* zall, int G, int PP, int xcd0, int n_mat, const int32_t* active,
+    const double* xall, T* yall, T* zall, int G, int PP, int n_mat, const int32_t* active,
     int* err) {
   typedef Mfma<T> MF;
   typedef typename MF::S S;
@@ -1781,7 +1780,7 @@ __global__ void __launch_bounds__(MT) k_band_solve_m(
   constexpr int YL = SB * M / MT;                 // solution-chunk entries per thread
   __shared__ S Ab[3][SB][SB + 1];                 // band chunks (double buffer), and the
   __shared__ S Yc[3][SB * MP];                    // inverse block and its right-hand side
-  const int2 pg = set_place(part_of, n_mat, G, PP, xcd0, err + CL);
+  const int2 pg = set_place(part_of, n_mat, G, PP, err + CL);
   const int g = pg.y;
   if (pg.x < 0) return;
   int n, B, rs, n1, ncb, sep;                     // n1: last row of the matrix; ncb: blocks
@@ -2069,10 +2068,10 @@ __global__ void __launch_bounds__(MT) k_band_solve_m(
 // (set_place), so it is the parts on the fullest XCD that are counted, against its eighth of
 // the machine: counted together, 14 matrices of 24 parts would put 40 work-groups on an XCD's
 // 32 slots.  The solves of one context are stream-ordered, so a launch may count on the whole
-// machine.  When several contexts solve concurrently (share > 1) their launches together get three quarters of it;
-// their matrices go round the XCDs one after another (xcd0), so an XCD holds at most
-// `together` parts - or, where that is not known or contexts wait for their turn, share times
-// one context's.
+// machine.  When several contexts solve concurrently (share > 1) an XCD may hold the fullest
+// part of each: which XCD a launch begins with differs from launch to launch, and groups that
+// wait for others must all have a slot (four contexts of two matrices with 16 work-groups a
+// matrix ran into the poll limit in 7 of 100 set-ups; with 8 in none of 300).
 static int solve_groups(BandSet& bs, const void* kernel, int which) {
   if (bs.solve_groups[which] > 0) return bs.solve_groups[which];
   int dev = 0, cus = 0, per_cu = 0;
@@ -2080,12 +2079,10 @@ static int solve_groups(BandSet& bs, const void* kernel, int which) {
   GX_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
   GX_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel,
                                                       which == 0 ? SOLVE_THREADS : MT, 0));
-  const int64_t full = (int64_t)cus * std::max(per_cu, 0) / 8;   // of an XCD
-  const int64_t capacity = bs.share > 1 ? full * 3 / 4 : full;
+  const int64_t capacity = (int64_t)cus * std::max(per_cu, 0) / 8;   // of an XCD
   std::vector<int64_t> parts(8, 0);
   for (const BandPart& p : bs.part) ++parts[p.mat & 7];
-  int64_t most = *std::max_element(parts.begin(), parts.end()) * std::max(bs.share, 1);
-  if (bs.together > 0) most = std::min<int64_t>(most, bs.together);
+  const int64_t most = *std::max_element(parts.begin(), parts.end()) * std::max(bs.share, 1);
   const int cap = which == 0 ? GMAX
                              : (int)std::min<int64_t>(GMAX, std::max<int64_t>(8, bs.max_B / 128));
   int G = 1;
@@ -2201,7 +2198,7 @@ static void launch_m(BandSet& bs, const BandArgs& a, const int64_t* d_xoff, doub
     hipLaunchKernelGGL(k_fill_mark32, dim3(nblocks(2 * rows * M, 256)), dim3(256), 0, st, y,
                        2 * rows * M, err + CL);
     hipLaunchKernelGGL((k_band_solve_m<float, M>), dim3(solve_grid(bs, G)), dim3(MT), 0, st, a,
-                       bs.d_part_of.p, bs.v32.p, bs.dinv32.p, d_xoff, x, y, z, G, PP, bs.xcd0, bs.n_mat,
+                       bs.d_part_of.p, bs.v32.p, bs.dinv32.p, d_xoff, x, y, z, G, PP, bs.n_mat,
                        active, err);
     hipLaunchKernelGGL(k_copy_out<float>, cgrid, dim3(256), 0, st, bs.d_part.p, d_xoff, M, z, x,
                        active);
@@ -2211,7 +2208,7 @@ static void launch_m(BandSet& bs, const BandArgs& a, const int64_t* d_xoff, doub
     hipLaunchKernelGGL(k_fill_mark, dim3(nblocks(2 * rows * M, 256)), dim3(256), 0, st, y,
                        2 * rows * M, err + CL);
     hipLaunchKernelGGL((k_band_solve_m<double, M>), dim3(solve_grid(bs, G)), dim3(MT), 0, st, a,
-                       bs.d_part_of.p, bs.v64.p, bs.dinv64.p, d_xoff, x, y, z, G, PP, bs.xcd0, bs.n_mat,
+                       bs.d_part_of.p, bs.v64.p, bs.dinv64.p, d_xoff, x, y, z, G, PP, bs.n_mat,
                        active, err);
     hipLaunchKernelGGL(k_copy_out<double>, cgrid, dim3(256), 0, st, bs.d_part.p, d_xoff, M, z, x,
                        active);
@@ -2274,15 +2271,15 @@ void band_solve(BandSet& bs, const int64_t* d_xoff, double* x, hipStream_t st, i
     if (bs.fp32)
       hipLaunchKernelGGL((k_band_solve_1<float, false>), grid, dim3(SOLVE_THREADS), 0, st, a,
                          bs.d_part_of.p, bs.v32.p, bs.dinv32.p, link32, d_xoff, x, y, z, G, PP,
-                         bs.xcd0, bs.n_mat, err);
+                         bs.n_mat, err);
     else if (bs.coarse)
       hipLaunchKernelGGL((k_band_solve_1<double, true>), grid, dim3(SOLVE_THREADS), 0, st, a,
                          bs.d_part_of.p, bs.v64.p, bs.dinv64.p, link64, d_xoff, x, y, z, G, PP,
-                         bs.xcd0, bs.n_mat, err);
+                         bs.n_mat, err);
     else
       hipLaunchKernelGGL((k_band_solve_1<double, false>), grid, dim3(SOLVE_THREADS), 0, st, a,
                          bs.d_part_of.p, bs.v64.p, bs.dinv64.p, link64, d_xoff, x, y, z, G, PP,
-                         bs.xcd0, bs.n_mat, err);
+                         bs.n_mat, err);
     hipLaunchKernelGGL(k_copy_out<double>, dim3(nblocks(bs.max_cols, 256), bs.n_part), dim3(256),
                        0, st, bs.d_part.p, d_xoff, 1, z, x, (const int32_t*)nullptr);
   } else {
@@ -2421,9 +2418,10 @@ void multi_solve_plan(MultiSolve& m, const std::vector<BandSet*>& sets,
       }
   for (BandPtrs& t : m.host)
     if (!link_pays(t.B, m.fp32, (int)t.G)) t.link = nullptr;
-  // a matrix's work-groups are neighbours in its XCD's list (take_place)
+  // a matrix's work-groups are neighbours in its XCD's list (take_place), the largest
+  // matrices first: where there are more parts than slots, the last ones to start are short
   std::vector<std::vector<int32_t>> lists(NX);
-  for (int j = 0; j < nm; ++j)
+  for (int j : order)
     for (int g = 0; g < (int)first(j).G; ++g)
       for (int q = mats[j]; q < mats[j + 1]; ++q) {
         lists[xcd[j]].push_back(q);

@@ -1065,8 +1065,6 @@ void geneo_coarse(gx_ctx* c, const gx_geneo_opts* o, const std::function<void()>
   const bool fp32 = o->precision == GX_MIXED;
   BandSet Mb;
   Mb.share = c->share;
-  Mb.xcd0 = c->xcd0;
-  Mb.together = c->together;
   std::vector<int64_t> doff(n_sub + 1, 0);
   for (int j = 0; j < n_sub; ++j) doff[j + 1] = doff[j] + 3 * sw.nD[j];
   DevBuf<int64_t> d_doff(n_sub + 1);
@@ -1537,17 +1535,7 @@ gx_status gx_geneo_setup_batch(int32_t n, gx_ctx* const* ctxs, const gx_geneo_op
       if (ctxs[k] == ctxs[i]) return GX_EINVAL;    // one set-up per context
   }
   const int T = std::min<int>(concurrent, n);
-  // the contexts' matrices go round the XCDs one after another
-  int first_mat = 0;
-  for (int i = 0; i < n; ++i) {
-    ctxs[i]->share = T;
-    ctxs[i]->xcd0 = first_mat & 7;
-    first_mat = (first_mat + std::max(opts[i]->n_sub, 0)) & 0xffff;
-  }
-  int64_t mats = 0;
-  for (int i = 0; i < n; ++i) mats += std::max(opts[i]->n_sub, 0);
-  for (int i = 0; i < n; ++i)
-    ctxs[i]->together = (int)std::min<int64_t>((mats + 7) / 8 * 2, 1 << 20);
+  for (int i = 0; i < n; ++i) ctxs[i]->share = T;
   std::vector<gx_status> st(n, GX_OK);
   std::atomic<int> next{0};
   auto work = [&]() {
@@ -1571,7 +1559,6 @@ gx_status gx_geneo_setup_batch(int32_t n, gx_ctx* const* ctxs, const gx_geneo_op
   gx_status first = GX_OK;
   for (int i = 0; i < n; ++i) {
     ctxs[i]->share = 1;
-    ctxs[i]->xcd0 = ctxs[i]->together = 0;
     if (status_out) status_out[i] = st[i];
     if (first == GX_OK) first = st[i];
   }

@@ -279,9 +279,6 @@ struct BandSet {
   int solve_groups[2] = {0, 0};                // work-groups per matrix: 1-RHS, m-RHS solve
   int force_groups[2] = {0, 0};                // requested (0: automatic, capped by residency)
   int share = 1;                               // contexts whose solves may run concurrently
-  int xcd0 = 0;                                // XCD of the first matrix's work-groups
-  int together = 0;                            // parts on the fullest XCD with all matrices of
-                                               // the contexts of the batch (0: not known)
   DevBuf<int> err;                             // error word of the solves (poll time-out),
                                                // then their eight work-group counters
   bool coarse = false;                         // the coarse matrix (own solve kernel name)
@@ -401,7 +398,6 @@ struct gx_ctx {
   // contexts set up at once on the device (gx_geneo_setup_batch): the set-up's
   // multi-work-group launches take this share of the machine's resident capacity
   int share = 1;
-  int xcd0 = 0, together = 0;                  // see BandSet
   // materials and loads of the last assembly (kept for the sensitivities)
   int32_t n_layers = 0;
   std::vector<double> eng;                     // 9 engineering constants per layer

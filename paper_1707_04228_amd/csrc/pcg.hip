@@ -354,8 +354,6 @@ gx_status gx_pcg_solve_batch(int32_t n, gx_ctx* const* ctxs, const double* const
     for (int i = 0; i < n; ++i) {
       BandSet& bs = ctxs[i]->sw.C;
       bs.share = share;
-      bs.xcd0 = share > 1 ? i & 7 : 0;             // one XCD after another
-      bs.together = share > 1 ? (share + 7) / 8 * 2 : 0;
       bs.solve_groups[0] = bs.solve_groups[1] = 0;
     }
   };
