@@ -1661,14 +1661,60 @@ __device__ inline V uniform_load(const V* p) {
   return out;
 }
 
-// (part, group) of this work-group in a launch over one band set of n_mat matrices, G groups
-// per part, both parts of a matrix (PP = 2 if the set has split matrices) in turn; part -1: none
-__device__ inline int2 set_place(const int32_t* part_of, int n_mat, int G, int PP,
-                                 int* counters) {
+// This work-group's part and group in a launch over one band set of n_mat matrices, up to G
+// groups per part, both parts of a matrix (PP = 2 if the set has split matrices) in turn;
+// part -1: none.
+// The groups of a matrix begin together.  Launches of other contexts may hold some of the
+// slots and wait for theirs in the same way, so the wait is bounded: after GATHER (20 ms, a
+// thousand times what a lone launch takes) those who are there share the matrix, and whoever
+// comes later leaves.  Two words per matrix, after the place counters, cleared by the marker
+// fill: arrivals, which number the groups, and how many of them take part.
+struct Place {
+  int part, g, G;
+};
+constexpr int64_t GATHER = 2000000;              // ticks of the 100 MHz clock
+__device__ inline Place set_place(const int32_t* part_of, int n_mat, int G, int PP, int* err) {
+  int* counters = err + CL;
   const int x = blockIdx.x & 7, q = take_place(counters + CL * x);
   const int j = q / (G * PP) * 8 + x, m = q % (G * PP);
-  if (j >= n_mat) return {-1, 0};
-  return {uniform_load(part_of + 2 * j + m % PP), m / PP};
+  if (j >= n_mat) return {-1, 0, G};
+  const int np = PP == 2 && uniform_load(part_of + 2 * j + 1) >= 0 ? 2 : 1;
+  if (m % PP >= np) return {-1, 0, G};           // no second part
+  if (G == 1) return {uniform_load(part_of + 2 * j + m % PP), 0, 1};
+  __shared__ int2 mine;                          // number among those present, groups per part
+  if (threadIdx.x == 0) {
+    int *w = counters + CL * 8 + 2 * j, *e = w + 1;
+    auto settle = [&](int n) {                   // once: the first to settle it counts
+      int none = 0;
+      __hip_atomic_compare_exchange_strong(e, &none, n, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+    };
+    int2 r = {atomicAdd(w, 1), G};
+    if (r.x == np * G - 1) settle(np * G);
+    const int64_t t0 = wall_clock64();
+    int64_t spins = 0;
+    int c;
+    while (!(c = __hip_atomic_load(e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
+      if ((++spins & 255) == 0) {
+        if (wall_clock64() - t0 > GATHER) {
+          const int n = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if (n >= np) settle(min(n, np * G));
+        }
+        if (spins > SPIN_LIMIT) {
+          atomicOr(err, 2);
+          break;
+        }
+      }
+      __builtin_amdgcn_s_sleep(1);
+    }
+    r.y = c / np;
+    if (r.x >= r.y * np) r.x = -1;
+    mine = r;
+  }
+  __syncthreads();
+  const int k = __builtin_amdgcn_readfirstlane(mine.x), groups = __builtin_amdgcn_readfirstlane(mine.y);
+  if (k < 0) return {-1, 0, groups};
+  return {uniform_load(part_of + 2 * j + k % np), k / np, groups};
 }
 
 // The parts of one band set (set_place)
@@ -1677,8 +1723,8 @@ __global__ void __launch_bounds__(SOLVE_THREADS) k_band_solve_1(
     BandArgs a, const int32_t* part_of, const T* v, const T* dinv, const T* link,
     const int64_t* xoff, const double* xall, double* yall, double* zall, int G, int PP, int n_mat,
     int* err) {
-  const int2 pg = set_place(part_of, n_mat, G, PP, err + CL);
-  if (pg.x < 0) return;
+  const Place pl = set_place(part_of, n_mat, G, PP, err);
+  if (pl.part < 0) return;
   auto load = [&](int i) -> Solve1<T> {
     const BandPart P = uniform_load(a.part + i);
     const int mp = P.kind == PART_WHOLE ? i
@@ -1690,10 +1736,10 @@ __global__ void __launch_bounds__(SOLVE_THREADS) k_band_solve_1(
             xall + uniform_load(xoff + P.mat), yall + P.yoff, zall + P.yoff,
             (P.kind == PART_LOWER ? zall : yall) + mo};
   };
-  const BandPart P = uniform_load(a.part + pg.x);
+  const BandPart P = uniform_load(a.part + pl.part);
   if (P.rows == 0) return;
-  band_solve_1_mat<T>(load, pg.x,
-                      P.kind == PART_WHOLE ? -1 : uniform_load(part_of + 2 * P.mat), pg.y, G,
+  band_solve_1_mat<T>(load, pl.part,
+                      P.kind == PART_WHOLE ? -1 : uniform_load(part_of + 2 * P.mat), pl.g, pl.G,
                       err);
 }
 
@@ -1770,7 +1816,7 @@ constexpr int AL = SB * SB / MT;                  // band-chunk entries per thre
 template <class T, int M>
 __global__ void __launch_bounds__(MT) k_band_solve_m(
     BandArgs a, const int32_t* part_of, const T* v, const T* dinv, const int64_t* xoff,
-    const double* xall, T* yall, T* zall, int G, int PP, int n_mat, const int32_t* active,
+    const double* xall, T* yall, T* zall, int groups, int PP, int n_mat, const int32_t* active,
     int* err) {
   typedef Mfma<T> MF;
   typedef typename MF::S S;
@@ -1780,9 +1826,9 @@ __global__ void __launch_bounds__(MT) k_band_solve_m(
   constexpr int YL = SB * M / MT;                 // solution-chunk entries per thread
   __shared__ S Ab[3][SB][SB + 1];                 // band chunks (double buffer), and the
   __shared__ S Yc[3][SB * MP];                    // inverse block and its right-hand side
-  const int2 pg = set_place(part_of, n_mat, G, PP, err + CL);
-  const int g = pg.y;
-  if (pg.x < 0) return;
+  const Place pl = set_place(part_of, n_mat, groups, PP, err);
+  const int g = pl.g, G = pl.G;
+  if (pl.part < 0) return;
   int n, B, rs, n1, ncb, sep;                     // n1: last row of the matrix; ncb: blocks
   const T *cb, *dv;                               // with columns of their own
   const int64_t *fcb, *lrb;
@@ -1790,7 +1836,7 @@ __global__ void __launch_bounds__(MT) k_band_solve_m(
   Y *y, *z;
   const Y* mate;                                  // the other part's scratch, row r at n1 - r
   bool lower;
-  const int mat = uniform_load(&a.part[pg.x].mat);
+  const int mat = uniform_load(&a.part[pl.part].mat);
   if (active && !uniform_load(active + mat)) return;
   auto use = [&](int part) {
     const BandPart P = uniform_load(a.part + part);
@@ -1808,7 +1854,7 @@ __global__ void __launch_bounds__(MT) k_band_solve_m(
     const int mp = P.kind == PART_WHOLE ? part : uniform_load(part_of + 2 * mat + !lower);
     mate = (lower ? zall : yall) + uniform_load(&a.part[mp].yoff) * M;
   };
-  use(pg.x);
+  use(pl.part);
   if (n == 0) return;
   // the separator of a split matrix is swept by the work-groups of both parts (see
   // band_solve_1_mat); the polls of every chunk are all the waiting it needs
@@ -2039,7 +2085,7 @@ __global__ void __launch_bounds__(MT) k_band_solve_m(
   // ---- backward: chunks from the far end of the band inwards
 #pragma unroll 1
   for (int seg = split ? 1 : 0; seg >= 0; --seg) {
-    if (!seg && split) use(pg.x);
+    if (!seg && split) use(pl.part);
     const int kbeg = seg ? sep / SB : 0;
     const int kend = seg || !split || lower ? ncb : sep / SB;
     for (int kb = kend - 1 - (seg ? 2 * g + own_lower : g); kb >= kbeg;
@@ -2131,8 +2177,9 @@ void band_link(BandSet& bs, hipStream_t st) {
 // The launch's error word (raised by a poll that timed out), zero until a check clears it;
 // the counters of take_place follow it
 static int* solve_err(BandSet& bs, hipStream_t st) {
-  if (!bs.err.n) {
-    bs.err.alloc(CL * (1 + 8));
+  const size_t words = CL * (1 + 8) + 2 * (size_t)bs.n_mat;
+  if (bs.err.n < words) {
+    bs.err.alloc(words);
     clear(bs.err, st);
   }
   return bs.err.p;
@@ -2142,9 +2189,16 @@ static unsigned solve_grid(const BandSet& bs, int G) {
   return (unsigned)((bs.n_mat + 7) / 8 * 8 * G * solve_parts(bs));
 }
 
-__global__ void k_fill_mark(double* p, int64_t n, int* counters) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// the place counters and the matrices' words of set_place
+__device__ inline void clear_places(int* counters, int n_mat, int64_t i) {
   if (i < 8) counters[CL * i] = 0;
+  for (int64_t j = i; j < 2 * n_mat; j += (int64_t)gridDim.x * blockDim.x)
+    counters[CL * 8 + j] = 0;
+}
+
+__global__ void k_fill_mark(double* p, int64_t n, int* counters, int n_mat) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  clear_places(counters, n_mat, i);
   if (i < n) p[i] = __longlong_as_double((long long)YMARK);
 }
 
@@ -2158,7 +2212,7 @@ static void alloc_solve1_scratch(BandSet& bs) {
 static double* solve1_scratch(BandSet& bs, hipStream_t st) {
   alloc_solve1_scratch(bs);
   hipLaunchKernelGGL(k_fill_mark, dim3(nblocks((int64_t)bs.ybuf.n, 256)), dim3(256), 0, st,
-                     bs.ybuf.p, (int64_t)bs.ybuf.n, solve_err(bs, st) + CL);
+                     bs.ybuf.p, (int64_t)bs.ybuf.n, solve_err(bs, st) + CL, bs.n_mat);
   return bs.ybuf.p;
 }
 
@@ -2175,9 +2229,9 @@ __global__ void k_copy_out(const BandPart* part, const int64_t* xoff, int w, con
   x[xoff[P.mat] + o] = (double)z[P.yoff * w + i];
 }
 
-__global__ void k_fill_mark32(float* p, int64_t n, int* counters) {
+__global__ void k_fill_mark32(float* p, int64_t n, int* counters, int n_mat) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < 8) counters[CL * i] = 0;
+  clear_places(counters, n_mat, i);
   if (i < n) p[i] = __uint_as_float(YMARK32);
 }
 
@@ -2196,7 +2250,7 @@ static void launch_m(BandSet& bs, const BandArgs& a, const int64_t* d_xoff, doub
     float* y = reinterpret_cast<float*>(bs.mbuf.p);
     float* z = y + rows * M;
     hipLaunchKernelGGL(k_fill_mark32, dim3(nblocks(2 * rows * M, 256)), dim3(256), 0, st, y,
-                       2 * rows * M, err + CL);
+                       2 * rows * M, err + CL, bs.n_mat);
     hipLaunchKernelGGL((k_band_solve_m<float, M>), dim3(solve_grid(bs, G)), dim3(MT), 0, st, a,
                        bs.d_part_of.p, bs.v32.p, bs.dinv32.p, d_xoff, x, y, z, G, PP, bs.n_mat,
                        active, err);
@@ -2206,7 +2260,7 @@ static void launch_m(BandSet& bs, const BandArgs& a, const int64_t* d_xoff, doub
     double* y = bs.mbuf.p;
     double* z = bs.mbuf.p + rows * M;
     hipLaunchKernelGGL(k_fill_mark, dim3(nblocks(2 * rows * M, 256)), dim3(256), 0, st, y,
-                       2 * rows * M, err + CL);
+                       2 * rows * M, err + CL, bs.n_mat);
     hipLaunchKernelGGL((k_band_solve_m<double, M>), dim3(solve_grid(bs, G)), dim3(MT), 0, st, a,
                        bs.d_part_of.p, bs.v64.p, bs.dinv64.p, d_xoff, x, y, z, G, PP, bs.n_mat,
                        active, err);
