@@ -1638,8 +1638,8 @@ __device__ __forceinline__ void band_solve_1_mat(Load load, int own, int upper, 
 // (matrix, group, part) in the order they start, from a counter that the marker fill resets.
 // The two parts of a matrix wait for each other, and so do the groups of a part: a matrix's
 // work-groups are neighbours in the list, so those running are a prefix of it, every
-// complete matrix of the prefix finishes, and its slots go to the next ones - no launch
-// waits for ever, however few of its work-groups are resident at a time.
+// complete matrix of the prefix finishes, and its slots go to the next ones.  Launches of
+// several contexts could each hold a part of the slots and wait for the rest: see gather.
 __device__ inline int take_place(int* counter) {
   __shared__ int q;
   if (threadIdx.x == 0) q = atomicAdd(counter, 1);
@@ -1661,29 +1661,17 @@ __device__ inline V uniform_load(const V* p) {
   return out;
 }
 
-// This work-group's part and group in a launch over one band set of n_mat matrices, up to G
-// groups per part, both parts of a matrix (PP = 2 if the set has split matrices) in turn;
-// part -1: none.
-// The groups of a matrix begin together.  Launches of other contexts may hold some of the
-// slots and wait for theirs in the same way, so the wait is bounded: after GATHER (20 ms, a
-// thousand times what a lone launch takes) those who are there share the matrix, and whoever
-// comes later leaves.  Two words per matrix, after the place counters, cleared by the marker
-// fill: arrivals, which number the groups, and how many of them take part.
-struct Place {
-  int part, g, G;
-};
+// The groups of a matrix (G to each of its np parts) begin together.  Launches of other
+// contexts may hold some of the slots and wait for theirs in the same way, so the wait is
+// bounded: after GATHER (20 ms, a thousand times what a lone launch takes) those who are there
+// share the matrix, and whoever comes later leaves.  w: two words of the matrix, cleared by the
+// marker fill: arrivals, which number the groups, and how many of them take part.  Returns this
+// work-group's number (-1: leave) and the groups per part, the same in every lane.
 constexpr int64_t GATHER = 2000000;              // ticks of the 100 MHz clock
-__device__ inline Place set_place(const int32_t* part_of, int n_mat, int G, int PP, int* err) {
-  int* counters = err + CL;
-  const int x = blockIdx.x & 7, q = take_place(counters + CL * x);
-  const int j = q / (G * PP) * 8 + x, m = q % (G * PP);
-  if (j >= n_mat) return {-1, 0, G};
-  const int np = PP == 2 && uniform_load(part_of + 2 * j + 1) >= 0 ? 2 : 1;
-  if (m % PP >= np) return {-1, 0, G};           // no second part
-  if (G == 1) return {uniform_load(part_of + 2 * j + m % PP), 0, 1};
-  __shared__ int2 mine;                          // number among those present, groups per part
+__device__ inline int2 gather(int* w, int np, int G, int* err) {
+  __shared__ int2 mine;
   if (threadIdx.x == 0) {
-    int *w = counters + CL * 8 + 2 * j, *e = w + 1;
+    int* e = w + 1;
     auto settle = [&](int n) {                   // once: the first to settle it counts
       int none = 0;
       __hip_atomic_compare_exchange_strong(e, &none, n, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
@@ -1712,9 +1700,26 @@ __device__ inline Place set_place(const int32_t* part_of, int n_mat, int G, int 
     mine = r;
   }
   __syncthreads();
-  const int k = __builtin_amdgcn_readfirstlane(mine.x), groups = __builtin_amdgcn_readfirstlane(mine.y);
-  if (k < 0) return {-1, 0, groups};
-  return {uniform_load(part_of + 2 * j + k % np), k / np, groups};
+  return {__builtin_amdgcn_readfirstlane(mine.x), __builtin_amdgcn_readfirstlane(mine.y)};
+}
+
+// This work-group's part and group in a launch over one band set of n_mat matrices, up to G
+// groups per part, both parts of a matrix (PP = 2 if the set has split matrices) in turn;
+// part -1: none.  The words of the matrices' gathers follow the place counters.
+struct Place {
+  int part, g, G;
+};
+__device__ inline Place set_place(const int32_t* part_of, int n_mat, int G, int PP, int* err) {
+  int* counters = err + CL;
+  const int x = blockIdx.x & 7, q = take_place(counters + CL * x);
+  const int j = q / (G * PP) * 8 + x, m = q % (G * PP);
+  if (j >= n_mat) return {-1, 0, G};
+  const int np = PP == 2 && uniform_load(part_of + 2 * j + 1) >= 0 ? 2 : 1;
+  if (m % PP >= np) return {-1, 0, G};           // no second part
+  if (G == 1) return {uniform_load(part_of + 2 * j + m % PP), 0, 1};
+  const int2 k = gather(counters + CL * 8 + 2 * j, np, G, err);
+  if (k.x < 0) return {-1, 0, k.y};
+  return {uniform_load(part_of + 2 * j + k.x % np), k.x / np, k.y};
 }
 
 // The parts of one band set (set_place)
@@ -1745,25 +1750,37 @@ __global__ void __launch_bounds__(SOLVE_THREADS) k_band_solve_1(
 
 // The parts of several band sets in one launch (all of one precision): the q-th work-group
 // of class x to start takes group work[2 i + 1] of part work[2 i], i = q n_class + x (none
-// if negative).
+// if negative).  Where a part has more than one group the matrix's groups gather first, as in
+// set_place: the table counts on all slots of the device, and the joint solves of another
+// thread's batch may hold some of them.
 template <class T>
 __global__ void __launch_bounds__(SOLVE_THREADS) k_band_solve_1_multi(const BandPtrs* __restrict__ tab,
                                                                        const int32_t* __restrict__ work,
                                                                        int n_class, int* err) {
   const int x = blockIdx.x % n_class;
   const int i = take_place(err + CL * (1 + x)) * n_class + x;
-  const int j = uniform_load(work + 2 * i), g = uniform_load(work + 2 * i + 1);
+  int j = uniform_load(work + 2 * i), g = uniform_load(work + 2 * i + 1);
   if (j < 0) return;
   auto load = [&](int p) -> Solve1<T> {
     const BandPtrs t = uniform_load(tab + p);
     return {t.n, t.cols, t.sep, t.N, t.B, t.B + 1, (int)t.kind, static_cast<const T*>(t.v),
             static_cast<const T*>(t.dinv), static_cast<const T*>(t.link), t.fcb, t.lrb, t.x, t.y, t.z, t.mate};
   };
-  const BandPtrs t = uniform_load(tab + j);
-  if (t.n == 0) return;
+  const int64_t rows = uniform_load(&tab[j].n);
+  const int kind = (int)uniform_load(&tab[j].kind);
+  int G = (int)uniform_load(&tab[j].G);
+  if (rows == 0) return;
   // (an upper part stands right before its lower part in the table)
-  const int upper = t.kind == PART_WHOLE ? -1 : t.kind == PART_UPPER ? j : j - 1;
-  band_solve_1_mat<T>(load, j, upper, g, (int)t.G, err);
+  const int first = kind == PART_LOWER ? j - 1 : j;
+  if (G > 1) {
+    const int np = kind == PART_WHOLE ? 1 : 2;
+    const int2 k = gather(err + CL * (1 + 8) + 2 * first, np, G, err);
+    if (k.x < 0) return;
+    j = first + k.x % np;
+    g = k.x / np;
+    G = k.y;
+  }
+  band_solve_1_mat<T>(load, j, kind == PART_WHOLE ? -1 : first, g, G, err);
 }
 
 // y and z scratch of every part of a multi-set solve back to the marker, its counters to 0
@@ -1771,6 +1788,7 @@ __global__ void k_fill_mark_multi(const BandPtrs* tab, int* counters) {
   const BandPtrs t = tab[blockIdx.y];
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (blockIdx.y == 0 && i < 8) counters[CL * i] = 0;
+  if (i < 2) counters[CL * 8 + 2 * blockIdx.y + i] = 0;   // the part's words of gather
   if (i < (t.n + SB - 1) / SB * SB) {
     t.y[i] = __longlong_as_double((long long)YMARK);
     t.z[i] = __longlong_as_double((long long)YMARK);
@@ -2495,8 +2513,10 @@ void multi_solve_plan(MultiSolve& m, const std::vector<BandSet*>& sets,
   to_dev(m.tab.p, m.host.data(), m.host.size(), st);
   if (m.work.n < wl.size()) m.work.alloc(wl.size());
   to_dev(m.work.p, wl.data(), wl.size(), st);
-  if (!m.err.n) {
-    m.err.alloc(CL * (1 + 8));
+  const size_t words = CL * (1 + 8) + 2 * m.host.size();   // (of a matrix's parts, the first's)
+  if (m.err.n < words) {
+    multi_solve_check(m, st);                      // a time-out not yet reported
+    m.err.alloc(words);
     clear(m.err, st);
   }
   GX_HIP(hipStreamSynchronize(st));                // wl and host are read by the copies

@@ -280,7 +280,8 @@ struct BandSet {
   int force_groups[2] = {0, 0};                // requested (0: automatic, capped by residency)
   int share = 1;                               // contexts whose solves may run concurrently
   DevBuf<int> err;                             // error word of the solves (poll time-out),
-                                               // then their eight work-group counters
+                                               // then their eight work-group counters,
+                                               // two gathering words per matrix
   bool coarse = false;                         // the coarse matrix (own solve kernel name)
   // column panels of solves with more right-hand sides than one launch takes
   DevBuf<double> panel;
@@ -314,7 +315,8 @@ struct MultiSolve {
   std::vector<BandPtrs> host;
   DevBuf<BandPtrs> tab;
   DevBuf<int32_t> work;                        // (part, group) per work-group, -1: none
-  DevBuf<int> err;                             // time-out word of the launches, counters
+  DevBuf<int> err;                             // time-out word of the launches, counters,
+                                               // two gathering words per part
   int n_part = 0, n_wg = 0, n_class = 1;       // work-group i is of class i mod n_class
   int64_t max_n = 0;
   bool fp32 = false;
