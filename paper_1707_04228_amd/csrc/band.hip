@@ -1227,8 +1227,10 @@ struct Solve1 {
   const double* mate;
 };
 
-// Work-group g of the G that solve part `own` (load(i): the Solve1 of part i; `upper`: the
-// upper part of a split matrix).  A split matrix is swept in two segments: the parts' own
+// Work-group g of the P that solve part `own` (load(i): the Solve1 of part i; `upper`: the
+// upper part of a split matrix).  P is the G of the plan unless groups came too late (gather);
+// which blocks of a sum count as complete and which as in flight follows G, whoever is there,
+// so the order of summation, and with it every bit of the result, is the plan's.  A split matrix is swept in two segments: the parts' own
 // columns, each by its work-groups, and the separator, held by the upper part, by the
 // work-groups of both (as many as the in-flight registers allow), so that none is idle
 // meanwhile.  The lower part's rows past its own columns (the separator) only sum its
@@ -1237,7 +1239,7 @@ struct Solve1 {
 // for the one before it, which the count of complete blocks rests on.
 template <class T, class Load>
 __device__ __forceinline__ void band_solve_1_mat(Load load, int own, int upper, int g, int G,
-                                                 int* err) {
+                                                 int P, int* err) {
   int n, cols, sep, B, rs, N;                       // (a part has less than 2^31 entries)
   const T *base, *dv, *link;
   const int64_t *fcb, *lrb;
@@ -1260,7 +1262,8 @@ __device__ __forceinline__ void band_solve_1_mat(Load load, int own, int upper, 
   const bool split = upper >= 0, own_lower = lower;
   // separator groups
   const bool both = 2 * G <= GMAX;
-  const int GS = both ? 2 * G : G, gs = both ? 2 * g + own_lower : own_lower ? -1 : g;
+  const int GS = both ? 2 * G : G, PS = both ? 2 * P : P;
+  const int gs = both ? 2 * g + own_lower : own_lower ? -1 : g;
   __shared__ double acc[SB];
   __shared__ double part[SW][SB];
   __shared__ double xs[FL][SB];               // polled solutions of blocks in flight
@@ -1269,12 +1272,13 @@ __device__ __forceinline__ void band_solve_1_mat(Load load, int own, int upper, 
   // ---- forward: wave w owns rows 8w..8w+7 of the block, lanes run along the columns
 #pragma unroll 1
   for (int seg = 0; seg < (split ? 2 : 1); ++seg) {
-  int kfirst = 0, step = G, mine = g;          // first block of the segment, of this group
+  int kfirst = 0, span = G, step = P, mine = g;   // first block of the segment, of this group
   if (seg) {
     if (gs < 0) break;
     use(upper);
     kfirst = sep / SB;
-    step = GS;
+    span = GS;
+    step = PS;
     mine = kfirst + gs;
     if (threadIdx.x < SB) {
       int64_t spins = 0;
@@ -1288,7 +1292,7 @@ __device__ __forceinline__ void band_solve_1_mat(Load load, int own, int upper, 
     const int i0 = k * SB;
     const int nb = (int)min<int>(SB, n - i0);
     const int kc = min(k, ncb);                // column blocks left of the block
-    const int kdone = min(max(k - step + 1, kfirst), kc);   // those < kdone are complete
+    const int kdone = min(max(k - span + 1, kfirst), kc);   // those < kdone are complete
     const int done_end = kdone * SB;
     const int ifirst = i0 + RPW * wave;
     // the right-hand side of the row this lane reduces
@@ -1343,7 +1347,7 @@ __device__ __forceinline__ void band_solve_1_mat(Load load, int own, int upper, 
         }
       }
     }
-    // blocks in flight, kdone .. kc - 1 (at most step - 1), the nearest of them left to the
+    // blocks in flight, kdone .. kc - 1 (at most span - 1), the nearest of them left to the
     // link below; up to FL at a time, the last ones together: their factor entries (and,
     // before the last, this block's inverse diagonal block and link) are loaded first; then
     // wave 0 polls their solutions (one round trip when they are done) and passes them on
@@ -1461,13 +1465,13 @@ __device__ __forceinline__ void band_solve_1_mat(Load load, int own, int upper, 
   // blocks of the segment: all from kbeg to kend
   const int kbeg = seg ? sep / SB : 0;
   const int kend = seg || !split || lower ? (cols + SB - 1) / SB : sep / SB;
-  const int step = seg ? GS : G;
+  const int span = seg ? GS : G, step = seg ? PS : P;
   const T* cb = base + B;
   for (int kb = kend - 1 - (seg ? gs : g); kb >= kbeg; kb -= step) {
     const int i0 = kb * SB;
     const int nb = (int)min<int>(SB, cols - i0);
     const int rend = min(min<int>(n, i0 + nb + B), (int)lrb[kb]);   // envelope end
-    const int kdone = min(kb + step, kend);    // row blocks >= kdone complete
+    const int kdone = min(kb + span, kend);    // row blocks >= kdone complete
     const int done_beg = min<int>(rend, kdone * SB);
     const int cidx = i0 + lane;
     double sacc = 0.0;
@@ -1513,10 +1517,11 @@ __device__ __forceinline__ void band_solve_1_mat(Load load, int own, int upper, 
         if (lane % V == e) sacc = t;
       }
     }
-    // row blocks in flight, kb + 1 .. kin (at most step - 1), the nearest of them left to
-    // the link below; up to FL at a time from the far end, the nearest together: factor entries and, before the last, the inverse
-    // diagonal block first, then the polls of their final solutions (rows inside the band
-    // only), the last together with this block's forward solution
+    // row blocks in flight, kb + 1 .. kin (at most span - 1), the nearest of them left to
+    // the link below; up to FL at a time from the far end, the nearest together: factor
+    // entries and, before the last, the inverse diagonal block first, then the polls of their
+    // final solutions (rows inside the band only), the last together with this block's
+    // forward solution
     const int kin = min<int>(kdone - 1, (rend - 1) / SB);   // last row block in flight
     const bool linked = link && kb + 1 < kdone && rend > (kb + 1) * SB;
     const int kn = linked ? kb + 1 : kb;
@@ -1664,11 +1669,12 @@ __device__ inline V uniform_load(const V* p) {
 // The groups of a matrix (G to each of its np parts) begin together.  Launches of other
 // contexts may hold some of the slots and wait for theirs in the same way, so the wait is
 // bounded: after GATHER (20 ms, a thousand times what a lone launch takes) those who are there
-// share the matrix, and whoever comes later leaves.  w: two words of the matrix, cleared by the
-// marker fill: arrivals, which number the groups, and how many of them take part.  Returns this
-// work-group's number (-1: leave) and the groups per part, the same in every lane.
+// share the matrix, and whoever comes later leaves; none but the time it takes depends on it.
+// w: two words of the matrix, cleared by the marker fill: arrivals, which number the groups, and
+// how many of them take part, `most` to a part.  Returns this work-group's number (-1: leave)
+// and the groups per part, the same in every lane.
 constexpr int64_t GATHER = 2000000;              // ticks of the 100 MHz clock
-__device__ inline int2 gather(int* w, int np, int G, int* err) {
+__device__ inline int2 gather(int* w, int np, int G, int most, int* err) {
   __shared__ int2 mine;
   if (threadIdx.x == 0) {
     int* e = w + 1;
@@ -1678,7 +1684,7 @@ __device__ inline int2 gather(int* w, int np, int G, int* err) {
                                            __HIP_MEMORY_SCOPE_AGENT);
     };
     int2 r = {atomicAdd(w, 1), G};
-    if (r.x == np * G - 1) settle(np * G);
+    if (r.x == np * G - 1) settle(np * min(G, most));
     const int64_t t0 = wall_clock64();
     int64_t spins = 0;
     int c;
@@ -1686,7 +1692,7 @@ __device__ inline int2 gather(int* w, int np, int G, int* err) {
       if ((++spins & 255) == 0) {
         if (wall_clock64() - t0 > GATHER) {
           const int n = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          if (n >= np) settle(min(n, np * G));
+          if (n >= np) settle(min(n, np * min(G, most)));
         }
         if (spins > SPIN_LIMIT) {
           atomicOr(err, 2);
@@ -1707,9 +1713,10 @@ __device__ inline int2 gather(int* w, int np, int G, int* err) {
 // groups per part, both parts of a matrix (PP = 2 if the set has split matrices) in turn;
 // part -1: none.  The words of the matrices' gathers follow the place counters.
 struct Place {
-  int part, g, G;
+  int part, g, P;                                // group g of the P that are there
 };
-__device__ inline Place set_place(const int32_t* part_of, int n_mat, int G, int PP, int* err) {
+__device__ inline Place set_place(const int32_t* part_of, int n_mat, int G, int PP, int most,
+                                  int* err) {
   int* counters = err + CL;
   const int x = blockIdx.x & 7, q = take_place(counters + CL * x);
   const int j = q / (G * PP) * 8 + x, m = q % (G * PP);
@@ -1717,7 +1724,7 @@ __device__ inline Place set_place(const int32_t* part_of, int n_mat, int G, int 
   const int np = PP == 2 && uniform_load(part_of + 2 * j + 1) >= 0 ? 2 : 1;
   if (m % PP >= np) return {-1, 0, G};           // no second part
   if (G == 1) return {uniform_load(part_of + 2 * j + m % PP), 0, 1};
-  const int2 k = gather(counters + CL * 8 + 2 * j, np, G, err);
+  const int2 k = gather(counters + CL * 8 + 2 * j, np, G, most, err);
   if (k.x < 0) return {-1, 0, k.y};
   return {uniform_load(part_of + 2 * j + k.x % np), k.x / np, k.y};
 }
@@ -1727,8 +1734,8 @@ template <class T, bool COARSE>
 __global__ void __launch_bounds__(SOLVE_THREADS) k_band_solve_1(
     BandArgs a, const int32_t* part_of, const T* v, const T* dinv, const T* link,
     const int64_t* xoff, const double* xall, double* yall, double* zall, int G, int PP, int n_mat,
-    int* err) {
-  const Place pl = set_place(part_of, n_mat, G, PP, err);
+    int most, int* err) {
+  const Place pl = set_place(part_of, n_mat, G, PP, most, err);
   if (pl.part < 0) return;
   auto load = [&](int i) -> Solve1<T> {
     const BandPart P = uniform_load(a.part + i);
@@ -1744,8 +1751,8 @@ __global__ void __launch_bounds__(SOLVE_THREADS) k_band_solve_1(
   const BandPart P = uniform_load(a.part + pl.part);
   if (P.rows == 0) return;
   band_solve_1_mat<T>(load, pl.part,
-                      P.kind == PART_WHOLE ? -1 : uniform_load(part_of + 2 * P.mat), pl.g, pl.G,
-                      err);
+                      P.kind == PART_WHOLE ? -1 : uniform_load(part_of + 2 * P.mat), pl.g, G,
+                      pl.P, err);
 }
 
 // The parts of several band sets in one launch (all of one precision): the q-th work-group
@@ -1756,7 +1763,8 @@ __global__ void __launch_bounds__(SOLVE_THREADS) k_band_solve_1(
 template <class T>
 __global__ void __launch_bounds__(SOLVE_THREADS) k_band_solve_1_multi(const BandPtrs* __restrict__ tab,
                                                                        const int32_t* __restrict__ work,
-                                                                       int n_class, int* err) {
+                                                                       int n_class, int most,
+                                                                       int* err) {
   const int x = blockIdx.x % n_class;
   const int i = take_place(err + CL * (1 + x)) * n_class + x;
   int j = uniform_load(work + 2 * i), g = uniform_load(work + 2 * i + 1);
@@ -1768,19 +1776,20 @@ __global__ void __launch_bounds__(SOLVE_THREADS) k_band_solve_1_multi(const Band
   };
   const int64_t rows = uniform_load(&tab[j].n);
   const int kind = (int)uniform_load(&tab[j].kind);
-  int G = (int)uniform_load(&tab[j].G);
+  const int G = (int)uniform_load(&tab[j].G);
+  int P = G;
   if (rows == 0) return;
   // (an upper part stands right before its lower part in the table)
   const int first = kind == PART_LOWER ? j - 1 : j;
   if (G > 1) {
     const int np = kind == PART_WHOLE ? 1 : 2;
-    const int2 k = gather(err + CL * (1 + 8) + 2 * first, np, G, err);
+    const int2 k = gather(err + CL * (1 + 8) + 2 * first, np, G, most, err);
     if (k.x < 0) return;
     j = first + k.x % np;
     g = k.x / np;
-    G = k.y;
+    P = k.y;
   }
-  band_solve_1_mat<T>(load, j, kind == PART_WHOLE ? -1 : first, g, G, err);
+  band_solve_1_mat<T>(load, j, kind == PART_WHOLE ? -1 : first, g, G, P, err);
 }
 
 // y and z scratch of every part of a multi-set solve back to the marker, its counters to 0
@@ -1834,8 +1843,8 @@ constexpr int AL = SB * SB / MT;                  // band-chunk entries per thre
 template <class T, int M>
 __global__ void __launch_bounds__(MT) k_band_solve_m(
     BandArgs a, const int32_t* part_of, const T* v, const T* dinv, const int64_t* xoff,
-    const double* xall, T* yall, T* zall, int groups, int PP, int n_mat, const int32_t* active,
-    int* err) {
+    const double* xall, T* yall, T* zall, int groups, int PP, int n_mat, int most,
+    const int32_t* active, int* err) {
   typedef Mfma<T> MF;
   typedef typename MF::S S;
   typedef T Y;                                    // hand-over scratch: the factor's precision
@@ -1844,8 +1853,8 @@ __global__ void __launch_bounds__(MT) k_band_solve_m(
   constexpr int YL = SB * M / MT;                 // solution-chunk entries per thread
   __shared__ S Ab[3][SB][SB + 1];                 // band chunks (double buffer), and the
   __shared__ S Yc[3][SB * MP];                    // inverse block and its right-hand side
-  const Place pl = set_place(part_of, n_mat, groups, PP, err);
-  const int g = pl.g, G = pl.G;
+  const Place pl = set_place(part_of, n_mat, groups, PP, most, err);
+  const int g = pl.g, G = pl.P;                   // (no sum here depends on their number)
   if (pl.part < 0) return;
   int n, B, rs, n1, ncb, sep;                     // n1: last row of the matrix; ncb: blocks
   const T *cb, *dv;                               // with columns of their own
@@ -2203,6 +2212,17 @@ static int* solve_err(BandSet& bs, hipStream_t st) {
   return bs.err.p;
 }
 static int solve_parts(const BandSet& bs) { return bs.split ? 2 : 1; }
+// Groups of a part that take part in a solve, at most: all of them, or with GX_SOLVE_PRESENT=k
+// in the environment k, as though the others had come too late (a testing aid: results must
+// not depend on it).
+static int most_groups() {
+  static const int most = [] {
+    const char* e = std::getenv("GX_SOLVE_PRESENT");
+    const int k = e ? std::atoi(e) : 0;
+    return k > 0 ? k : GMAX;
+  }();
+  return most;
+}
 static unsigned solve_grid(const BandSet& bs, int G) {
   return (unsigned)((bs.n_mat + 7) / 8 * 8 * G * solve_parts(bs));
 }
@@ -2271,7 +2291,7 @@ static void launch_m(BandSet& bs, const BandArgs& a, const int64_t* d_xoff, doub
                        2 * rows * M, err + CL, bs.n_mat);
     hipLaunchKernelGGL((k_band_solve_m<float, M>), dim3(solve_grid(bs, G)), dim3(MT), 0, st, a,
                        bs.d_part_of.p, bs.v32.p, bs.dinv32.p, d_xoff, x, y, z, G, PP, bs.n_mat,
-                       active, err);
+                       most_groups(), active, err);
     hipLaunchKernelGGL(k_copy_out<float>, cgrid, dim3(256), 0, st, bs.d_part.p, d_xoff, M, z, x,
                        active);
   } else {
@@ -2281,7 +2301,7 @@ static void launch_m(BandSet& bs, const BandArgs& a, const int64_t* d_xoff, doub
                        2 * rows * M, err + CL, bs.n_mat);
     hipLaunchKernelGGL((k_band_solve_m<double, M>), dim3(solve_grid(bs, G)), dim3(MT), 0, st, a,
                        bs.d_part_of.p, bs.v64.p, bs.dinv64.p, d_xoff, x, y, z, G, PP, bs.n_mat,
-                       active, err);
+                       most_groups(), active, err);
     hipLaunchKernelGGL(k_copy_out<double>, cgrid, dim3(256), 0, st, bs.d_part.p, d_xoff, M, z, x,
                        active);
   }
@@ -2343,15 +2363,15 @@ void band_solve(BandSet& bs, const int64_t* d_xoff, double* x, hipStream_t st, i
     if (bs.fp32)
       hipLaunchKernelGGL((k_band_solve_1<float, false>), grid, dim3(SOLVE_THREADS), 0, st, a,
                          bs.d_part_of.p, bs.v32.p, bs.dinv32.p, link32, d_xoff, x, y, z, G, PP,
-                         bs.n_mat, err);
+                         bs.n_mat, most_groups(), err);
     else if (bs.coarse)
       hipLaunchKernelGGL((k_band_solve_1<double, true>), grid, dim3(SOLVE_THREADS), 0, st, a,
                          bs.d_part_of.p, bs.v64.p, bs.dinv64.p, link64, d_xoff, x, y, z, G, PP,
-                         bs.n_mat, err);
+                         bs.n_mat, most_groups(), err);
     else
       hipLaunchKernelGGL((k_band_solve_1<double, false>), grid, dim3(SOLVE_THREADS), 0, st, a,
                          bs.d_part_of.p, bs.v64.p, bs.dinv64.p, link64, d_xoff, x, y, z, G, PP,
-                         bs.n_mat, err);
+                         bs.n_mat, most_groups(), err);
     hipLaunchKernelGGL(k_copy_out<double>, dim3(nblocks(bs.max_cols, 256), bs.n_part), dim3(256),
                        0, st, bs.d_part.p, d_xoff, 1, z, x, (const int32_t*)nullptr);
   } else {
@@ -2530,10 +2550,10 @@ void multi_solve(MultiSolve& m, hipStream_t st) {
                      dim3(256), 0, st, m.tab.p, m.err.p + CL);
   if (m.fp32)
     hipLaunchKernelGGL(k_band_solve_1_multi<float>, dim3((unsigned)m.n_wg), dim3(SOLVE_THREADS),
-                       0, st, m.tab.p, m.work.p, m.n_class, m.err.p);
+                       0, st, m.tab.p, m.work.p, m.n_class, most_groups(), m.err.p);
   else
     hipLaunchKernelGGL(k_band_solve_1_multi<double>, dim3((unsigned)m.n_wg), dim3(SOLVE_THREADS),
-                       0, st, m.tab.p, m.work.p, m.n_class, m.err.p);
+                       0, st, m.tab.p, m.work.p, m.n_class, most_groups(), m.err.p);
   hipLaunchKernelGGL(k_copy_out_multi, dim3(nblocks(m.max_n, 256), nm), dim3(256), 0, st,
                      m.tab.p);
   GX_HIP(hipGetLastError());
