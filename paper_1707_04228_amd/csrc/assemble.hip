@@ -681,6 +681,9 @@ gx_status gx_assemble(gx_ctx* c, const gx_mesh* m, const gx_plystack* ps, const 
   GX_REQUIRE(m->n_nodes > 0 && m->n_elems > 0 && m->xyz && m->conn && m->elem_layer,
              "bad mesh");
   GX_REQUIRE(m->n_nodes < ((int64_t)1 << 31) / 3, "too many nodes");
+  // the incidence lists and the load lists are 20 entries per element or face, 32-bit offsets
+  GX_REQUIRE(m->n_elems <= INT32_MAX / 20, "too many elements");
+  GX_REQUIRE(ld->n_faces <= INT32_MAX / 20, "too many load faces");
   GX_REQUIRE(ps->n_layers >= 1 && ps->eng && ps->angle_deg, "bad ply stack");
   Timer tm(c->stream);
   hipStream_t s = c->stream;
@@ -777,8 +780,10 @@ gx_status gx_assemble(gx_ctx* c, const gx_mesh* m, const gx_plystack* ps, const 
   GX_REQUIRE(!(herr & ERR_LONELY), "a node belongs to no element");
   GX_REQUIRE(!(herr & ERR_ROW), "a block row has more than 128 blocks");
   GX_REQUIRE(!(herr & ERR_MATERIAL), "singular material compliance");
-  const int64_t nnzb = nnz32;
-  GX_REQUIRE(nnzb > 0, "matrix too large");
+  // rows of at most MAX_ROW blocks: only with so many can the 32-bit offsets have wrapped
+  const int64_t nnzb =
+      N > INT32_MAX / MAX_ROW ? scanned32_exact(nnz32, N + 1, tmp.p, s) : (int64_t)nnz32;
+  GX_REQUIRE(nnzb <= INT32_MAX, "matrix too large");
   c->nnzb = nnzb;
   c->col.alloc(nnzb);
   hipLaunchKernelGGL(k_pattern_pack, dim3(nblocks(N, 4)), dim3(256), 0, s, N, rows.p,

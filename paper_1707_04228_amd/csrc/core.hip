@@ -297,6 +297,13 @@ static int64_t scan_impl(T* data, int64_t n, int64_t* tmp, hipStream_t s) {
 void exclusive_scan32_async(int32_t* data, int64_t n, int64_t* tmp, hipStream_t s) {
   scan_rec<int32_t>(data, n, tmp, s);
 }
+int64_t scanned32_exact(int32_t last, int64_t n, const int64_t* tmp, hipStream_t s) {
+  const int64_t nb = (n + SCAN_TILE - 1) / SCAN_TILE;
+  if (nb <= 1) return last;                        // (a tile's own sum fits)
+  int64_t before = 0;                              // the exact sum before the last tile
+  to_host(&before, tmp + nb - 1, 1, s);
+  return before + (int64_t)(uint32_t)((uint32_t)last - (uint32_t)before);
+}
 int64_t exclusive_scan(int64_t* data, int64_t n, int64_t* tmp, hipStream_t s) {
   return scan_impl<int64_t>(data, n, tmp, s);
 }

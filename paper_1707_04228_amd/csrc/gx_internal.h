@@ -197,6 +197,9 @@ size_t scan_tmp_size(int64_t n);
 int64_t exclusive_scan(int64_t* data, int64_t n, int64_t* tmp, hipStream_t s);
 // the same for int32 values, without waiting for the total
 void exclusive_scan32_async(int32_t* data, int64_t n, int64_t* tmp, hipStream_t s);
+// the n-th value of that scan in 64 bits, where 32 may have wrapped: last is what the scan
+// left there, tmp its scratch.  Values of a tile must sum to less than 2^32.
+int64_t scanned32_exact(int32_t last, int64_t n, const int64_t* tmp, hipStream_t s);
 
 __device__ inline double wave_sum_d(double s) {
   for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
