@@ -415,8 +415,10 @@ gx_status gx_kernel_time(gx_ctx* ctx, int32_t which, int32_t reps, double* avg_m
 gx_status gx_tune(gx_ctx* ctx, int32_t param, int64_t value);
 
 /* Counters of the last setup / solve (host [5]): eigensolver iterations, PCG iterations,
- * stored entries of the interior band factors, stored entries of the eigensolver's
- * Neumann band factors, and FP64 fall-backs of the mixed path (bit 0: an FP32 interior
+ * band entries of the interior factors, band entries of the eigensolver's Neumann
+ * factors (each entry of a matrix once: a matrix of order n >= 3 bandwidths is kept in two
+ * parts that both hold the rows between them, up to a third more storage; where that does
+ * not fit, a set-up keeps all matrices whole), and FP64 fall-backs of the mixed path (bit 0: an FP32 interior
  * factor broke down and the interior factors were rebuilt in FP64; bit 1: the same for the
  * eigensolver's factors). */
 gx_status gx_stats(gx_ctx* ctx, int64_t* out);

@@ -2189,12 +2189,17 @@ static const void* solve1_kernel(const BandSet& bs) {
 void band_link(BandSet& bs, hipStream_t st) {
   if (!link_pays(bs.max_B, bs.fp32, solve_groups(bs, solve1_kernel(bs), 0))) return;
   const dim3 grid(nblocks(bs.max_cols, SB), bs.n_part);
+  try {
+    if (bs.fp32) bs.link32.alloc(2 * bs.n_inv);
+    else bs.link64.alloc(2 * bs.n_inv);
+  } catch (const Error& e) {
+    if (e.code != GX_ENOMEM) throw;
+    return;                                        // the solves go without
+  }
   if (bs.fp32) {
-    bs.link32.alloc(2 * bs.n_inv);
     hipLaunchKernelGGL(k_link<float>, grid, dim3(512), 0, st, bs.d_part.p, bs.v32.p, bs.dinv32.p,
                        bs.link32.p);
   } else {
-    bs.link64.alloc(2 * bs.n_inv);
     hipLaunchKernelGGL(k_link<double>, grid, dim3(512), 0, st, bs.d_part.p, bs.v64.p,
                        bs.dinv64.p, bs.link64.p);
   }
@@ -2596,7 +2601,8 @@ static void split_rows(int64_t n, int64_t B, size_t n_mat, int64_t* n1, int64_t*
 }
 
 void band_layout(BandSet& bs, const std::vector<int64_t>& n, const std::vector<int64_t>& B,
-                 bool fp32, hipStream_t st, const std::vector<int32_t>* first_node) {
+                 bool fp32, hipStream_t st, const std::vector<int32_t>* first_node,
+                 bool may_split) {
   bs.n_mat = (int)n.size();
   bs.n = n;
   bs.B = B;
@@ -2625,7 +2631,7 @@ void band_layout(BandSet& bs, const std::vector<int64_t>& n, const std::vector<i
     bs.max_n = std::max<int64_t>(bs.max_n, n[j]);
     bs.max_B = std::max<int64_t>(bs.max_B, bs.B[j]);
     int64_t n1 = 0, n2 = 0;
-    split_rows(n[j], B[j], n.size(), &n1, &n2);
+    if (may_split) split_rows(n[j], B[j], n.size(), &n1, &n2);
     for (int h = 0; h < (n2 ? 2 : 1); ++h) {
       BandPart p{};
       p.mat = (int)j;
@@ -2809,9 +2815,6 @@ extern "C" gx_status gx_band_factor_solve(gx_ctx* c, int32_t n_mat, const int64_
   hipStream_t s = c->stream;
   const bool fp32 = precision == GX_MIXED;
   BandSet bs;
-  band_layout(bs, nv, bv, fp32, s);
-  bs.force_groups[0] = bs.force_groups[1] = groups;
-  band_zero(bs, s);
   DevBuf<int64_t> d_off(n_mat + 1), d_doff(n_mat + 1), d_xoff(n_mat), d_bw(n_mat);
   to_dev(d_off.p, off.data(), n_mat + 1, s);
   to_dev(d_bw.p, bv.data(), n_mat, s);
@@ -2823,11 +2826,22 @@ extern "C" gx_status gx_band_factor_solve(gx_ctx* c, int32_t n_mat, const int64_
     hipLaunchKernelGGL(k_band_diag, dim3(nblocks(doff[n_mat], 256)), dim3(256), 0, s,
                        doff[n_mat], band, d_off.p, d_bw.p, d_doff.p, n_mat, dsc.p);
   }
-  hipLaunchKernelGGL(k_band_import, dim3(nblocks(off[n_mat], 256)), dim3(256), 0, s,
-                     off[n_mat], band, fp32 ? dsc.p : nullptr, d_off.p, d_bw.p, d_doff.p, n_mat,
-                     band_view(bs), fp32 ? bs.v32.p : nullptr, fp32 ? nullptr : bs.v64.p);
-  GX_HIP(hipGetLastError());
-  band_factor(c, bs, s, "the given band matrices");
+  auto factor = [&](bool may_split) {
+    band_layout(bs, nv, bv, fp32, s, nullptr, may_split);
+    bs.force_groups[0] = bs.force_groups[1] = groups;
+    band_zero(bs, s);
+    hipLaunchKernelGGL(k_band_import, dim3(nblocks(off[n_mat], 256)), dim3(256), 0, s,
+                       off[n_mat], band, fp32 ? dsc.p : nullptr, d_off.p, d_bw.p, d_doff.p, n_mat,
+                       band_view(bs), fp32 ? bs.v32.p : nullptr, fp32 ? nullptr : bs.v64.p);
+    GX_HIP(hipGetLastError());
+    band_factor(c, bs, s, "the given band matrices");
+  };
+  try {
+    factor(true);
+  } catch (const Error& e) {
+    if (e.code != GX_ENOMEM || !bs.split) throw;
+    factor(false);                                 // no room for the rows stored twice
+  }
   if (nrhs == 1) band_link(bs, s);
   if (fp32)
     hipLaunchKernelGGL(k_scale_rhs, dim3(nblocks(doff[n_mat] * nrhs, 256)), dim3(256), 0, s,

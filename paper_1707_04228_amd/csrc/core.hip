@@ -138,6 +138,7 @@ void* dev_alloc(size_t bytes, int* dev, hipError_t* err) {
     (void)hipGetLastError();
     *err = hipMalloc(&p, bytes);
   }
+  if (*err != hipSuccess) (void)hipGetLastError();  // reported here, not by the next call
   return *err == hipSuccess ? p : nullptr;
 }
 

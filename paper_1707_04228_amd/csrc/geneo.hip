@@ -1076,7 +1076,7 @@ void geneo_coarse(gx_ctx* c, const gx_geneo_opts* o, const std::function<void()>
     std::vector<int64_t> B =
         list_bandwidth(c, sw.D_nodes.p, sw.d_offD.p, sw.d_nD.p, sw.D_loc.p, sw.nD, &env, &first);
     for (int j = 0; j < n_sub; ++j) n3[j] = 3 * sw.nD[j];
-    band_layout(Mb, n3, B, fp32, s, &first);
+    band_layout(Mb, n3, B, fp32, s, &first, c->split);
     c->neumann_envelope = 0;
     for (int64_t e : Mb.env) c->neumann_envelope += e;
     c->neumann_flops = Mb.env_flops;
@@ -1110,7 +1110,7 @@ void geneo_coarse(gx_ctx* c, const gx_geneo_opts* o, const std::function<void()>
       if (!fp32 || e.code != GX_ENOTSPD) throw;
       // an FP32 factor broke down: this matrix set is refactored in FP64 (reported)
       c->fp64_fallbacks |= 2;
-      band_layout(Mb, n3, B, false, s, &first);
+      band_layout(Mb, n3, B, false, s, &first, c->split);
       bv = band_view(Mb);
       band_zero(Mb, s);
       hipLaunchKernelGGL(k_neumann_fill<double>, dim3((unsigned)maxD, n_sub), dim3(64), 0, s, g,
@@ -1430,18 +1430,8 @@ void geneo_coarse(gx_ctx* c, const gx_geneo_opts* o, const std::function<void()>
 
 using namespace gx;
 
-extern "C" {
-
-gx_status gx_geneo_setup(gx_ctx* c, const gx_geneo_opts* o, int32_t* nev_out,
-                         int64_t* n0_out) {
-  GX_API_BEGIN(c)
-  if (!c->assembled) throw Error(GX_ESTATE, "gx_assemble has not been called");
-  if (c->matrix_only) throw Error(GX_ESTATE, "needs an assembled mesh, not a loaded matrix");
-  GX_REQUIRE(o && o->elem_part, "null options");
-  GX_REQUIRE(o->n_sub >= 1 && o->n_sub <= 4096, "n_sub out of range");
-  GX_REQUIRE(o->overlap >= 1 && o->overlap <= 16, "overlap must be in [1, 16]");
-  GX_REQUIRE(o->precision == GX_FP64 || o->precision == GX_MIXED, "bad precision");
-  GX_REQUIRE(o->nev_max <= 32, "nev_max must be <= 32");
+// One set-up of the context (gx_geneo_setup).
+static void setup(gx_ctx* c, const gx_geneo_opts* o) {
   c->setup_done = false;
   c->sw = Schwarz();
   c->fp64_fallbacks = 0;
@@ -1483,6 +1473,31 @@ gx_status gx_geneo_setup(gx_ctx* c, const gx_geneo_opts* o, int32_t* nev_out,
     Timer t2(c->stream);
     interior_factors(c, o->precision);
     c->phase_ms[2] = t2.ms();
+  }
+}
+
+extern "C" {
+
+gx_status gx_geneo_setup(gx_ctx* c, const gx_geneo_opts* o, int32_t* nev_out,
+                         int64_t* n0_out) {
+  GX_API_BEGIN(c)
+  if (!c->assembled) throw Error(GX_ESTATE, "gx_assemble has not been called");
+  if (c->matrix_only) throw Error(GX_ESTATE, "needs an assembled mesh, not a loaded matrix");
+  GX_REQUIRE(o && o->elem_part, "null options");
+  GX_REQUIRE(o->n_sub >= 1 && o->n_sub <= 4096, "n_sub out of range");
+  GX_REQUIRE(o->overlap >= 1 && o->overlap <= 16, "overlap must be in [1, 16]");
+  GX_REQUIRE(o->precision == GX_FP64 || o->precision == GX_MIXED, "bad precision");
+  GX_REQUIRE(o->nev_max <= 32, "nev_max must be <= 32");
+  c->setup_done = false;
+  c->split = true;
+  try {
+    setup(c, o);
+  } catch (const Error& e) {
+    // no room: once more with every matrix in one part (the rows of a separator are stored
+    // twice, up to a third of a matrix)
+    if (e.code != GX_ENOMEM) throw;
+    c->split = false;
+    setup(c, o);
   }
   if (nev_out)
     for (int j = 0; j < o->n_sub; ++j) nev_out[j] = c->sw.two_level ? c->sw.nev[j] : 0;

@@ -400,6 +400,9 @@ struct gx_ctx {
   double mrhs_ms = 0.0, mrhs_bytes = 0.0;
   int64_t mrhs_calls = 0;
   int tune[4] = {0, 0, 0, 0};                  // see gx_tune
+  // band matrices may be stored in two parts (band_layout); a set-up that finds no room for
+  // the rows stored twice is done again without
+  bool split = true;
   // contexts set up at once on the device (gx_geneo_setup_batch): the set-up's
   // multi-work-group launches take this share of the machine's resident capacity
   int share = 1;
@@ -434,8 +437,10 @@ double interior_refactor_ms(gx_ctx* c);
 // the first node its rows couple to, then, for all nodes again, the last one; they give the
 // envelope (env, env_flops, the block tables), otherwise the band itself is taken.  The
 // storage is left unset: the caller zeroes all of it (band_zero) before it fills it.
+// may_split: matrices may be stored in two parts, which takes the rows of a separator twice.
 void band_layout(BandSet& bs, const std::vector<int64_t>& n, const std::vector<int64_t>& B,
-                 bool fp32, hipStream_t st, const std::vector<int32_t>* first_node = nullptr);
+                 bool fp32, hipStream_t st, const std::vector<int32_t>* first_node = nullptr,
+                 bool may_split = true);
 void band_zero(BandSet& bs, hipStream_t st);
 inline BandView band_view(const BandSet& bs) { return {bs.d_part.p, bs.d_part_of.p}; }
 void band_factor(gx_ctx* c, BandSet& bs, hipStream_t st, const char* what);
@@ -468,7 +473,8 @@ void band_factor_start(BandSet& bs, hipStream_t st, hipStream_t la, FactorJob& j
                        const char* what,
                        bool threaded = false);
 void band_factor_finish(FactorJob& job);
-// the links of a factored set's blocks, before its one-right-hand-side solves
+// the links of a factored set's blocks, before its one-right-hand-side solves (which do
+// without where there is no room for them)
 void band_link(BandSet& bs, hipStream_t st);
 // The interior factorisation as a job that can run on a side stream (see schwarz.hip).
 struct InteriorJob {

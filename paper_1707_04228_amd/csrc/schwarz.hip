@@ -333,7 +333,7 @@ void interior_factors_prepare(gx_ctx* c, int precision, hipStream_t s, InteriorJ
   for (int j = 0; j < n_sub; ++j) job.n[j] = 3 * sw.nI[j];
   sw.precision = precision;
   job.fp32 = precision == GX_MIXED;
-  band_layout(sw.A, job.n, job.B, job.fp32, s, &job.first);
+  band_layout(sw.A, job.n, job.B, job.fp32, s, &job.first, c->split);
   sw.A.force_groups[0] = c->tune[0];
   sw.A.force_groups[1] = c->tune[1];
   if (job.fp32) {
@@ -365,7 +365,7 @@ void interior_factors_finish(gx_ctx* c, InteriorJob& job) {
   } catch (const Error& e) {
     if (!job.fp32 || e.code != GX_ENOTSPD) throw;
     c->fp64_fallbacks |= 1;
-    band_layout(sw.A, job.n, job.B, false, s, &job.first);
+    band_layout(sw.A, job.n, job.B, false, s, &job.first, c->split);
     interior_fill(c, job.maxI, s);
     band_factor(c, sw.A, s, "the subdomain matrices");
     sw.precision = GX_FP64;
