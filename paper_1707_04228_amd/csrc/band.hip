@@ -2600,9 +2600,34 @@ static void split_rows(int64_t n, int64_t B, size_t n_mat, int64_t* n1, int64_t*
   *n2 = (b - b / 2) * SB;
 }
 
+// Whether a set's matrices gain by two parts (split_rows).  Where whole matrices leave no
+// work-group idle (G each, fewer than GMAX) and a group's share of a block, 64 B w / G bytes,
+// takes longer than a hand-over, the chain costs nothing, and two parts add the separator's
+// fill and groups that do not divide by two.  Decided by the widest matrix for the whole set:
+// the groups of a launch follow its fullest XCD, so a few split matrices would halve those of
+// all.  Split against whole, a one-right-hand-side solve (us) and a factorisation with one
+// solve (ms), at B w / G bytes (FP64 but where noted):
+//     736:  64 of n =  6,000, B =   368          570 /   608     9.7 /  11.1
+//     832:  24 of     20,000,     2,080, FP32  1,148 / 1,160    48.8 /  48.3
+//   1,024:  32 of     16,000,     1,024        1,545 / 1,717    29.6 /  33.6
+//   1,305:  24 of     20,000,     1,632        2,172 / 2,110    47.6 /  51.3
+//   1,638:  48 of     16,000,     1,024        2,560 / 2,230    44.6 /  47.3
+//   1,664:  48 of     20,000,     2,080, FP32  3,370 / 2,980   103.4 / 102.9
+//   3,264:  64 of     20,000,     1,632        5,630 / 5,412   136.2 / 134.7
+// (and a factor is solved with tens of times).
+constexpr int64_t SPLIT_BYTES = 1500;
+static bool split_pays(const std::vector<int64_t>& B, bool fp32) {
+  int dev = 0, cus = 0;
+  GX_HIP(hipGetDevice(&dev));
+  GX_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+  const int64_t G = std::max<int64_t>(cus / (int64_t)B.size(), 1);
+  return G >= GMAX || *std::max_element(B.begin(), B.end()) * (fp32 ? 4 : 8) <= SPLIT_BYTES * G;
+}
+
 void band_layout(BandSet& bs, const std::vector<int64_t>& n, const std::vector<int64_t>& B,
                  bool fp32, hipStream_t st, const std::vector<int32_t>* first_node,
                  bool may_split) {
+  may_split = may_split && split_pays(B, fp32);
   bs.n_mat = (int)n.size();
   bs.n = n;
   bs.B = B;

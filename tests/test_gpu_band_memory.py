@@ -34,8 +34,9 @@ def test_whole_matrix_where_two_parts_do_not_fit():
     band, x, b = _system(n, B)
     s = gx.Solver()
     # (before any memory is held: what the device allocates for the kernels themselves)
-    s.band_factor_solve([400], [20], _system(400, 20)[0], _system(400, 20)[2])
-    torch.cuda.synchronize()
+    small = _system(400, 20)
+    torch.cuda.synchronize()                       # (the solver has a stream of its own)
+    s.band_factor_solve([400], [20], small[0], small[2])
     torch.cuda.empty_cache()
     held = torch.empty(torch.cuda.mem_get_info()[0] - whole - 100_000_000, dtype=torch.uint8,
                        device="cuda")
@@ -66,6 +67,7 @@ def test_set_up_where_two_parts_do_not_fit():
             # a request that cannot be met empties the library's cache of released blocks
             band = torch.zeros(8_000_000 * 101, dtype=torch.float64, device="cuda")
             x = torch.zeros(8_000_000, dtype=torch.float64, device="cuda")
+            torch.cuda.synchronize()
             torch.cuda.empty_cache()
             full = torch.empty(torch.cuda.mem_get_info()[0] - 300_000_000, dtype=torch.uint8,
                                device="cuda")
