@@ -407,11 +407,13 @@ gx_status gx_kernel_time(gx_ctx* ctx, int32_t which, int32_t reps, double* avg_m
                          double* bytes);
 
 /* Tuning knobs, applied by the next gx_geneo_setup (0 = automatic choice):
- * param 0: work-groups per subdomain for the single right-hand-side band solves (PCG);
- * param 1: work-groups per subdomain for the multi-column band solves (eigensolver).
- * Values 1..8; the library lowers a request that would not keep every work-group of the
- * pipelined launch resident on the device.  The batched PCG (gx_pcg_solve_batch) plans the
- * work-groups of its joint subdomain solve itself and ignores param 0. */
+ * param 0: work-groups for the single right-hand-side band solves (PCG), per subdomain, or
+ * for each of the two parts of one whose matrix is eliminated from both ends;
+ * param 1: the same for the multi-column band solves (eigensolver).
+ * Values 1..8 (the automatic choice goes up to 16); the library lowers a request that would
+ * not keep every work-group of the pipelined launch resident on the device.  The batched PCG
+ * (gx_pcg_solve_batch) plans the work-groups of its joint subdomain solve itself and ignores
+ * param 0. */
 gx_status gx_tune(gx_ctx* ctx, int32_t param, int64_t value);
 
 /* Counters of the last setup / solve (host [5]): eigensolver iterations, PCG iterations,

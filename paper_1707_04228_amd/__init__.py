@@ -477,10 +477,10 @@ class Solver:
         self._check(lib.gx_tune(self.h, param, value))
 
     @_on_stream
-    def autotune(self, candidates=(1, 2, 3, 4), reps=3):
+    def autotune(self, candidates=(0, 1, 2, 3, 4, 8), reps=3):
         """Pick the work-groups per subdomain of the preconditioner's band solves by timing
-        them (gx_kernel_time 1) for each candidate; returns {candidate: ms} and keeps the
-        fastest."""
+        them (gx_kernel_time 1) for each candidate (0: the library's own choice, up to 16);
+        returns {candidate: ms} and keeps the fastest."""
         times = {}
         for g in candidates:
             self.tune(0, g)
