@@ -413,7 +413,9 @@ gx_status gx_kernel_time(gx_ctx* ctx, int32_t which, int32_t reps, double* avg_m
  * Values 1..8 (the automatic choice goes up to 16); the library lowers a request that would
  * not keep every work-group of the pipelined launch resident on the device.  The batched PCG
  * (gx_pcg_solve_batch) plans the work-groups of its joint subdomain solve itself and ignores
- * param 0. */
+ * param 0.
+ * param 2, a testing aid: the context's band solves go on as though no more than that many
+ * of a part's work-groups had come in time; the results are the same bit for bit. */
 gx_status gx_tune(gx_ctx* ctx, int32_t param, int64_t value);
 
 /* Counters of the last setup / solve (host [5]): eigensolver iterations, PCG iterations,

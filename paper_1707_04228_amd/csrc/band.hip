@@ -2217,17 +2217,8 @@ static int* solve_err(BandSet& bs, hipStream_t st) {
   return bs.err.p;
 }
 static int solve_parts(const BandSet& bs) { return bs.split ? 2 : 1; }
-// Groups of a part that take part in a solve, at most: all of them, or with GX_SOLVE_PRESENT=k
-// in the environment k, as though the others had come too late (a testing aid: results must
-// not depend on it).
-static int most_groups() {
-  static const int most = [] {
-    const char* e = std::getenv("GX_SOLVE_PRESENT");
-    const int k = e ? std::atoi(e) : 0;
-    return k > 0 ? k : GMAX;
-  }();
-  return most;
-}
+// Groups of a part that take part in a solve, at most
+static int most_groups(int most) { return most > 0 ? most : GMAX; }
 static unsigned solve_grid(const BandSet& bs, int G) {
   return (unsigned)((bs.n_mat + 7) / 8 * 8 * G * solve_parts(bs));
 }
@@ -2296,7 +2287,7 @@ static void launch_m(BandSet& bs, const BandArgs& a, const int64_t* d_xoff, doub
                        2 * rows * M, err + CL, bs.n_mat);
     hipLaunchKernelGGL((k_band_solve_m<float, M>), dim3(solve_grid(bs, G)), dim3(MT), 0, st, a,
                        bs.d_part_of.p, bs.v32.p, bs.dinv32.p, d_xoff, x, y, z, G, PP, bs.n_mat,
-                       most_groups(), active, err);
+                       most_groups(bs.most), active, err);
     hipLaunchKernelGGL(k_copy_out<float>, cgrid, dim3(256), 0, st, bs.d_part.p, d_xoff, M, z, x,
                        active);
   } else {
@@ -2306,7 +2297,7 @@ static void launch_m(BandSet& bs, const BandArgs& a, const int64_t* d_xoff, doub
                        2 * rows * M, err + CL, bs.n_mat);
     hipLaunchKernelGGL((k_band_solve_m<double, M>), dim3(solve_grid(bs, G)), dim3(MT), 0, st, a,
                        bs.d_part_of.p, bs.v64.p, bs.dinv64.p, d_xoff, x, y, z, G, PP, bs.n_mat,
-                       most_groups(), active, err);
+                       most_groups(bs.most), active, err);
     hipLaunchKernelGGL(k_copy_out<double>, cgrid, dim3(256), 0, st, bs.d_part.p, d_xoff, M, z, x,
                        active);
   }
@@ -2368,15 +2359,15 @@ void band_solve(BandSet& bs, const int64_t* d_xoff, double* x, hipStream_t st, i
     if (bs.fp32)
       hipLaunchKernelGGL((k_band_solve_1<float, false>), grid, dim3(SOLVE_THREADS), 0, st, a,
                          bs.d_part_of.p, bs.v32.p, bs.dinv32.p, link32, d_xoff, x, y, z, G, PP,
-                         bs.n_mat, most_groups(), err);
+                         bs.n_mat, most_groups(bs.most), err);
     else if (bs.coarse)
       hipLaunchKernelGGL((k_band_solve_1<double, true>), grid, dim3(SOLVE_THREADS), 0, st, a,
                          bs.d_part_of.p, bs.v64.p, bs.dinv64.p, link64, d_xoff, x, y, z, G, PP,
-                         bs.n_mat, most_groups(), err);
+                         bs.n_mat, most_groups(bs.most), err);
     else
       hipLaunchKernelGGL((k_band_solve_1<double, false>), grid, dim3(SOLVE_THREADS), 0, st, a,
                          bs.d_part_of.p, bs.v64.p, bs.dinv64.p, link64, d_xoff, x, y, z, G, PP,
-                         bs.n_mat, most_groups(), err);
+                         bs.n_mat, most_groups(bs.most), err);
     hipLaunchKernelGGL(k_copy_out<double>, dim3(nblocks(bs.max_cols, 256), bs.n_part), dim3(256),
                        0, st, bs.d_part.p, d_xoff, 1, z, x, (const int32_t*)nullptr);
   } else {
@@ -2417,11 +2408,13 @@ void multi_solve_plan(MultiSolve& m, const std::vector<BandSet*>& sets,
   m.fp32 = sets[0]->fp32;
   m.host.clear();
   m.max_n = 0;
+  m.most = 0;
   std::vector<int> mats;                           // first part of each matrix in the table
   for (size_t k = 0; k < sets.size(); ++k) {
     BandSet& bs = *sets[k];
     GX_REQUIRE(bs.fp32 == m.fp32 && !bs.coarse && x[k] && xoff[k],
                "multi-set solve: band sets of one precision with right-hand sides");
+    if (bs.most > 0) m.most = m.most ? std::min(m.most, bs.most) : bs.most;
     alloc_solve1_scratch(bs);
     double *y = bs.ybuf.p, *z = y + bs.ybuf.n / 2;
     for (int j = 0; j < bs.n_mat; ++j) {
@@ -2555,10 +2548,10 @@ void multi_solve(MultiSolve& m, hipStream_t st) {
                      dim3(256), 0, st, m.tab.p, m.err.p + CL);
   if (m.fp32)
     hipLaunchKernelGGL(k_band_solve_1_multi<float>, dim3((unsigned)m.n_wg), dim3(SOLVE_THREADS),
-                       0, st, m.tab.p, m.work.p, m.n_class, most_groups(), m.err.p);
+                       0, st, m.tab.p, m.work.p, m.n_class, most_groups(m.most), m.err.p);
   else
     hipLaunchKernelGGL(k_band_solve_1_multi<double>, dim3((unsigned)m.n_wg), dim3(SOLVE_THREADS),
-                       0, st, m.tab.p, m.work.p, m.n_class, most_groups(), m.err.p);
+                       0, st, m.tab.p, m.work.p, m.n_class, most_groups(m.most), m.err.p);
   hipLaunchKernelGGL(k_copy_out_multi, dim3(nblocks(m.max_n, 256), nm), dim3(256), 0, st,
                      m.tab.p);
   GX_HIP(hipGetLastError());
@@ -2854,6 +2847,7 @@ extern "C" gx_status gx_band_factor_solve(gx_ctx* c, int32_t n_mat, const int64_
   auto factor = [&](bool may_split) {
     band_layout(bs, nv, bv, fp32, s, nullptr, may_split);
     bs.force_groups[0] = bs.force_groups[1] = groups;
+    bs.most = c->tune[2];
     band_zero(bs, s);
     hipLaunchKernelGGL(k_band_import, dim3(nblocks(off[n_mat], 256)), dim3(256), 0, s,
                        off[n_mat], band, fp32 ? dsc.p : nullptr, d_off.p, d_bw.p, d_doff.p, n_mat,

@@ -1082,6 +1082,7 @@ void geneo_coarse(gx_ctx* c, const gx_geneo_opts* o, const std::function<void()>
     c->neumann_flops = Mb.env_flops;
     Mb.force_groups[0] = c->tune[0];
     Mb.force_groups[1] = c->tune[1];
+    Mb.most = c->tune[2];
     c->neumann_entries = Mb.total;
     BandView bv = band_view(Mb);
     DevBuf<int> ferr(1);
@@ -1410,6 +1411,7 @@ void geneo_coarse(gx_ctx* c, const gx_geneo_opts* o, const std::function<void()>
   }
   band_layout(sw.C, {n0}, {n0 - 1}, false, s);
   sw.C.coarse = true;
+  sw.C.most = c->tune[2];
   band_zero(sw.C, s);
   hipLaunchKernelGGL(k_coarse_fill, dim3(nblocks(n0 * n0, 256)), dim3(256), 0, s, n0, K0.p,
                      sw.C.B[0], sw.C.B[0] + 1, sw.C.v64.p);
@@ -1508,10 +1510,10 @@ gx_status gx_geneo_setup(gx_ctx* c, const gx_geneo_opts* o, int32_t* nev_out,
 
 gx_status gx_tune(gx_ctx* c, int32_t param, int64_t value) {
   GX_API_BEGIN(c)
-  GX_REQUIRE(param >= 0 && param < 2, "unknown tuning parameter");
+  GX_REQUIRE(param >= 0 && param < 3, "unknown tuning parameter");
   GX_REQUIRE(value >= 0 && value <= 8, "value out of range");
   c->tune[param] = (int)value;
-  if (c->setup_done) {                             // takes effect at the next solve
+  if (c->setup_done && param < 2) {                // takes effect at the next solve
     c->sw.A.force_groups[param] = (int)value;
     c->sw.A.solve_groups[param] = 0;
   }

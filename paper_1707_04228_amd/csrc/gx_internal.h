@@ -281,6 +281,8 @@ struct BandSet {
   bool fp32 = false;
   int solve_groups[2] = {0, 0};                // work-groups per matrix: 1-RHS, m-RHS solve
   int force_groups[2] = {0, 0};                // requested (0: automatic, capped by residency)
+  int most = 0;                                // as though only so many groups of a part came
+                                               // in time (0: all; see gx_tune)
   int share = 1;                               // contexts whose solves may run concurrently
   DevBuf<int> err;                             // error word of the solves (poll time-out),
                                                // then their eight work-group counters,
@@ -320,6 +322,7 @@ struct MultiSolve {
   DevBuf<int32_t> work;                        // (part, group) per work-group, -1: none
   DevBuf<int> err;                             // time-out word of the launches, counters,
                                                // two gathering words per part
+  int most = 0;                                // the sets' least (BandSet::most)
   int n_part = 0, n_wg = 0, n_class = 1;       // work-group i is of class i mod n_class
   int64_t max_n = 0;
   bool fp32 = false;

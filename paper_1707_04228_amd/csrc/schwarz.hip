@@ -336,6 +336,7 @@ void interior_factors_prepare(gx_ctx* c, int precision, hipStream_t s, InteriorJ
   band_layout(sw.A, job.n, job.B, job.fp32, s, &job.first, c->split);
   sw.A.force_groups[0] = c->tune[0];
   sw.A.force_groups[1] = c->tune[1];
+  sw.A.most = c->tune[2];
   if (job.fp32) {
     sw.dg.alloc(3 * N);
     hipLaunchKernelGGL(k_diag, dim3(nblocks(N, 256)), dim3(256), 0, s, c->row_ptr.p,

@@ -1,15 +1,11 @@
 """Solves whose groups do not all come in time: the result is the same bit for bit.
 
 The groups that share a matrix wait for each other only so long; then those present solve it.
-A child process is told that no more than k groups of each part come (GX_SOLVE_PRESENT) and has
-to return the bytes that this process, with all of them, returns: for the band solver's edge
-shapes with one and several right-hand sides in both precisions, and for the solutions of a
-batch, whose subdomain solves go in one launch.
+Contexts that are told that no more than k groups of each part come (gx_tune, param 2) have to
+return the bytes that contexts with all of them return: for the band solver's edge shapes with
+one and several right-hand sides in both precisions, and for the solutions of a batch, whose
+subdomain solves go in one launch.
 """
-import os
-import subprocess
-import sys
-
 import numpy as np
 import pytest
 
@@ -21,7 +17,7 @@ SHAPES = [(384, 127), (385, 1), (448, 0), (705, 235), (1000, 333), (2049, 640), 
           (383, 20), (3000, 90), (5000, 300)]
 
 
-def results():
+def results(present):
     import torch
     import paper_1707_04228_amd as gx
     out = {}
@@ -35,6 +31,7 @@ def results():
         bands.append(band.ravel())
     band = torch.tensor(np.concatenate(bands), device="cuda")
     s = gx.Solver()
+    s.tune(2, present)
     for name, prec in (("fp64", gx.GX_FP64), ("mixed", gx.GX_MIXED)):
         for nrhs in (1, 16):
             x = torch.tensor(rng.standard_normal(nrhs * sum(n for n, _ in SHAPES)), device="cuda")
@@ -49,6 +46,8 @@ def results():
         cfgs.append(cfg)
     for name, prec in (("fp64", gx.GX_FP64), ("mixed", gx.GX_MIXED)):
         b = gx.Batch(cfgs, precision=prec)
+        for ctx in b.solvers:
+            ctx.tune(2, present)
         b.setup(concurrent=1)
         xs, it, _, st = b.solve(rtol=1e-10, maxit=500)
         assert np.all(st == gx.GX_OK)
@@ -59,14 +58,7 @@ def results():
 
 
 @pytest.mark.parametrize("present", [1, 3])
-def test_late_groups_change_no_bit(present, tmp_path):
-    ref = results()
-    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-    code = ("import sys; sys.path[:0] = [%r, %r]; import numpy as np, test_gpu_late_groups as t; "
-            "np.savez(%r, **t.results())" % (root, os.path.join(root, "tests"),
-                                             str(tmp_path / "late.npz")))
-    subprocess.run([sys.executable, "-c", code], check=True, timeout=100,
-                   env=dict(os.environ, GX_SOLVE_PRESENT=str(present)))
-    late = np.load(tmp_path / "late.npz")
+def test_late_groups_change_no_bit(present):
+    ref, late = results(0), results(present)
     for key, v in ref.items():
         assert late[key].tobytes() == v.tobytes(), key
