@@ -1024,7 +1024,7 @@ void band_factor_finish(FactorJob& job) {
 // the 16 tiles of either product, its operands straight from LDS.
 template <class T>
 __global__ void __launch_bounds__(512) k_link(const BandPart* part, const T* v, const T* dinv,
-                                              T* link) {
+                                              double* link) {
   __shared__ double D[SB][SB + 1], L[2][SB][SB + 1];
   const BandPart& P = part[blockIdx.y];
   const int64_t n = P.rows, ncb = (P.cols + SB - 1) / SB, b = blockIdx.x;
@@ -1041,7 +1041,7 @@ __global__ void __launch_bounds__(512) k_link(const BandPart* part, const T* v, 
   }
   __syncthreads();
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
-  T* out = link + 2 * P.boff + 2 * b * SB * SB;
+  double* out = link + 2 * P.boff + 2 * b * SB * SB;
   for (int q = 0; q < 4; ++q) {
     const int which = q >> 1, tile = w + 8 * (q & 1), rt = tile >> 2, ct = tile & 3;
     v4d acc = {0, 0, 0, 0};
@@ -1053,7 +1053,7 @@ __global__ void __launch_bounds__(512) k_link(const BandPart* part, const T* v, 
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e)
-      out[(int64_t)which * SB * SB + (16 * rt + 4 * e + lk) * SB + 16 * ct + li] = (T)acc[e];
+      out[(int64_t)which * SB * SB + (16 * rt + 4 * e + lk) * SB + 16 * ct + li] = acc[e];
   }
 }
 
@@ -1218,7 +1218,7 @@ struct Solve1 {
   int kind;
   const T* base;
   const T* dv;
-  const T* link;
+  const double* link;
   const int64_t* fcb;
   const int64_t* lrb;
   const double* x;
@@ -1241,7 +1241,8 @@ template <class T, class Load>
 __device__ __forceinline__ void band_solve_1_mat(Load load, int own, int upper, int g, int G,
                                                  int P, int* err) {
   int n, cols, sep, B, rs, N;                       // (a part has less than 2^31 entries)
-  const T *base, *dv, *link;
+  const T *base, *dv;
+  const double* link;
   const int64_t *fcb, *lrb;
   const double *x, *mate;                           // row r at x[dx r], mate[-r]
   double *y, *z;
@@ -1354,7 +1355,8 @@ __device__ __forceinline__ void band_solve_1_mat(Load load, int own, int upper, 
     // through LDS
     const bool linked = link && k < ncb && kdone < k;
     const int kin = linked ? kc - 1 : kc;
-    T dd[DL], lm[DL];
+    T dd[DL];
+    double lm[DL];
     int kf = kdone;
 #pragma unroll 1
     for (;;) {
@@ -1439,7 +1441,7 @@ __device__ __forceinline__ void band_solve_1_mat(Load load, int own, int upper, 
           if (!__any(is_mark(yv)) || poll_give_up(spins, err)) break;
         }
 #pragma unroll
-        for (int u = 0; u < DL; ++u) pr[u] = (double)lm[u] * yv;
+        for (int u = 0; u < DL; ++u) pr[u] = lm[u] * yv;
         yr -= reduce_rows8(pr, lane);
       }
       const int row = wave + SW * (lane >> 3);
@@ -1525,7 +1527,8 @@ __device__ __forceinline__ void band_solve_1_mat(Load load, int own, int upper, 
     const int kin = min<int>(kdone - 1, (rend - 1) / SB);   // last row block in flight
     const bool linked = link && kb + 1 < kdone && rend > (kb + 1) * SB;
     const int kn = linked ? kb + 1 : kb;
-    T dd[DL], lm[DL];
+    T dd[DL];
+    double lm[DL];
     double yown = 0.0;
     int kl = max(kin, kn);                         // the farthest one not yet taken
 #pragma unroll 1
@@ -1630,7 +1633,7 @@ __device__ __forceinline__ void band_solve_1_mat(Load load, int own, int upper, 
       if (!in) zv = 0.0;
       double pr2[DL];
 #pragma unroll
-      for (int u = 0; u < DL; ++u) pr2[u] = (double)lm[u] * zv;
+      for (int u = 0; u < DL; ++u) pr2[u] = lm[u] * zv;
       zr -= reduce_rows8(pr2, lane);
       if ((lane & 7) == 0 && row < nb) hand_over(z + i0 + row, zr);
     }
@@ -1732,7 +1735,7 @@ __device__ inline Place set_place(const int32_t* part_of, int n_mat, int G, int 
 // The parts of one band set (set_place)
 template <class T, bool COARSE>
 __global__ void __launch_bounds__(SOLVE_THREADS) k_band_solve_1(
-    BandArgs a, const int32_t* part_of, const T* v, const T* dinv, const T* link,
+    BandArgs a, const int32_t* part_of, const T* v, const T* dinv, const double* link,
     const int64_t* xoff, const double* xall, double* yall, double* zall, int G, int PP, int n_mat,
     int most, int* err) {
   const Place pl = set_place(part_of, n_mat, G, PP, most, err);
@@ -1772,7 +1775,7 @@ __global__ void __launch_bounds__(SOLVE_THREADS) k_band_solve_1_multi(const Band
   auto load = [&](int p) -> Solve1<T> {
     const BandPtrs t = uniform_load(tab + p);
     return {t.n, t.cols, t.sep, t.N, t.B, t.B + 1, (int)t.kind, static_cast<const T*>(t.v),
-            static_cast<const T*>(t.dinv), static_cast<const T*>(t.link), t.fcb, t.lrb, t.x, t.y, t.z, t.mate};
+            static_cast<const T*>(t.dinv), t.link, t.fcb, t.lrb, t.x, t.y, t.z, t.mate};
   };
   const int64_t rows = uniform_load(&tab[j].n);
   const int kind = (int)uniform_load(&tab[j].kind);
@@ -2190,18 +2193,17 @@ void band_link(BandSet& bs, hipStream_t st) {
   if (!link_pays(bs.max_B, bs.fp32, solve_groups(bs, solve1_kernel(bs), 0))) return;
   const dim3 grid(nblocks(bs.max_cols, SB), bs.n_part);
   try {
-    if (bs.fp32) bs.link32.alloc(2 * bs.n_inv);
-    else bs.link64.alloc(2 * bs.n_inv);
+    bs.link.alloc(2 * bs.n_inv);
   } catch (const Error& e) {
     if (e.code != GX_ENOMEM) throw;
     return;                                        // the solves go without
   }
   if (bs.fp32) {
     hipLaunchKernelGGL(k_link<float>, grid, dim3(512), 0, st, bs.d_part.p, bs.v32.p, bs.dinv32.p,
-                       bs.link32.p);
+                       bs.link.p);
   } else {
     hipLaunchKernelGGL(k_link<double>, grid, dim3(512), 0, st, bs.d_part.p, bs.v64.p,
-                       bs.dinv64.p, bs.link64.p);
+                       bs.dinv64.p, bs.link.p);
   }
   GX_HIP(hipGetLastError());
 }
@@ -2350,23 +2352,22 @@ void band_solve(BandSet& bs, const int64_t* d_xoff, double* x, hipStream_t st, i
   if (ncol == 1 && !active) {
     const int G = solve_groups(bs, solve1_kernel(bs), 0), PP = solve_parts(bs);
     const bool linked = link_pays(bs.max_B, bs.fp32, G);
-    const float* link32 = linked ? bs.link32.p : nullptr;
-    const double* link64 = linked ? bs.link64.p : nullptr;
+    const double* link = linked ? bs.link.p : nullptr;
     const dim3 grid(solve_grid(bs, G));
     int* err = solve_err(bs, st);
     double* y = solve1_scratch(bs, st);
     double* z = y + bs.ybuf.n / 2;
     if (bs.fp32)
       hipLaunchKernelGGL((k_band_solve_1<float, false>), grid, dim3(SOLVE_THREADS), 0, st, a,
-                         bs.d_part_of.p, bs.v32.p, bs.dinv32.p, link32, d_xoff, x, y, z, G, PP,
+                         bs.d_part_of.p, bs.v32.p, bs.dinv32.p, link, d_xoff, x, y, z, G, PP,
                          bs.n_mat, most_groups(bs.most), err);
     else if (bs.coarse)
       hipLaunchKernelGGL((k_band_solve_1<double, true>), grid, dim3(SOLVE_THREADS), 0, st, a,
-                         bs.d_part_of.p, bs.v64.p, bs.dinv64.p, link64, d_xoff, x, y, z, G, PP,
+                         bs.d_part_of.p, bs.v64.p, bs.dinv64.p, link, d_xoff, x, y, z, G, PP,
                          bs.n_mat, most_groups(bs.most), err);
     else
       hipLaunchKernelGGL((k_band_solve_1<double, false>), grid, dim3(SOLVE_THREADS), 0, st, a,
-                         bs.d_part_of.p, bs.v64.p, bs.dinv64.p, link64, d_xoff, x, y, z, G, PP,
+                         bs.d_part_of.p, bs.v64.p, bs.dinv64.p, link, d_xoff, x, y, z, G, PP,
                          bs.n_mat, most_groups(bs.most), err);
     hipLaunchKernelGGL(k_copy_out<double>, dim3(nblocks(bs.max_cols, 256), bs.n_part), dim3(256),
                        0, st, bs.d_part.p, d_xoff, 1, z, x, (const int32_t*)nullptr);
@@ -2429,9 +2430,7 @@ void multi_solve_plan(MultiSolve& m, const std::vector<BandSet*>& sets,
                      : static_cast<const void*>(bs.v64.p + p.off);
         t.dinv = m.fp32 ? static_cast<const void*>(bs.dinv32.p + p.boff)
                         : static_cast<const void*>(bs.dinv64.p + p.boff);
-        t.link = bs.link32.n   ? static_cast<const void*>(bs.link32.p + 2 * p.boff)
-                 : bs.link64.n ? static_cast<const void*>(bs.link64.p + 2 * p.boff)
-                               : nullptr;
+        t.link = bs.link.n ? bs.link.p + 2 * p.boff : nullptr;
         t.x = x[k] + xoff[k][j];
         t.y = y + p.yoff;
         t.z = z + p.yoff;
@@ -2629,8 +2628,7 @@ void band_layout(BandSet& bs, const std::vector<int64_t>& n, const std::vector<i
   bs.d_poff.release();
   bs.ybuf.release();
   bs.mbuf.release();
-  bs.link64.release();
-  bs.link32.release();
+  bs.link.release();
   bs.max_n = bs.max_B = 0;
   bs.max_cols = 0;
   bs.total = bs.stored = bs.rows = bs.n_inv = 0;

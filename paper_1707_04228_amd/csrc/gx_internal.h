@@ -275,9 +275,10 @@ struct BandSet {
   DevBuf<double> dinv64;
   DevBuf<float> dinv32;
   // for the one-right-hand-side solves (band_link): block b's links to its neighbours at
-  // 2 boff + 8192 b, D_b L(b, b - 1) and then D_b^T L(b + 1, b)^T with D_b its inverse block
-  DevBuf<double> link64;
-  DevBuf<float> link32;
+  // 2 boff + 8192 b, D_b L(b, b - 1) and then D_b^T L(b + 1, b)^T with D_b its inverse block;
+  // in FP64 for FP32 factors too, whose two products a solve would form one after the other
+  // in FP64
+  DevBuf<double> link;
   bool fp32 = false;
   int solve_groups[2] = {0, 0};                // work-groups per matrix: 1-RHS, m-RHS solve
   int force_groups[2] = {0, 0};                // requested (0: automatic, capped by residency)
@@ -300,7 +301,7 @@ struct BandSet {
 struct BandPtrs {
   const void* v;                               // factor (precision of the launch)
   const void* dinv;                            // inverse 64x64 diagonal blocks
-  const void* link;                            // links between neighbouring blocks
+  const double* link;                          // links between neighbouring blocks
   double* x;                                   // right-hand side in, solution out (matrix)
   double* y;                                   // forward-solution scratch (64-aligned length)
   double* z;                                   // backward-solution scratch
