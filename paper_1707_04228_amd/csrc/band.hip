@@ -1796,22 +1796,27 @@ __global__ void __launch_bounds__(SOLVE_THREADS) k_band_solve_1_multi(const Band
 }
 
 // y and z scratch of every part of a multi-set solve back to the marker, its counters to 0
-__global__ void k_fill_mark_multi(const BandPtrs* tab, int* counters) {
-  const BandPtrs t = tab[blockIdx.y];
+// (65,535 matrices may have twice as many parts as a grid has rows: a row takes several)
+__global__ void k_fill_mark_multi(const BandPtrs* tab, int n_part, int* counters) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (blockIdx.y == 0 && i < 8) counters[CL * i] = 0;
-  if (i < 2) counters[CL * 8 + 2 * blockIdx.y + i] = 0;   // the part's words of gather
-  if (i < (t.n + SB - 1) / SB * SB) {
-    t.y[i] = __longlong_as_double((long long)YMARK);
-    t.z[i] = __longlong_as_double((long long)YMARK);
+  for (int q = blockIdx.y; q < n_part; q += gridDim.y) {
+    const BandPtrs t = tab[q];
+    if (i < 2) counters[CL * 8 + 2 * q + i] = 0;   // the part's words of gather
+    if (i < (t.n + SB - 1) / SB * SB) {
+      t.y[i] = __longlong_as_double((long long)YMARK);
+      t.z[i] = __longlong_as_double((long long)YMARK);
+    }
   }
 }
 
 // x <- z for every part of a multi-set solve
-__global__ void k_copy_out_multi(const BandPtrs* tab) {
-  const BandPtrs t = tab[blockIdx.y];
+__global__ void k_copy_out_multi(const BandPtrs* tab, int n_part) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < t.cols) t.x[t.kind == PART_LOWER ? t.N - 1 - i : i] = t.z[i];
+  for (int q = blockIdx.y; q < n_part; q += gridDim.y) {
+    const BandPtrs t = tab[q];
+    if (i < t.cols) t.x[t.kind == PART_LOWER ? t.N - 1 - i : i] = t.z[i];
+  }
 }
 
 // ---- M right-hand sides per matrix (M a multiple of 8, at most MC; row-major, row
@@ -2452,7 +2457,7 @@ void multi_solve_plan(MultiSolve& m, const std::vector<BandSet*>& sets,
   const int nm = (int)mats.size();
   m.n_part = (int)m.host.size();
   mats.push_back(m.n_part);
-  GX_REQUIRE(m.n_part > 0 && m.n_part <= 65535, "multi-set solve: 1 to 65535 parts");
+  GX_REQUIRE(nm > 0 && nm <= 65535, "multi-set solve: 1 to 65535 matrices");
   // Work-groups per part.  A matrix waits at the pace of its slowest group, so all of them
   // are to be resident, and work-group i runs on XCD i mod NX (each with its share of the
   // resident capacity).  Matrices go to XCDs largest first, each to the least loaded one
@@ -2542,17 +2547,17 @@ void multi_solve_plan(MultiSolve& m, const std::vector<BandSet*>& sets,
 // Solves every matrix of the table in place (marker fill, solve, copy-out on st).
 void multi_solve(MultiSolve& m, hipStream_t st) {
   GX_REQUIRE(m.n_part > 0, "multi-set solve: no table");
-  const unsigned nm = (unsigned)m.n_part;
-  hipLaunchKernelGGL(k_fill_mark_multi, dim3(nblocks((m.max_n + SB - 1) / SB * SB, 256), nm),
-                     dim3(256), 0, st, m.tab.p, m.err.p + CL);
+  const unsigned nr = (unsigned)std::min(m.n_part, 65535);
+  hipLaunchKernelGGL(k_fill_mark_multi, dim3(nblocks((m.max_n + SB - 1) / SB * SB, 256), nr),
+                     dim3(256), 0, st, m.tab.p, m.n_part, m.err.p + CL);
   if (m.fp32)
     hipLaunchKernelGGL(k_band_solve_1_multi<float>, dim3((unsigned)m.n_wg), dim3(SOLVE_THREADS),
                        0, st, m.tab.p, m.work.p, m.n_class, most_groups(m.most), m.err.p);
   else
     hipLaunchKernelGGL(k_band_solve_1_multi<double>, dim3((unsigned)m.n_wg), dim3(SOLVE_THREADS),
                        0, st, m.tab.p, m.work.p, m.n_class, most_groups(m.most), m.err.p);
-  hipLaunchKernelGGL(k_copy_out_multi, dim3(nblocks(m.max_n, 256), nm), dim3(256), 0, st,
-                     m.tab.p);
+  hipLaunchKernelGGL(k_copy_out_multi, dim3(nblocks(m.max_n, 256), nr), dim3(256), 0, st,
+                     m.tab.p, m.n_part);
   GX_HIP(hipGetLastError());
 }
 
