@@ -564,6 +564,17 @@ __global__ void k_gram_sum(const int64_t* nrows, int m, const int32_t* active, i
                2 * MAXM * MAXM);
 }
 
+// The place of v[t] among v[0 .. m) in decreasing order (ties: the lower index first; NaNs,
+// which a basis that lost rank may leave, last): for t = 0 .. m - 1 always a permutation
+__device__ inline int rank_down(const double* v, int m, int t) {
+  int rank = 0;
+  for (int a = 0; a < m; ++a) {
+    const bool na = v[a] != v[a], nt = v[t] != v[t];
+    rank += na == nt ? v[a] > v[t] || (!(v[t] > v[a]) && a < t) : nt;
+  }
+  return rank;
+}
+
 // Small dense Rayleigh-Ritz per subdomain: G_B c = mu G_M c, largest mu first.
 // G layout: [G_M (m x m, ld m) | G_B] inside a 2 MAXM^2 slot.  Output: c (m x m row-major,
 // column b = b-th Ritz vector) and theta_b = 1 / mu_b.
@@ -720,14 +731,10 @@ __global__ void __launch_bounds__(256) k_rayleigh_ritz(int m, const int32_t* act
       __syncthreads();
     }
   }
-  // order by decreasing mu (ties: the lower column first)
+  // order by decreasing mu
   if (t < m) mu[t] = H[t][t];
   __syncthreads();
-  if (t < m) {
-    int rank = 0;
-    for (int a = 0; a < m; ++a) rank += mu[a] > mu[t] || (mu[a] == mu[t] && a < t);
-    perm[rank] = t;
-  }
+  if (t < m) perm[rank_down(mu, m, t)] = t;
   __syncthreads();
   // c = D L^-T V (column b = Ritz vector of the b-th largest mu)
   if (t < m) {
