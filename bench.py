@@ -45,7 +45,7 @@ FP64_PEAK_TFLOPS = 78.6
 # the FETCH_SIZE / WRITE_SIZE counters of `bench.py --traffic-probe [--precision mixed]`
 # scaled by a 4 GiB copy.  Valid for the solve kernel as it stands: retake the counters
 # when it changes.
-SOLVE_TRAFFIC_BYTES = {"fp64": 145.5e9, "mixed": 72.6e9}
+SOLVE_TRAFFIC_BYTES = {"fp64": 134.3e9, "mixed": 67.0e9}
 
 
 def run_step(gx, torch, cfg, precision):

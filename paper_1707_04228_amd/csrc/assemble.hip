@@ -5,9 +5,9 @@
 //   1. node -> element incidence (counting sort, each list sorted by element number);
 //   2. block-CSR pattern: per node, the sorted union of the nodes of its elements;
 //   3. material stiffness of each layer from engineering constants (C = S^-1, Table 1);
-//   4. element matrices K_e = sum_q B'^T C B' det J w, one wavefront per element on the FP64
-//      matrix instruction: B' gives the strains in the ply's axes at the Gauss point (the
-//      geometric frame turned by the ply angle), where the layer's stiffness C is constant;
+//   4. element matrices K_e = sum_q B^T C_q B det J w, one wavefront per element: C_q is the
+//      layer's stiffness turned into global axes at the Gauss point (from the geometric frame
+//      there and the ply angle), and sums are scalar, in the order of the definition;
 //   5. deterministic gather: every block row sums its elements' blocks in element order
 //      (no floating-point atomics), then clamped DOFs become identity rows / columns;
 //   6. consistent face loads from a 3x3 Gauss rule on each loaded face.

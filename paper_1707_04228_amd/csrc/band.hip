@@ -1081,10 +1081,10 @@ void band_factor(gx_ctx* c, BandSet& bs, hipStream_t st, const char* what) {
 // the device is, so few matrices need many groups; then the chain of (n + B) / 128 hand-overs
 // per sweep, which the links (k_link) and lane sums in registers shorten.  Per solve, one
 // chain per matrix and four groups -> now (FP64 but where noted): 4 matrices of n = 3,500, B =
-// 370: 0.29 -> 0.13 ms; 6 of 16,000, 1,020: 1.77 -> 0.59 ms; 16 of 37,000, 1,220 (9.5 GB): 4.85
-// -> 1.98 ms; 5 of 45,000, 2,080, FP32: 6.12 -> 1.38 ms; 16 of 91,000, 1,630 (26 GB): 15.1 ->
-// 5.65 ms.  64 of those fill the device with one group per compute unit and stay where they
-// were (118 GB in 22 to 23 ms, FP32 59 GB in 12.9 ms).
+// 370: 0.29 -> 0.13 ms; 6 of 16,000, 1,020: 1.77 -> 0.60 ms; 16 of 37,000, 1,220 (9.5 GB): 4.85
+// -> 2.05 ms; 5 of 45,000, 2,080, FP32: 6.12 -> 1.40 ms; 16 of 91,000, 1,630 (26 GB): 15.1 ->
+// 5.80 ms.  64 of those fill the device with one group per compute unit; they are kept whole
+// (split_pays) and stay where they were: 118 GB in 21.9 ms, FP32 59 GB in 12.4 ms.
 constexpr int SW = SOLVE_THREADS / 64;           // waves per work-group (8)
 constexpr int CL = 32;                            // words from one place counter to the next
                                                   // (and to the error word): a line of its
@@ -1840,7 +1840,7 @@ __global__ void k_copy_out_multi(const BandPtrs* tab, int n_part) {
 // unit; leaving out the solution rows, the band or the products takes about a quarter off
 // each), and for narrow bands the hand-overs.  So what a block needs besides its chunks, its
 // right-hand side and its inverse block, is loaded before the sweep and waits in registers
-// and in LDS buffers of its own: per solve of 32 columns, 8 matrices of n = 3,500, B = 370
+// and in LDS buffers of its own: per solve of 32 columns, 4 matrices of n = 3,500, B = 370
 // 0.51 -> 0.46 ms, 6 of 16,000, 1,020 1.92 -> 1.66, 16 of 91,000, 1,630 18.7 -> 17.4 and, FP32, 5 of
 // 45,000, 2,080 3.92 -> 3.25 ms.  (Half the waves with the band straight in registers, no LDS
 // for it: 2.11 and 21.1 ms in the second and third.)
@@ -2149,7 +2149,8 @@ __global__ void __launch_bounds__(MT) k_band_solve_m(
 // (set_place), so it is the parts on the fullest XCD that are counted, against its eighth of
 // the machine: counted together, 14 matrices of 24 parts would put 40 work-groups on an XCD's
 // 32 slots.  The solves of one context are stream-ordered, so a launch may count on the whole
-// machine.  When several contexts solve concurrently (share > 1) an XCD may hold the fullest
+// machine; the eigensolver's run beside the interior factorisation, whose updates may hold slots
+// for some milliseconds, in which the groups gather.  When several contexts solve concurrently (share > 1) an XCD may hold the fullest
 // part of each: which XCD a launch begins with differs from launch to launch, and groups that
 // wait for others must all have a slot (four contexts of two matrices with 16 work-groups a
 // matrix ran into the poll limit in 7 of 100 set-ups; with 8 in none of 300).
@@ -2182,7 +2183,9 @@ static int solve_groups(BandSet& bs, const void* kernel, int which) {
 // reduction per block, so they pay where a step is bound by the hand-over and not by a
 // group's share of the stream (64 B w / G bytes at about 22 GB/s).  Measured with eight
 // groups, unlinked -> linked, at B w / G bytes: 370: 182 -> 141 us, 1,020: 727 -> 652 us,
-// 1,040: 2,033 -> 1,831 us, 1,220: 2,032 -> 2,072 us, 1,630: 5,767 -> 5,907 us.
+// 1,040 (FP32): 2,079 -> 1,885 us, 1,220: 2,032 -> 2,072 us, 1,630: 5,767 -> 5,907 us; with
+// sixteen, at 510: 731 -> 555 us, 520 (FP32): 1,940 -> 1,372 us.  (The joint solve of a batch
+// asks with its own counts, for the links that a set's own solves were given.)
 static bool link_pays(int64_t B, bool fp32, int G) {
   return G > 1 && B * (fp32 ? 4 : 8) <= 1100 * (int64_t)G;
 }
@@ -2877,7 +2880,3 @@ extern "C" gx_status gx_band_factor_solve(gx_ctx* c, int32_t n_mat, const int64_
   GX_HIP(hipStreamSynchronize(s));
   GX_API_END(c)
 }
-
-namespace gx {
-
-}  // namespace gx

@@ -407,8 +407,8 @@ struct gx_ctx {
   // band matrices may be stored in two parts (band_layout); a set-up that finds no room for
   // the rows stored twice is done again without
   bool split = true;
-  // contexts set up at once on the device (gx_geneo_setup_batch): the set-up's
-  // multi-work-group launches take this share of the machine's resident capacity
+  // contexts set up at once on the device (gx_geneo_setup_batch): the work-groups of their
+  // multi-work-group launches are counted together, on the fullest XCD of each (solve_groups)
   int share = 1;
   // materials and loads of the last assembly (kept for the sensitivities)
   int32_t n_layers = 0;

@@ -348,8 +348,8 @@ gx_status gx_pcg_solve_batch(int32_t n, gx_ctx* const* ctxs, const double* const
     runs[i].done = true;
     runs[i].post_pending = false;
   };
-  // the coarse solves of all systems run concurrently: each context's gets an equal share of
-  // the machine (work-group counts chosen again), restored afterwards
+  // the coarse solves of all systems run concurrently: their work-groups are counted
+  // together (work-group counts chosen again), restored afterwards
   auto set_share = [&](int share) {
     for (int i = 0; i < n; ++i) {
       BandSet& bs = ctxs[i]->sw.C;
