@@ -2279,6 +2279,29 @@ __global__ void k_fill_mark32(float* p, int64_t n, int* counters, int n_mat) {
   if (i < n) p[i] = __uint_as_float(YMARK32);
 }
 
+static void alloc_solvem_scratch(BandSet& bs) {
+  const int64_t rows = std::max<int64_t>(bs.rows, 8);
+  if (bs.mbuf.n < (size_t)(2 * rows * MC)) bs.mbuf.alloc(2 * rows * MC);
+}
+
+static void alloc_panel(BandSet& bs, hipStream_t st) {
+  if (bs.d_poff.n) return;
+  std::vector<int64_t> po(bs.n_mat + 1, 0);
+  for (int j = 0; j < bs.n_mat; ++j) po[j + 1] = po[j] + bs.n[j] * MC;
+  bs.panel.alloc(po[bs.n_mat]);
+  bs.d_poff.alloc(bs.n_mat + 1);
+  to_dev(bs.d_poff.p, po.data(), bs.n_mat + 1, st);
+}
+
+// The scratch of solves with ncol right-hand sides, so that it is missed, if there is no room,
+// while the set can still be laid out again
+void band_reserve(BandSet& bs, hipStream_t st, int ncol) {
+  (void)solve_err(bs, st);
+  if (ncol == 1) alloc_solve1_scratch(bs);
+  else alloc_solvem_scratch(bs);
+  if (ncol > MC) alloc_panel(bs, st);
+}
+
 template <int M>
 static void launch_m(BandSet& bs, const BandArgs& a, const int64_t* d_xoff, double* x,
                      hipStream_t st, const int32_t* active) {
@@ -2287,8 +2310,8 @@ static void launch_m(BandSet& bs, const BandArgs& a, const int64_t* d_xoff, doub
   const int PP = solve_parts(bs);
   int* err = solve_err(bs, st);
   // y and z scratch of M columns: segments at yoff * M (64-aligned row offsets)
+  alloc_solvem_scratch(bs);
   const int64_t rows = std::max<int64_t>(bs.rows, 8);
-  if (bs.mbuf.n < (size_t)(2 * rows * MC)) bs.mbuf.alloc(2 * rows * MC);
   const dim3 cgrid(nblocks(bs.max_cols * M, 256), bs.n_part);
   if (bs.fp32) {                                   // FP32 scratch in the same buffer
     float* y = reinterpret_cast<float*>(bs.mbuf.p);
@@ -2337,13 +2360,7 @@ void band_solve(BandSet& bs, const int64_t* d_xoff, double* x, hipStream_t st, i
              "banded solve: right-hand sides must be 1 or a multiple of 8 up to 64");
   if (ncol > MC) {
     // panels of at most MC columns through a scratch block; the factor is read once per panel
-    if (!bs.d_poff.n) {
-      std::vector<int64_t> po(bs.n_mat + 1, 0);
-      for (int j = 0; j < bs.n_mat; ++j) po[j + 1] = po[j] + bs.n[j] * MC;
-      bs.panel.alloc(po[bs.n_mat]);
-      bs.d_poff.alloc(bs.n_mat + 1);
-      to_dev(bs.d_poff.p, po.data(), bs.n_mat + 1, st);
-    }
+    alloc_panel(bs, st);
     for (int c0 = 0; c0 < ncol; c0 += MC) {
       const int w = std::min(MC, ncol - c0);
       const dim3 grid(nblocks((int64_t)bs.max_n * w, 256), bs.n_mat);
@@ -2860,6 +2877,7 @@ extern "C" gx_status gx_band_factor_solve(gx_ctx* c, int32_t n_mat, const int64_
                        band_view(bs), fp32 ? bs.v32.p : nullptr, fp32 ? nullptr : bs.v64.p);
     GX_HIP(hipGetLastError());
     band_factor(c, bs, s, "the given band matrices");
+    band_reserve(bs, s, nrhs);
   };
   try {
     factor(true);

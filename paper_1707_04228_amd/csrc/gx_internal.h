@@ -480,6 +480,8 @@ void band_factor_finish(FactorJob& job);
 // the links of a factored set's blocks, before its one-right-hand-side solves (which do
 // without where there is no room for them)
 void band_link(BandSet& bs, hipStream_t st);
+// the scratch of its solves with ncol right-hand sides
+void band_reserve(BandSet& bs, hipStream_t st, int ncol);
 // The interior factorisation as a job that can run on a side stream (see schwarz.hip).
 struct InteriorJob {
   std::vector<int64_t> n, B, env;

@@ -371,6 +371,7 @@ void interior_factors_finish(gx_ctx* c, InteriorJob& job) {
     band_factor(c, sw.A, s, "the subdomain matrices");
     sw.precision = GX_FP64;
   }
+  band_reserve(sw.A, s, 1);
   band_link(sw.A, s);
   std::vector<int64_t> xo(n_sub + 1, 0);
   for (int j = 0; j < n_sub; ++j) xo[j + 1] = xo[j] + job.n[j];

@@ -94,3 +94,38 @@ def test_set_up_where_two_parts_do_not_fit():
     (nev, n0, it, x), (nev2, n02, it2, x2) = runs
     assert nev == nev2 and n0 == n02 and abs(it - it2) <= 1
     assert np.abs(x - x2).max() <= 1e-8 * np.abs(x).max()
+
+
+def test_whole_matrix_where_the_scratch_of_two_parts_does_not_fit():
+    """The factors of both parts fit (the storage with its padding, the inverse blocks), the
+    scratch of a solve with 16 right-hand sides does not: 25 MB, 8 MB are left."""
+    import torch
+    import paper_1707_04228_amd as gx
+    n, B, m = 36000, 12000, 16
+    band, x, b = _system(n, B)
+    rhs = b[:, None] * torch.arange(1.0, m + 1, dtype=torch.float64, device="cuda")
+    s = gx.Solver()
+    small = _system(400, 20)
+    torch.cuda.synchronize()                       # (the solver has a stream of its own)
+    s.band_factor_solve([400], [20], small[0], small[2])
+    # a request that cannot be met empties the library's cache of released blocks
+    full = torch.empty(20_000_000_000, dtype=torch.float64, device="cuda")
+    y = torch.zeros(40_000_000, dtype=torch.float64, device="cuda")
+    torch.cuda.synchronize()
+    with pytest.raises(gx.GxError, match="GX_ENOMEM"):
+        s.band_factor_solve([40_000_000], [499], full, y)
+    del full, y
+    torch.cuda.empty_cache()
+    sep = n - (n - B) // 64 * 64
+    two = 8 * ((n + sep + 128) * (B + 1) + 1024) + 8 * 64 * n + 8_000_000
+    held = []                                      # (the device counts late what was given back)
+    while len(held) < 8 and torch.cuda.mem_get_info()[0] > two + 4_000_000:
+        held.append(torch.empty(torch.cuda.mem_get_info()[0] - two, dtype=torch.uint8,
+                                device="cuda"))
+    assert torch.cuda.mem_get_info()[0] <= two + 4_000_000
+    got = s.band_factor_solve([n], [B], band, rhs.reshape(-1)).reshape(n, m)
+    del held
+    torch.cuda.empty_cache()
+    ref = x[:, None] * torch.arange(1.0, m + 1, dtype=torch.float64, device="cuda")
+    assert (got - ref).abs().max() <= 1e-12 * ref.abs().max()
+    s.close()
